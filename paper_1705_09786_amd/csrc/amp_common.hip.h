@@ -30,6 +30,7 @@ __device__ __forceinline__ unsigned ld_u32(const unsigned* p) {
 // are then in the L2 all of them read through, so a release needs no L2 write-back, only the wait.  Measured with
 // two workgroups handing 4 KB back and forth on one die: 0.93 us per hand-over instead of 1.31 us, every word right.
 __shared__ int s_nowb;
+__shared__ unsigned s_first_seq;   // admission number of this replica's first admission of the launch
 __device__ __forceinline__ void fence_release() {
   if (s_nowb)
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");

@@ -150,7 +150,7 @@ struct AmpDev {
   int g_eoff[9];
   int g_PE, g_PA;             // parts of the gradient w.r.t. h through the edges (sum of the edge tiles) / of the
                               // gradients the three GRU nodes return (candidate tiles, then update, then reset)
-  unsigned n_total, first_seq;
+  unsigned n_total, pad1;
   int admit_bounded, n_updaters;  // staleness-bounded admission on / workers that apply updates
   float max_staleness;            // its bound: updates per worker during an instance's life
   unsigned* ctl;              // [0] abort code, [1] done, [2] abort detail, [3] updates applied by all workers,
@@ -158,7 +158,8 @@ struct AmpDev {
   unsigned* slot_seq;         // [mak] admission number held by each slot
   int* slot_inst;             // [mak] the slot's instance: index into the launch's instance set; sign bit set = a
                               // forward-only (evaluation) instance, which the loss layer retires instead of turning round
-  const int* adm_inst;        // [n_total] the same word for every admission of the launch, in admission order
+  const int* adm_inst;        // [n_total] the same word for every admission of the launch, in admission order; null = the
+                              // data set's instances in order, over and over
   int* smeta;                 // [mak][4] written at admission: admission number, length, node offset (RNN: instance), token offset
   float* loss_out;            // [n_total] summed loss of each admission
   int* correct_out;           // [n_total]
@@ -177,4 +178,10 @@ struct AmpDev {
   long long watchdog_ticks;
   void* buf[AMP_MAX_BUFS];    // model-specific per-slot storage
   long long stride[AMP_MAX_BUFS];
+};
+
+// What changes from launch to launch of the same description: passed by value.
+#define AMP_MAX_REPLICAS 128
+struct AmpLaunch {
+  unsigned first_seq[AMP_MAX_REPLICAS];   // admission number of each replica's first admission
 };

@@ -1613,8 +1613,8 @@ __device__ __noinline__ void role_g_readout(const GQ AmpDev* D, const GQ WorkerD
     const float d = yhat - v.target;
     LOG(W->node, 0, seq, 0);
     if (threadIdx.x == 0) {
-      ((GQ float*)D->loss_out)[seq - D->first_seq] = 0.5f * d * d;
-      ((GQ float*)D->yhat_out)[seq - D->first_seq] = yhat;
+      ((GQ float*)D->loss_out)[seq - s_first_seq] = 0.5f * d * d;
+      ((GQ float*)D->yhat_out)[seq - s_first_seq] = yhat;
     }
     if (!D->train || uni(gd.slot_inst[s]) < 0) {   // an evaluation instance: retired here, nothing turns round
       publish_barrier();

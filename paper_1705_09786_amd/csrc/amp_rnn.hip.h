@@ -401,8 +401,8 @@ __device__ __noinline__ void role_rnn_out(const GQ AmpDev* D, const GQ WorkerDev
     const int label = D->data.lab[D->data.lab_off[inst]];
     softmax_xent_wave0(ys, R, label, ds, &s_loss, &s_pred);
     if (threadIdx.x == 0) {
-      D->loss_out[seq - D->first_seq] = s_loss;
-      D->correct_out[seq - D->first_seq] = s_pred == label;
+      D->loss_out[seq - s_first_seq] = s_loss;
+      D->correct_out[seq - s_first_seq] = s_pred == label;
     }
     if (!D->train || D->slot_inst[s] < 0) {   // an evaluation instance: retired here, nothing turns round
       publish_barrier();

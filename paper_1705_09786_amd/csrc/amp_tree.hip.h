@@ -1520,7 +1520,7 @@ __device__ __noinline__ void role_tree_out(const GQ AmpDev* D, const GQ WorkerDe
       // d logits; zero for an evaluation node, which then adds nothing to the gradient sums below
       const float keep = M.aux[k] ? 0.f : 1.f;
       for (int r = 0; r < R; ++r) z[r] = keep * (expf(z[r] - m) * inv - (r == label ? 1.f : 0.f));
-      const unsigned idx = M.seq[k] - D->first_seq;
+      const unsigned idx = M.seq[k] - s_first_seq;
       __hip_atomic_fetch_add((GQ float*)&D->loss_out[idx], -(zl - m - logf(se)), __ATOMIC_RELAXED, AGENT);
       if (am == label) __hip_atomic_fetch_add((GQ int*)&D->correct_out[idx], 1, __ATOMIC_RELAXED, AGENT);
     }
