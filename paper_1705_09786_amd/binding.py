@@ -154,6 +154,14 @@ def _ip(a):
     return a.ctypes.data_as(_i32p)
 
 
+_ONE = (ct.c_float * 1)()
+
+
+def _fp(a):
+    """A float32 array's memory as a call argument (a third of the time ndarray.ctypes.data_as takes)."""
+    return (ct.c_float * a.size).from_buffer(a)
+
+
 def to_c_instance(model: int, inst: dict):
     """dict (as produced by synth) -> (Instance, list of arrays kept alive)."""
     ci = Instance()
@@ -292,7 +300,7 @@ class Amp:
         n = ct.c_size_t()
         self._chk(self.L.amp_param_count(self.h, node, ct.byref(n)))
         out = np.empty(n.value, np.float32)
-        self._chk(self.L.amp_get_params(self.h, node, out.ctypes.data_as(_f32p), out.size, ct.byref(n)))
+        self._chk(self.L.amp_get_params(self.h, node, _fp(out), out.size, ct.byref(n)))
         return out
 
     def submit(self, inst: dict, which=0, key=0):
@@ -351,9 +359,9 @@ class Amp:
 
     def get_instance_losses(self):
         n = ct.c_size_t()
-        self.L.amp_get_instance_losses(self.h, ct.cast(ct.c_void_p(1), _f32p), 0, ct.byref(n))
+        self.L.amp_get_instance_losses(self.h, _ONE, 0, ct.byref(n))
         out = np.empty(max(n.value, 1), np.float32)
-        self._chk(self.L.amp_get_instance_losses(self.h, out.ctypes.data_as(_f32p), out.size, ct.byref(n)))
+        self._chk(self.L.amp_get_instance_losses(self.h, _fp(out), out.size, ct.byref(n)))
         return out[:n.value]
 
     def get_event_log(self):

@@ -7,7 +7,9 @@
 #define AMP_MAX_NODES 144   // the largest model: an RNN whose cell has 64 copies (3 + 2 x 63 nodes)
 #define AMP_MAX_WORKERS 128
 #define AMP_MAX_BUFS 24
-#define AMP_THREADS 512
+#ifndef AMP_THREADS
+#define AMP_THREADS 512      // a model's kernel may define its own (amp_mlp.hip)
+#endif
 #define AMP_LDS_BYTES 163840   // 160 KB per workgroup on gfx950
 #define AMP_DYN_LDS_BYTES (AMP_LDS_BYTES - 6144)   // dynamic part; the rest is for static __shared__
 #define AMP_TREE_LOOKUP_MAX_MUF 16384
@@ -39,6 +41,10 @@ AMP_HD static inline int amp_ldrow(int cols) {
 #define MSG_LOCAL(c) ((c) & 0xfffffu)
 #define MSG_MAKE(dirb, slot, local) (((dirb) ? MSG_DIR_B : 0u) | ((unsigned)(slot) << 20) | (unsigned)(local))
 #define AMP_MAX_MAK 2047
+// MLP messages carry the instance in their position bits ([19] an evaluation instance, [18:0] its index), so that no
+// worker has to look the slot up before it can fetch; sets of more instances leave MLP_LOOKUP there.
+#define MLP_LOOKUP 0x7ffffu
+#define MLP_LOCAL(inst, eval) (((eval) ? 0x80000u : 0u) | ((unsigned)(inst) < MLP_LOOKUP ? (unsigned)(inst) : MLP_LOOKUP))
 
 // Values of ctl[0] when the kernel stopped itself.
 #define ABORT_WATCHDOG 1u

@@ -142,6 +142,7 @@ struct amp_ctx {
   bool stage_locked = false;
   hipEvent_t ev_begin = nullptr, ev_end = nullptr, ev_chunk[2] = {nullptr, nullptr};
   int cu_count = 0;
+  unsigned launches = 0;       // launches that have come to their end
   bool params_fresh = false;   // the nodes' host copies hold what the device holds
   std::string err;
 };
@@ -171,20 +172,22 @@ const char* arena_name(const amp_ctx* c) {
   return c->static_dev >= 0 ? "the library's built-in arena (amp_create_static)" : "the arena";
 }
 
-// At least `bytes` of host staging memory (contents are lost when it grows).
+// At least `bytes` of host staging memory (contents are lost when it changes).  A context's first call makes do with the
+// heap; one that is used again gets page-locked memory, whose allocation (50 to 100 us) its calls then earn back.
 int need_stage(amp_ctx* c, size_t bytes) {
-  if (c->stage_bytes >= bytes) return AMP_OK;
+  const bool lock = c->static_dev < 0 && c->launches > 0;
+  if (c->stage_bytes >= bytes && (c->stage_locked || !lock)) return AMP_OK;
   if (c->stage) {
     if (c->stage_locked)
       (void)hipHostFree(c->stage);
     else
       std::free(c->stage);
   }
+  bytes = align_up(std::max(bytes, c->stage_bytes), 65536);
   c->stage = nullptr;
   c->stage_bytes = 0;
-  bytes = align_up(bytes, 65536);
   void* p = nullptr;
-  c->stage_locked = c->static_dev < 0 && hipHostMalloc(&p, bytes, hipHostMallocDefault) == hipSuccess;
+  c->stage_locked = lock && hipHostMalloc(&p, bytes, hipHostMallocDefault) == hipSuccess;
   if (!c->stage_locked) {
     (void)hipGetLastError();
     p = std::malloc(bytes);
@@ -197,6 +200,14 @@ int need_stage(amp_ctx* c, size_t bytes) {
 
 constexpr size_t CHUNK = 1u << 20;             // piece of a large copy that goes through the staging memory
 constexpr size_t SMALL_PARAMS = 512u << 10;    // all nodes' parameters up to this size come back in one copy (about 20 us)
+constexpr size_t TINY_PARAMS = 128u << 10;     // up to this size with a training call's results: 3 us there, a wait less later
+
+// The parameters of all nodes as they lie in the arena, from the staging memory into the nodes' host copies.
+void take_params(amp_ctx* c, const char* image) {
+  for (HostNode& o : c->nodes)
+    if (!o.dirty) std::memcpy(o.params.data(), image + (o.off_P - c->par_begin), o.count() * 4);
+  c->params_fresh = true;
+}
 
 // Everything replica r owns in the static part of the arena lies rep_stride bytes after replica r - 1's.
 char* rep_ptr(const amp_ctx* c, int r, size_t off) { return c->arena + (size_t)r * c->rep_stride + off; }
@@ -339,7 +350,11 @@ size_t lds_floats(const amp_ctx* c, HostWorker& w) {
     case ROLE_G_READOUT:
       f = wfl + r4(c->dims.hidden) + AMP_THREADS;
       break;
-    case ROLE_MLP_LIN:   // weights and a gradient accumulator of the same layout
+    case ROLE_MLP_LIN:   // weights in registers and their optimizer slots in LDS, or weights and a gradient accumulator in LDS
+      if (n.rows <= 128 && n.cols <= 128 && 2 * wfl + r4(ldw) + 2 * r4(R) + r4(C) + r4(8 * std::max(R, C)) <= avail) {
+        f = 4 * 128 + 64 + 2 * (128 * 128 + 128) + 32 * 132;
+        break;
+      }
       f = 2 * wfl + r4(ldw) + r4(R) + r4(R) + r4(C) + r4(8 * std::max(R, C));
       break;
     default:   // RNN output layer
@@ -683,7 +698,7 @@ int amp_finalize(amp_ctx* c, int max_active_keys, int max_instance_len, int max_
   if (c->model == AMP_MODEL_MLP) {
     for (int l = 0; l < 3; ++l) add_worker(ROLE_MLP_LIN, l, 0, 1, l);
     for (size_t i = 0; i < c->workers.size(); ++i) c->workers[i].ring = (int)i;
-    nrings = 4;
+    nrings = 6;   // 4, 5: the backward messages of layers 0 and 1
   } else if (c->model == AMP_MODEL_RNN) {
     // rings: 0 controller, 1 cell, 2 output layer, 3.. the cell's further replicas
     add_worker(ROLE_RNN_CELL, 1, 0, 1, 0);
@@ -808,7 +823,7 @@ int amp_finalize(amp_ctx* c, int max_active_keys, int max_instance_len, int max_
     c->off_buf[i] = take(c->buf_bytes[i]);
   };
   if (c->model == AMP_MODEL_MLP) {
-    for (int i = 0; i < 4; ++i) buf(i, H);
+    for (int i = 0; i < 4; ++i) buf(i, r4(H));
   } else if (c->model == AMP_MODEL_RNN) {
     const size_t SP = c->nodes[1].segp;
     buf(0, ((size_t)c->max_len + 1) * SP);
@@ -864,8 +879,6 @@ int amp_finalize(amp_ctx* c, int max_active_keys, int max_instance_len, int max_
   if (c->static_end > c->arena_bytes)
     return fail(c, AMP_ENOMEM, "finalize: %s of %zu bytes is too small, %zu needed before instances", arena_name(c),
                 c->arena_bytes, c->static_end);
-  if (int rc = need_stage(c, std::max(sizeof(AmpDev) * (size_t)c->replicas,
-                                      std::min<size_t>(8 * max_instances + 65536, 16 * CHUNK)))) return rc;
   c->finalized = true;
   c->state_zeroed = false;
   return AMP_OK;
@@ -1030,9 +1043,7 @@ int amp_get_params(amp_ctx* c, int node_id, float* host, size_t cap, size_t* n) 
       if (int rc = need_stage(c, all)) return rc;
       HIPCHK(c, hipMemcpyAsync(c->stage, c->arena + c->par_begin, all, hipMemcpyDeviceToHost, c->stream));
       HIPCHK(c, hipStreamSynchronize(c->stream));
-      for (HostNode& o : c->nodes)
-        if (!o.dirty) std::memcpy(o.params.data(), c->stage + (o.off_P - c->par_begin), o.count() * 4);
-      c->params_fresh = true;
+      take_params(c, c->stage);
     } else {
       return fetch(c, (char*)host, nd.off_P, nd.count() * 4);
     }
@@ -1538,7 +1549,9 @@ int launch_once(amp_ctx* c, const Resident& res, size_t out_begin, int epochs, b
   if (L.end > c->arena_bytes)
     return fail(c, AMP_ENOMEM, "%s of %zu bytes is too small, %zu needed", arena_name(c), c->arena_bytes, L.end);
   const size_t res_bytes = L.res_end - L.res_begin;
-  if (int rc = need_stage(c, std::max(res_bytes, sizeof(AmpDev) * (size_t)R))) return rc;
+  const size_t par_bytes = c->par_end - c->par_begin;
+  const bool params_too = train && R == 1 && c->node_replicas == 1 && par_bytes <= TINY_PARAMS;
+  if (int rc = need_stage(c, std::max(res_bytes + (params_too ? par_bytes : 0), sizeof(AmpDev) * (size_t)R))) return rc;
   amp_ctx::Described& said = c->described[train ? 0 : 1];
   if (adm || said.gen != c->gen || said.out_begin != out_begin || said.epochs != epochs || said.R != R) {
     AmpDev* Ds = (AmpDev*)c->stage;
@@ -1563,7 +1576,10 @@ int launch_once(amp_ctx* c, const Resident& res, size_t out_begin, int epochs, b
   HIPCHK(c, amp_launch(c->model, (const AmpDev*)(c->arena + c->off_devs[train ? 0 : 1]), R, (int)wpr, &args, c->stream));
   HIPCHK(c, hipEventRecord(c->ev_end, c->stream));
   HIPCHK(c, hipMemcpyAsync(c->stage, c->arena + L.res_begin, res_bytes, hipMemcpyDeviceToHost, c->stream));
+  if (params_too)
+    HIPCHK(c, hipMemcpyAsync(c->stage + res_bytes, c->arena + c->par_begin, par_bytes, hipMemcpyDeviceToHost, c->stream));
   HIPCHK(c, hipStreamSynchronize(c->stream));
+  c->launches++;
   float ms = 0;
   HIPCHK(c, hipEventElapsedTime(&ms, c->ev_begin, c->ev_end));
   seconds += ms * 1e-3;
@@ -1587,6 +1603,7 @@ int launch_once(amp_ctx* c, const Resident& res, size_t out_begin, int epochs, b
       return fail(c, AMP_EDEVICE, "kernel stopped itself: %s (replica %d, worker %u)", why, r, ctl[2]);
     }
   }
+  if (params_too) take_params(c, c->stage + res_bytes);
   c->last_stats.assign(NSTAT * wpr * R, 0);
   for (int r = 0; r < R; ++r) {
     std::memcpy(c->last_stats.data() + NSTAT * wpr * r, at(L.off_stats[r]), 8 * NSTAT * wpr);

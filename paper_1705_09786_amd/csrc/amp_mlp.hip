@@ -1,4 +1,6 @@
-// Persistent kernel of the pipelined MLP.
+// Persistent kernel of the pipelined MLP.  256 threads: a message is one small matrix-vector product, most of whose
+// instructions every wave executes whatever its share, so one wave per SIMD gets through it sooner than two.
+#define AMP_THREADS 256
 #include <hip/hip_runtime.h>
 #include "amp_worker.hip.h"
 #include "amp_mlp.hip.h"

@@ -31,8 +31,7 @@ __device__ __forceinline__ bool ctrl_wait(const GQ AmpDev* D, const GQ RingDev& 
   unsigned spins = 0;
   for (;;) {
     const unsigned long long e = __hip_atomic_load(slot, __ATOMIC_RELAXED, AGENT);
-    if ((unsigned)(e >> 32) == want) {
-      fence_acquire();
+    if ((unsigned)(e >> 32) == want) {   // the controller reads nothing of a payload: no acquire
       code = (unsigned)e;
       head++;
       return true;
@@ -71,7 +70,9 @@ __device__ __noinline__ void role_ctrl(const GQ AmpDev* D, const GQ WorkerDev* W
     unsigned in_order = 0;   // without an admission list: the data set's instances in order, over and over
     // Synchronisation of a replicated node's copies (Section 5): after every sync_every retirements a request goes to
     // every copy's ring; a new round waits until every copy has reported that it loaded the previous one.
-    const int NR = D->model == 2 ? D->node_replicas : 1;
+    const int model = D->model;
+    const Ring first = ring_regs(D, 1);
+    const int NR = model == 2 ? D->node_replicas : 1;
     const unsigned sync_every = NR > 1 ? (unsigned)D->sync_every : 0u;
     unsigned sync_round = 0, sync_due = 0;
     int sync_acks = NR;
@@ -90,7 +91,7 @@ __device__ __noinline__ void role_ctrl(const GQ AmpDev* D, const GQ WorkerDev* W
         D->slot_seq[s] = seq;
         D->slot_inst[s] = word;
         log_event(D, W, &s_logn, 0, 3, seq, word < 0 ? 1u : 0u);
-        if (D->model == 3) {
+        if (model == 3) {
           // tree: the slot's instance facts for the workers, then one token message per leaf to the lookup (worker 1)
           const int toff = D->data.tok_off[inst], L = D->data.tok_off[inst + 1] - toff;
           int* sm = D->smeta + 4 * s;
@@ -102,7 +103,7 @@ __device__ __noinline__ void role_ctrl(const GQ AmpDev* D, const GQ WorkerDev* W
           const unsigned t = ring_reserve(D->ring[1], L);
           for (int l = 0; l < L; ++l) ring_put(D->ring[1], t + l, MSG_MAKE(0, s, l));
         } else {
-          if (D->model == 2) {
+          if (model == 2) {
             // RNN: admission number, length, instance, token offset
             const int toff = D->data.tok_off[inst];
             int* sm = D->smeta + 4 * s;
@@ -112,9 +113,14 @@ __device__ __noinline__ void role_ctrl(const GQ AmpDev* D, const GQ WorkerDev* W
             sm[3] = toff;
           }
           fence_release();
-          // RNN with a replicated cell: the Cond in front of the copies routes on the admission number
-          const int rep = D->model == 2 ? (int)(seq % (unsigned)D->node_replicas) : 0;
-          ring_post(D->ring[rep == 0 ? 1 : 2 + rep], MSG_MAKE(0, s, 0));
+          if (model == 1) {
+            // MLP: the message carries the instance; this is the ring's only producer
+            ring_put(first, next, MSG_MAKE(0, s, MLP_LOCAL(inst, word < 0)));
+          } else {
+            // RNN with a replicated cell: the Cond in front of the copies routes on the admission number
+            const int rep = model == 2 ? (int)(seq % (unsigned)D->node_replicas) : 0;
+            ring_post(D->ring[rep == 0 ? 1 : 2 + rep], MSG_MAKE(0, s, 0));
+          }
         }
         next++;
         active++;
