@@ -4,11 +4,25 @@
 #include "amp_batch.hip.h"
 #include "amp_tree.hip.h"
 #include "amp_rnn.hip.h"
+#include "amp_rnn_cell.hip.h"
 
 static __device__ __forceinline__ void rnn_worker(const GQ AmpDev* D, const GQ WorkerDev* W) {
   if (W->role == ROLE_RNN_CELL) {
+    // weights in registers wherever the rest fits the LDS (the threshold and the table decide; the choice is made anew
+    // in every launch, and what is carried over between launches has one layout)
+    if (rnn_reg_fits(D, W)) {
+      const bool sgd = D->node[W->node].opt == 0, sync = D->node_replicas > 1 && D->sync_every > 0;
+      if (sgd && !sync)
+        role_rnn_cell_reg<true, false>(D, W);
+      else if (sgd)
+        role_rnn_cell_reg<true, true>(D, W);
+      else if (!sync)
+        role_rnn_cell_reg<false, false>(D, W);
+      else
+        role_rnn_cell_reg<false, true>(D, W);
+    }
     // hidden = emb = 128 (8 row blocks, 16 column groups) has products with fixed trip counts
-    if (D->node[1].rows == 128 && D->node[1].cols == 256 && D->node[1].seg0 == 128)
+    else if (D->node[1].rows == 128 && D->node[1].cols == 256 && D->node[1].seg0 == 128)
       role_rnn_cell<8, 16>(D, W);
     else
       role_rnn_cell<0, 0>(D, W);
