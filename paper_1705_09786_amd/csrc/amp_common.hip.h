@@ -14,6 +14,7 @@
 // HBM pointers to GQ (global) and LDS pointers to LDSQ.
 #define GQ __attribute__((address_space(1)))
 #define LDSQ __attribute__((address_space(3)))
+typedef float v2f __attribute__((ext_vector_type(2)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef int v4i __attribute__((ext_vector_type(4)));
 

@@ -11,15 +11,11 @@ static __device__ __forceinline__ void rnn_worker(const GQ AmpDev* D, const GQ W
     // weights in registers wherever the rest fits the LDS (the threshold and the table decide; the choice is made anew
     // in every launch, and what is carried over between launches has one layout)
     if (rnn_reg_fits(D, W)) {
-      const bool sgd = D->node[W->node].opt == 0, sync = D->node_replicas > 1 && D->sync_every > 0;
-      if (sgd && !sync)
-        role_rnn_cell_reg<true, false>(D, W);
-      else if (sgd)
-        role_rnn_cell_reg<true, true>(D, W);
-      else if (!sync)
-        role_rnn_cell_reg<false, false>(D, W);
+      const int opt = D->node[W->node].opt;
+      if (D->node_replicas > 1 && D->sync_every > 0)
+        opt == 0 ? role_rnn_cell_reg<0, true>(D, W) : opt == 1 ? role_rnn_cell_reg<1, true>(D, W) : role_rnn_cell_reg<2, true>(D, W);
       else
-        role_rnn_cell_reg<false, true>(D, W);
+        opt == 0 ? role_rnn_cell_reg<0, false>(D, W) : opt == 1 ? role_rnn_cell_reg<1, false>(D, W) : role_rnn_cell_reg<2, false>(D, W);
     }
     // hidden = emb = 128 (8 row blocks, 16 column groups) has products with fixed trip counts
     else if (D->node[1].rows == 128 && D->node[1].cols == 256 && D->node[1].seg0 == 128)

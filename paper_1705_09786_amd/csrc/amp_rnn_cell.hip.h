@@ -22,15 +22,19 @@
 #pragma once
 
 #define RC_KB 16      // sequences in the worker's hands at a time
-#define RC_LDX 272    // input rows: embedding at 0, previous output at 128; 16 modulo the 64 banks, so that four messages' reads spread
+#define RC_LDX 144    // rows of the previous output: 16 modulo the 64 banks, so that four messages' reads spread
 #define RC_LDD 144    // delta rows, the same
 #define RC_PS 384     // a pending pair: delta (128), input (256)
 #define RC_TB 1088    // a wave's 16 x 68 floats for turning its weights from one layout into the other
 #define RC_H 128      // where an input row's second segment starts
 
+// Row stride of the table and its gradient: whole 64-wide pieces, zero beyond the embedding, so that the forward product
+// takes its operands straight from a token's row.
+__device__ __forceinline__ int rnn_reg_ldt(int E) { return ((E + 63) & ~63) + 16; }
+
 // LDS floats of this worker with room for `pairs` pending pairs.
 __device__ __forceinline__ int rnn_reg_floats(int V, int E, int pairs) {
-  return 2 * ((V * E + 3) & ~3) + RC_KB * (RC_LDX + RC_LDD) + 8 * RC_TB + 128 + pairs * RC_PS;
+  return 2 * V * rnn_reg_ldt(E) + RC_KB * (RC_LDX + RC_LDD) + 128 + 8 * RC_TB + 128 + pairs * RC_PS;
 }
 __device__ __forceinline__ int rnn_reg_pairs(const GQ NodeDev& nd, const GQ WorkerDev* W) {
   const int held = (int)W->wstate[0] + 1;   // pairs carried over from the previous launch, and room for one more
@@ -127,31 +131,45 @@ __device__ __forceinline__ void rnn_reg_sgd(float (&wb)[64], const LDSQ float* d
   for (int j = 0; j < 32; ++j) wb[16 * Q + j] -= sc * acc[j >> 2][j & 3];
 }
 
-// Momentum / Adam on 16 rows: the slots are in HBM, consecutive lanes = consecutive columns, and arrive while the
-// gradient is formed.
-template <int Q>
-__device__ __forceinline__ void rnn_reg_slots(float (&wb)[64], const LDSQ float* dp, const LDSQ float* xp, int count, float inv,
-                                              const OptCoef& o, GQ float* Mq, GQ float* Vq, int row0, int rows, int cols, int ncol) {
+// Momentum (OPT 1) / Adam (OPT 2).  The slots are in HBM, consecutive lanes = consecutive columns.  They arrive while the
+// first gradient is formed, as many rows' together as the registers hold -- all 64 for momentum, 32 for Adam: a fetch
+// behind another row's store would wait for that store.
+template <int OPT, int R0, int NR>
+__device__ __forceinline__ void rnn_reg_fetch(float (&m)[NR], float (&v)[NR], const GQ float* Mq, const GQ float* Vq, int row0, int rows,
+                                              int cols, int col) {
+#pragma unroll
+  for (int j = 0; j < NR; ++j) {
+    const int at = (row0 + R0 + j < rows ? row0 + R0 + j : rows - 1) * cols + col;
+    m[j] = Mq[at];
+    if (OPT == 2) v[j] = Vq[at];
+  }
+}
+
+// One optimizer step on rows 16 Q .. + 15, whose slots are m[J0 ..], v[J0 ..].
+template <int OPT, int Q, int J0, int NR>
+__device__ __forceinline__ void rnn_reg_step(float (&wb)[64], float (&m)[NR], float (&v)[NR], const LDSQ float* dp, const LDSQ float* xp,
+                                             int count, float inv, const OptCoef& o, GQ float* Mq, GQ float* Vq, int row0, int rows,
+                                             int cols, int ncol) {
   const int r0 = row0 + 16 * Q;
   if (r0 >= rows) return;
   const v4f zero = {0.f, 0.f, 0.f, 0.f};
   v4f acc[8] = {zero, zero, zero, zero, zero, zero, zero, zero};
-  const int col = ncol >= 0 ? ncol : 0;
-  float m[16], v[16];
-#pragma unroll
-  for (int j = 0; j < 16; ++j) {
-    const int at = (r0 + j < rows ? r0 + j : rows - 1) * cols + col;
-    m[j] = Mq[at];
-    v[j] = o.kind == 2 ? Vq[at] : 0.f;
-  }
   rnn_reg_gradient<Q, 1>(acc, dp, xp, count);
+  if (J0 == 0) {   // every slot is there before the first is stored
+#pragma unroll
+    for (int j = 0; j < NR; ++j) {
+      asm volatile("" : "+v"(m[j]));
+      if (OPT == 2) asm volatile("" : "+v"(v[j]));
+    }
+  }
   if (ncol >= 0) {
 #pragma unroll
     for (int j = 0; j < 16; ++j)
       if (r0 + j < rows) {
-        wb[16 * Q + j] = opt_step(o, wb[16 * Q + j], acc[(4 * Q + (j >> 2)) & 7][j & 3] * inv, m[j], v[j]);
-        Mq[(r0 + j) * cols + col] = m[j];
-        if (o.kind == 2) Vq[(r0 + j) * cols + col] = v[j];
+        float none = 0.f;
+        wb[16 * Q + j] = opt_step(o, wb[16 * Q + j], acc[(4 * Q + (j >> 2)) & 7][j & 3] * inv, m[J0 + j], OPT == 2 ? v[J0 + j] : none);
+        Mq[(r0 + j) * cols + ncol] = m[J0 + j];
+        if (OPT == 2) Vq[(r0 + j) * cols + ncol] = v[J0 + j];
       }
   }
 }
@@ -170,9 +188,9 @@ __device__ __forceinline__ int rnn_reg_here_s(int v) {   // the same in a scalar
 
 __shared__ unsigned s_rc_ctl;   // a request to the worker itself (message code), taken between two batches; 0 = none
 
-// SGD: plain SGD, no optimizer slots.  SYNC: the launch may send synchronisation requests to the cell's copies.  Both are
+// OPT: the node's optimizer.  SYNC: the launch may send synchronisation requests to the cell's copies.  Both are
 // compiled apart because the weights leave half of the registers: what a launch does not use would cost it spills.
-template <bool SGD, bool SYNC>
+template <int OPT, bool SYNC>
 __device__ __noinline__ void role_rnn_cell_reg(const GQ AmpDev* D, const GQ WorkerDev* W) {
   const int nc = uni(W->node), nl = nc - 1;   // the cell's node and the table's (1 and 0; a copy's own pair)
   const GQ NodeDev& nd = D->node[nc];
@@ -184,8 +202,10 @@ __device__ __noinline__ void role_rnn_cell_reg(const GQ AmpDev* D, const GQ Work
   const int H = t.R, E = uni(D->emb), V = uni(D->vocab), C = t.C, SP = B.SP;
   const int tid0 = threadIdx.x, lane0 = tid0 & 63, wave = uni(tid0 >> 6), wa = wave >> 2, wc = wave & 3;
   Lds L{amp_lds};
-  LDSQ float* Tab = (LDSQ float*)L.take(V * E);
-  LDSQ float* Gk = (LDSQ float*)L.take(V * E);
+  const int ldt = rnn_reg_ldt(E), NT = V * ldt;
+  LDSQ float* Tab = (LDSQ float*)L.take(NT);
+  LDSQ float* Gk = (LDSQ float*)L.take(NT);
+  LDSQ float* Z = (LDSQ float*)L.take(128);   // the zero state a sequence starts from
   LDSQ float* X = (LDSQ float*)L.take(RC_KB * RC_LDX);
   LDSQ float* Dl = (LDSQ float*)L.take(RC_KB * RC_LDD);   // gradient w.r.t. the hidden state; in a backward step the delta
   LDSQ float* P = (LDSQ float*)L.take(8 * RC_TB);         // parts of the products; between batches the waves' turning space
@@ -220,11 +240,13 @@ __device__ __noinline__ void role_rnn_cell_reg(const GQ AmpDev* D, const GQ Work
     wb[r] = row < H && ncol >= 0 ? ndP[row * C + ncol] : 0.f;
   }
   rnn_reg_turn(wb, wf, tb);
-  for (int i = tid0; i < V * E; i += AMP_THREADS) {
-    Tab[i] = lkP[i];
-    Gk[i] = lkG[i];
+  for (int i = tid0; i < NT; i += AMP_THREADS) {
+    const int r = i / ldt, c = i - r * ldt;
+    Tab[i] = c < E ? lkP[r * E + c] : 0.f;
+    Gk[i] = c < E ? lkG[r * E + c] : 0.f;
   }
-  for (int i = tid0; i < RC_KB * RC_LDX; i += AMP_THREADS) X[i] = 0.f;
+  if (tid0 < 128) Z[tid0] = 0.f;
+  for (int i = tid0; i < RC_KB * RC_LDX; i += AMP_THREADS) X[i] = 0.f;   // beyond the hidden size it stays zero
   for (int i = tid0; i < RC_KB * RC_LDD; i += AMP_THREADS) Dl[i] = 0.f;
   if (tid0 < 128) bl[tid0] = tid0 < H && has_bias ? ndP[H * C + tid0] : 0.f;
   // pairs carried over from the previous launch (HBM layout: [delta (Rp) | input in the node's column layout])
@@ -425,7 +447,10 @@ __device__ __noinline__ void role_rnn_cell_reg(const GQ AmpDev* D, const GQ Work
         for (int r = 0; r < 64; ++r)
           if (r0 + r < H && ncol >= 0) cS[(r0 + r) * C + ncol] = wb[r];
         if (has_bias && tid < H) cS[H * C + tid] = bl[tid];
-        for (int i = tid; i < V * E; i += AMP_THREADS) lS[i] = Tab[i];
+        for (int i = tid; i < V * E; i += AMP_THREADS) {
+          const int r = i / E;
+          lS[i] = Tab[r * ldt + i - r * E];
+        }
         LOG(nl, 5, rnd, 0);
         LOG(nc, 5, rnd, 0);
         publish_barrier();
@@ -454,7 +479,9 @@ __device__ __noinline__ void role_rnn_cell_reg(const GQ AmpDev* D, const GQ Work
         for (int i = tid; i < V * E; i += AMP_THREADS) {
           float m = 0.f;
           for (int q = 0; q < NR; ++q) m += lS0[q * lstr + i];
-          Tab[i] = m * inv + (Tab[i] - lS[i]);
+          const int r = i / E;
+          LDSQ float* w = Tab + r * ldt + i - r * E;
+          *w = m * inv + (*w - lS[i]);
         }
         rnn_reg_turn(wb, wf, tb);
         LOG(nl, 6, rnd, 0);
@@ -490,22 +517,15 @@ __device__ __noinline__ void role_rnn_cell_reg(const GQ AmpDev* D, const GQ Work
       }
     }
     if (nF > 0) {
-      // lookup: the token's row as the table stands now, recorded for the backward pass
-      for (int i = tid; i < nF * 128; i += AMP_THREADS) {
-        const int k = uni(M.fidx[i >> 7]), c = i & 127;
-        LDSQ float* x = X + k * RC_LDX + c;
-        const float v = c < E ? Tab[uni(M.a[k]) * E + c] : 0.f;
-        *x = v;
-        if (uni(M.aux[k])) x[RC_H] = 0.f;   // a sequence's first step starts from zero
-        if (c < E) B.es[B.erow(uni(M.s[k]), uni(M.n[k])) + c] = v;
-      }
-      lds_barrier();
       // parts over the column pieces: P[piece][message][128 rows]
       if (on)
         for (int m0 = 0; m0 < nF; m0 += 4) {
           int mi = m0 + (lane & 3);
           if (mi > nF - 1) mi = nF - 1;   // rows beyond the batch repeat its last message; their results are dropped
-          const v4f r = rnn_reg_dot(wf, X + M.fidx[mi] * RC_LDX + 64 * wc + (lane >> 2));
+          const int k = M.fidx[mi];
+          // lookup: the token's row as the table stands now; a sequence's first step starts from the zero state
+          const LDSQ float* x = wc < 2 ? Tab + M.a[k] * ldt + 64 * wc : (M.aux[k] ? Z : X + k * RC_LDX) + 64 * (wc - 2);
+          const v4f r = rnn_reg_dot(wf, x + (lane >> 2));
 #pragma unroll
           for (int e = 0; e < 4; ++e) P[(wc * RC_KB + m0 + e) * 128 + 64 * wa + lane] = r[e];
         }
@@ -520,17 +540,28 @@ __device__ __noinline__ void role_rnn_cell_reg(const GQ AmpDev* D, const GQ Work
     PHASE(2);
     if (nF > 0) {
       lds_barrier();
-      for (int i = tid; i < nF * 128; i += AMP_THREADS) {
-        const int g = i >> 7, c = i & 127;
-        if (c < H) {
-          const int k = uni(M.fidx[g]);
-          float z = bl[c];
-          for (int b = 0; b < nE; ++b) z += P[(b * RC_KB + g) * 128 + c];
-          for (int b = 2; b < 2 + nH; ++b) z += P[(b * RC_KB + g) * 128 + c];
-          const float y = tanhf(z);
-          X[k * RC_LDX + RC_H + c] = y;
-          B.hs[B.hrow(uni(M.s[k]), uni(M.n[k]) + 1) + c] = y;
+      // a wave per message, two units a lane; the token's row is recorded for the backward pass on the way
+      for (int g = wave; g < nF; g += AMP_THREADS / 64) {
+        const int k = uni(M.fidx[g]), ks = uni(M.s[k]), kt = uni(M.n[k]), c = 2 * lane;
+        const v2f ev = *(const LDSQ v2f*)(Tab + uni(M.a[k]) * ldt + (c < ldt ? c : 0));
+        v2f z = *(const LDSQ v2f*)(bl + c);
+        for (int b = 0; b < nE; ++b) z += *(const LDSQ v2f*)(P + (b * RC_KB + g) * 128 + c);
+        for (int b = 2; b < 2 + nH; ++b) z += *(const LDSQ v2f*)(P + (b * RC_KB + g) * 128 + c);
+        const v2f y = {tanhf(z.x), tanhf(z.y)};
+        LDSQ float* x = X + k * RC_LDX + c;
+        GQ float* hr = B.hs + B.hrow(ks, kt + 1) + c;
+        GQ float* er = B.es + B.erow(ks, kt) + c;
+        if (c + 1 < H) {
+          *(LDSQ v2f*)x = y;
+          *(GQ v2f*)hr = y;
+        } else if (c < H) {
+          *x = y.x;
+          *hr = y.x;
         }
+        if (c + 1 < E)
+          *(GQ v2f*)er = ev;
+        else if (c < E)
+          *er = ev.x;
       }
     }
     PHASE(3);
@@ -580,27 +611,34 @@ __device__ __noinline__ void role_rnn_cell_reg(const GQ AmpDev* D, const GQ Work
     PHASE(5);
     if (nB > 0) {
       lds_barrier();
+      // wave 0 and 1: the lookup's gradient, in arrival order: column c of every row belongs to thread c, no other thread
+      // touches it (LDS float additions in place of read and write were slower: 1.9 instead of 1.1 us for this phase)
       if (tid < 128) {
-        // the lookup's gradient, in arrival order: column c of every row belongs to thread c, no other thread touches it
-        if (tid < E) {
-          for (int k0 = 0; k0 < nB; k0 += 8) {
-            float d[8];
-            int a[8];
+        for (int k0 = 0; k0 < nB; k0 += 8) {   // eight rows' fetches are in flight together
+          float d[8];
+          int at[8];
 #pragma unroll
-            for (int k = 0; k < 8; ++k) {
-              const int kk = k0 + k < nB ? k0 + k : k0;
-              d[k] = P[kk * 256 + tid] + (nH > 1 ? P[(RC_KB + kk) * 256 + tid] : 0.f);
-              a[k] = M.a[M.bidx[kk]];
-            }
+          for (int k = 0; k < 8; ++k) at[k] = M.bidx[k0 + k < nB ? k0 + k : k0];
+#pragma unroll
+          for (int k = 0; k < 8; ++k) {
+            const int kk = k0 + k < nB ? k0 + k : k0;
+            at[k] = M.a[at[k]] * ldt + tid;
+            d[k] = P[kk * 256 + tid];
+            if (nH > 1) d[k] += P[(RC_KB + kk) * 256 + tid];
+          }
+          if (tid < E) {
 #pragma unroll
             for (int k = 0; k < 8; ++k)
-              if (k0 + k < nB) Gk[a[k] * E + tid] += d[k];
+              if (k0 + k < nB) Gk[at[k]] += d[k];
           }
         }
       } else {
-        for (int i = tid - 128; i < nB * 128; i += AMP_THREADS - 128) {
-          const int k = i >> 7, c = i & 127;
-          if (c < H) Dl[M.bidx[k] * RC_LDD + c] = P[k * 256 + RC_H + c] + (nH > 1 ? P[(RC_KB + k) * 256 + RC_H + c] : 0.f);
+        // the other six: what travels down the loop
+        for (int k = wave - 2; k < nB; k += AMP_THREADS / 64 - 2) {
+          const int c = 2 * lane;
+          v2f d = *(const LDSQ v2f*)(P + k * 256 + RC_H + c);
+          if (nH > 1) d += *(const LDSQ v2f*)(P + (RC_KB + k) * 256 + RC_H + c);
+          *(LDSQ v2f*)(Dl + uni(M.bidx[k]) * RC_LDD + c) = d;   // beyond the hidden size: dropped when the delta is formed
         }
       }
     }
@@ -621,21 +659,28 @@ __device__ __noinline__ void role_rnn_cell_reg(const GQ AmpDev* D, const GQ Work
       // the cell's own update (Section 3)
       tstep++;
       if (bounded && tid == 0) note_update(D);
-      const OptCoef o = opt_at(ob, tstep);
+      OptCoef o = opt_at(ob, tstep);
+      o.kind = OPT;
       const float inv = nd_mean ? 1.f / (float)count : 1.f;
       const LDSQ float* dp = Q + 64 * wa + lane;
       const LDSQ float* xp = Q + 128 + 64 * wc + lane;
       if (on) {
-        if (SGD) {
+        if (OPT == 0) {
           rnn_reg_sgd<0>(wb, dp, xp, (int)count, o.lr * inv);
           rnn_reg_sgd<2>(wb, dp, xp, (int)count, o.lr * inv);
         } else {
-          const int r0 = rnn_reg_here_s(64 * wa);
-          rnn_reg_slots<0>(wb, dp, xp, (int)count, inv, o, ndM, ndV, r0, H, C, ncol);
-          rnn_reg_slots<1>(wb, dp, xp, (int)count, inv, o, ndM, ndV, r0, H, C, ncol);
-          rnn_reg_slots<2>(wb, dp, xp, (int)count, inv, o, ndM, ndV, r0, H, C, ncol);
-          rnn_reg_slots<3>(wb, dp, xp, (int)count, inv, o, ndM, ndV, r0, H, C, ncol);
+          constexpr int NR = OPT == 1 ? 64 : 32;
+          const int r0 = rnn_reg_here_s(64 * wa), col = ncol >= 0 ? ncol : 0;
+          float m[NR], v[NR];
+          rnn_reg_fetch<OPT, 0>(m, v, ndM, ndV, r0, H, C, col);
+          rnn_reg_step<OPT, 0, 0>(wb, m, v, dp, xp, (int)count, inv, o, ndM, ndV, r0, H, C, ncol);
+          rnn_reg_step<OPT, 1, 16>(wb, m, v, dp, xp, (int)count, inv, o, ndM, ndV, r0, H, C, ncol);
+          if (OPT == 2 && r0 + 32 < H) rnn_reg_fetch<OPT, 32>(m, v, ndM, ndV, r0, H, C, col);
+          rnn_reg_step<OPT, 2, 32 % NR>(wb, m, v, dp, xp, (int)count, inv, o, ndM, ndV, r0, H, C, ncol);
+          rnn_reg_step<OPT, 3, 48 % NR>(wb, m, v, dp, xp, (int)count, inv, o, ndM, ndV, r0, H, C, ncol);
         }
+        // (forming the row-per-lane copy's gradient by a second pass of products instead spilled, and was slower: 115 against
+        // 102 ms for 4,000 sequences)
         rnn_reg_turn(wb, wf, tb);
       }
       // the bias, by the last two waves
@@ -654,9 +699,10 @@ __device__ __noinline__ void role_rnn_cell_reg(const GQ AmpDev* D, const GQ Work
       lstep++;
       if (bounded && tid == 0) note_update(D);
       const float sc = lk_lr * (lk_mean ? 1.f / (float)lcount : 1.f);
-      for (int i = tid; i < V * E; i += AMP_THREADS) {
-        Tab[i] -= sc * Gk[i];
-        Gk[i] = 0.f;
+      // by the waves that have no bias to update; the padding's gradient is zero
+      for (int i = 4 * tid; tid < AMP_THREADS - 128 && i < NT; i += 4 * (AMP_THREADS - 128)) {
+        *(LDSQ v4f*)(Tab + i) -= sc * *(const LDSQ v4f*)(Gk + i);
+        *(LDSQ v4f*)(Gk + i) = (v4f){0.f, 0.f, 0.f, 0.f};
       }
       lcount = 0;
       LOG(nl, 2, 0, 0);
@@ -681,8 +727,9 @@ __device__ __noinline__ void role_rnn_cell_reg(const GQ AmpDev* D, const GQ Work
     endG[H * C + tid0] = g;
   }
   for (int i = tid0; i < V * E; i += AMP_THREADS) {
-    tabP[i] = Tab[i];
-    tabG[i] = Gk[i];
+    const int r = i / E, at = r * ldt + i - r * E;
+    tabP[i] = Tab[at];
+    tabG[i] = Gk[at];
   }
   for (int i = tid0; i < (int)count * pd.stride; i += AMP_THREADS) {
     const int k = i / pd.stride, j = i - k * pd.stride, lc = j - pd.Rp;
