@@ -22,6 +22,8 @@ static __device__ __forceinline__ void rnn_worker(const GQ AmpDev* D, const GQ W
       role_rnn_cell<8, 16>(D, W);
     else
       role_rnn_cell<0, 0>(D, W);
+  } else if (rnn_out_fits(D)) {
+    role_rnn_out_batch(D, W);
   } else {
     role_rnn_out(D, W);
   }

@@ -368,7 +368,222 @@ __device__ __noinline__ void role_rnn_cell(const GQ AmpDev* D, const GQ WorkerDe
   }
 }
 
-// Output layer + softmax loss of the RNN: forward and backward in one event.
+// Output layer + softmax loss of the RNN: forward and backward in one event.  The messages that wait are taken
+// together (cut where an update falls due): what bounds a message taken alone is the chain of fetches and barriers --
+// 6 us, at which eight copies of the cell saturated this worker -- and a batch goes through that chain once.  The
+// gradient is accumulated in registers, messages in ring order.
+#define RO_KB 16   // messages at once
+#define RO_NE 12   // accumulator elements per thread: n_class * hidden <= 12 * 512
+
+__device__ __forceinline__ bool rnn_out_fits(const GQ AmpDev* D) {
+  const GQ NodeDev& nd = D->node[2];
+  const int Rp = amp_round16(nd.rows), ldw = amp_ldrow(nd.cols);
+  return nd.rows <= 64 && nd.rows * nd.cols <= RO_NE * AMP_THREADS && Rp * ldw + Rp + RO_KB * (D->node[1].segp + 64) <= AMP_DYN_LDS_BYTES / 4;
+}
+
+__device__ __noinline__ void role_rnn_out_batch(const GQ AmpDev* D, const GQ WorkerDev* W) {
+  const GQ NodeDev& nd = D->node[2];
+  const Tile t = make_tile(nd, W);
+  const RnnBufs B = rnn_bufs(D);
+  const int R = t.R, C = t.C, SP = B.SP, ldw = t.ldw, nd_muf = uni(nd.muf), NR = uni(D->node_replicas);
+  const bool train = uni(D->train) != 0;
+  const GQ int* smeta = uni_gq<int>(D->smeta);
+  const GQ int* slot_inst = uni_gq<int>(D->slot_inst);
+  const GQ int* lab = uni_gq<int>(D->data.lab);
+  const GQ int* lab_off = uni_gq<int>(D->data.lab_off);
+  GQ float* loss_out = uni_gq<float>(D->loss_out);
+  GQ int* correct_out = uni_gq<int>(D->correct_out);
+  GQ float* ndG = uni_gq<float>(nd.G);
+  GQ float* ndM = uni_gq<float>(nd.M);
+  GQ float* ndV = uni_gq<float>(nd.V);
+  Lds L{amp_lds};
+  float* Wg = L.take(t.Rp * ldw);
+  float* bg = L.take(t.Rp);
+  LDSQ float* Wl = (LDSQ float*)Wg;
+  LDSQ float* bl = (LDSQ float*)bg;
+  LDSQ float* hbuf = (LDSQ float*)L.take(RO_KB * SP);   // per message: the cell's last output
+  LDSQ float* zbuf = (LDSQ float*)L.take(RO_KB * 64);   // per message: logits, then their gradient
+  tile_load(nd, t, Wg, bg);
+  // this thread's accumulator elements e = threadIdx.x + 512 j, and the bias gradient of row threadIdx.x
+  float gacc[RO_NE], gb = (int)threadIdx.x < R ? ndG[R * C + threadIdx.x] : 0.f;
+  int er[RO_NE], ec[RO_NE];
+#pragma unroll
+  for (int j = 0; j < RO_NE; ++j) {
+    const int e = threadIdx.x + AMP_THREADS * j;
+    er[j] = e < R * C ? e / C : -1;
+    ec[j] = e < R * C ? e - (e / C) * C : 0;
+    gacc[j] = er[j] >= 0 ? ndG[e] : 0.f;
+  }
+  const OptCoef ob = opt_base(nd);
+  const bool mean = uni(nd.mean) != 0;
+  BatchMsg& M = s_M;
+  __syncthreads();
+  const Ring mine = ring_regs(D, uni(W->ring)), ctl = ring_regs(D, 0);
+  unsigned head = 0, count = uni(W->wstate[0]), tstep = uni(W->wstate[1]);
+  for (;;) {
+    const int n = wait_batch(D, mine, head, RO_KB, train ? nd_muf - (int)count : RO_KB, s_codes, &s_n, [](unsigned) { return true; });
+    if (n == 0) break;
+    if (threadIdx.x < 64) {
+      const int k = threadIdx.x;
+      const bool in = k < n;
+      bool tr = false;
+      if (in) {
+        const int s = MSG_SLOT(s_codes[k]);
+        const v4i sm = *(const GQ v4i*)(smeta + 4 * s);   // admission number, length, instance, -
+        tr = train && slot_inst[s] >= 0;
+        M.s[k] = s;
+        M.seq[k] = (unsigned)sm.x;
+        M.L[k] = sm.y;
+        M.aux[k] = tr;
+        M.a[k] = lab[lab_off[sm.z]];
+        M.off0[k] = (int)B.hrow(s, sm.y);
+      }
+      const unsigned long long mt = __ballot(tr);
+      if (k == 0) M.nB = __popcll(mt);
+      // a training message is a forward and a backward event (the loss turns it round), an evaluation one a forward event
+      if (s_log_cap) {
+        const unsigned base = s_logn, at = base + (unsigned)k + (unsigned)__popcll(mt & ((1ull << k) - 1ull));
+        const unsigned total = (unsigned)n + (unsigned)__popcll(mt);
+        GQ unsigned long long* logp = (GQ unsigned long long*)s_log_ptr;
+        if (base + total > s_log_cap) {
+          if (k == 0) raise_abort(D, ABORT_LOG_FULL, blockIdx.x);
+        } else {
+          if (in) {
+            const unsigned long long tail = ((unsigned long long)M.seq[k] << 32) | (2ull << 20);
+            logp[at] = tail;
+            if (tr) logp[at + 1] = tail | (1ull << 28);
+          }
+          if (k == 0) s_logn = base + total;
+        }
+      }
+    }
+    lds_barrier();
+    const int nB = uni(M.nB);
+    for (int idx = threadIdx.x; idx < n * (SP >> 2); idx += AMP_THREADS) {
+      const int k = idx / (SP >> 2), c = (idx - k * (SP >> 2)) << 2;
+      *(LDSQ v4f*)(hbuf + k * SP + c) = *(const GQ v4f*)(B.hs + M.off0[k] + c);
+    }
+    lds_barrier();
+    // logits: four lanes share a row, every fourth column each
+    for (int idx = threadIdx.x; idx < ((n * R * 4 + 63) & ~63); idx += AMP_THREADS) {
+      const int o = idx >> 2, p = idx & 3, k = o / R, r = o - k * R;
+      const bool in = o < n * R;
+      const LDSQ float* w = Wl + (in ? r : 0) * ldw;
+      const LDSQ float* h = hbuf + (in ? k : 0) * SP;
+      float a0 = 0.f, a1 = 0.f;
+      int c = p;
+      for (; c + 4 < C; c += 8) {
+        a0 = fmaf(w[c], h[c], a0);
+        a1 = fmaf(w[c + 4], h[c + 4], a1);
+      }
+      if (c < C) a0 = fmaf(w[c], h[c], a0);
+      float a = a0 + a1;
+      a += __shfl_xor(a, 1);
+      a += __shfl_xor(a, 2);
+      if (in && p == 0) zbuf[k * 64 + r] = a + bl[r];
+    }
+    lds_barrier();
+    // softmax cross-entropy per message; z becomes p - onehot(label)
+    if ((int)threadIdx.x < n) {
+      const int k = threadIdx.x, label = M.a[k];
+      LDSQ float* z = zbuf + k * 64;
+      float m = z[0];
+      int am = 0;
+      for (int r = 1; r < R; ++r)
+        if (z[r] > m) {
+          m = z[r];
+          am = r;
+        }
+      const float zl = z[label];
+      float se = 0.f;
+      for (int r = 0; r < R; ++r) {
+        const float e = expf(z[r] - m);
+        z[r] = e;
+        se += e;
+      }
+      // zero for an evaluation instance, which then adds nothing to the gradient sums below
+      const bool tr = M.aux[k] != 0;
+      for (int r = 0; r < R; ++r) z[r] = tr ? z[r] / se - (r == label ? 1.f : 0.f) : 0.f;
+      const unsigned idx = M.seq[k] - s_first_seq;
+      loss_out[idx] = -(zl - m - logf(se));
+      correct_out[idx] = am == label;
+    }
+    if (nB > 0) {
+      lds_barrier();
+      // the gradient w.r.t. the cell's output
+      for (int idx = threadIdx.x; idx < n * C; idx += AMP_THREADS) {
+        const int k = idx / C, c = idx - k * C;
+        if (M.aux[k]) {
+          const LDSQ float* z = zbuf + k * 64;
+          float a = 0.f;
+          for (int r = 0; r < R; ++r) a = fmaf(Wl[r * ldw + c], z[r], a);
+          B.dh[(long long)M.s[k] * SP + c] = a;
+        }
+      }
+    }
+    // every wave's HBM stores have landed before wave 0 publishes the batch
+    publish_barrier();
+    if (threadIdx.x < 64) {
+      fence_release();
+      const int k = threadIdx.x;
+      if (k < n) {
+        if (M.aux[k]) {
+          // back to the copy of the cell that ran this instance forward (ring 1, or 2 + r for copy r >= 1)
+          const int rep = NR > 1 ? (int)(M.seq[k] % (unsigned)NR) : 0;
+          ring_post(D->ring[rep == 0 ? 1 : 2 + rep], MSG_MAKE(1, M.s[k], M.L[k] - 1));
+        } else {
+          ring_post(ctl, MSG_MAKE(1, M.s[k], 0));   // retired here
+        }
+      }
+    }
+    if (nB > 0) {
+      // the gradients join the accumulator behind the post, messages in ring order
+#pragma unroll
+      for (int j = 0; j < RO_NE; ++j)
+        if (er[j] >= 0) {
+          float a = gacc[j];
+          for (int k = 0; k < n; ++k) a = fmaf(zbuf[k * 64 + er[j]], hbuf[k * SP + ec[j]], a);
+          gacc[j] = a;
+        }
+      if ((int)threadIdx.x < R)
+        for (int k = 0; k < n; ++k) gb += zbuf[k * 64 + threadIdx.x];
+      count += (unsigned)nB;
+      if ((int)count >= nd_muf) {
+        // the node's own update (Section 3)
+        tstep++;
+        if (threadIdx.x == 0) note_update(D);
+        const OptCoef o = opt_at(ob, tstep);
+        const float inv = mean ? 1.f / (float)count : 1.f;
+        lds_barrier();   // every thread has read its column of the old weights
+#pragma unroll
+        for (int j = 0; j < RO_NE; ++j)
+          if (er[j] >= 0) {
+            const int li = er[j] * ldw + ec[j];
+            Wl[li] = opt_apply(o, Wl[li], gacc[j] * inv, ndM, ndV, (long long)er[j] * C + ec[j]);
+            gacc[j] = 0.f;
+          }
+        if ((int)threadIdx.x < R) {
+          bl[threadIdx.x] = opt_apply(o, bl[threadIdx.x], gb * inv, ndM, ndV, (long long)R * C + threadIdx.x);
+          gb = 0.f;
+        }
+        count = 0;
+        LOG(2, 2, 0, 0);
+      }
+    }
+    lds_barrier();
+  }
+  tile_store(nd, t, Wg, bg);
+#pragma unroll
+  for (int j = 0; j < RO_NE; ++j)
+    if (er[j] >= 0) ndG[threadIdx.x + AMP_THREADS * j] = gacc[j];
+  if ((int)threadIdx.x < R) ndG[R * C + threadIdx.x] = gb;
+  if (threadIdx.x == 0) {
+    W->wstate[0] = count;
+    W->wstate[1] = tstep;
+  }
+}
+
+// The same one message at a time, for output layers beyond that size.
 __device__ __noinline__ void role_rnn_out(const GQ AmpDev* D, const GQ WorkerDev* W) {
   float* lds = amp_lds;
   const GQ NodeDev& nd = D->node[2];

@@ -174,6 +174,20 @@ def test_rnn_cell_at_the_edges_of_its_register_tiles(emb, hidden, mak, muf, opt)
     compare(g, rt, len(data), opt=opt)
 
 
+@pytest.mark.parametrize("hidden,n_class,mak,muf,opt", [(96, 64, 24, 5, SGD), (97, 64, 24, 5, SGD), (33, 1, 40, 16, RNN_ADAM_MUF3),
+                                                        (128, 3, 40, 1, SGD)])
+def test_rnn_output_layer_at_the_edges_of_its_batches(hidden, n_class, mak, muf, opt):
+    """The largest output layer whose gradient the worker holds in registers (12 elements for each of 512 threads) and the
+    next larger one, a single class, more messages waiting than a batch takes (16), an update per gradient."""
+    dims = dict(vocab=20, emb=40, hidden=hidden, n_class=n_class)
+    data = synth.make_rnn(150, 35, dims, min_len=1, max_len=3)
+    fp = synth.init_params("rnn", dims, 9)
+    g = gpu_train("rnn", dims, fp, data, mak, muf, opt)
+    check_controller_log(g["logs"], mak, len(data))
+    rt = oracle_replay("rnn", dims, fp, data, g["logs"], muf, opt)
+    compare(g, rt, len(data), opt=opt)
+
+
 TREE_SMALLVOCAB = dict(vocab=64, emb=300, hidden=150, n_class=5)
 TREE_ODD = dict(vocab=97, emb=50, hidden=37, n_class=5)
 
