@@ -1387,8 +1387,15 @@ __device__ __noinline__ void role_tree_out(const GQ AmpDev* D, const GQ WorkerDe
   for (int i = threadIdx.x; i < D->mak; i += AMP_THREADS) done_cnt[i] = 0;
   // this thread's accumulator elements e = threadIdx.x + 512 j (row e / C, column e % C), and the bias gradient of row threadIdx.x
   GQ float* ndG = (GQ float*)nd.G;
+  // ... and their optimizer slots, in registers for the life of the launch (in HBM a step with slots is a fetch and a store
+  // behind each other in every update)
   constexpr int NE = 12;   // n_class * H <= 12 * 512
-  float gacc[NE], gb;
+  const int nj = (R * C + AMP_THREADS - 1) / AMP_THREADS;
+  GQ float* ndM = uni_gq<float>(nd.M);
+  GQ float* ndV = uni_gq<float>(nd.V);
+  const OptCoef ob = opt_base(nd);
+  const bool mean = uni(nd.mean) != 0, bounded = uni(D->admit_bounded) != 0;
+  float gacc[NE], gb, sm[NE], sv[NE], bm = 0.f, bv = 0.f;
   int er[NE], ec[NE];
 #pragma unroll
   for (int j = 0; j < NE; ++j) {
@@ -1396,19 +1403,24 @@ __device__ __noinline__ void role_tree_out(const GQ AmpDev* D, const GQ WorkerDe
     er[j] = e < R * C ? e / C : -1;
     ec[j] = e < R * C ? e - (e / C) * C : 0;
     gacc[j] = er[j] >= 0 ? ndG[e] : 0.f;
+    sm[j] = er[j] >= 0 && ob.kind != 0 ? ndM[e] : 0.f;
+    sv[j] = er[j] >= 0 && ob.kind == 2 ? ndV[e] : 0.f;
   }
+  if ((int)threadIdx.x < R && ob.kind != 0) bm = ndM[R * C + threadIdx.x];
+  if ((int)threadIdx.x < R && ob.kind == 2) bv = ndV[R * C + threadIdx.x];
   gb = (int)threadIdx.x < R ? ndG[R * C + threadIdx.x] : 0.f;
   BatchMsg& M = s_M;
   __syncthreads();
   const Ring mine = ring_regs(D, uni(W->ring));
   unsigned head = 0;
   unsigned count = W->wstate[0], tstep = W->wstate[1];
-  for (;;) {
-    const int room = wr.train ? nd_muf - (int)count : KB_MAX;
-    const int n = wait_batch(D, mine, head, KB, room, s_codes, &s_n, [](unsigned) { return true; });
-    if (n == 0) break;
-    if (threadIdx.x < 64) {
-      const int k = threadIdx.x;
+  // Wave 1 takes the next batch while wave 0 publishes the present one, as in the cells: a batch is a chain of round
+  // trips (ring, slot, node, inputs), and with small batches -- an update every few gradients -- that chain is its time.
+  const int wave = threadIdx.x >> 6;
+  auto take_batch = [&](int room) {
+    const int n = poll_batch(D, mine, head, KB, room, s_codes, &s_n, [](unsigned) { return true; });
+    if (n > 0) {
+      const int k = threadIdx.x & 63;
       if (k < n) {
         const unsigned code = s_codes[k];
         const int s = MSG_SLOT(code), nn = MSG_LOCAL(code);
@@ -1461,7 +1473,13 @@ __device__ __noinline__ void role_tree_out(const GQ AmpDev* D, const GQ WorkerDe
         }
       }
     }
-    lds_barrier();
+  };
+  if (wave == 1) take_batch(wr.train ? nd_muf - (int)count : KB_MAX);
+  lds_barrier();
+  for (;;) {
+    const int n = s_n;
+    if (n == 0) break;
+    head += n;
     for (int idx = threadIdx.x; idx < n * (Hp >> 2); idx += AMP_THREADS) {
       const int k = idx / (Hp >> 2), c = (idx - k * (Hp >> 2)) << 2;
       const v4f hv = *(const GQ v4f*)(B.hc + M.off0[k] + c);
@@ -1524,7 +1542,7 @@ __device__ __noinline__ void role_tree_out(const GQ AmpDev* D, const GQ WorkerDe
       __hip_atomic_fetch_add((GQ float*)&D->loss_out[idx], -(zl - m - logf(se)), __ATOMIC_RELAXED, AGENT);
       if (am == label) __hip_atomic_fetch_add((GQ int*)&D->correct_out[idx], 1, __ATOMIC_RELAXED, AGENT);
     }
-    if (D->train) {
+    if (wr.train) {
       lds_barrier();
       // dh[k][c] = sum_r W[r][c] dz[k][r]
       for (int idx = threadIdx.x; idx < n * C; idx += AMP_THREADS) {
@@ -1534,10 +1552,38 @@ __device__ __noinline__ void role_tree_out(const GQ AmpDev* D, const GQ WorkerDe
         for (int r = 0; r < R; ++r) a = fmaf(Wl[r * ldw + c], z[r], a);
         B.gout[M.dst0[k] + c] = a;
       }
+    }
+    // what lane k of wave 0 needs of message k for its joins, before the batch's record is given up
+    const int nB = uni(M.nB);
+    int js = 0, jn = 0, jaux = 0, jpar = 0, jL = 0;
+    if (threadIdx.x < 64 && (int)threadIdx.x < n) {
+      const int k = threadIdx.x;
+      js = M.s[k];
+      jn = M.n[k];
+      jaux = M.aux[k];
+      jpar = M.par[k];
+      jL = M.L[k];
+    }
+    // every wave's HBM stores have landed before wave 0 publishes the batch
+    publish_barrier();
+    if (threadIdx.x < 64) {
+      fence_release();
+      if ((int)threadIdx.x < n) {
+        if (jaux) {
+          if (atomicAdd((int*)&done_cnt[js], 1) + 1 == 2 * jL - 1) {
+            done_cnt[js] = 0;
+            ring_post(wr.ctl, MSG_MAKE(1, js, 0));
+          }
+        } else {
+          tree_grad_part_done(wr, B, js, jn, jpar < 0, jn < jL);
+        }
+      }
+    }
+    if (wr.train) {
       // G[r][c] += sum_k dz[k][r] h[k][c], messages in ring order
 #pragma unroll
       for (int j = 0; j < NE; ++j)
-        if (er[j] >= 0) {
+        if (j < nj && er[j] >= 0) {
           float a = gacc[j];
           int k = 0;
           for (; k + 7 < n; k += 8) {   // eight messages' operands are read together, then added in ring order
@@ -1555,53 +1601,46 @@ __device__ __noinline__ void role_tree_out(const GQ AmpDev* D, const GQ WorkerDe
         }
       if ((int)threadIdx.x < R)
         for (int k = 0; k < n; ++k) gb += zbuf[k * 64 + threadIdx.x];
-    }
-    // every wave's HBM stores have landed before wave 0 publishes the batch
-    publish_barrier();
-    if (threadIdx.x < 64) {
-      fence_release();
-      const int k = threadIdx.x;
-      if (k < n) {
-        if (M.aux[k]) {
-          if (atomicAdd((int*)&done_cnt[M.s[k]], 1) + 1 == 2 * M.L[k] - 1) {
-            done_cnt[M.s[k]] = 0;
-            ring_post(wr.ctl, MSG_MAKE(1, M.s[k], 0));
-          }
-        } else {
-          tree_grad_part_done(wr, B, M.s[k], M.n[k], M.par[k] < 0, M.n[k] < M.L[k]);
-        }
-      }
-    }
-    if (D->train) {
-      count += M.nB;
-      if ((int)count >= nd.muf) {
-        // the node's own update (Section 3)
+      count += nB;
+      if ((int)count >= nd_muf) {
+        // the node's own update (Section 3); every thread owns its elements, and the old weights have been read
         tstep++;
-        if (threadIdx.x == 0) note_update(D);
-        const OptCoef o = opt_coef(nd, tstep);
-        const float inv = nd.mean ? 1.f / (float)count : 1.f;
+        if (bounded && threadIdx.x == 0) note_update(D);
+        const OptCoef o = opt_at(ob, tstep);
+        const float inv = mean ? 1.f / (float)count : 1.f;
 #pragma unroll
         for (int j = 0; j < NE; ++j)
-          if (er[j] >= 0) {
+          if (j < nj && er[j] >= 0) {
             const int li = er[j] * ldw + ec[j];
-            Wl[li] = opt_apply(o, Wl[li], gacc[j] * inv, nd.M, nd.V, (long long)er[j] * C + ec[j]);
+            Wl[li] = opt_step(o, Wl[li], gacc[j] * inv, sm[j], sv[j]);
             gacc[j] = 0.f;
           }
         if ((int)threadIdx.x < R) {
-          bl[threadIdx.x] = opt_apply(o, bl[threadIdx.x], gb * inv, nd.M, nd.V, (long long)R * C + threadIdx.x);
+          bl[threadIdx.x] = opt_step(o, bl[threadIdx.x], gb * inv, bm, bv);
           gb = 0.f;
         }
         count = 0;
-        LOG(3, 2, 0, 0);
+        // recorded by the wave that records the next batch's events, so that the update comes first
+        if (threadIdx.x == 64) log_event(D, W, &s_logn, 3, 2, 0, 0);
       }
     }
+    if (wave == 1) take_batch(wr.train ? nd_muf - (int)count : KB_MAX);
     lds_barrier();
   }
   tile_store(nd, t, Wg, bg);
 #pragma unroll
   for (int j = 0; j < NE; ++j)
-    if (er[j] >= 0) ndG[threadIdx.x + AMP_THREADS * j] = gacc[j];
-  if ((int)threadIdx.x < R) ndG[R * C + threadIdx.x] = gb;
+    if (er[j] >= 0) {
+      const int e = threadIdx.x + AMP_THREADS * j;
+      ndG[e] = gacc[j];
+      if (ob.kind != 0) ndM[e] = sm[j];
+      if (ob.kind == 2) ndV[e] = sv[j];
+    }
+  if ((int)threadIdx.x < R) {
+    ndG[R * C + threadIdx.x] = gb;
+    if (ob.kind != 0) ndM[R * C + threadIdx.x] = bm;
+    if (ob.kind == 2) ndV[R * C + threadIdx.x] = bv;
+  }
   if (threadIdx.x == 0) {
     W->wstate[0] = count;
     W->wstate[1] = tstep;
