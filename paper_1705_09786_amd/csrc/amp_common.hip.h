@@ -445,6 +445,38 @@ __device__ __forceinline__ float opt_apply(const OptCoef& o, float w, float g, G
   return w - o.lr * (m * o.c1) / (sqrtf(v * o.c2) + o.eps);
 }
 
+// The optimizer of the node this workgroup serves, copied into LDS when the kernel starts: an update reads it there
+// instead of fetching the descriptor from HBM.
+struct NodeOpt {
+  OptCoef o;
+  int mean;
+  float *M, *V;
+};
+__shared__ NodeOpt s_opt;
+__device__ __forceinline__ void hold_node_opt(const GQ NodeDev& nd) {   // ONE thread
+  s_opt.o.kind = nd.opt;
+  s_opt.o.lr = nd.lr;
+  s_opt.o.mom = nd.mom;
+  s_opt.o.b1 = nd.b1;
+  s_opt.o.b2 = nd.b2;
+  s_opt.o.eps = nd.eps;
+  s_opt.o.c1 = s_opt.o.c2 = 1.f;
+  s_opt.mean = nd.mean;
+  s_opt.M = nd.M;
+  s_opt.V = nd.V;
+}
+__device__ __forceinline__ OptCoef held_opt(unsigned tstep) {
+  OptCoef o;
+  o.kind = uni(s_opt.o.kind);
+  o.lr = uni(s_opt.o.lr);
+  o.mom = uni(s_opt.o.mom);
+  o.b1 = uni(s_opt.o.b1);
+  o.b2 = uni(s_opt.o.b2);
+  o.eps = uni(s_opt.o.eps);
+  o.c1 = o.c2 = 1.f;
+  return opt_at(o, tstep);
+}
+
 // The same with the slots in registers.
 __device__ __forceinline__ float opt_step(const OptCoef& o, float w, float g, float& m, float& v) {
   if (o.kind == 0) return w - o.lr * g;

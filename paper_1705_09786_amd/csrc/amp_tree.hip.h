@@ -517,81 +517,62 @@ __device__ __forceinline__ void tree_bwd_mfma(const LDSQ float* Wl, const Tile& 
     tree_bwd_blocks<BR, 4, NRBT, NCGT>(Wl, t, Dl, M, nB, obase);
 }
 
-// The optimizer step on the LDS weights from the accumulators of tree_update_from_pend (layout described there).
-template <int NRBT, int NCGT>
-__device__ __forceinline__ void tree_update_apply(LDSQ float* Wl, LDSQ float* bl, const GQ NodeDev& nd, const Tile& t,
-                                                  const TreeShape<NRBT, NCGT>& sh, v4f (&g)[TREE_GU][4], unsigned n_grad,
-                                                  unsigned tstep, const LDSQ int* rowmap, const LDSQ int* colmap, float gb) {
+// Momentum / Adam slots of units U0 .. U0 + US - 1 of a wave, fetched from HBM together: element (v, e) of a unit lies at gi
+// (-1 = padding) of the node's slot arrays.
+template <int US>
+struct TreeSlots {
+  int gi[US][4][4];
+  float m[US][4][4], v[US][4][4];
+};
+template <int US>
+__device__ __forceinline__ void tree_slots_fetch(TreeSlots<US>& sl, int u0, int NU, int NRB, int cols, int kind, const GQ float* Mq,
+                                                 const GQ float* Vq, const LDSQ int* rowmap, const LDSQ int* colmap) {
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, i = lane & 15, q = lane >> 4;
-  const int NRB = sh.NRB, Cp = sh.NCG * 16, CM = (Cp + 63) >> 6, NU = NRB * CM;
-  const OptCoef o = opt_coef(nd, tstep);
-  const float inv = nd.mean ? 1.f / (float)n_grad : 1.f;
-  // optimizer step from the accumulators.  Plain SGD needs no per-element slots: padding rows and columns
-  // have a zero gradient (their delta / input entries are zero), so whole 16-byte groups are updated.
-  if (o.kind == 0) {
-    const float sc = o.lr * inv;
 #pragma unroll
-    for (int u = 0; u < TREE_GU; ++u) {
-      const int id = wave + 8 * u, cm = id / NRB, rb = id - cm * NRB, lc = cm * 64 + 4 * i;
-      if (id < NU && lc < Cp) {
+  for (int u = 0; u < US; ++u) {
+    const int id = wave + 8 * (u0 + u), cm = id / NRB, rb = id - cm * NRB;
+    if (id < NU) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int nc = colmap[cm * 64 + 4 * i + v];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          LDSQ v4f* wp = (LDSQ v4f*)(Wl + (rb * 16 + 4 * q + e) * sh.ldw + lc);
-          const v4f gv = {g[u][0][e], g[u][1][e], g[u][2][e], g[u][3][e]};
-          *wp = *wp - sc * gv;
+          const int nr = rowmap[rb * 16 + 4 * q + e];
+          sl.gi[u][v][e] = (nr >= 0 && nc >= 0) ? nr * cols + nc : -1;
         }
       }
-    }
-  } else {
-    // momentum / Adam: the slots are in HBM.  A unit's sixteen elements per lane are fetched together, then stepped,
-    // then stored (a fetch behind the previous element's stores would wait for them).
-    GQ float* Mq = (GQ float*)nd.M;
-    GQ float* Vq = (GQ float*)nd.V;
 #pragma unroll
-    for (int u = 0; u < TREE_GU; ++u) {
-      const int id = wave + 8 * u, cm = id / NRB, rb = id - cm * NRB;
-      if (id < NU) {
-        long long gi[4][4];
-        float mo[4][4], vo[4][4];
+      for (int v = 0; v < 4; ++v)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const int nc = colmap[cm * 64 + 4 * i + v];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const int nr = rowmap[rb * 16 + 4 * q + e];
-            gi[v][e] = (nr >= 0 && nc >= 0) ? (long long)nr * t.C + nc : -1;
-            const long long at = gi[v][e] >= 0 ? gi[v][e] : 0;
-            mo[v][e] = Mq[at];
-            vo[v][e] = o.kind == 2 ? Vq[at] : 0.f;
-          }
+        for (int e = 0; e < 4; ++e) {
+          const int at = sl.gi[u][v][e] >= 0 ? sl.gi[u][v][e] : 0;
+          sl.m[u][v][e] = Mq[at];
+          sl.v[u][v][e] = kind == 2 ? Vq[at] : 0.f;
         }
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const int lc = cm * 64 + 4 * i + v;
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-            if (gi[v][e] >= 0) {
-              const int r = rb * 16 + 4 * q + e;
-              const float gr = g[u][v][e] * inv, w = Wl[r * sh.ldw + lc];
-              if (o.kind == 1) {
-                const float m = fmaf(o.mom, mo[v][e], gr);
-                Mq[gi[v][e]] = m;
-                Wl[r * sh.ldw + lc] = w - o.lr * m;
-              } else {
-                const float m = fmaf(o.b1, mo[v][e], (1.f - o.b1) * gr);
-                const float vv = fmaf(o.b2, vo[v][e], (1.f - o.b2) * gr * gr);
-                Mq[gi[v][e]] = m;
-                Vq[gi[v][e]] = vv;
-                Wl[r * sh.ldw + lc] = w - o.lr * (m * o.c1) / (sqrtf(vv * o.c2) + o.eps);
-              }
-            }
-        }
-      }
     }
   }
-  if ((int)threadIdx.x < t.R && nd.has_bias) {
-    const int r = threadIdx.x;
-    bl[r] = opt_apply(o, bl[r], gb * inv, nd.M, nd.V, (long long)nd.rows * t.C + rowmap[r]);
+}
+template <int US, int GU>
+__device__ __forceinline__ void tree_slots_step(TreeSlots<US>& sl, int u0, int NU, int NRB, const OptCoef& o, float inv, v4f (&g)[GU][4],
+                                                LDSQ float* Wl, int ldw, GQ float* Mq, GQ float* Vq) {
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, i = lane & 15, q = lane >> 4;
+#pragma unroll
+  for (int u = 0; u < US; ++u) {
+    const int id = wave + 8 * (u0 + u), cm = id / NRB, rb = id - cm * NRB;
+    if (u0 + u < GU && id < NU) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int at = sl.gi[u][v][e];
+          if (at >= 0) {
+            LDSQ float* w = Wl + (rb * 16 + 4 * q + e) * ldw + cm * 64 + 4 * i + v;
+            *w = opt_step(o, *w, g[(u0 + u) % GU][v][e] * inv, sl.m[u][v][e], sl.v[u][v][e]);
+            Mq[at] = sl.m[u][v][e];
+            if (o.kind == 2) Vq[at] = sl.v[u][v][e];
+          }
+        }
+    }
   }
 }
 
@@ -606,20 +587,22 @@ __device__ __forceinline__ void tree_update_apply(LDSQ float* Wl, LDSQ float* bl
 // four.  Lane (i, q) ends up with G[rb*16 + 4q + e][cm*64 + 4i + v] in g[u][v][e].
 // gb = the accumulated bias gradient of tile row threadIdx.x; n_grad = the
 // number of gradients (messages) behind the count pending rows.
-template <int NRBT, int NCGT>
-__device__ __noinline__ void tree_update_from_pend(LDSQ float* Wl, LDSQ float* bl, const GQ NodeDev* ndp, Tile t,
-                                                   const GQ float* pend, unsigned count, unsigned n_grad, unsigned tstep,
-                                                   const LDSQ int* rowmap, const LDSQ int* colmap, float gb) {
+// GU = units per wave: a tile of few units fetches for those alone (a wave without a unit repeats the first one's fetches
+// and drops them), and with one or two the next sixteen pairs are on the way while the matrix cores work on the present
+// ones.  More units leave no registers for that.
+template <int NRBT, int NCGT, int GU>
+__device__ __forceinline__ void tree_update_units(LDSQ float* Wl, LDSQ float* bl, const GQ NodeDev& nd, const Tile& t, const GQ float* pend,
+                                                  unsigned count, unsigned n_grad, unsigned tstep, const LDSQ int* rowmap,
+                                                  const LDSQ int* colmap, float gb) {
   const TreeShape<NRBT, NCGT> sh(t);
-  const GQ NodeDev& nd = *ndp;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, i = lane & 15, q = lane >> 4;
   const int NRB = sh.NRB, Rp = NRB * 16, Cp = sh.NCG * 16, stride = Rp + Cp, CM = (Cp + 63) >> 6, NU = NRB * CM;
   const v4f zero = {0.f, 0.f, 0.f, 0.f};
-  v4f g[TREE_GU][4];
-  int aoff[TREE_GU], xoff[TREE_GU];
-  bool xin[TREE_GU];
+  v4f g[GU][4];
+  int aoff[GU], xoff[GU];
+  bool xin[GU];
 #pragma unroll
-  for (int u = 0; u < TREE_GU; ++u) {
+  for (int u = 0; u < GU; ++u) {
     const int id = wave + 8 * u < NU ? wave + 8 * u : 0, cm = id / NRB, rb = id - cm * NRB, lc = cm * 64 + 4 * i;
     aoff[u] = rb * 16 + i;
     xin[u] = lc < Cp;
@@ -627,39 +610,130 @@ __device__ __noinline__ void tree_update_from_pend(LDSQ float* Wl, LDSQ float* b
 #pragma unroll
     for (int v = 0; v < 4; ++v) g[u][v] = zero;
   }
+  // One unit: the optimizer's slots arrive while the gradient is formed (an update every few gradients is a chain
+  // of round trips); more units leave the registers to the gradient.
+  constexpr bool EARLY = GU == 1;
+  constexpr int US = EARLY ? 1 : 2;
+  const int kind = uni(s_opt.o.kind);
+  GQ float* Mq = uni_gq<float>(s_opt.M);
+  GQ float* Vq = uni_gq<float>(s_opt.V);
+  TreeSlots<US> sl;
+  float bm = 0.f, bv = 0.f;
+  const bool bias = (int)threadIdx.x < t.R && nd.has_bias;
+  int bat = 0;
+  if (kind != 0) {
+    if (bias) {
+      bat = nd.rows * t.C + rowmap[threadIdx.x];
+      bm = Mq[bat];
+      if (kind == 2) bv = Vq[bat];
+    }
+    if (EARLY) tree_slots_fetch<US>(sl, 0, NU, NRB, t.C, kind, Mq, Vq, rowmap, colmap);
+  }
   constexpr int NH = 4;
-  for (unsigned k0 = 0; k0 < count; k0 += 4 * NH) {
-    // NH groups of four pending pairs per round, all fetches in flight together
-    float a[NH][TREE_GU];
-    v4f x[NH][TREE_GU];
+  // NH groups of four pending pairs, all fetches in flight together
+  auto fetch = [&](unsigned k0, float (&a)[NH][GU], v4f (&x)[NH][GU]) {
 #pragma unroll
     for (int h = 0; h < NH; ++h) {
       const unsigned k = k0 + 4 * h + q;
-      const bool kin = k < count;
-      const GQ float* e = pend + (long long)(kin ? k : count - 1) * stride;
+      const GQ float* e = pend + (long long)(k < count ? k : count - 1) * stride;
 #pragma unroll
-      for (int u = 0; u < TREE_GU; ++u) {
-        const float av = e[aoff[u]];
-        const v4f xv = *(const GQ v4f*)(e + xoff[u]);
-        a[h][u] = kin ? av : 0.f;
-        x[h][u] = xin[u] ? xv : zero;
+      for (int u = 0; u < GU; ++u) {
+        a[h][u] = e[aoff[u]];
+        x[h][u] = *(const GQ v4f*)(e + xoff[u]);
       }
     }
-    asm volatile("" : "+v"(x[0][0]), "+v"(x[0][1]), "+v"(x[0][2]), "+v"(x[0][3]), "+v"(x[1][0]), "+v"(x[1][1]), "+v"(x[1][2]),
-                      "+v"(x[1][3]), "+v"(x[2][0]), "+v"(x[2][1]), "+v"(x[2][2]), "+v"(x[2][3]), "+v"(x[3][0]), "+v"(x[3][1]),
-                      "+v"(x[3][2]), "+v"(x[3][3]));
+  };
+  auto work = [&](unsigned k0, float (&a)[NH][GU], v4f (&x)[NH][GU]) {
 #pragma unroll
-    for (int h = 0; h < NH; ++h)
+    for (int h = 0; h < NH; ++h) {
+      const bool kin = k0 + 4 * h + q < count;
 #pragma unroll
-      for (int u = 0; u < TREE_GU; ++u)
+      for (int u = 0; u < GU; ++u)
         if (wave + 8 * u < NU) {
-          g[u][0] = MFMA(a[h][u], x[h][u].x, g[u][0]);
-          g[u][1] = MFMA(a[h][u], x[h][u].y, g[u][1]);
-          g[u][2] = MFMA(a[h][u], x[h][u].z, g[u][2]);
-          g[u][3] = MFMA(a[h][u], x[h][u].w, g[u][3]);
+          const float av = kin ? a[h][u] : 0.f;
+          const v4f xv = xin[u] ? x[h][u] : zero;
+          g[u][0] = MFMA(av, xv.x, g[u][0]);
+          g[u][1] = MFMA(av, xv.y, g[u][1]);
+          g[u][2] = MFMA(av, xv.z, g[u][2]);
+          g[u][3] = MFMA(av, xv.w, g[u][3]);
         }
+    }
+  };
+  float a0[NH][GU];
+  v4f x0[NH][GU];
+  if (GU > 2) {
+    for (unsigned k0 = 0; k0 < count; k0 += 4 * NH) {
+      fetch(k0, a0, x0);
+      asm volatile("" ::: "memory");
+      work(k0, a0, x0);
+    }
+  } else {
+    float a1[NH][GU];
+    v4f x1[NH][GU];
+    if (count > 0) fetch(0, a0, x0);
+    for (unsigned k0 = 0; k0 < count; k0 += 8 * NH) {
+      if (k0 + 4 * NH < count) fetch(k0 + 4 * NH, a1, x1);
+      asm volatile("" ::: "memory");   // the fetches are issued before the products below start
+      work(k0, a0, x0);
+      if (k0 + 4 * NH >= count) break;
+      if (k0 + 8 * NH < count) fetch(k0 + 8 * NH, a0, x0);
+      asm volatile("" ::: "memory");
+      work(k0 + 4 * NH, a1, x1);
+    }
   }
-  tree_update_apply<NRBT, NCGT>(Wl, bl, nd, t, sh, g, n_grad, tstep, rowmap, colmap, gb);
+  const OptCoef o = held_opt(tstep);
+  const float inv = uni(s_opt.mean) ? 1.f / (float)n_grad : 1.f;
+  // optimizer step from the accumulators.  Plain SGD needs no per-element slots: padding rows and columns
+  // have a zero gradient (their delta / input entries are zero), so whole 16-byte groups are updated.
+  if (kind == 0) {
+    const float sc = o.lr * inv;
+#pragma unroll
+    for (int u = 0; u < GU; ++u) {
+      const int id = wave + 8 * u, cm = id / NRB, rb = id - cm * NRB, lc = cm * 64 + 4 * i;
+      if (id < NU && lc < Cp) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          LDSQ v4f* wp = (LDSQ v4f*)(Wl + (rb * 16 + 4 * q + e) * sh.ldw + lc);
+          const v4f gv = {g[u][0][e], g[u][1][e], g[u][2][e], g[u][3][e]};
+          *wp = *wp - sc * gv;
+        }
+      }
+    }
+  } else if (EARLY) {
+    tree_slots_step<US, GU>(sl, 0, NU, NRB, o, inv, g, Wl, sh.ldw, Mq, Vq);
+  } else {
+#pragma unroll
+    for (int u0 = 0; u0 < GU; u0 += US) {
+      tree_slots_fetch<US>(sl, u0, NU, NRB, t.C, kind, Mq, Vq, rowmap, colmap);
+      asm volatile("" ::: "memory");   // every fetch is issued before the first store
+      tree_slots_step<US, GU>(sl, u0, NU, NRB, o, inv, g, Wl, sh.ldw, Mq, Vq);
+    }
+  }
+  if (bias) {
+    bl[threadIdx.x] = opt_step(o, bl[threadIdx.x], gb * inv, bm, bv);
+    if (kind != 0) Mq[bat] = bm;
+    if (kind == 2) Vq[bat] = bv;
+  }
+}
+
+template <int NRBT, int NCGT>
+__device__ __noinline__ void tree_update_from_pend(LDSQ float* Wl, LDSQ float* bl, const GQ NodeDev* ndp, Tile t,
+                                                   const GQ float* pend, unsigned count, unsigned n_grad, unsigned tstep,
+                                                   const LDSQ int* rowmap, const LDSQ int* colmap, float gb) {
+  if (NRBT) {
+    constexpr int GU = NRBT ? (NRBT * ((NCGT * 16 + 63) >> 6) + 7) >> 3 : 1;
+    tree_update_units<NRBT, NCGT, GU>(Wl, bl, *ndp, t, pend, count, n_grad, tstep, rowmap, colmap, gb);
+  } else {
+    const int units = (t.Rp >> 4) * ((amp_round16(t.Cl) + 63) >> 6);
+    if (units <= 8)
+      tree_update_units<0, 0, 1>(Wl, bl, *ndp, t, pend, count, n_grad, tstep, rowmap, colmap, gb);
+    else if (units <= 16)
+      tree_update_units<0, 0, 2>(Wl, bl, *ndp, t, pend, count, n_grad, tstep, rowmap, colmap, gb);
+    else if (units <= 24)
+      tree_update_units<0, 0, 3>(Wl, bl, *ndp, t, pend, count, n_grad, tstep, rowmap, colmap, gb);
+    else
+      tree_update_units<0, 0, 4>(Wl, bl, *ndp, t, pend, count, n_grad, tstep, rowmap, colmap, gb);
+  }
 }
 
 // ------------------------------------------------------------ products of a tile whose weights stay in HBM

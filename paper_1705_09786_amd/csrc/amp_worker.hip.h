@@ -201,6 +201,7 @@ __device__ __forceinline__ void persistent_worker(const AmpDev* Dp, int workers_
     s_first_seq = args.first_seq[replica];
     s_log_cap = W->tile == 0 ? W->log_cap : 0u;
     s_log_ptr = W->log;
+    if (W->node >= 0) hold_node_opt(D->node[W->node]);
     for (int i = 0; i < AMP_NSTAT; ++i) s_stat[i] = 0;
     t_begin = wall_clock64();
     // packed: the whole replica shares one L2 if block b really runs on die b % 8 (hardware register XCC_ID, id 20,
