@@ -10,7 +10,8 @@
 //     with a row per lane (forward: contraction over columns) and with a column per lane (backward, update);
 //   * the products are v_mfma_f32_4x4x1 over 16 blocks: one operand is four messages' values, broadcast to all blocks,
 //     the other 64 rows (columns) of the weights.  The batch is padded to multiples of 4 messages, where 16x16x4 pads to
-//     16 -- with 16 sequences in flight a batch has about 8 messages of either direction -- at the same matrix rate;
+//     16 -- with 16 sequences in flight a batch has about 7 messages of either direction -- and the rate is higher: two waves
+//     on a SIMD issue 512 flop every 5 cycles, measured, against 2,048 every 32 for 16x16x4;
 //   * the present input rows, the gradients travelling down the loop, the table, its gradient and the pending
 //     (delta, input) pairs are in LDS; HBM holds only the history that the backward steps come back for, stored as it
 //     arises and fetched behind the forward product;
@@ -44,6 +45,10 @@ __device__ __forceinline__ bool rnn_reg_fits(const GQ AmpDev* D, const GQ Worker
   const GQ NodeDev& nd = D->node[W->node];
   const int pairs = rnn_reg_pairs(nd, W);
   if (nd.rows > 128 || D->emb > 128 || nd.seg0 != D->emb || pairs > 96 || D->vocab > 4096) return false;
+  // Small cells with far more sequences in flight than this worker's places: role_rnn_cell takes up to 64 at once, and its
+  // padding to 16 costs a small matrix little (hidden = emb = 32, 64 in flight, 1,000 sequences: 16.1 ms there, 17.2 here;
+  // at 128 the register layout is the faster one at 64 in flight too).
+  if (nd.rows <= 64 && D->emb <= 64 && D->mak > 3 * RC_KB * D->node_replicas) return false;
   return rnn_reg_floats(D->vocab, D->emb, pairs) <= AMP_DYN_LDS_BYTES / 4;
 }
 
