@@ -226,7 +226,11 @@ __device__ __noinline__ void role_mlp_regs(const GQ AmpDev* D, const GQ WorkerDe
   GQ float* loss_out = uni_gq<float>(D->loss_out);
   GQ int* correct_out = uni_gq<int>(D->correct_out);
   const unsigned first_seq = uni(s_first_seq);
-  const int cin = c0 < HS ? c0 : 0, rin = r0 < HS ? r0 : 0;   // the storage rows' padding up to HS holds zeros
+  // the storage rows' padding up to HS holds zeros; beyond it a row has nothing to read
+  const int rin = r0 < HS ? r0 : 0;
+  int cin[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) cin[k] = c0 + 4 * k < HS ? c0 + 4 * k : -1;
   MlpRings rq = mlp_rings(D, li);
   unsigned code, count = uni(W->wstate[0]), tstep = uni(W->wstate[1]);
   __syncthreads();
@@ -243,9 +247,11 @@ __device__ __noinline__ void role_mlp_regs(const GQ AmpDev* D, const GQ WorkerDe
     } else {
       v4f t[4];
 #pragma unroll
-      for (int k = 0; k < 4; ++k) t[k] = ld_shared4(act_in + at + (cin + 4 * k < HS ? cin + 4 * k : 0));
+      for (int k = 0; k < 4; ++k) t[k] = ld_shared4(act_in + at + (cin[k] < 0 ? 0 : cin[k]));
+      // zero beyond the input, as load_row has it: the registers there are weights like any other to the updates below,
+      // and a step with a zero input leaves them zero
 #pragma unroll
-      for (int k = 0; k < 16; ++k) x[k] = t[k / 4][k & 3];   // columns beyond the input meet zero weights
+      for (int k = 0; k < 16; ++k) x[k] = cin[k / 4] < 0 ? 0.f : t[k / 4][k & 3];
     }
     int label = 0;
     if (LAST) label = lab[inst];   // one label per instance

@@ -25,6 +25,7 @@ SGD = dict(kind="sgd", lr=0.05)
 # leaves fp32 rounding too little room under 1e-5; each run has its own event order, so a case close to the
 # limit fails now and then.
 ADAM = dict(kind="adam", lr=0.0005, beta1=0.9, beta2=0.999, eps=1e-6)
+MLP_MOM = dict(kind="momentum", lr=0.005, momentum=0.9)
 
 
 # Momentum 0.9 at lr = 0.02 is an unstable training run on this task (losses spike to twice their initial value);
@@ -51,6 +52,27 @@ def test_mlp_mak1_is_synchronous_sgd():
     for k in range(3):
         refv = np.concatenate([P[k]["W"].reshape(-1), P[k]["b"]])
         assert np.linalg.norm(g["params"][k] - refv) / np.linalg.norm(refv) <= 1e-5
+
+
+@pytest.mark.parametrize("d_in,hidden,n_class,mak,muf,opt", [
+    (64, 16, 10, 4, 1, SGD), (64, 37, 10, 4, 1, SGD), (64, 64, 10, 4, 1, SGD), (64, 100, 10, 4, 1, SGD),
+    (64, 112, 10, 4, 1, SGD), (64, 124, 10, 4, 1, SGD), (5, 125, 2, 4, 1, SGD),
+    (64, 16, 10, 4, 3, SGD), (64, 37, 10, 4, 3, SGD), (64, 64, 10, 4, 3, SGD), (64, 100, 10, 4, 3, SGD),
+    (64, 112, 10, 4, 3, SGD), (64, 124, 10, 4, 3, SGD),
+    (64, 37, 10, 8, 3, MLP_MOM), (64, 100, 10, 8, 3, MLP_MOM), (64, 37, 10, 4, 3, ADAM), (64, 100, 10, 4, 1, ADAM),
+    (5, 37, 10, 1, 1, SGD), (127, 37, 64, 4, 2, SGD), (128, 100, 1, 4, 1, SGD),
+    (129, 100, 10, 4, 1, SGD), (200, 37, 10, 4, 1, SGD), (200, 80, 10, 4, 3, SGD), (200, 64, 10, 4, 3, ADAM),
+    (784, 16, 10, 4, 1, SGD)])
+def test_mlp_sizes_replay_parity(d_in, hidden, n_class, mak, muf, opt):
+    """Layers that fill only a part of the 16-column groups and 32-row waves of the register layout, up to its limits
+    (128 columns, 64 classes), and inputs wider than that, whose layer keeps its weights in LDS beside two layers in registers.
+    The tolerance is the one of every replay (fp32 against float64)."""
+    dims = dict(d_in=d_in, hidden=hidden, n_class=n_class)
+    data = synth.make_mlp(200, 37, dims)
+    fp = synth.init_params("mlp", dims, 10)
+    g = gpu_train("mlp", dims, fp, data, mak, muf, opt)
+    check_controller_log(g["logs"], mak, len(data))
+    compare_up_to_relu_decisions("mlp", dims, fp, data, g, muf, opt)
 
 
 # The recurrent model under Adam at lr = 0.002 is a chaotic training run: the checker's own result moves by O(1)
