@@ -350,12 +350,13 @@ size_t lds_floats(const amp_ctx* c, HostWorker& w) {
     case ROLE_G_READOUT:
       f = wfl + r4(c->dims.hidden) + AMP_THREADS;
       break;
-    case ROLE_MLP_LIN:   // weights in registers and their optimizer slots in LDS, or weights and a gradient accumulator in LDS
-      if (n.rows <= 128 && n.cols <= 128 && 2 * wfl + r4(ldw) + 2 * r4(R) + r4(C) + r4(8 * std::max(R, C)) <= avail) {
+    case ROLE_MLP_LIN:   // weights in registers and their optimizer slots in LDS, or (wide inputs) weights and a gradient accumulator in LDS
+      if (n.rows <= 128 && n.cols <= 128)
         f = 4 * 128 + 64 + 2 * (128 * 128 + 128) + 32 * 132;
-        break;
-      }
-      f = 2 * wfl + r4(ldw) + r4(R) + r4(R) + r4(C) + r4(8 * std::max(R, C));
+      else if (w.aux == 0)
+        f = 2 * wfl + r4(ldw) + r4(R) + r4(R) + r4(C) + r4(8 * std::max(R, C));
+      else
+        return 0;   // a hidden layer of more than 128 units: its tile alone is beyond half the LDS
       break;
     default:   // RNN output layer
       f = wfl + r4(C) + r4(R) + r4(R) + r4(C) + r4(8 * std::max(R, C));

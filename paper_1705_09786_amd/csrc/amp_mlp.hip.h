@@ -495,16 +495,21 @@ __device__ __forceinline__ void role_mlp_layer(const GQ AmpDev* D, const GQ Work
     role_mlp_regs<FIRST, LAST, false, false>(D, W);
 }
 
-// ------------------------------------------------------------ larger layers
-// Any shape: weights, bias and the gradient accumulator (same layout) stay in LDS for the life of the launch; the
-// accumulator rests in HBM between launches.
-__device__ __noinline__ void role_mlp_any(const GQ AmpDev* D, const GQ WorkerDev* W) {
+// ------------------------------------------------------------ a first layer of more than 128 inputs
+// Weights, bias and the gradient accumulator (same layout) stay in LDS for the life of the launch; the accumulator rests
+// in HBM between launches.  Only the first layer can be that large: a hidden layer beyond 128 x 128 does not fit the LDS
+// twice, and the host refuses it.
+//
+// What bounds it: the passes over the tile, one per gradient and one per update.  Each thread takes four neighbouring
+// elements at a time and steps row and column along with the index.  Element by element, with a division by the row
+// length for each, an update per gradient took 21.1 us per instance at 64 x 200 with these 256 threads (15.3 with the 512
+// of the other models' kernels); this takes 12.1, and at 16 x 784 12.6 instead of 21.1 (15.5 with 512).
+__device__ __noinline__ void role_mlp_wide(const GQ AmpDev* D, const GQ WorkerDev* W) {
   float* lds = amp_lds;
   const GQ NodeDev& nd = D->node[uni(W->node)];
   const Tile t = make_tile(nd, W);
   const int HS = amp_round4(uni(D->hidden));   // row stride of the slot storage
-  const int R = t.R, C = t.C, li = uni(W->aux), ldw = t.ldw, muf = uni(nd.muf), train = uni(D->train);
-  const bool first = li == 0, last = li == 2;
+  const int R = t.R, C = t.C, ldw = t.ldw, muf = uni(nd.muf);
   Lds L{lds};
   float* Wg = L.take(t.Rp * ldw);
   float* bg = L.take(t.Rp);
@@ -515,46 +520,44 @@ __device__ __noinline__ void role_mlp_any(const GQ AmpDev* D, const GQ WorkerDev
   LDSQ float* xs = (LDSQ float*)L.take(ldw);
   LDSQ float* ys = (LDSQ float*)L.take(R);
   LDSQ float* ds = (LDSQ float*)L.take(R);
-  LDSQ float* dx = (LDSQ float*)L.take(C);
-  LDSQ float* part = (LDSQ float*)L.take(8 * (R > C ? R : C));
+  LDSQ float* part = (LDSQ float*)L.take(8 * R);
   tile_load(nd, t, Wg, bg);
   GQ float* ndG = uni_gq<float>(nd.G);
   GQ float* ndM = uni_gq<float>(nd.M);
   GQ float* ndV = uni_gq<float>(nd.V);
-  const long long boff = (long long)uni(nd.rows) * C;
-  const int has_bias = uni(nd.has_bias);
+  const int boff = R * C;
   for (int i = threadIdx.x; i < t.Rp * ldw; i += AMP_THREADS) {
     const int lr = i / ldw, c = i - lr * ldw;
-    Gl[i] = (lr < R && c < C) ? ndG[(long long)lr * C + c] : 0.f;
+    Gl[i] = (lr < R && c < C) ? ndG[lr * C + c] : 0.f;
   }
-  for (int i = threadIdx.x; i < t.Rp; i += AMP_THREADS) gbl[i] = (i < R && has_bias) ? ndG[boff + i] : 0.f;
+  for (int i = threadIdx.x; i < t.Rp; i += AMP_THREADS) gbl[i] = i < R ? ndG[boff + i] : 0.f;
   for (int i = threadIdx.x; i < ldw; i += AMP_THREADS) xs[i] = 0.f;
   __syncthreads();
-  const GQ float* act_in = first ? nullptr : uni_gq<float>(D->buf[li - 1]);
-  GQ float* act_out = last ? nullptr : uni_gq<float>(D->buf[li]);
-  const GQ float* g_in = last ? nullptr : uni_gq<float>(D->buf[2 + li]);
-  GQ float* g_out = first ? nullptr : uni_gq<float>(D->buf[2 + li - 1]);
+  GQ float* act_out = uni_gq<float>(D->buf[0]);
+  const GQ float* g_in = uni_gq<float>(D->buf[2]);
   const GQ float* datax = uni_gq<float>(D->data.x);
-  const GQ int* lab = uni_gq<int>(D->data.lab);
-  const GQ int* lab_off = uni_gq<int>(D->data.lab_off);
   const GQ unsigned* slot_seq = uni_gq<unsigned>(D->slot_seq);
   const GQ int* slot_inst = uni_gq<int>(D->slot_inst);
-  GQ float* loss_out = uni_gq<float>(D->loss_out);
-  GQ int* correct_out = uni_gq<int>(D->correct_out);
-  const unsigned first_seq = uni(s_first_seq);
-  MlpRings q = mlp_rings(D, li);
+  const OptCoef ob = opt_base(nd);
+  const int mean = uni(nd.mean);
+  // this thread's first group of four elements and the way from one to the next (rows of ldw / 4 groups)
+  const int lq = ldw >> 2, row0 = (int)threadIdx.x / lq, cq0 = (int)threadIdx.x - row0 * lq;
+  const int drow = AMP_THREADS / lq, dcq = AMP_THREADS - drow * lq;
+#define MLP_FOR_GROUPS                                                                              \
+  for (int q = threadIdx.x, lr = row0, cq = cq0; q < R * lq;                                        \
+       q += AMP_THREADS, cq += dcq, lr += drow + (cq >= lq ? 1 : 0), cq -= cq >= lq ? lq : 0)
+  MlpRings rq = mlp_rings(D, 0);
   unsigned code;
   unsigned count = W->wstate[0], tstep = W->wstate[1];
-  while (mlp_wait(D, q, code)) {
+  while (mlp_wait(D, rq, code)) {
     // this path reads its inputs through the L1
     if (threadIdx.x == 0) fence_acquire();
     lds_barrier();
     const int s = MSG_SLOT(code);
     const unsigned seq = uni(slot_seq[s]);
-    const int word = uni(slot_inst[s]), inst = word & 0x7fffffff;
-    const bool fwd_only = !train || word < 0;   // an evaluation instance: the loss layer retires it
-    const GQ float* x = first ? datax + (long long)inst * C : act_in + (long long)s * HS;
-    bool backward = (code & MSG_DIR_B) != 0;
+    const int inst = uni(slot_inst[s]) & 0x7fffffff;
+    const GQ float* x = datax + (long long)inst * C;
+    const bool backward = (code & MSG_DIR_B) != 0;
     for (int c = threadIdx.x; c < C; c += AMP_THREADS) xs[c] = x[c];
     if (backward)
       for (int r = threadIdx.x; r < R; r += AMP_THREADS)
@@ -563,90 +566,85 @@ __device__ __noinline__ void role_mlp_any(const GQ AmpDev* D, const GQ WorkerDev
     if (!backward) {
       gemv_rows(Wl, ldw, R, C, bl, xs, part, ys);
       LOG(W->node, 0, seq, 0);
-      if (!last) {
-        for (int r = threadIdx.x; r < R; r += AMP_THREADS) act_out[(long long)s * HS + r] = fmaxf(ys[r], 0.f);
-        publish_barrier();
-        if (threadIdx.x == 0) {
-          fence_release();
-          mlp_post(false, q.next, q.next_tail, MSG_MAKE(0, s, MSG_LOCAL(code)));
-        }
-        continue;
-      }
-      const int label = lab[lab_off[inst]];
-      softmax_xent_wave0((float*)ys, R, label, (float*)ds, &s_loss, &s_pred);
+      for (int r = threadIdx.x; r < R; r += AMP_THREADS) act_out[(long long)s * HS + r] = fmaxf(ys[r], 0.f);
+      publish_barrier();
       if (threadIdx.x == 0) {
-        loss_out[seq - first_seq] = s_loss;
-        correct_out[seq - first_seq] = s_pred == label;
+        fence_release();
+        mlp_post(false, rq.next, rq.next_tail, MSG_MAKE(0, s, MSG_LOCAL(code)));
       }
-      if (fwd_only) {
-        publish_barrier();
-        if (threadIdx.x == 0) {
-          fence_release();
-          ring_post(q.ctl, MSG_MAKE(1, s, 0));
-        }
-        continue;
-      }
-      backward = true;   // the loss layer starts backpropagation
+      continue;
     }
     LOG(W->node, 1, seq, 0);
-    if (!first) {
-      gemv_cols(Wl, ldw, R, C, ds, part, dx);
-      for (int c = threadIdx.x; c < C; c += AMP_THREADS) g_out[(long long)s * HS + c] = dx[c];
+    if (threadIdx.x == 0) ring_post(rq.ctl, MSG_MAKE(1, s, 0));   // retired: what it left is in LDS now
+    MLP_FOR_GROUPS {
+      LDSQ v4f* g = (LDSQ v4f*)Gl + q;
+      const v4f x4 = ((const LDSQ v4f*)xs)[cq];
+      const float d = ds[lr];
+      v4f a = *g;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) a[e] = fmaf(d, x4[e], a[e]);
+      *g = a;
     }
-    // every wave's HBM stores have landed before thread 0 publishes
-    publish_barrier();
-    if (threadIdx.x == 0) {
-      fence_release();
-      if (first)
-        ring_post(q.ctl, MSG_MAKE(1, s, 0));
-      else
-        mlp_post(false, q.prev, q.prev_tail, MSG_MAKE(1, s, MSG_LOCAL(code)));
-    }
-    tile_accumulate_lds(t, Gl, gbl, ds, xs);
+    for (int lr = threadIdx.x; lr < R; lr += AMP_THREADS) gbl[lr] += ds[lr];
     count++;
     if ((int)count >= muf) {
-      // the node's own update (Section 3) from the accumulator in LDS
+      // the node's own update (Section 3) from the accumulator in LDS; every thread steps the elements it has summed
       tstep++;
       if (threadIdx.x == 0) note_update(D);
-      lds_barrier();
-      const OptCoef o = opt_coef(nd, tstep);
-      const float inv = nd.mean ? 1.f / (float)count : 1.f;
-      for (int i = threadIdx.x; i < R * ldw; i += AMP_THREADS) {
-        const int lr = i / ldw, c = i - lr * ldw;
-        if (c < C) {
-          Wl[i] = opt_apply(o, Wl[i], Gl[i] * inv, ndM, ndV, (long long)lr * C + c);
-          Gl[i] = 0.f;
+      const OptCoef o = opt_at(ob, tstep);
+      const float inv = mean ? 1.f / (float)count : 1.f;
+      MLP_FOR_GROUPS {
+        LDSQ v4f *g = (LDSQ v4f*)Gl + q, *w = (LDSQ v4f*)Wl + q;
+        v4f ga = *g, wa = *w;
+        float m[4], v[4];
+        const int at = lr * C + 4 * cq;
+        if (o.kind != 0) {   // the slots are in HBM, all eight fetched together
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            m[e] = ndM[4 * cq + e < C ? at + e : 0];
+            v[e] = o.kind == 2 ? ndV[4 * cq + e < C ? at + e : 0] : 0.f;
+          }
         }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          wa[e] = opt_step(o, wa[e], ga[e] * inv, m[e], v[e]);
+          if (o.kind != 0 && 4 * cq + e < C) {
+            ndM[at + e] = m[e];
+            if (o.kind == 2) ndV[at + e] = v[e];
+          }
+        }
+        *w = wa;
+        *g = (v4f){0.f, 0.f, 0.f, 0.f};
       }
-      if (has_bias)
-        for (int lr = threadIdx.x; lr < R; lr += AMP_THREADS) {
-          bl[lr] = opt_apply(o, bl[lr], gbl[lr] * inv, ndM, ndV, boff + lr);
-          gbl[lr] = 0.f;
-        }
+      for (int lr = threadIdx.x; lr < R; lr += AMP_THREADS) {
+        bl[lr] = opt_apply(o, bl[lr], gbl[lr] * inv, ndM, ndV, boff + lr);
+        gbl[lr] = 0.f;
+      }
       count = 0;
       LOG(W->node, 2, 0, 0);
     }
-    lds_barrier();
   }
+#undef MLP_FOR_GROUPS
   tile_store(nd, t, Wg, bg);
   for (int i = threadIdx.x; i < R * ldw; i += AMP_THREADS) {
     const int lr = i / ldw, c = i - lr * ldw;
-    if (c < C) ndG[(long long)lr * C + c] = Gl[i];
+    if (c < C) ndG[lr * C + c] = Gl[i];
   }
-  if (has_bias)
-    for (int lr = threadIdx.x; lr < R; lr += AMP_THREADS) ndG[boff + lr] = gbl[lr];
+  for (int lr = threadIdx.x; lr < R; lr += AMP_THREADS) ndG[boff + lr] = gbl[lr];
   if (threadIdx.x == 0) {
     W->wstate[0] = count;
     W->wstate[1] = tstep;
-    s_stat[0] = q.waited;
-    s_stat[1] = q.messages;
+    s_stat[0] = rq.waited;
+    s_stat[1] = rq.messages;
   }
 }
 
 __device__ __forceinline__ void role_mlp_lin(const GQ AmpDev* D, const GQ WorkerDev* W) {
   const GQ NodeDev& nd = D->node[W->node];
-  if (nd.rows > MLP_MAX || nd.cols > MLP_MAX || !s_nowb)
-    role_mlp_any(D, W);
+  if (!s_nowb) {   // four workers a replica are packed at every number of replicas; the hand-overs rely on it
+    if (threadIdx.x == 0) raise_abort(D, ABORT_BAD_STATE, blockIdx.x);
+  } else if (W->aux == 0 && nd.cols > MLP_MAX)
+    role_mlp_wide(D, W);
   else if (W->aux == 0)
     role_mlp_layer<true, false>(D, W);
   else if (W->aux == 1)

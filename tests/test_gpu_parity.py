@@ -62,7 +62,7 @@ def test_mlp_mak1_is_synchronous_sgd():
     (64, 37, 10, 8, 3, MLP_MOM), (64, 100, 10, 8, 3, MLP_MOM), (64, 37, 10, 4, 3, ADAM), (64, 100, 10, 4, 1, ADAM),
     (5, 37, 10, 1, 1, SGD), (127, 37, 64, 4, 2, SGD), (128, 100, 1, 4, 1, SGD),
     (129, 100, 10, 4, 1, SGD), (200, 37, 10, 4, 1, SGD), (200, 80, 10, 4, 3, SGD), (200, 64, 10, 4, 3, ADAM),
-    (784, 16, 10, 4, 1, SGD)])
+    (136, 112, 10, 8, 3, MLP_MOM), (784, 16, 10, 4, 1, SGD)])
 def test_mlp_sizes_replay_parity(d_in, hidden, n_class, mak, muf, opt):
     """Layers that fill only a part of the 16-column groups and 32-row waves of the register layout, up to its limits
     (128 columns, 64 classes), and inputs wider than that, whose layer keeps its weights in LDS beside two layers in registers.
