@@ -1,6 +1,6 @@
 """Builds the HIP library (kernels + C boundary) for gfx950, in-tree: libamp.so, and libamp_strict.so, the same
-sources compiled with -DAMP_STRICT_JOIN (joins completed with explicit acquire / release ordering instead of the
-fence-free shortcut; the parity suite runs both so that a mismatch can be attributed).  Every model's persistent kernel
+sources compiled with -DAMP_STRICT_JOIN (joins completed, and messages handed over inside one die, with explicit acquire /
+release ordering instead of the fence-free shortcuts; the parity suite runs both so that a mismatch can be attributed).  Every model's persistent kernel
 is a source file of its own, compiled side by side."""
 from __future__ import annotations
 

@@ -30,15 +30,32 @@ __device__ __forceinline__ unsigned ld_u32(const unsigned* p) {
 // one die, checked against the hardware's die number when the kernel starts).  Stores that have been acknowledged
 // are then in the L2 all of them read through, so a release needs no L2 write-back, only the wait.  Measured with
 // two workgroups handing 4 KB back and forth on one die: 0.93 us per hand-over instead of 1.31 us, every word right.
+// The HIP memory model has no such rule: it is how gfx950's caches work.  -DAMP_STRICT_JOIN keeps to the model instead, here and
+// wherever strict_release / strict_acquire or ring_put_near stand.
 __shared__ int s_nowb;
 __shared__ unsigned s_first_seq;   // admission number of this replica's first admission of the launch
 __device__ __forceinline__ void fence_release() {
-  if (s_nowb)
+#ifndef AMP_STRICT_JOIN
+  if (s_nowb) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  else
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    return;
+  }
+#endif
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
 }
 __device__ __forceinline__ void fence_acquire() { __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent"); }
+
+// Fences of the strict build alone, at hand-overs that otherwise do without.
+__device__ __forceinline__ void strict_release() {
+#ifdef AMP_STRICT_JOIN
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+#endif
+}
+__device__ __forceinline__ void strict_acquire() {
+#ifdef AMP_STRICT_JOIN
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+#endif
+}
 
 // Data another workgroup of a packed launch has published, read past the L1 (which may hold an older line) from the L2
 // that both share: agent-scope loads do that, so no cache has to be invalidated first (159 ns per acquire).  Only where
@@ -104,11 +121,21 @@ __device__ __forceinline__ void ring_put(const R& r, unsigned ticket, unsigned c
   __hip_atomic_store((GQ unsigned long long*)&r.ent[ticket & r.mask], e, __ATOMIC_RELAXED, AGENT);
 }
 
-// The same where every reader polls through the same L2 (s_nowb): a store that goes no further than that L2 is enough and
-// gets there sooner (0.68 us per hand-over of 8 KB between two workgroups instead of 0.78, every word right).
+// The same where every reader polls through this workgroup's L2 (s_nowb), after every wave's stores have been acknowledged.
+// No scope of the memory model says "this die": an agent-scope store is written on through the L2, for the other dies'
+// sake, and a workgroup-scope one promises nothing to another workgroup.  So the instruction is spelt out: the L1 writes
+// every store through, a store that goes no further than the L2 is in front of all pollers, and it gets there sooner (0.68
+// us per hand-over of 8 KB between two workgroups instead of 0.78; 1,024 instances through the 64-128-128-10 MLP take 3.74
+// ms instead of 4.09).  A reader past the L1 (ld_shared) then finds the payload, whose address it learns from the entry.
 __device__ __forceinline__ void ring_put_near(const Ring& r, unsigned ticket, unsigned code) {
   unsigned long long e = ((unsigned long long)(ticket + 1u) << 32) | code;
-  __hip_atomic_store(&r.ent[ticket & r.mask], e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  GQ unsigned long long* slot = &r.ent[ticket & r.mask];
+#ifdef AMP_STRICT_JOIN
+  strict_release();
+  __hip_atomic_store(slot, e, __ATOMIC_RELAXED, AGENT);
+#else
+  asm volatile("global_store_dwordx2 %0, %1, off sc0" ::"v"(slot), "v"(e) : "memory");
+#endif
 }
 
 __device__ __forceinline__ void raise_abort(const GQ AmpDev* D, unsigned code, unsigned detail) {
@@ -567,8 +594,9 @@ __device__ __forceinline__ void note_update(const GQ AmpDev* D) {
 // parts' writes.  Built with -DAMP_STRICT_JOIN the completing arrival makes the
 // edge explicit: its read-modify-write acquires (and so synchronises with every
 // earlier arrival's release fence through the counter's release sequence) and a
-// release fence precedes the post.  The two builds must give the same results;
-// a parity test runs both.
+// release fence precedes the post; the hand-overs inside one die get their agent-scope
+// fences back too (fence_release, ring_put_near).  The two builds must give the same
+// results; a parity test runs both.
 __device__ __forceinline__ bool join_arrive(GQ int* counter, int expect) {
 #ifdef AMP_STRICT_JOIN
   const int old = __hip_atomic_fetch_add(counter, 1, __ATOMIC_ACQ_REL, AGENT);

@@ -40,7 +40,7 @@ __device__ __forceinline__ void mlp_post(bool near, const Ring& r, unsigned& tai
 __shared__ unsigned s_mlp[2][2];
 
 // Whole workgroup: wave 0 polls both rings, everybody gets the code of the message taken; false when the run is over.
-// Nothing is invalidated: where s_nowb holds, the caller reads what it was sent with ld_shared.
+// Nothing is invalidated (but in the strict build): where s_nowb holds, the caller reads what it was sent with ld_shared.
 __device__ __forceinline__ bool mlp_wait(const GQ AmpDev* D, MlpRings& q, unsigned& code) {
   unsigned* out = s_mlp[q.buf];   // two buffers: a wave may still read the one while wave 0 fills the other
   q.buf ^= 1u;
@@ -76,6 +76,7 @@ __device__ __forceinline__ bool mlp_wait(const GQ AmpDev* D, MlpRings& q, unsign
     const unsigned taken = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)e, lane);
     q.waited += (unsigned long long)(wall_clock64() - t0);
     q.messages += 1u - stop;
+    strict_acquire();
     if (threadIdx.x == 0) {
       out[0] = taken;
       out[1] = stop ? 0u : 1u + (unsigned)lane;
@@ -335,9 +336,10 @@ __device__ __noinline__ void role_mlp_regs(const GQ AmpDev* D, const GQ WorkerDe
     if (threadIdx.x == 0) {
       if (back && !FIRST)
         mlp_post(true, rq.prev, rq.prev_tail, MSG_MAKE(1, s, local));
-      else if (LAST || back)
+      else if (LAST || back) {
+        strict_release();
         ring_post(rq.ctl, MSG_MAKE(1, s, 0));   // done: an evaluation instance, or back at the first layer
-      else
+      } else
         mlp_post(true, rq.next, rq.next_tail, MSG_MAKE(0, s, local));
     }
     // the gradient; the node's own update (Section 3) when enough of them have arrived
@@ -575,7 +577,10 @@ __device__ __noinline__ void role_mlp_wide(const GQ AmpDev* D, const GQ WorkerDe
       continue;
     }
     LOG(W->node, 1, seq, 0);
-    if (threadIdx.x == 0) ring_post(rq.ctl, MSG_MAKE(1, s, 0));   // retired: what it left is in LDS now
+    if (threadIdx.x == 0) {
+      strict_release();
+      ring_post(rq.ctl, MSG_MAKE(1, s, 0));   // retired: what it left is in LDS now
+    }
     MLP_FOR_GROUPS {
       LDSQ v4f* g = (LDSQ v4f*)Gl + q;
       const v4f x4 = ((const LDSQ v4f*)xs)[cq];

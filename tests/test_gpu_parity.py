@@ -336,6 +336,24 @@ def test_threshold_lowered_between_training_calls():
     assert first is not None
 
 
+@pytest.mark.parametrize("d_in", [64, 200])
+def test_strict_build_mlp_replay_parity(d_in):
+    """The MLP's hand-overs inside one die with agent-scope fences, and without: both builds replay to the same
+    tolerance.  With one instance in flight there is one order of events, and the builds agree to the bit."""
+    dims = dict(d_in=d_in, hidden=64, n_class=10)
+    data = synth.make_mlp(200, 37, dims)
+    fp = synth.init_params("mlp", dims, 10)
+    one = []
+    for strict in (True, False):
+        g = gpu_train("mlp", dims, fp, data, 4, 1, SGD, strict=strict)
+        check_controller_log(g["logs"], 4, len(data))
+        compare_up_to_relu_decisions("mlp", dims, fp, data, g, 1, SGD)
+        one.append(gpu_train("mlp", dims, fp, data, 1, 1, SGD, strict=strict, log=False))
+    assert np.array_equal(one[0]["losses"], one[1]["losses"])
+    for a, b in zip(one[0]["params"], one[1]["params"]):
+        assert np.array_equal(a, b)
+
+
 @pytest.mark.parametrize("model", ["tree", "ggnn"])
 def test_strict_join_build_replay_parity(model):
     """The library built with explicitly ordered join completion (acquire on the completing arrival, release before
