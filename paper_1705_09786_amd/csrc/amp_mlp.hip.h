@@ -286,7 +286,8 @@ __device__ __noinline__ void role_mlp_regs(const GQ AmpDev* D, const GQ WorkerDe
         const float se = wave_sum(e);
         const float dz = lane < R ? e / se - (lane == label ? 1.f : 0.f) : 0.f;
         if (wave == 3) {   // not among the waves that write the result below
-          const int best = __builtin_ctzll(__ballot(z == m));   // the first class with the largest logit
+          const unsigned long long top = __ballot(lane < R && z == m);   // none where every logit is NaN
+          const int best = top ? __builtin_ctzll(top) : 0;   // the first class with the largest logit
           const float zl = lane_of(z, uni(label));
           if (lane == 0) {
             loss_out[seq - first_seq] = -(zl - m - logf(se));

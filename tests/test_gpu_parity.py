@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 from oracle import direct
-from paper_1705_09786_amd import synth
+from paper_1705_09786_amd import runner, synth
 
 from oracle import amp as oamp
 
@@ -73,6 +73,20 @@ def test_mlp_sizes_replay_parity(d_in, hidden, n_class, mak, muf, opt):
     g = gpu_train("mlp", dims, fp, data, mak, muf, opt)
     check_controller_log(g["logs"], mak, len(data))
     compare_up_to_relu_decisions("mlp", dims, fp, data, g, muf, opt)
+
+
+def test_mlp_logits_without_a_largest():
+    """Parameters that a diverged run has left at NaN: no logit is the largest, the loss is NaN and the prediction class 0,
+    as in the other models' loss layers."""
+    dims = dict(d_in=8, hidden=16, n_class=3)
+    data = synth.make_mlp(30, 37, dims)
+    fp = synth.init_params("mlp", dims, 10)
+    fp[2] = np.full_like(fp[2], np.nan)
+    tr = runner.Trainer("mlp", dims, fp, 4, 1, 0, len(data), arena_bytes=1 << 28)
+    tr.submit_all(data, which=1)
+    ev = tr.amp.eval()
+    assert np.isnan(ev["mean_loss"])
+    assert ev["accuracy"] == np.mean([i["label"] == 0 for i in data]) > 0
 
 
 # The recurrent model under Adam at lr = 0.002 is a chaotic training run: the checker's own result moves by O(1)
