@@ -89,6 +89,26 @@ def test_mlp_logits_without_a_largest():
     assert ev["accuracy"] == np.mean([i["label"] == 0 for i in data]) > 0
 
 
+def test_mlp_instances_beyond_a_message_s_index():
+    """A message carries an instance index of up to 19 bits less one; the workers look larger ones up in the slot table.  At
+    learning rate zero every loss of a set that reaches past the limit is the plain forward pass's."""
+    dims = dict(d_in=3, hidden=16, n_class=5)
+    n = 0x7ffff + 40
+    data = synth.make_mlp(n, 37, dims)
+    fp = synth.init_params("mlp", dims, 10)
+    g = gpu_train("mlp", dims, fp, data, 8, 1, dict(kind="sgd", lr=0.0), log=False)
+    P = direct.unpack("mlp", dims, fp)
+    h = np.array([i["x"] for i in data], np.float64)
+    for k in range(3):
+        h = h @ P[k]["W"].T + P[k]["b"]
+        h = np.maximum(h, 0.0) if k < 2 else h
+    h -= h.max(axis=1, keepdims=True)
+    ref = np.log(np.exp(h).sum(axis=1)) - h[np.arange(n), [i["label"] for i in data]]
+    assert np.abs(g["losses"] - ref).max() <= 1e-5 * max(1.0, ref.max())
+    for a, b in zip(g["params"], fp):
+        assert np.array_equal(a, b)
+
+
 # The recurrent model under Adam at lr = 0.002 is a chaotic training run: the checker's own result moves by O(1)
 # when its initial parameters are perturbed by 1e-7 (relative), so no fp32 implementation can follow it to 1e-5.
 # At lr = 5e-4 over 300 sequences the same perturbation stays at 1e-7 (the CPU suite checks this), and that
