@@ -41,14 +41,30 @@ __device__ __forceinline__ int rnn_reg_pairs(const GQ NodeDev& nd, const GQ Work
   const int held = (int)W->wstate[0] + 1;   // pairs carried over from the previous launch, and room for one more
   return nd.muf > held ? nd.muf : held;
 }
+// Far more sequences in flight than this worker's sixteen places, and a small matrix: role_rnn_cell takes up to 64 messages at
+// once, and its padding to 16 costs a small product little, while a batch here takes the same time whatever part of the
+// 64-wide pieces is used.  Where the two meet, measured over hidden = emb = 16 .. 128, 17 .. 192 in flight and an update every
+// 2 .. 48 (time there / time here, plain SGD; n = sequences in flight for each copy):
+//   update every 16: hidden 16 at n = 28 1.06, 32 0.95, 48 0.82; hidden 32 at 32 1.00, 40 0.90; hidden 48 at 40 1.02,
+//   48 0.98; hidden 64 at 48 1.05, 64 1.02
+//   n = 64: hidden 16 at an update every 10 1.02, 12 0.93; hidden 32 at 12 0.98; hidden 48 at 12 1.07, 14 0.98, 16 0.95;
+//   hidden 64 at 16 1.02, 24 0.97, 32 0.94 -- and 1.5 .. 1.7 at 4: updates cut the batches there short
+//   more than one piece of rows: hidden 72 at n = 48 and every 24 0.99, n = 64 0.90; hidden 80 1.01, 0.90; hidden 96 1.11,
+//   0.98; hidden 128 1.50; with optimizer slots 1.04 .. 1.15 at hidden 80
+//   evaluation: hidden 16 at n = 24 1.01, 28 0.88; hidden 32 at 28 0.99, 32 0.89; hidden 48 at 33 1.04, 40 0.96; hidden 64
+//   at 40 1.07, 48 0.97; hidden 72 at 40 0.99; hidden 80 at 40 1.04, 48 0.92; hidden 96 at 48 1.04, 64 0.92; hidden 112 1.18
+//   emb unlike hidden, n = 64: 32 x 128 at every 32 0.96, evaluation 0.89; 64 x 96 1.08, 0.95; 80 x 128 1.00, 1.01
+__device__ __forceinline__ bool rnn_many_in_flight(const GQ AmpDev* D, const GQ NodeDev& nd) {
+  const int n = D->mak / D->node_replicas, mean = (nd.rows + D->emb) / 2;
+  const int side = (nd.rows > mean ? nd.rows : mean) - (nd.rows > 64 ? 24 : 0);
+  if (!D->train) return side <= 80 && n >= 16 + side / 2;
+  return side <= 64 && n >= 24 + side / 2 && nd.muf >= 10 + side / 8 && (nd.rows <= 64 || nd.opt == 0);
+}
 __device__ __forceinline__ bool rnn_reg_fits(const GQ AmpDev* D, const GQ WorkerDev* W) {
   const GQ NodeDev& nd = D->node[W->node];
   const int pairs = rnn_reg_pairs(nd, W);
   if (nd.rows > 128 || D->emb > 128 || nd.seg0 != D->emb || pairs > 96 || D->vocab > 4096) return false;
-  // Small cells with far more sequences in flight than this worker's places: role_rnn_cell takes up to 64 at once, and its
-  // padding to 16 costs a small matrix little (hidden = emb = 32, 64 in flight, 1,000 sequences: 16.1 ms there, 17.2 here;
-  // at 128 the register layout is the faster one at 64 in flight too).
-  if (nd.rows <= 64 && D->emb <= 64 && D->mak > 3 * RC_KB * D->node_replicas) return false;
+  if (rnn_many_in_flight(D, nd)) return false;
   return rnn_reg_floats(D->vocab, D->emb, pairs) <= AMP_DYN_LDS_BYTES / 4;
 }
 

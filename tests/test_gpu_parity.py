@@ -230,6 +230,36 @@ def test_rnn_cell_at_the_edges_of_its_register_tiles(emb, hidden, mak, muf, opt)
     compare(g, rt, len(data), opt=opt)
 
 
+@pytest.mark.parametrize("emb,hidden,mak,muf,opt", [
+    (32, 32, 40, 14, SGD), (32, 32, 39, 14, SGD), (32, 32, 40, 13, SGD), (64, 64, 64, 18, SGD), (64, 64, 55, 18, RNN_ADAM),
+    (70, 66, 60, 40, SGD)])
+def test_rnn_cell_with_many_sequences_in_flight(emb, hidden, mak, muf, opt):
+    """Either side of the lines between the two cell workers, and a model that crosses them: trained with `mak` in flight, then
+    with 8, then with `mak` again, an evaluation with `mak` in front of each.  Pending pairs and sums are handed from worker
+    to worker; the whole run replays to the tolerance of every replay."""
+    dims = dict(vocab=20, emb=emb, hidden=hidden, n_class=10)
+    data = synth.make_rnn(100, 33, dims, min_len=1, max_len=14)
+    valid = synth.make_rnn(80, 34, dims, min_len=1, max_len=14)
+    fp = synth.init_params("rnn", dims, 8)
+    g = gpu_train("rnn", dims, fp, data, mak, muf, opt)
+    a = g["trainer"].amp
+    rt = oracle_replay("rnn", dims, fp, data, g["logs"], muf, opt)
+    compare(g, rt, len(data), opt=opt)
+    for inst in valid:
+        a.submit(inst, which=1)
+    for call, m in ((1, 8), (2, mak)):
+        a.set_max_active_keys(mak)
+        ev = a.eval()
+        ref, _ = direct.evaluate("rnn", dims, direct.unpack("rnn", dims, g["params"]), valid)
+        assert abs(ev["mean_loss"] - ref) <= 1e-5 * max(1.0, abs(ref))
+        a.set_max_active_keys(m)
+        a.train(1)
+        first = call * len(data)
+        rt.replay(data, named_logs("rnn", dims, a.get_event_log()[1:]), first_seq=first)
+        g = dict(g, params=g["trainer"].params(), losses=a.get_instance_losses().astype(np.float64))
+        compare(g, rt, len(data), opt=opt, ref_losses=[rt.loss[first + i] for i in range(len(data))])
+
+
 @pytest.mark.parametrize("hidden,n_class,mak,muf,opt", [(96, 64, 24, 5, SGD), (97, 64, 24, 5, SGD), (33, 1, 40, 16, RNN_ADAM_MUF3),
                                                         (128, 3, 40, 1, SGD)])
 def test_rnn_output_layer_at_the_edges_of_its_batches(hidden, n_class, mak, muf, opt):
