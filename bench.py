@@ -203,7 +203,7 @@ def run_config(config, steps, warmup, mak=None, muf=None, n=None):
             "traffic": traffic["bytes"] if traffic else None,
             "traffic_unit": "HBM bytes per launch (rocprofv3 FETCH_SIZE + WRITE_SIZE, separate runs; profiles/hbm_traffic.md)",
             "traffic_source": traffic["source"] if traffic else None,
-            "kernel": "amp_persistent", "occupied_cus": n_workers, "peak_whole_chip": mfma_chip,
+            "kernel": "amp_persistent_" + model, "occupied_cus": n_workers, "peak_whole_chip": mfma_chip,
             "frac_whole_chip": ach_f / mfma_chip, "algorithmic_flops_per_launch": flops,
             "lds_equivalent": {"achieved": ach_b, "peak": lds_chip * n_workers / N_CU, "unit": "GB/s",
                                "frac": ach_b / (lds_chip * n_workers / N_CU), "frac_whole_chip": ach_b / lds_chip,

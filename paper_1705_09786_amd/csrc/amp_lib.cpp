@@ -1508,7 +1508,7 @@ void describe(const amp_ctx* c, const Resident& res, const LaunchLayout& L, int 
   D.max_staleness = (float)c->max_staleness;
   D.n_updaters = (int)wpr - 1;   // every worker but the controller applies updates
   D.n_total = (unsigned)L.n_total[r];
-    D.ctl = (unsigned*)(c->arena + L.off_ctl[r]);
+  D.ctl = (unsigned*)(c->arena + L.off_ctl[r]);
   D.slot_seq = (unsigned*)rep_ptr(c, r, c->off_slot_seq);
   D.smeta = (int*)rep_ptr(c, r, c->off_smeta);
   D.slot_inst = (int*)rep_ptr(c, r, c->off_slot_inst);
