@@ -73,6 +73,17 @@ def test_mlp_sizes_replay_parity(d_in, hidden, n_class, mak, muf, opt):
     g = gpu_train("mlp", dims, fp, data, mak, muf, opt)
     check_controller_log(g["logs"], mak, len(data))
     compare_up_to_relu_decisions("mlp", dims, fp, data, g, muf, opt)
+    # forward only: a call of its own, and mixed with training instances under a zero step
+    a, valid = g["trainer"].amp, synth.make_mlp(60, 38, dims)
+    for inst in valid:
+        a.submit(inst, which=1)
+    ref, acc = direct.evaluate("mlp", dims, direct.unpack("mlp", dims, g["params"]), valid)
+    evs = [a.eval()]
+    a.set_optimizer(-1, 0, lr=0.0)
+    evs.append(a.train_eval(1))
+    for ev in evs:
+        assert ev["n_instances"] == len(valid)
+        assert abs(ev["mean_loss"] - ref) <= 1e-5 * max(1.0, abs(ref)) and abs(ev["accuracy"] - acc) < 1e-9
 
 
 def test_mlp_logits_without_a_largest():
@@ -258,6 +269,32 @@ def test_rnn_cell_with_many_sequences_in_flight(emb, hidden, mak, muf, opt):
         rt.replay(data, named_logs("rnn", dims, a.get_event_log()[1:]), first_seq=first)
         g = dict(g, params=g["trainer"].params(), losses=a.get_instance_losses().astype(np.float64))
         compare(g, rt, len(data), opt=opt, ref_losses=[rt.loss[first + i] for i in range(len(data))])
+
+
+@pytest.mark.parametrize("mak,sync", [(80, 0), (80, 30), (78, 30)])
+def test_rnn_cell_copies_with_many_sequences_in_flight(mak, sync):
+    """Two copies of a small cell at and one below the number in flight that gives each the worker of the larger batches,
+    with and without synchronisation rounds; the evaluation behind the epoch's average takes that worker in any case."""
+    dims = dict(vocab=20, emb=32, hidden=32, n_class=10)
+    data = synth.make_rnn(240, 33, dims, min_len=1, max_len=14)
+    valid = synth.make_rnn(80, 34, dims, min_len=1, max_len=14)
+    fp = synth.init_params("rnn", dims, 8)
+    g = gpu_train("rnn", dims, fp, data, mak, 14, SGD, lookup_muf=14, node_replicas={1: 2}, group_sync=sync)
+    rt = oracle_runtime("rnn", dict(dims, node_replicas=2), fp, 14, SGD, lookup_muf=14)
+    names = [n.name for n in rt.ppt]
+    rt.replay(data, [[(names[node], k, s, l) for (node, k, s, l) in w] for w in g["logs"][1:]])
+    oamp.average_node_replicas(rt)
+    for k, node in enumerate(rt.ppt):
+        ref = oamp.C.pack_node(node.P)
+        assert rel_err(g["params"][k], ref) <= 1e-5, node.name
+        assert elementwise_err(g["params"][k], ref)[0] <= elem_tol(SGD), node.name
+    ref = np.array([rt.loss[i] for i in range(len(data))])
+    assert (np.abs(g["losses"] - ref) <= 1e-5 * np.maximum(np.abs(ref), 1.0)).all()
+    a = g["trainer"].amp
+    for inst in valid:
+        a.submit(inst, which=1)
+    ref, _ = direct.evaluate("rnn", dims, direct.unpack("rnn", dims, g["params"][:3]), valid)
+    assert abs(a.eval()["mean_loss"] - ref) <= 1e-5 * max(1.0, abs(ref))
 
 
 @pytest.mark.parametrize("hidden,n_class,mak,muf,opt", [(96, 64, 24, 5, SGD), (97, 64, 24, 5, SGD), (33, 1, 40, 16, RNN_ADAM_MUF3),
