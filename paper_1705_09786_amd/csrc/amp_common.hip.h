@@ -597,20 +597,21 @@ __device__ __forceinline__ void note_update(const GQ AmpDev* D) {
 // release fence precedes the post; the hand-overs inside one die get their agent-scope
 // fences back too (fence_release, ring_put_near).  The two builds must give the same
 // results; a parity test runs both.
-__device__ __forceinline__ bool join_arrive(GQ int* counter, int expect) {
+// In two halves, so that a lane with several arrivals has them on their way together.
+__device__ __forceinline__ int join_add(GQ int* counter) {
 #ifdef AMP_STRICT_JOIN
-  const int old = __hip_atomic_fetch_add(counter, 1, __ATOMIC_ACQ_REL, AGENT);
-  if (old + 1 != expect) return false;
-  __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, AGENT);
-  fence_release();
-  return true;
+  return __hip_atomic_fetch_add(counter, 1, __ATOMIC_ACQ_REL, AGENT);
 #else
-  const int old = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, AGENT);
-  if (old + 1 != expect) return false;
-  __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, AGENT);
-  return true;
+  return __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, AGENT);
 #endif
 }
+__device__ __forceinline__ bool join_done(GQ int* counter, int old, int expect) {
+  if (old + 1 != expect) return false;
+  __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, AGENT);
+  strict_release();
+  return true;
+}
+__device__ __forceinline__ bool join_arrive(GQ int* counter, int expect) { return join_done(counter, join_add(counter), expect); }
 
 __device__ __forceinline__ bool join_arrive(int* counter, int expect) { return join_arrive((GQ int*)counter, expect); }
 

@@ -33,6 +33,12 @@ AMP_HD static inline int amp_ldrow(int cols) {
   return l;
 }
 
+// LDS floats of a streamed tree tile (weights in HBM): bias, pre-activations / deltas of kb messages, row map and offsets, and
+// nw waves' partial sums of (16 NBF) x (16 RG + 4) floats, 64 x 68 at most (or two chunks of 64 inputs x 68 floats).  Four waves' where that costs no batch size
+// (fewer rounds until the sums have met), two otherwise.
+AMP_HD static inline int amp_stream_floats(int Rp, int ldy, int kb, int nw) { return 3 * Rp + amp_round4(kb * ldy) + nw * 64 * 68; }
+AMP_HD static inline int amp_stream_parts(int Rp, int ldy, int kb) { return amp_stream_floats(Rp, ldy, kb, 4) <= AMP_DYN_LDS_BYTES / 4 ? 4 : 2; }
+
 // Message code carried by a ring entry: [31] direction, [30:20] slot,
 // [19:0] position inside the instance.
 #define MSG_CTL_SLOT 2047u   // not an instance's slot (those are 0 .. AMP_MAX_MAK - 1): a request to the worker itself

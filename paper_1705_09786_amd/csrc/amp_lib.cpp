@@ -277,13 +277,13 @@ size_t lds_floats(const amp_ctx* c, HostWorker& w) {
     case ROLE_TREE_BRANCH: {
       // the largest batch (a multiple of 16 messages) whose pre-activation rows fit beside the weights
       const size_t ldy = amp_ldrow((int)R);
-      // tree cells: aux 1 = the weights stay in HBM, aux 2 = LDS-resident with the deltas in rows of their own
+      // tree cells: aux 1 = the weights stay in HBM, aux 2 = role_tree_cell_lds, aux 0 = weights in LDS, inputs from HBM
       if (w.role != ROLE_RNN_CELL && w.aux == 2) w.aux = 0;
       if (w.aux == 1 && w.role != ROLE_RNN_CELL) {
         // weights stay in HBM: rows must be 16-byte aligned and unpadded
         if (c->dims.hidden % 4 || c->dims.emb % 4) return 0;
         for (w.kb = 64; w.kb >= 16; w.kb -= 16) {
-          f = r4(Rp) + r4((size_t)w.kb * ldy) + 2 * r4(Rp) + 2 * 64 * 68;
+          f = (size_t)amp_stream_floats((int)Rp, (int)ldy, w.kb, amp_stream_parts((int)Rp, (int)ldy, w.kb));
           if (f <= avail) break;
         }
         if (w.kb < 16) return 0;
@@ -291,6 +291,19 @@ size_t lds_floats(const amp_ctx* c, HostWorker& w) {
       }
       // the update's register accumulator holds 8 waves x 4 (16-row, 64-column) units
       if ((Rp / 16) * ((amp_round16(n.cl()) + 63) / 64) > 32) return 0;
+      if (w.role != ROLE_RNN_CELL) {
+        // a batch's inputs and deltas beside the weights, if there is room for 32 messages.  (96 x 304 weights leave 22
+        // rows: 16 replicas of the hidden-150 tree on 5 + 8 tiles then take 13.4 ms an epoch of 4,272 trees, and 11.4 ms
+        // with batches of up to 64 whose inputs come from HBM.)
+        const size_t maps = 2 * r4(Rp) + (size_t)(amp_round16(n.cl()) + 63) / 64 * 64, row = ldw + ldy;
+        const size_t rows = wfl + maps < avail ? std::min<size_t>(64, (avail - wfl - maps) / row) : 0;
+        if (rows >= 32) {
+          w.kb = (int)rows;
+          w.aux = 2;
+          f = wfl + maps + rows * row;
+          break;
+        }
+      }
       // a sequence has one message in flight, so the recurrent cell never sees more than max_active_keys at once
       const int kb_top = w.role == ROLE_RNN_CELL ? std::min(64, amp_round16(c->max_mak)) : 64;
       for (w.kb = kb_top; w.kb >= 16; w.kb -= 16) {
@@ -298,12 +311,6 @@ size_t lds_floats(const amp_ctx* c, HostWorker& w) {
         if (f <= avail) break;
       }
       if (w.kb < 16) return 0;
-      // a tree cell keeps the deltas in rows of their own (waves without a share of the forward product form them
-      // meanwhile) where that costs no batch size
-      if (w.role != ROLE_RNN_CELL && f + r4((size_t)w.kb * ldy) <= avail) {
-        f += r4((size_t)w.kb * ldy);
-        w.aux = 2;
-      }
       if (w.role == ROLE_RNN_CELL) {
         // the lookup's gradient accumulator beside the cell's weights, if it fits (worker aux = 1)
         const size_t lkg = r4((size_t)c->dims.vocab * c->dims.emb);
@@ -811,7 +818,9 @@ int amp_finalize(amp_ctx* c, int max_active_keys, int max_instance_len, int max_
   }
   for (HostWorker& w : c->workers) {
     w.off_state = take(64);
-    if (w.node >= 0 && c->nodes[w.node].name.compare(0, 6, "lookup") != 0 && w.role != ROLE_TREE_OUT) {
+    // (cells that keep the gradient in registers have no list of pending pairs)
+    const bool in_regs = (w.role == ROLE_TREE_LEAF || w.role == ROLE_TREE_BRANCH) && w.aux == 2;
+    if (w.node >= 0 && c->nodes[w.node].name.compare(0, 6, "lookup") != 0 && w.role != ROLE_TREE_OUT && !in_regs) {
       w.pend_bytes = pend_stride(c, w) * 4 * AMP_DENSE_MAX_MUF * rows_per_message(c, w);
       w.off_pend = take(w.pend_bytes);
     }

@@ -3,32 +3,39 @@
 #include "amp_worker.hip.h"
 #include "amp_batch.hip.h"
 #include "amp_tree.hip.h"
+#include "amp_tree_cell.hip.h"
+
+template <bool BR, int GU>
+static __device__ __forceinline__ void tree_cell_opt(const GQ AmpDev* D, const GQ WorkerDev* W) {
+  const int opt = D->node[W->node].opt;
+  if (opt == 0) role_tree_cell_lds<BR, GU, 0>(D, W);
+  else if (opt == 1) role_tree_cell_lds<BR, GU, 1>(D, W);
+  else role_tree_cell_lds<BR, GU, 2>(D, W);
+}
+
+template <bool BR>
+static __device__ __forceinline__ void tree_cell_worker(const GQ AmpDev* D, const GQ WorkerDev* W) {
+  const GQ NodeDev& nd = D->node[W->node];
+  const int cl = ((nd.cols - nd.seg0) / nd.seg + 1) * nd.segp, rows = amp_round16(nd.nblocks * W->nu);
+  if (W->aux == 1) return role_tree_cell<BR, 0, 0, true>(D, W);
+  if (W->aux == 0) {
+    // hidden 150 / embedding 300 on 5 + 8 tiles, the fewest that fit the LDS: products with fixed trip counts
+    if (rows == 96 && amp_round16(cl) == 304) return role_tree_cell<BR, 6, 19, false>(D, W);
+    return role_tree_cell<BR, 0, 0, false>(D, W);
+  }
+  // units of 16 rows x 64 columns a wave owns of the gradient
+  const int units = (rows >> 4) * ((amp_round16(cl) + 63) >> 6);
+  if (units <= 8) tree_cell_opt<BR, 1>(D, W);
+  else if (units <= 16) tree_cell_opt<BR, 2>(D, W);
+  else if (units <= 24) tree_cell_opt<BR, 3>(D, W);
+  else tree_cell_opt<BR, 4>(D, W);
+}
 
 static __device__ __forceinline__ void tree_worker(const GQ AmpDev* D, const GQ WorkerDev* W) {
   switch (W->role) {
     case ROLE_TREE_LOOKUP: role_tree_lookup(D, W); break;
-    case ROLE_TREE_LEAF:
-    case ROLE_TREE_BRANCH: {
-      // hidden 150 / embedding 300 (nineteen 16-column groups) split into tiles of six, four or three 16-row blocks
-      // (5 + 8 tiles, the fewest that fit LDS; 8 leaf tiles; 16 branch tiles) has instantiations with fixed trip counts
-      const GQ NodeDev& nd = D->node[W->node];
-      const int rp = amp_round16(nd.nblocks * W->nu), cl = (nd.cols / nd.seg) * nd.segp;
-      const bool c19 = amp_round16(cl) == 304;
-      if (W->role == ROLE_TREE_LEAF) {
-        if (W->aux == 1) role_tree_cell<false, 0, 0, true>(D, W);
-        else if (c19 && rp == 96) role_tree_cell<false, 6, 19, false>(D, W);
-        else if (c19 && rp == 64) role_tree_cell<false, 4, 19, false>(D, W);
-        else if (c19 && rp == 48) role_tree_cell<false, 3, 19, false>(D, W);
-        else role_tree_cell<false, 0, 0, false>(D, W);
-      } else {
-        if (W->aux == 1) role_tree_cell<true, 0, 0, true>(D, W);
-        else if (c19 && rp == 96) role_tree_cell<true, 6, 19, false>(D, W);
-        else if (c19 && rp == 64) role_tree_cell<true, 4, 19, false>(D, W);
-        else if (c19 && rp == 48) role_tree_cell<true, 3, 19, false>(D, W);
-        else role_tree_cell<true, 0, 0, false>(D, W);
-      }
-      break;
-    }
+    case ROLE_TREE_LEAF: tree_cell_worker<false>(D, W); break;
+    case ROLE_TREE_BRANCH: tree_cell_worker<true>(D, W); break;
     case ROLE_TREE_OUT: role_tree_out(D, W); break;
     default: break;
   }

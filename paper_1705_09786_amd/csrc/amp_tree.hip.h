@@ -37,6 +37,7 @@ struct TreeBufs {
   int H, Hp, E, Ep, NNmax, Lmax, TL, TB;
   __device__ __forceinline__ long long node(int s, int n) const { return (long long)s * NNmax + n; }
   __device__ __forceinline__ long long leaf(int s, int l) const { return (long long)s * Lmax + l; }
+  __device__ __forceinline__ unsigned node32(int s, int n) const { return (unsigned)(s * NNmax + n); }   // nodes of all slots < 2^31
 };
 
 __device__ __forceinline__ TreeBufs tree_bufs(const GQ AmpDev* D) {
@@ -135,20 +136,8 @@ __device__ __forceinline__ void batch_split_and_log(const GQ AmpDev* D, const Wo
   }
 }
 
-// A tile has finished its units of node n: when all tiles have, the node's
-// [h; c] goes to the output layer and, through Isu / Concat, to its parent,
-// which fires once both children are there.  One lane, after a release fence.
-__device__ __forceinline__ void tree_node_part_done(const WorkerRegs& W, const TreeBufs& B, int s, int n, int parent_code) {
-  GQ int* c = B.cnt + B.node(s, n) * 4;
-  if (!join_arrive(c + 0, W.ntiles)) return;
-  ring_post(W.out, MSG_MAKE(0, s, n));
-  if (parent_code < 0) return;
-  const int p = parent_code >> 1;
-  if (join_arrive(B.cnt + B.node(s, p) * 4 + 1, 2)) ring_post(W.branch, MSG_MAKE(0, s, p));
-}
-
-// One gradient part for node n has been written: Bcast's backward waits for
-// the output layer's part and (unless n is the root) every parent tile's.
+// One gradient part for node n has been written by the output layer: Bcast's backward waits for its part and (unless n is
+// the root) every parent tile's.
 __device__ __forceinline__ void tree_grad_part_done(const WorkerRegs& W, const TreeBufs& B, int s, int n, bool is_root, bool is_leaf) {
   const int expect = is_root ? 1 : 1 + B.TB;
   if (join_arrive(B.cnt + B.node(s, n) * 4 + 2, expect)) {
@@ -156,6 +145,70 @@ __device__ __forceinline__ void tree_grad_part_done(const WorkerRegs& W, const T
       ring_post(W.leaf, MSG_MAKE(1, s, n));
     else
       ring_post(W.branch, MSG_MAKE(1, s, n));
+  }
+}
+
+// What a lane needs of its message to publish it.
+struct TreePost {
+  int s, n, a, b, par, L;
+  bool in, fwd;
+};
+__device__ __forceinline__ TreePost tree_post_of(const BatchMsg& M, int r, bool in, bool fwd) {
+  TreePost p;
+  p.s = M.s[r];
+  p.n = M.n[r];
+  p.a = M.a[r];
+  p.b = M.b[r];
+  p.par = M.par[r];
+  p.L = M.L[r];
+  p.in = in;
+  p.fwd = fwd;
+  return p;
+}
+
+// A cell tile's batch is written: joins and posts, one message per lane of the calling wave (all 64 lanes), after a release
+// fence.  Forward: when all tiles have done node n, its [h; c] goes to the output layer and, through Isu / Concat, to its
+// parent, which fires once both children are there.  Backward: a part for each child (branch cells) or for the
+// embedding's gradient (leaf cells) has arrived.  Every step of this is an atomic's round trip, so the lanes take each step
+// together: the arrivals of all messages, then the parents' arrivals beside one reservation per ring (a lane for each
+// ring), then the entries.  (Message by message, join after join, a batch whose tile arrives last took 3.4 us here; its
+// node waits for that tile.)
+template <bool BR>
+__device__ __forceinline__ void tree_publish(const WorkerRegs& W, const TreeBufs& B, const TreePost& p) {
+  const int lane = threadIdx.x & 63;
+  const unsigned long long lt = (1ull << lane) - 1ull;
+  const bool f = p.in && p.fwd, b = p.in && !p.fwd;
+  GQ int* c0 = B.cnt + B.node(p.s, BR && b ? p.a : p.n) * 4 + (p.fwd ? 0 : BR ? 2 : 3);
+  GQ int* c1 = B.cnt + B.node(p.s, BR && b ? p.b : p.n) * 4 + 2;
+  int o0 = 0, o1 = 0, o2 = 0;
+  if (p.in) o0 = join_add(c0);
+  if (BR && b) o1 = join_add(c1);
+  const bool d0 = p.in && join_done(c0, o0, p.fwd ? W.ntiles : BR ? 1 + B.TB : B.TL);
+  const bool d1 = BR && b && join_done(c1, o1, 1 + B.TB);
+  // the parent's other child
+  const bool up = f && d0 && p.par >= 0;
+  GQ int* cp = B.cnt + B.node(p.s, up ? p.par >> 1 : p.n) * 4 + 1;
+  if (up) o2 = join_add(cp);
+  const bool leaf0 = b && d0 && (!BR || p.a < p.L), leaf1 = d1 && p.b < p.L;   // leaf cells: to the lookup
+  const bool br0 = b && d0 && !leaf0, br1 = d1 && !leaf1;
+  const unsigned long long mo = __ballot(f && d0), ml0 = __ballot(leaf0), ml1 = __ballot(leaf1), mb0 = __ballot(br0), mb1 = __ballot(br1);
+  const Ring& down = BR ? W.leaf : W.lookup;
+  const unsigned want = lane == 0 ? __popcll(mo) : lane == 1 ? __popcll(ml0) + __popcll(ml1) : lane == 2 ? __popcll(mb0) + __popcll(mb1) : 0u;
+  GQ unsigned* tail = lane == 0 ? W.out.tail : lane == 1 ? down.tail : W.branch.tail;
+  unsigned t = 0;
+  if (want) t = __hip_atomic_fetch_add(tail, want, __ATOMIC_RELAXED, AGENT);
+  const unsigned to = __shfl(t, 0), tl = __shfl(t, 1), tb = __shfl(t, 2);
+  if (f && d0) ring_put(W.out, to + __popcll(mo & lt), MSG_MAKE(0, p.s, p.n));
+  if (leaf0) ring_put(down, tl + __popcll(ml0 & lt), MSG_MAKE(1, p.s, BR ? p.a : p.n));
+  if (leaf1) ring_put(down, tl + __popcll(ml0) + __popcll(ml1 & lt), MSG_MAKE(1, p.s, p.b));
+  if (br0) ring_put(W.branch, tb + __popcll(mb0 & lt), MSG_MAKE(1, p.s, p.a));
+  if (br1) ring_put(W.branch, tb + __popcll(mb0) + __popcll(mb1 & lt), MSG_MAKE(1, p.s, p.b));
+  const bool d2 = up && join_done(cp, o2, 2);
+  const unsigned long long mp = __ballot(d2);
+  if (mp) {
+    if (lane == 0) t = ring_reserve(W.branch, __popcll(mp));
+    t = __shfl(t, 0);
+    if (d2) ring_put(W.branch, t + __popcll(mp & lt), MSG_MAKE(0, p.s, p.par >> 1));
   }
 }
 
@@ -744,198 +797,148 @@ __device__ __noinline__ void tree_update_from_pend(LDSQ float* Wl, LDSQ float* b
 // (node row of tile row lr) * cols, row 0 for the padding rows of the last
 // 16-row block, whose results are dropped or meet a zero delta.
 
-// Y[j][r] = b[r] + sum_c W[r][c] x_j[c] as a K-chunked product: the batch's inputs go through LDS 64 columns
-// at a time (Xs, two buffers of kb rows x 68 floats, fetched once per chunk by the whole workgroup), every wave
-// owns up to three 16-row blocks of the weights for all message blocks, and both the next chunk's inputs and the
-// next chunk's weight rows are fetched while the matrix cores work on the present chunk.
-#define TREE_XC 64        // columns per chunk
-#define TREE_XS (TREE_XC + 4)
-
-// NJ = 16-row blocks a wave owns in this pass (blocks r0 + wave, + 8, ...); a wave whose last block lies beyond the
-// tile skips that block's fetches and products.
-template <bool BR, int NBF, int NJ>
+// Y[j][r] = b[r] + sum_c W[r][c] x_j[c], the columns split over the waves: wave w takes the 32-column chunks w, w + 8, ... of
+// RG 16-row blocks and all NBF message blocks, weights and inputs straight from memory to operand registers (either is
+// fetched once, whole lines), the next chunk's on their way while the matrix cores work on the present one, and no
+// barrier until the waves' partial sums meet (through part, nw waves' at a time).  (With the row blocks dealt to the waves, five of them -- hidden 1024 on 64
+// tiles -- leave three waves and half of three SIMDs idle: 44 us a batch of 47 instead of 28 us a batch of 37.)
+template <bool BR, int NBF, int RG>
 __device__ __forceinline__ void tree_fwd_stream_pass(const GQ float* P, const LDSQ int* rowoff, const Tile& t,
                                                      const LDSQ float* bl, const GQ float* xbase, const BatchMsg& M, int nF,
-                                                     LDSQ float* Y, int ldy, LDSQ float* Xs, int r0) {
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, i = lane & 15, q = lane >> 4;
-  const int NRB = t.Rp >> 4, NCH = (t.Cl + TREE_XC - 1) / TREE_XC;
+                                                     LDSQ float* Y, int ldy, LDSQ float* part, int nw, int r0) {
+  const int wave = uni((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63, i = lane & 15, q = lane >> 4;
+  const int NRB = t.Rp >> 4, nr = NRB - r0 < RG ? NRB - r0 : RG, NCH = (t.Cl + 31) >> 5;
+  constexpr int RS = 16 * RG + 4, WS = 16 * NBF * RS;   // floats of a message's / a wave's partial sums
   const v4f zero = {0.f, 0.f, 0.f, 0.f};
-  constexpr int NX = NBF > 2 ? 2 : 1;   // staging passes of 32 messages
-  // staging role of this thread: message row sm (+ 32 per pass), 16-byte piece sp of the chunk
-  const int sm = threadIdx.x >> 4, sp = (threadIdx.x & 15) << 2;
-  const GQ float* xp0[NX];
-  const GQ float* xp1[NX];
+  const GQ float* wrow[RG];
 #pragma unroll
-  for (int a = 0; a < NX; ++a) {
-    int mi = sm + 32 * a;
-    if (mi > nF - 1) mi = nF - 1;   // rows beyond the batch repeat its last message; their results are dropped
-    const int m = M.fidx[mi];
-    xp0[a] = xbase + M.off0[m] + sp;
-    xp1[a] = xbase + M.off1[m] + sp - t.segp;
+  for (int j = 0; j < RG; ++j) wrow[j] = P + rowoff[(j < nr ? r0 + j : r0) * 16 + i] + 4 * q;
+  const GQ float *x0[NBF], *x1[NBF];
+#pragma unroll
+  for (int nb = 0; nb < NBF; ++nb) {
+    const int mi = nb * 16 + i, m = M.fidx[mi < nF ? mi : nF - 1];   // rows beyond the batch repeat its last message; their results are dropped
+    x0[nb] = xbase + M.off0[m] + 4 * q;
+    x1[nb] = xbase + M.off1[m] + 4 * q - t.segp;
   }
-  auto xfetch = [&](int ch, int a) -> v4f {
-    const int lc = ch * TREE_XC + sp;
-    const bool in = lc < t.Cl;
-    const v4f v = *(const GQ v4f*)(in ? (BR && lc >= t.segp ? xp1[a] : xp0[a]) + ch * TREE_XC : xp0[a]);
-    return in ? v : zero;
+  struct Op {
+    v4f w[RG][2], x[NBF][2];
   };
-  {
-    // this wave's row blocks: r0 + wave, + 8, ...; only the last can lie beyond the tile
-    const bool last_in = r0 + wave + 8 * (NJ - 1) < NRB;
-    const GQ float* wrow[NJ];
+  auto fetch = [&](int ch, Op& o) {
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-      const int rb = r0 + wave + 8 * j < NRB ? r0 + wave + 8 * j : NRB - 1;
-      wrow[j] = P + rowoff[rb * 16 + i] + 4 * q;
+    for (int h = 0; h < 2; ++h) {
+      const int c0 = ch * 32 + 16 * h, lc = c0 + 4 * q;
+      const bool in = lc < t.Cl;
+#pragma unroll
+      for (int nb = 0; nb < NBF; ++nb) {
+        const v4f v = *(const GQ v4f*)(in ? (BR && lc >= t.segp ? x1[nb] : x0[nb]) + c0 : x0[nb]);
+        o.x[nb][h] = in ? v : zero;
+      }
+#pragma unroll
+      for (int j = 0; j < RG; ++j)
+        if (j < nr) o.w[j][h] = *(const GQ v4f*)(in ? wrow[j] + c0 : wrow[j]);   // beyond the input: x is zero
     }
-    auto wfetch = [&](int ch, int j, int g) -> v4f {
-      const int lc = ch * TREE_XC + g * 16 + 4 * q;
-      return *(const GQ v4f*)(lc < t.Cl ? wrow[j] + ch * TREE_XC + g * 16 : wrow[j]);   // beyond the input: x is zero
-    };
-    v4f acc[NJ][NBF];
+  };
+  v4f acc[RG][NBF];
 #pragma unroll
-    for (int j = 0; j < NJ; ++j)
+  for (int j = 0; j < RG; ++j)
 #pragma unroll
-      for (int nb = 0; nb < NBF; ++nb) acc[j][nb] = zero;
-    v4f wa[NJ][4], wb[NJ][4], xr[NX];
-    // prologue: chunk 0
+    for (int nb = 0; nb < NBF; ++nb) acc[j][nb] = zero;
+  auto work = [&](const Op& o) {
 #pragma unroll
-    for (int a = 0; a < NX; ++a) xr[a] = xfetch(0, a);
+    for (int h = 0; h < 2; ++h)
 #pragma unroll
-    for (int j = 0; j < NJ; ++j)
+      for (int j = 0; j < RG; ++j)
+        if (j < nr) {
 #pragma unroll
-      for (int g = 0; g < 4; ++g) wa[j][g] = (j < NJ - 1 || last_in) ? wfetch(0, j, g) : zero;
-    lds_barrier();   // the previous pass has finished with Xs
+          for (int e = 0; e < 4; ++e)
 #pragma unroll
-    for (int a = 0; a < NX; ++a) *(LDSQ v4f*)(Xs + (sm + 32 * a) * TREE_XS + sp) = xr[a];
+            for (int nb = 0; nb < NBF; ++nb) acc[j][nb] = MFMA(o.w[j][h][e], o.x[nb][h][e], acc[j][nb]);
+        }
+  };
+  Op a, b;
+  if (wave < NCH) fetch(wave, a);
+  for (int ch = wave; ch < NCH; ch += 16) {
+    if (ch + 8 < NCH) fetch(ch + 8, b);
+    asm volatile("" ::: "memory");   // the fetches are issued before the products below start
+    work(a);
+    if (ch + 8 >= NCH) break;
+    if (ch + 16 < NCH) fetch(ch + 16, a);
+    asm volatile("" ::: "memory");
+    work(b);
+  }
+  // lane (i, q) holds rows 4 q .. 4 q + 3 of message i of a block
+  LDSQ float* mine = part + (wave & (nw - 1)) * WS + i * RS + 4 * q;
+  for (int s = 8 - nw; s >= 0; s -= nw) {   // waves s .. s + nw - 1 hand theirs to the nw in front of them, the last to everybody
+    lds_barrier();                          // part is free
+    if (wave >= s && wave < s + nw) {
+#pragma unroll
+      for (int j = 0; j < RG; ++j)
+#pragma unroll
+        for (int nb = 0; nb < NBF; ++nb) *(LDSQ v4f*)(mine + nb * 16 * RS + j * 16) = acc[j][nb];
+    }
     lds_barrier();
-    for (int ch = 0; ch < NCH; ch += 2) {
-      // ---- even chunk: operands wa, Xs buffer 0; fetch chunk ch + 1 into wb / xr
+    if (wave < s && wave >= s - nw) {
 #pragma unroll
-      for (int a = 0; a < NX; ++a) xr[a] = xfetch(ch + 1, a);
+      for (int j = 0; j < RG; ++j)
 #pragma unroll
-      for (int j = 0; j < NJ; ++j)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) wb[j][g] = (j < NJ - 1 || last_in) ? wfetch(ch + 1, j, g) : zero;
-      asm volatile("" ::: "memory");   // the fetches are issued before the products below start
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        v4f x[NBF];
-#pragma unroll
-        for (int nb = 0; nb < NBF; ++nb) x[nb] = *(const LDSQ v4f*)(Xs + (nb * 16 + i) * TREE_XS + g * 16 + 4 * q);
-#pragma unroll
-        for (int e = 0; e < 4; ++e)   // component-major: consecutive products go to different accumulators
-#pragma unroll
-          for (int j = 0; j < NJ - 1; ++j)
-#pragma unroll
-            for (int nb = 0; nb < NBF; ++nb) acc[j][nb] = MFMA(wa[j][g][e], x[nb][e], acc[j][nb]);
-        if (last_in) {
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-#pragma unroll
-            for (int nb = 0; nb < NBF; ++nb) acc[NJ - 1][nb] = MFMA(wa[NJ - 1][g][e], x[nb][e], acc[NJ - 1][nb]);
-        }
-      }
-#pragma unroll
-      for (int a = 0; a < NX; ++a) *(LDSQ v4f*)(Xs + 64 * TREE_XS + (sm + 32 * a) * TREE_XS + sp) = xr[a];
-      lds_barrier();
-      if (ch + 1 >= NCH) break;
-      // ---- odd chunk: operands wb, Xs buffer 1; fetch chunk ch + 2 into wa / xr
-#pragma unroll
-      for (int a = 0; a < NX; ++a) xr[a] = xfetch(ch + 2, a);
-#pragma unroll
-      for (int j = 0; j < NJ; ++j)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) wa[j][g] = (j < NJ - 1 || last_in) ? wfetch(ch + 2, j, g) : zero;
-      asm volatile("" ::: "memory");
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        v4f x[NBF];
-#pragma unroll
-        for (int nb = 0; nb < NBF; ++nb)
-          x[nb] = *(const LDSQ v4f*)(Xs + 64 * TREE_XS + (nb * 16 + i) * TREE_XS + g * 16 + 4 * q);
-#pragma unroll
-        for (int e = 0; e < 4; ++e)   // component-major: consecutive products go to different accumulators
-#pragma unroll
-          for (int j = 0; j < NJ - 1; ++j)
-#pragma unroll
-            for (int nb = 0; nb < NBF; ++nb) acc[j][nb] = MFMA(wb[j][g][e], x[nb][e], acc[j][nb]);
-        if (last_in) {
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-#pragma unroll
-            for (int nb = 0; nb < NBF; ++nb) acc[NJ - 1][nb] = MFMA(wb[NJ - 1][g][e], x[nb][e], acc[NJ - 1][nb]);
-        }
-      }
-#pragma unroll
-      for (int a = 0; a < NX; ++a) *(LDSQ v4f*)(Xs + (sm + 32 * a) * TREE_XS + sp) = xr[a];
-      lds_barrier();
+        for (int nb = 0; nb < NBF; ++nb) acc[j][nb] += *(const LDSQ v4f*)(mine + nb * 16 * RS + j * 16);
     }
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-      const int rb = r0 + wave + 8 * j;
-      if (rb < NRB) {
-        const v4f b4 = *(const LDSQ v4f*)(bl + rb * 16 + 4 * q);
-#pragma unroll
-        for (int nb = 0; nb < NBF; ++nb) *(LDSQ v4f*)(Y + (nb * 16 + i) * ldy + rb * 16 + 4 * q) = acc[j][nb] + b4;
-      }
-    }
+  }
+  const int per = nr * 4;   // groups of four rows
+  for (int idx = threadIdx.x; idx < nF * per; idx += AMP_THREADS) {
+    const int k = idx / per, r = (idx - k * per) << 2;
+    const LDSQ float* p = part + k * RS + r;
+    v4f s = *(const LDSQ v4f*)p + *(const LDSQ v4f*)(p + WS);
+    if (nw == 4) s += *(const LDSQ v4f*)(p + 2 * WS) + *(const LDSQ v4f*)(p + 3 * WS);
+    *(LDSQ v4f*)(Y + k * ldy + r0 * 16 + r) = s + *(const LDSQ v4f*)(bl + r0 * 16 + r);
   }
 }
 
 template <bool BR, int NBF>
 __device__ __forceinline__ void tree_fwd_stream_blocks(const GQ float* P, const LDSQ int* rowoff, const Tile& t,
                                                        const LDSQ float* bl, const GQ float* xbase, const BatchMsg& M, int nF,
-                                                       LDSQ float* Y, int ldy, LDSQ float* Xs) {
-  const int NRB = t.Rp >> 4;
-  for (int r0 = 0; r0 < NRB; r0 += 24) {
-    const int left = NRB - r0;
-    if (left > 16)
-      tree_fwd_stream_pass<BR, NBF, 3>(P, rowoff, t, bl, xbase, M, nF, Y, ldy, Xs, r0);
-    else if (left > 8)
-      tree_fwd_stream_pass<BR, NBF, 2>(P, rowoff, t, bl, xbase, M, nF, Y, ldy, Xs, r0);
-    else
-      tree_fwd_stream_pass<BR, NBF, 1>(P, rowoff, t, bl, xbase, M, nF, Y, ldy, Xs, r0);
-  }
+                                                       LDSQ float* Y, int ldy, LDSQ float* part, int nw) {
+  constexpr int RG = NBF < 3 ? 6 : NBF == 3 ? 5 : 4;
+  for (int r0 = 0; r0 < t.Rp >> 4; r0 += RG) tree_fwd_stream_pass<BR, NBF, RG>(P, rowoff, t, bl, xbase, M, nF, Y, ldy, part, nw, r0);
 }
 
+// Ends without a barrier.
 template <bool BR>
 __device__ __forceinline__ void tree_fwd_stream(const GQ float* P, const LDSQ int* rowoff, const Tile& t, const LDSQ float* bl,
                                                 const GQ float* xbase, const BatchMsg& M, int nF, LDSQ float* Y, int ldy,
-                                                LDSQ float* Xs) {
+                                                LDSQ float* part, int nw) {
   const int NBF = (nF + 15) >> 4;
   if (NBF == 1)
-    tree_fwd_stream_blocks<BR, 1>(P, rowoff, t, bl, xbase, M, nF, Y, ldy, Xs);
+    tree_fwd_stream_blocks<BR, 1>(P, rowoff, t, bl, xbase, M, nF, Y, ldy, part, nw);
   else if (NBF == 2)
-    tree_fwd_stream_blocks<BR, 2>(P, rowoff, t, bl, xbase, M, nF, Y, ldy, Xs);
+    tree_fwd_stream_blocks<BR, 2>(P, rowoff, t, bl, xbase, M, nF, Y, ldy, part, nw);
   else if (NBF == 3)
-    tree_fwd_stream_blocks<BR, 3>(P, rowoff, t, bl, xbase, M, nF, Y, ldy, Xs);
+    tree_fwd_stream_blocks<BR, 3>(P, rowoff, t, bl, xbase, M, nF, Y, ldy, part, nw);
   else
-    tree_fwd_stream_blocks<BR, 4>(P, rowoff, t, bl, xbase, M, nF, Y, ldy, Xs);
+    tree_fwd_stream_blocks<BR, 4>(P, rowoff, t, bl, xbase, M, nF, Y, ldy, part, nw);
 }
 
 // dx_j[c] = sum_r W[r][c] delta_j[r].  A wave owns every 8th block of 64 weight columns for all NBB message
 // blocks.  For a (16-row block, 64-column block) unit lane (i, q) fetches rows 4q .. 4q+3 of the block at columns
 // 4i .. 4i+3 -- 16 bytes per fetch, 256 contiguous bytes per row across the 16 lanes -- and component e of those
 // fetches is the weight operand of output tile e, whose 16 columns are 4m + e: one fetch feeds four products, and
-// a lane ends up with 16 consecutive columns of its message's input gradient.  The rows are walked TREE_SR blocks
+// a lane ends up with 16 consecutive columns of its message's input gradient.  The rows are walked SR blocks
 // at a time with two register buffers, the next stretch in flight while the matrix cores work on the present one.
-#define TREE_SR 4
-template <bool BR, int NBB>
+template <bool BR, int NBB, int SR>
 __device__ __forceinline__ void tree_bwd_stream_blocks(const GQ float* P, const LDSQ int* rowoff, const Tile& t,
                                                        const LDSQ float* Dl, int ldd, const BatchMsg& M, int nB, GQ float* obase) {
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, i = lane & 15, q = lane >> 4;
   const int NRB = t.Rp >> 4, CM = (amp_round16(t.Cl) + 63) >> 6;
-  const int NGC = (NRB + TREE_SR - 1) / TREE_SR;                 // row stretches per column block
+  const int NGC = (NRB + SR - 1) / SR;                 // row stretches per column block
   const int ncb = wave < CM ? (CM - wave + 7) >> 3 : 0;           // column blocks of this wave
   const int T = ncb * NGC;
   const v4f zero = {0.f, 0.f, 0.f, 0.f};
   const LDSQ float* dp = Dl + i * ldd + 4 * q;
-  auto afetch = [&](int it, v4f (&a)[TREE_SR][4]) {
-    const int cb = wave + 8 * (it / NGC), g0 = (it % NGC) * TREE_SR;
+  auto afetch = [&](int it, v4f (&a)[SR][4]) {
+    const int cb = wave + 8 * (it / NGC), g0 = (it % NGC) * SR;
     const int col = cb * 64 + 4 * i < t.Cl ? cb * 64 + 4 * i : 0;
 #pragma unroll
-    for (int g = 0; g < TREE_SR; ++g) {
+    for (int g = 0; g < SR; ++g) {
       const int gg = g0 + g < NRB ? g0 + g : NRB - 1;
 #pragma unroll
       for (int sx = 0; sx < 4; ++sx) a[g][sx] = *(const GQ v4f*)(P + rowoff[gg * 16 + 4 * q + sx] + col);
@@ -946,10 +949,10 @@ __device__ __forceinline__ void tree_bwd_stream_blocks(const GQ float* P, const 
   for (int nb = 0; nb < NBB; ++nb)
 #pragma unroll
     for (int e = 0; e < 4; ++e) acc[nb][e] = zero;
-  auto work = [&](int it, v4f (&a)[TREE_SR][4]) {
-    const int cb = wave + 8 * (it / NGC), gc = it % NGC, g0 = gc * TREE_SR;
+  auto work = [&](int it, v4f (&a)[SR][4]) {
+    const int cb = wave + 8 * (it / NGC), gc = it % NGC, g0 = gc * SR;
 #pragma unroll
-    for (int g = 0; g < TREE_SR; ++g)
+    for (int g = 0; g < SR; ++g)
       if (g0 + g < NRB) {
 #pragma unroll
         for (int nb = 0; nb < NBB; ++nb) {
@@ -980,7 +983,7 @@ __device__ __forceinline__ void tree_bwd_stream_blocks(const GQ float* P, const 
       }
     }
   };
-  v4f a0[TREE_SR][4], a1[TREE_SR][4];
+  v4f a0[SR][4], a1[SR][4];
   if (T > 0) afetch(0, a0);
   for (int it = 0; it < T; it += 2) {
     if (it + 1 < T) afetch(it + 1, a1);
@@ -993,18 +996,30 @@ __device__ __forceinline__ void tree_bwd_stream_blocks(const GQ float* P, const 
   }
 }
 
+// Row blocks per stretch: four, or three where that leaves less of the last stretch empty (a stretch's fetches are made whole:
+// five row blocks as 4 + 1 fetch eight blocks' weights).
+template <bool BR, int NBB>
+__device__ __forceinline__ void tree_bwd_stream_sr(const GQ float* P, const LDSQ int* rowoff, const Tile& t, const LDSQ float* Dl,
+                                                   int ldd, const BatchMsg& M, int nB, GQ float* obase) {
+  const int NRB = t.Rp >> 4;
+  if ((NRB + 2) / 3 * 3 < (NRB + 3) / 4 * 4)
+    tree_bwd_stream_blocks<BR, NBB, 3>(P, rowoff, t, Dl, ldd, M, nB, obase);
+  else
+    tree_bwd_stream_blocks<BR, NBB, 4>(P, rowoff, t, Dl, ldd, M, nB, obase);
+}
+
 template <bool BR>
 __device__ __forceinline__ void tree_bwd_stream(const GQ float* P, const LDSQ int* rowoff, const Tile& t, const LDSQ float* Dl,
                                                 int ldd, const BatchMsg& M, int nB, GQ float* obase) {
   const int NBB = (nB + 15) >> 4;
   if (NBB == 1)
-    tree_bwd_stream_blocks<BR, 1>(P, rowoff, t, Dl, ldd, M, nB, obase);
+    tree_bwd_stream_sr<BR, 1>(P, rowoff, t, Dl, ldd, M, nB, obase);
   else if (NBB == 2)
-    tree_bwd_stream_blocks<BR, 2>(P, rowoff, t, Dl, ldd, M, nB, obase);
+    tree_bwd_stream_sr<BR, 2>(P, rowoff, t, Dl, ldd, M, nB, obase);
   else if (NBB == 3)
-    tree_bwd_stream_blocks<BR, 3>(P, rowoff, t, Dl, ldd, M, nB, obase);
+    tree_bwd_stream_sr<BR, 3>(P, rowoff, t, Dl, ldd, M, nB, obase);
   else
-    tree_bwd_stream_blocks<BR, 4>(P, rowoff, t, Dl, ldd, M, nB, obase);
+    tree_bwd_stream_sr<BR, 4>(P, rowoff, t, Dl, ldd, M, nB, obase);
 }
 
 // The update of a streamed tile: as tree_update_from_pend, in passes of 8 waves
@@ -1089,14 +1104,202 @@ __device__ __noinline__ void tree_update_stream(GQ float* P, LDSQ float* bl, con
 // ------------------------------------------------------------ leaf / branch cells
 // BR = false: rows [i; o; u] over the embedding.
 // BR = true : rows [i; f_l; f_r; o; u] over [h_l; h_r].
+
+// One wave takes the next batch from the ring and decodes it into M: row r of a batch = its forward messages, then its
+// backward ones, each in ring order; the event record keeps the ring's order.
+template <bool BR>
+__device__ __forceinline__ void tree_take(const GQ AmpDev* D, const WorkerRegs& wr, const TreeBufs& B, const Ring& mine, unsigned head,
+                                          int room, const GQ int* smeta, const GQ int* tnode) {
+  BatchMsg& M = s_M;
+  const int n = poll_batch(D, mine, head, wr.kb, room, s_codes, &s_n, code_is_b);
+  if (n == 0) return;
+  const int lane = threadIdx.x & 63;
+  const bool in = lane < n, logs = wr.log_cap && wr.tile == 0;
+  const unsigned code = s_codes[in ? lane : 0], base = s_logn;
+  const bool isb = in && code_is_b(code), fits = base + (unsigned)n <= wr.log_cap;
+  const unsigned long long mb = __ballot(isb), mf = __ballot(in && !isb), lt = (1ull << lane) - 1ull;
+  const int nF = __popcll(mf);
+  if (in) {
+    const int s = MSG_SLOT(code), nn = MSG_LOCAL(code), r = isb ? nF + __popcll(mb & lt) : __popcll(mf & lt);
+    const v4i sl = tree_slot(smeta, s);
+    const v4i tn = tree_node(tnode, sl.z, nn);
+    M.s[r] = s;
+    M.n[r] = nn;
+    M.a[r] = tn.x;
+    M.b[r] = tn.y;
+    M.par[r] = tn.z;
+    M.L[r] = sl.y;
+    if (isb)
+      M.bidx[r - nF] = r;
+    else
+      M.fidx[r] = r;
+    if (BR) {
+      const int na = s * B.NNmax + tn.x, nb = s * B.NNmax + tn.y;
+      M.off0[r] = na * 2 * B.Hp;
+      M.off1[r] = nb * 2 * B.Hp;
+      M.dst0[r] = (na * B.TB + wr.tile) * B.Hp;
+      M.dst1[r] = (nb * B.TB + wr.tile) * B.Hp;
+    } else {
+      const int l = s * B.Lmax + nn;
+      M.off0[r] = M.off1[r] = l * B.Ep;
+      M.dst0[r] = M.dst1[r] = (l * B.TL + wr.tile) * B.Ep;
+    }
+    if (logs && fits)
+      wr.log[base + lane] = ((unsigned long long)(unsigned)sl.x << 32) | ((unsigned)(isb ? 1 : 0) << 28) | ((unsigned)wr.node << 20) |
+                            ((unsigned)nn & 0xfffffu);
+  }
+  if (lane == 0) {
+    M.nF = nF;
+    M.nB = n - nF;
+    if (logs) {
+      if (fits)
+        s_logn = base + (unsigned)n;
+      else
+        raise_abort(D, ABORT_LOG_FULL, blockIdx.x);
+    }
+  }
+}
+
+// What the delta of one (backward message, unit) pair is formed from: the gate values, the output layer's part, NP of the
+// parent tiles' parts and the c's.  All of it is fetched before anything is used; a root, without a parent, reads its parts'
+// places and drops them.  (Fetched one after the other where each is needed, with a branch for the root, these are five
+// round trips: 2.6 us a batch of 46.)
+template <bool BR, int NP>
+struct TreeDelta {
+  float pp[NP], out, dcp, i_, o_, g_, tc, fl, fr, cl, cr;
+  __device__ __forceinline__ void fetch(const TreeBufs& B, const BatchMsg& M, int r, int u, const GQ float* xbase) {
+    const int H = B.H, Hp = B.Hp;
+    const long long nn = B.node32(M.s[r], M.n[r]);
+    const GQ float* gt = B.gate + nn * (6 * H) + u;
+    const GQ float* gp = B.gpar + nn * (B.TB * Hp) + u;
+    if (NP <= 8 || B.TB > 8) {
+#pragma unroll
+      for (int a = 0; a < NP; ++a) pp[a] = gp[(a < B.TB ? a : B.TB - 1) * Hp];
+    } else {
+#pragma unroll
+      for (int a = 0; a < 8; ++a) pp[a] = gp[(a < B.TB ? a : B.TB - 1) * Hp];
+    }
+    out = B.gout[nn * H + u];
+    dcp = B.gc[nn * H + u];
+    i_ = gt[0];
+    o_ = gt[3 * H];
+    g_ = gt[4 * H];
+    tc = gt[5 * H];
+    if (BR) {
+      fl = gt[H];
+      fr = gt[2 * H];
+      cl = xbase[M.off0[r] + Hp + u];
+      cr = xbase[M.off1[r] + Hp + u];
+    }
+  }
+  // The delta of unit u = u0 + j (tile order [gate][unit]) into its row ds, and the gradient w.r.t. the children's c.
+  __device__ __forceinline__ void form(const TreeBufs& B, const BatchMsg& M, int r, int j, int nu, int u, LDSQ float* ds) const {
+    const int H = B.H;
+    float p = 0.f;
+#pragma unroll
+    for (int a = 0; a < NP; ++a)
+      if (a < B.TB) p += pp[a];   // in tile order
+    if (B.TB > NP) {
+      const GQ float* gp = B.gpar + B.node(M.s[r], M.n[r]) * B.TB * B.Hp + u;
+      for (int q0 = NP; q0 < B.TB; q0 += NP) {
+        float more[NP];
+#pragma unroll
+        for (int a = 0; a < NP; ++a) more[a] = gp[(q0 + a < B.TB ? q0 + a : B.TB - 1) * B.Hp];
+#pragma unroll
+        for (int a = 0; a < NP; ++a)
+          if (q0 + a < B.TB) p += more[a];
+      }
+    }
+    const bool root = M.par[r] < 0;
+    const float dh = root ? out : out + p, dc = root ? 0.f : dcp;
+    const float dct = dc + dh * o_ * (1.f - tc * tc);
+    const float d_o = dh * tc * o_ * (1.f - o_);
+    const float d_i = dct * g_ * i_ * (1.f - i_);
+    const float d_g = dct * i_ * (1.f - g_ * g_);
+    ds[j] = d_i;
+    if (BR) {
+      ds[nu + j] = dct * cl * fl * (1.f - fl);
+      ds[2 * nu + j] = dct * cr * fr * (1.f - fr);
+      ds[3 * nu + j] = d_o;
+      ds[4 * nu + j] = d_g;
+      B.gc[B.node(M.s[r], M.a[r]) * H + u] = dct * fl;
+      B.gc[B.node(M.s[r], M.b[r]) * H + u] = dct * fr;
+    } else {
+      ds[nu + j] = d_o;
+      ds[2 * nu + j] = d_g;
+    }
+  }
+};
+
+// Unit u of node nn from its pre-activations (row y of the tile, unit j of nu): state, and what the way back needs.
+template <bool BR>
+__device__ __forceinline__ void tree_activate(const TreeBufs& B, long long nn, const LDSQ float* y, int j, int nu, int u, float cl, float cr) {
+  const int H = B.H, Hp = B.Hp;
+  GQ float* hcn = B.hc + nn * 2 * Hp;
+  GQ float* gt = B.gate + nn * 6 * H;
+  float c_, o_;
+  if (BR) {
+    const float i_ = sigmoidf_(y[j]), fl = sigmoidf_(y[nu + j]), fr = sigmoidf_(y[2 * nu + j]);
+    o_ = sigmoidf_(y[3 * nu + j]);
+    const float g_ = tanhf(y[4 * nu + j]);
+    c_ = i_ * g_ + fl * cl + fr * cr;
+    gt[u] = i_;
+    gt[H + u] = fl;
+    gt[2 * H + u] = fr;
+    gt[3 * H + u] = o_;
+    gt[4 * H + u] = g_;
+  } else {
+    const float i_ = sigmoidf_(y[j]);
+    o_ = sigmoidf_(y[nu + j]);
+    const float g_ = tanhf(y[2 * nu + j]);
+    c_ = i_ * g_;
+    gt[u] = i_;
+    gt[3 * H + u] = o_;
+    gt[4 * H + u] = g_;
+  }
+  const float tc = tanhf(c_);
+  gt[5 * H + u] = tc;
+  hcn[u] = o_ * tc;
+  hcn[Hp + u] = c_;
+}
+
+// All deltas of a batch into the rows from Y on.  Out of line: inlined, its fetches in flight take registers from the streamed
+// products, whose loops then reload theirs from scratch (hidden 1024: 91 ms an epoch of 384 trees instead of 83).
+// (The buffers' addresses come through LDS, where the role left them: read from the descriptor in HBM they cost 1.5 %.)
+__shared__ TreeBufs s_bufs;
+template <bool BR>
+__device__ __noinline__ void tree_form_deltas(int nB, int nu, int u0, LDSQ float* Y, int ldy) {
+  TreeBufs B;
+  B.xin = uni_gq<float>((const void*)s_bufs.xin);
+  B.hc = uni_gq<float>((const void*)s_bufs.hc);
+  B.gate = uni_gq<float>((const void*)s_bufs.gate);
+  B.gout = uni_gq<float>((const void*)s_bufs.gout);
+  B.gpar = uni_gq<float>((const void*)s_bufs.gpar);
+  B.gc = uni_gq<float>((const void*)s_bufs.gc);
+  B.H = uni(s_bufs.H);
+  B.Hp = uni(s_bufs.Hp);
+  B.NNmax = uni(s_bufs.NNmax);
+  B.TB = uni(s_bufs.TB);
+  const BatchMsg& M = s_M;
+  const GQ float* xbase = BR ? B.hc : B.xin;
+  for (int i = threadIdx.x; i < nB * nu; i += AMP_THREADS) {
+    const int k = i / nu, r = M.bidx[k], u = u0 + i - k * nu;
+    TreeDelta<BR, 16> d;
+    d.fetch(B, M, r, u, xbase);
+    d.form(B, M, r, i - k * nu, nu, u, Y + k * ldy);
+  }
+}
+
+// The cells role_tree_cell_lds has no room for.  STREAM: the tile's weights stay in HBM (worker aux = 1); otherwise they
+// are in LDS, which is left with fewer rows for a batch's inputs than pay (aux = 0).
 // NRBT / NCGT: the tile's 16-row blocks / 16-column groups when known at compile time, else 0.
-// STREAM: the tile's weights stay in HBM (worker aux = 1) instead of LDS.
 template <bool BR, int NRBT, int NCGT, bool STREAM>
 __device__ __noinline__ void role_tree_cell(const GQ AmpDev* D, const GQ WorkerDev* W) {
   float* lds = amp_lds;
   const GQ NodeDev& nd = D->node[W->node];
   const Tile t = make_tile(nd, W);
   const TreeBufs B = tree_bufs(D);
+  if (threadIdx.x == 0) s_bufs = B;   // read after the barriers below
   const Pend pd = make_pend(W, t);
   GQ float* pend = (GQ float*)pd.base;
   const WorkerRegs wr = worker_regs(D, W);
@@ -1111,17 +1314,13 @@ __device__ __noinline__ void role_tree_cell(const GQ AmpDev* D, const GQ WorkerD
   LDSQ float* bl = (LDSQ float*)bg;
   const int yfloats = KB * ldy;
   LDSQ float* Y = (LDSQ float*)L.take(yfloats);   // forward: pre-activations; backward: deltas
-  // LDS-resident weights: the deltas have rows of their own, so that waves without a share of the forward product
-  // can form them while the others are at it
-  // (worker aux = 2: the host found room for them at the same batch size)
-  const bool SIDE = !STREAM && uni(W->aux) == 2;
-  LDSQ float* Yd = SIDE ? (LDSQ float*)L.take(yfloats) : Y;
   // node row of a tile row / node column of an LDS column (-1 = padding)
   const int CMW = STREAM ? 0 : ((amp_round16(t.Cl) + 63) >> 6) << 6;
   LDSQ int* rowmap = (LDSQ int*)L.take(t.Rp);
   LDSQ int* colmap = (LDSQ int*)L.take(CMW);
   LDSQ int* rowoff = (LDSQ int*)L.take(STREAM ? t.Rp : 0);   // streamed weights: node row * cols
-  LDSQ float* Xs = (LDSQ float*)L.take(STREAM ? 2 * 64 * TREE_XS : 0);   // streamed weights: input chunks
+  const int nw = amp_stream_parts(t.Rp, ldy, KB);
+  LDSQ float* part = (LDSQ float*)L.take(STREAM ? nw * 64 * 68 : 0);   // streamed weights: the waves' partial sums
   GQ float* ndP = uni_gq<float>(nd.P);
   if (STREAM) {
     for (int i = threadIdx.x; i < t.Rp; i += AMP_THREADS) {
@@ -1132,8 +1331,6 @@ __device__ __noinline__ void role_tree_cell(const GQ AmpDev* D, const GQ WorkerD
     tile_load(nd, t, Wg, bg);
   }
   for (int i = threadIdx.x; i < yfloats; i += AMP_THREADS) Y[i] = 0.f;
-  if (SIDE)
-    for (int i = threadIdx.x; i < yfloats; i += AMP_THREADS) Yd[i] = 0.f;
   for (int i = threadIdx.x; i < t.Rp; i += AMP_THREADS) rowmap[i] = i < R ? t.grow(i) : -1;
   for (int i = threadIdx.x; i < CMW; i += AMP_THREADS) colmap[i] = t.ncol(i);
   __syncthreads();
@@ -1150,111 +1347,13 @@ __device__ __noinline__ void role_tree_cell(const GQ AmpDev* D, const GQ WorkerD
   // Wave 1 takes the next batch from the ring and decodes it while wave 0 is still publishing the present one
   // (wave 0 keeps what its joins need in registers, so the batch's LDS record is free from the publish barrier on).
   const int wave = threadIdx.x >> 6;
-  auto take_batch = [&](int room) {
-    const int n = poll_batch(D, mine, head, KB, room, s_codes, &s_n, code_is_b);
-    if (n > 0) {
-      const int k = threadIdx.x & 63;
-      if (k < n) {
-        const unsigned code = s_codes[k];
-        const int s = MSG_SLOT(code), nn = MSG_LOCAL(code);
-        const v4i sm = tree_slot(smeta, s);
-        const v4i tn = tree_node(tnode, sm.z, nn);
-        M.s[k] = s;
-        M.n[k] = nn;
-        M.seq[k] = (unsigned)sm.x;
-        M.a[k] = tn.x;
-        M.b[k] = tn.y;
-        M.par[k] = tn.z;
-        M.L[k] = sm.y;
-        M.aux[k] = code_is_b(code);
-        if (BR) {
-          M.off0[k] = (int)(B.node(s, tn.x) * 2 * Hp);
-          M.off1[k] = (int)(B.node(s, tn.y) * 2 * Hp);
-          M.dst0[k] = (int)((B.node(s, tn.x) * B.TB + wr.tile) * Hp);
-          M.dst1[k] = (int)((B.node(s, tn.y) * B.TB + wr.tile) * Hp);
-        } else {
-          M.off0[k] = M.off1[k] = (int)(B.leaf(s, nn) * B.Ep);
-          M.dst0[k] = M.dst1[k] = (int)((B.leaf(s, nn) * B.TL + wr.tile) * B.Ep);
-        }
-      }
-      batch_split_and_log(D, wr, M, n, wr.node, false);
-    }
-  };
-  if (wave == 1) take_batch(nd_muf - (int)count);
+  if (wave == 1) tree_take<BR>(D, wr, B, mine, head, nd_muf - (int)count, smeta, tnode);
   lds_barrier();
   for (;;) {
     const int n = s_n;
     if (n == 0) break;
     head += n;
     const int nF = M.nF, nB = M.nB;
-    // The deltas of the batch's backward messages (tile order [gate][unit], zero beyond R) into Yd, pair i =
-    // (message, unit) by thread first + j * stride.
-    auto form_deltas = [&](int first, int stride) {
-      for (int i = first; i < nB * (ldy - R); i += stride) {
-        const int k = i / (ldy - R), r = R + i - k * (ldy - R);
-        Yd[k * ldy + r] = 0.f;
-      }
-      for (int i = first; i < nB * nu; i += stride) {
-        const int k = i / nu, j = i - k * nu, m = M.bidx[k], u = u0 + j;
-        const long long nn = B.node(M.s[m], M.n[m]);
-        const GQ float* gt = B.gate + nn * 6 * H;
-        float dh = B.gout[nn * H + u], dc = 0.f;
-        if (M.par[m] >= 0) {
-          const GQ float* gp = B.gpar + nn * B.TB * Hp + u;
-          float p = 0.f;
-          int q = 0;
-          for (; q + 15 < B.TB; q += 16) {   // sixteen parts in flight at a time, added in tile order
-            float pp[16];
-#pragma unroll
-            for (int a = 0; a < 16; ++a) pp[a] = gp[(q + a) * Hp];
-#pragma unroll
-            for (int a = 0; a < 16; ++a) p += pp[a];
-          }
-          for (; q + 3 < B.TB; q += 4) {
-            const float p0 = gp[q * Hp], p1 = gp[(q + 1) * Hp], p2 = gp[(q + 2) * Hp], p3 = gp[(q + 3) * Hp];
-            p = (((p + p0) + p1) + p2) + p3;
-          }
-          for (; q < B.TB; ++q) p += gp[q * Hp];
-          dh += p;
-          dc = B.gc[nn * H + u];
-        }
-        const float i_ = gt[u], o_ = gt[3 * H + u], g_ = gt[4 * H + u], tc = gt[5 * H + u];
-        const float dct = dc + dh * o_ * (1.f - tc * tc);
-        const float d_o = dh * tc * o_ * (1.f - o_);
-        const float d_i = dct * g_ * i_ * (1.f - i_);
-        const float d_g = dct * i_ * (1.f - g_ * g_);
-        LDSQ float* ds = Yd + k * ldy;
-        if (BR) {
-          const long long na = B.node(M.s[m], M.a[m]), nb = B.node(M.s[m], M.b[m]);
-          const float fl = gt[H + u], fr = gt[2 * H + u];
-          ds[j] = d_i;
-          ds[nu + j] = dct * xbase[M.off0[m] + Hp + u] * fl * (1.f - fl);
-          ds[2 * nu + j] = dct * xbase[M.off1[m] + Hp + u] * fr * (1.f - fr);
-          ds[3 * nu + j] = d_o;
-          ds[4 * nu + j] = d_g;
-          B.gc[na * H + u] = dct * fl;
-          B.gc[nb * H + u] = dct * fr;
-        } else {
-          ds[j] = d_i;
-          ds[nu + j] = d_o;
-          ds[2 * nu + j] = d_g;
-        }
-      }
-    };
-    // Waves without a share of the forward product (tree_fwd_mfma: a 16-message block is shared by 8, 4 or 2 waves,
-    // each taking every wpn-th 16-row block) form the deltas meanwhile.
-    int n_side = 0, side_rank = -1;
-    if (SIDE && nF > 0 && nB > 0) {
-      const TreeShape<NRBT, NCGT> sh(t);
-      const int NBF = (nF + 15) >> 4, wpn = NBF == 1 ? 8 : NBF == 2 ? 4 : 2, me = uni((int)(threadIdx.x >> 6));
-      for (int w = 0; w < AMP_THREADS / 64; ++w) {
-        const int nbw = w / wpn, subw = (w - nbw * wpn + (wpn >> 1) * (nbw & 1)) % wpn;
-        if (!(nbw < NBF && subw < sh.NRB)) {
-          if (w == me) side_rank = n_side;
-          ++n_side;
-        }
-      }
-    }
     PHASE(0);
     // ---------------- forward messages of the batch
     if (nF > 0) {
@@ -1266,53 +1365,30 @@ __device__ __noinline__ void role_tree_cell(const GQ AmpDev* D, const GQ WorkerD
         pcr = xbase[M.off1[m] + Hp + u];
         asm volatile("" ::: "memory");
       }
-      if (side_rank >= 0) form_deltas(side_rank * 64 + (int)(threadIdx.x & 63), n_side * 64);
       if (STREAM)
-        tree_fwd_stream<BR>(ndP, rowoff, t, bl, xbase, M, nF, Y, ldy, Xs);
+        tree_fwd_stream<BR>(ndP, rowoff, t, bl, xbase, M, nF, Y, ldy, part, nw);
       else
         tree_fwd_mfma<BR, NRBT, NCGT>(Wl, t, bl, xbase, M, nF, Y);
       lds_barrier();
       PHASE(1);
       for (int i = threadIdx.x; i < nF * nu; i += AMP_THREADS) {
         const int k = i / nu, j = i - k * nu, m = M.fidx[k], u = u0 + j;
-        const LDSQ float* y = Y + k * ldy;
-        const long long nn = B.node(M.s[m], M.n[m]);
-        GQ float* hcn = B.hc + nn * 2 * Hp;
-        GQ float* gt = B.gate + nn * 6 * H;
-        float c_, o_;
-        if (BR) {
-          const bool first = i == (int)threadIdx.x;
-          const float cl = first ? pcl : xbase[M.off0[m] + Hp + u];
-          const float cr = first ? pcr : xbase[M.off1[m] + Hp + u];
-          const float i_ = sigmoidf_(y[j]), fl = sigmoidf_(y[nu + j]), fr = sigmoidf_(y[2 * nu + j]);
-          o_ = sigmoidf_(y[3 * nu + j]);
-          const float g_ = tanhf(y[4 * nu + j]);
-          c_ = i_ * g_ + fl * cl + fr * cr;
-          gt[u] = i_;
-          gt[H + u] = fl;
-          gt[2 * H + u] = fr;
-          gt[3 * H + u] = o_;
-          gt[4 * H + u] = g_;
-        } else {
-          const float i_ = sigmoidf_(y[j]);
-          o_ = sigmoidf_(y[nu + j]);
-          const float g_ = tanhf(y[2 * nu + j]);
-          c_ = i_ * g_;
-          gt[u] = i_;
-          gt[3 * H + u] = o_;
-          gt[4 * H + u] = g_;
-        }
-        const float tc = tanhf(c_);
-        gt[5 * H + u] = tc;
-        hcn[u] = o_ * tc;
-        hcn[Hp + u] = c_;
+        const bool first = i == (int)threadIdx.x;
+        const float cl = BR ? (first ? pcl : xbase[M.off0[m] + Hp + u]) : 0.f;
+        const float cr = BR ? (first ? pcr : xbase[M.off1[m] + Hp + u]) : 0.f;
+        tree_activate<BR>(B, B.node(M.s[m], M.n[m]), Y + k * ldy, j, nu, u, cl, cr);
       }
       lds_barrier();
       PHASE(2);
     }
     // ---------------- backward messages of the batch
     if (nB > 0) {
-      if (n_side == 0) form_deltas((int)threadIdx.x, AMP_THREADS);
+      // deltas (tile order [gate][unit], zero beyond R) take the pre-activations' place
+      for (int i = threadIdx.x; i < nB * (ldy - R); i += AMP_THREADS) {
+        const int k = i / (ldy - R), r = R + i - k * (ldy - R);
+        Y[k * ldy + r] = 0.f;
+      }
+      tree_form_deltas<BR>(nB, nu, u0, Y, ldy);
       lds_barrier();
       PHASE(3);
       // The (delta, input) pairs join the pending gradients: entry = [delta (Rp) | input in LDS column layout (Cp)].
@@ -1336,7 +1412,7 @@ __device__ __noinline__ void role_tree_cell(const GQ AmpDev* D, const GQ WorkerD
         const int perd = pd.Rp >> 2, totald = nB * perd;
         for (int idx = threadIdx.x; idx < totald; idx += AMP_THREADS) {
           const int k = idx / perd, j = (idx - k * perd) << 2;
-          *(GQ v4f*)(pend + (long long)(count + k) * pd.stride + j) = *(const LDSQ v4f*)(Yd + k * ldy + j);   // ldy >= Rp, zero beyond R
+          *(GQ v4f*)(pend + (long long)(count + k) * pd.stride + j) = *(const LDSQ v4f*)(Y + k * ldy + j);   // ldy >= Rp, zero beyond R
         }
       }
       if ((int)threadIdx.x < R) {
@@ -1345,17 +1421,17 @@ __device__ __noinline__ void role_tree_cell(const GQ AmpDev* D, const GQ WorkerD
         for (; k + 7 < nB; k += 8) {
           float y[8];
 #pragma unroll
-          for (int a = 0; a < 8; ++a) y[a] = Yd[(k + a) * ldy + threadIdx.x];
+          for (int a = 0; a < 8; ++a) y[a] = Y[(k + a) * ldy + threadIdx.x];
 #pragma unroll
           for (int a = 0; a < 8; ++a) accb += y[a];
         }
-        for (; k < nB; ++k) accb += Yd[k * ldy + threadIdx.x];
+        for (; k < nB; ++k) accb += Y[k * ldy + threadIdx.x];
       }
       PHASE(4);
       if (STREAM)
-        tree_bwd_stream<BR>(ndP, rowoff, t, Yd, ldy, M, nB, obase);
+        tree_bwd_stream<BR>(ndP, rowoff, t, Y, ldy, M, nB, obase);
       else
-        tree_bwd_mfma<BR, NRBT, NCGT>(Wl, t, Yd, M, nB, obase);
+        tree_bwd_mfma<BR, NRBT, NCGT>(Wl, t, Y, M, nB, obase);
 #pragma unroll
       for (int a = 0; a < 4; ++a)
         if (xd[a]) *(GQ v4f*)xd[a] = xin[a] ? xv[a] : (v4f){0.f, 0.f, 0.f, 0.f};
@@ -1368,33 +1444,15 @@ __device__ __noinline__ void role_tree_cell(const GQ AmpDev* D, const GQ WorkerD
       }
       PHASE(5);
     }
-    // what lane k of wave 0 needs of message k for its joins, before the batch's record is given up
-    int js = 0, jn = 0, jaux = 0, jpar = 0, ja = 0, jb = 0, jL = 0;
-    if (threadIdx.x < 64 && (int)threadIdx.x < n) {
-      const int k = threadIdx.x;
-      js = M.s[k];
-      jn = M.n[k];
-      jaux = M.aux[k];
-      jpar = M.par[k];
-      ja = M.a[k];
-      jb = M.b[k];
-      jL = M.L[k];
-    }
+    // what lane r of wave 0 needs of row r for its joins, before the batch's record is given up
+    const int lane = threadIdx.x & 63;
+    const TreePost tp = tree_post_of(M, lane < n ? lane : 0, lane < n, lane < nF);
     // every wave's HBM stores have landed before wave 0 publishes the batch
     publish_barrier();
     // ---------------- joins and posts, one lane per message
-    if (threadIdx.x < 64) {
+    if (wave == 0) {
       fence_release();
-      if ((int)threadIdx.x < n) {
-        if (!jaux) {
-          tree_node_part_done(wr, B, js, jn, jpar);
-        } else if (BR) {
-          tree_grad_part_done(wr, B, js, ja, false, ja < jL);
-          tree_grad_part_done(wr, B, js, jb, false, jb < jL);
-        } else {
-          if (join_arrive(B.cnt + B.node(js, jn) * 4 + 3, B.TL)) ring_post(wr.lookup, MSG_MAKE(1, js, jn));
-        }
-      }
+      tree_publish<BR>(wr, B, tp);
     }
     PHASE(6);
     count += nB;
@@ -1411,7 +1469,7 @@ __device__ __noinline__ void role_tree_cell(const GQ AmpDev* D, const GQ WorkerD
       // recorded by the wave that records the next batch's events, so that the update comes first
       if (threadIdx.x == 64) log_event(D, W, &s_logn, wr.node, 2, 0, 0);
     }
-    if (wave == 1) take_batch(nd_muf - (int)count);
+    if (wave == 1) tree_take<BR>(D, wr, B, mine, head, nd_muf - (int)count, smeta, tnode);
     lds_barrier();
     PHASE(7);
   }

@@ -336,6 +336,54 @@ def test_tree_replay_parity(dims, tiles, mak, muf, lmuf, opt, n):
     compare(g, rt, len(data), opt=opt)
 
 
+TREE_MOM = dict(kind="momentum", lr=0.005, momentum=0.9)
+
+
+# (hidden, emb, n_class, leaf tiles, branch tiles, mak, muf, lookup muf, optimizer, trees): cells with 1 to 4 gradient
+# units of 16 x 64 a wave, optimizer slots in registers (up to two units) and fetched, ragged rows and columns, input
+# segments of more than one 64-group fetch, batches of fewer rows than 64; output layers on either side of 8, 16 and 64
+# classes and of one, two and more column groups a thread
+@pytest.mark.parametrize("hidden,emb,n_class,tl,tb,mak,muf,lmuf,opt,n", [
+    (150, 300, 8, 10, 17, 64, 7, 333, TREE_MOM, 48), (150, 300, 9, 8, 16, 32, 5, 100, dict(ADAM, lr=0.0002), 32),
+    (150, 60, 17, 10, 9, 32, 50, 1000, TREE_MOM, 48), (24, 32, 2, 1, 1, 16, 3, 5, SGD, 48),
+    (37, 300, 64, 3, 5, 64, 11, 50, SGD, 48), (260, 24, 5, 20, 52, 16, 9, 40, SGD, 16), (12, 520, 16, 3, 1, 8, 4, 9, TREE_MOM, 24),
+    (61, 50, 40, 4, 7, 16, 3, 7, dict(ADAM, lr=0.0002), 32)])
+def test_tree_cell_sizes_replay_parity(hidden, emb, n_class, tl, tb, mak, muf, lmuf, opt, n):
+    dims = dict(vocab=97, emb=emb, hidden=hidden, n_class=n_class)
+    data = synth.make_tree(n, 33, dims)
+    fp = synth.init_params("tree", dims, 8)
+    g = gpu_train("tree", dims, fp, data, mak, muf, opt, tiles={1: tl, 2: tb}, lookup_muf=lmuf)
+    check_controller_log(g["logs"], mak, len(data))
+    rt = oracle_replay("tree", dims, fp, data, g["logs"], muf, opt, lookup_muf=lmuf)
+    compare(g, rt, len(data), opt=opt)
+    # gradients, slots and update counts carried into a second call, and an evaluation in between
+    a, valid = g["trainer"].amp, synth.make_tree(12, 34, dims, max_leaves=12)
+    for inst in valid:
+        a.submit(inst, which=1)
+    ref, acc = direct.evaluate("tree", dims, direct.unpack("tree", dims, g["params"]), valid)
+    ev = a.eval()
+    assert abs(ev["mean_loss"] - ref) <= 1e-5 * max(1.0, abs(ref)) and abs(ev["accuracy"] - acc) < 1e-9
+
+
+@pytest.mark.parametrize("opt", [SGD, TREE_MOM, dict(ADAM, lr=0.0002)])
+def test_tree_gradients_carried_between_calls(opt):
+    """Two calls of one epoch: what the cells and the output layer have accumulated since their last update, the optimizers'
+    slots and the numbers of updates rest in the arena between them.  The checker replays both as one run."""
+    dims = dict(vocab=97, emb=50, hidden=37, n_class=5)
+    data = synth.make_tree(24, 35, dims)
+    fp = synth.init_params("tree", dims, 8)
+    leaves = sum(i["n_leaves"] for i in data)
+    muf = next(m for m in (7, 9, 11, 13) if leaves % m and (leaves - len(data)) % m and (2 * leaves - len(data)) % m)
+    g = gpu_train("tree", dims, fp, data, 8, muf, opt, tiles={1: 3, 2: 5}, lookup_muf=11)
+    rt = oracle_replay("tree", dims, fp, data, g["logs"], muf, opt, lookup_muf=11)
+    compare(g, rt, len(data), opt=opt)
+    a = g["trainer"].amp
+    a.train(1)
+    rt.replay(data, named_logs("tree", dims, a.get_event_log()[1:]), first_seq=len(data))
+    g2 = dict(g, params=g["trainer"].params(), losses=a.get_instance_losses().astype(np.float64))
+    compare(g2, rt, len(data), opt=opt, ref_losses=[rt.loss[len(data) + s] for s in range(len(data))])
+
+
 TREE_HBM = dict(vocab=97, emb=40, hidden=36, n_class=5)
 
 
