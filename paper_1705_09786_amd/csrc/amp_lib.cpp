@@ -322,11 +322,11 @@ size_t lds_floats(const amp_ctx* c, HostWorker& w) {
     case ROLE_TREE_OUT: {
       // the register-resident gradient accumulator holds 12 elements per thread
       if (R * C > 12 * AMP_THREADS) return 0;
-      for (w.kb = 64; w.kb >= 16; w.kb -= 16) {
-        f = wfl + r4((size_t)w.kb * amp_round4(c->dims.hidden)) + r4((size_t)w.kb * 64) + r4(c->max_mak);
+      for (w.kb = 64; w.kb >= 4; w.kb -= 4) {
+        f = wfl + (size_t)w.kb * amp_ldrow(amp_round4(c->dims.hidden)) + 2 * (size_t)w.kb * amp_ldrow((int)Rp) + r4(c->max_mak);
         if (f <= avail) break;
       }
-      if (w.kb < 16) return 0;
+      if (w.kb < 4) return 0;
       break;
     }
     case ROLE_G_EDGE: {

@@ -4,6 +4,7 @@
 #include "amp_batch.hip.h"
 #include "amp_tree.hip.h"
 #include "amp_tree_cell.hip.h"
+#include "amp_tree_out.hip.h"
 
 template <bool BR, int GU>
 static __device__ __forceinline__ void tree_cell_opt(const GQ AmpDev* D, const GQ WorkerDev* W) {
@@ -36,7 +37,14 @@ static __device__ __forceinline__ void tree_worker(const GQ AmpDev* D, const GQ 
     case ROLE_TREE_LOOKUP: role_tree_lookup(D, W); break;
     case ROLE_TREE_LEAF: tree_cell_worker<false>(D, W); break;
     case ROLE_TREE_BRANCH: tree_cell_worker<true>(D, W); break;
-    case ROLE_TREE_OUT: role_tree_out(D, W); break;
+    case ROLE_TREE_OUT: {
+      // groups of four columns of the gradient, dealt to 384 threads; the host admits up to 6144 elements in 64 rows
+      const int n = D->n_class * ((D->hidden + 3) >> 2);
+      if (n <= 384) role_tree_out<1>(D, W);
+      else if (n <= 2 * 384) role_tree_out<2>(D, W);
+      else role_tree_out<5>(D, W);
+      break;
+    }
     default: break;
   }
 }

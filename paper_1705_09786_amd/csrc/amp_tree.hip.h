@@ -1485,296 +1485,3 @@ __device__ __noinline__ void role_tree_cell(const GQ AmpDev* D, const GQ WorkerD
     W->wstate[1] = tstep;
   }
 }
-
-// ------------------------------------------------------------ output layer + loss at every node
-// The node where a forward message turns round (Section 4: the loss layer
-// initiates backpropagation).  The batch's h vectors are fetched into LDS
-// together; logits, softmax loss, d logits and W^T d logits are then computed
-// thread-parallel over (message, class) and (message, column).  The node's
-// gradient accumulator (n_class x H, spread over the threads) stays in
-// registers from one update to the next; between launches it rests in HBM.
-__device__ __noinline__ void role_tree_out(const GQ AmpDev* D, const GQ WorkerDev* W) {
-  float* lds = amp_lds;
-  const GQ NodeDev& nd = D->node[3];
-  const Tile t = make_tile(nd, W);
-  const TreeBufs B = tree_bufs(D);
-  const WorkerRegs wr = worker_regs(D, W);
-  const int R = t.R, C = t.C, H = B.H, Hp = B.Hp, KB = wr.kb, ldw = t.ldw, nd_muf = uni(nd.muf);
-  const GQ int* smeta = uni_gq<int>(D->smeta);
-  const GQ int* tnode = uni_gq<int>(D->data.tnode);
-  const GQ int* slot_inst = uni_gq<int>(D->slot_inst);
-  GQ float* probe = uni_gq<float>(D->probe);
-  GQ unsigned* probe_n = uni_gq<unsigned>(D->probe_n);
-  const unsigned probe_period = uni(D->probe_period), probe_cap = uni(D->probe_cap);
-  const int probe_w = uni(D->probe_w);
-  Lds L{lds};
-  float* Wg = L.take(t.Rp * t.ldw);
-  float* bg = L.take(t.Rp);
-  LDSQ float* Wl = (LDSQ float*)Wg;
-  LDSQ float* bl = (LDSQ float*)bg;
-  LDSQ float* hbuf = (LDSQ float*)L.take(KB * Hp);    // per message: the node's h
-  LDSQ float* zbuf = (LDSQ float*)L.take(KB * 64);    // per message: logits, then d logits (R <= 64)
-  LDSQ int* done_cnt = (LDSQ int*)L.take(D->mak);     // eval: nodes scored per slot
-  tile_load(nd, t, Wg, bg);
-  for (int i = threadIdx.x; i < D->mak; i += AMP_THREADS) done_cnt[i] = 0;
-  // this thread's accumulator elements e = threadIdx.x + 512 j (row e / C, column e % C), and the bias gradient of row threadIdx.x
-  GQ float* ndG = (GQ float*)nd.G;
-  // ... and their optimizer slots, in registers for the life of the launch (in HBM a step with slots is a fetch and a store
-  // behind each other in every update)
-  constexpr int NE = 12;   // n_class * H <= 12 * 512
-  const int nj = (R * C + AMP_THREADS - 1) / AMP_THREADS;
-  GQ float* ndM = uni_gq<float>(nd.M);
-  GQ float* ndV = uni_gq<float>(nd.V);
-  const OptCoef ob = opt_base(nd);
-  const bool mean = uni(nd.mean) != 0, bounded = uni(D->admit_bounded) != 0;
-  float gacc[NE], gb, sm[NE], sv[NE], bm = 0.f, bv = 0.f;
-  int er[NE], ec[NE];
-#pragma unroll
-  for (int j = 0; j < NE; ++j) {
-    const int e = threadIdx.x + AMP_THREADS * j;
-    er[j] = e < R * C ? e / C : -1;
-    ec[j] = e < R * C ? e - (e / C) * C : 0;
-    gacc[j] = er[j] >= 0 ? ndG[e] : 0.f;
-    sm[j] = er[j] >= 0 && ob.kind != 0 ? ndM[e] : 0.f;
-    sv[j] = er[j] >= 0 && ob.kind == 2 ? ndV[e] : 0.f;
-  }
-  if ((int)threadIdx.x < R && ob.kind != 0) bm = ndM[R * C + threadIdx.x];
-  if ((int)threadIdx.x < R && ob.kind == 2) bv = ndV[R * C + threadIdx.x];
-  gb = (int)threadIdx.x < R ? ndG[R * C + threadIdx.x] : 0.f;
-  BatchMsg& M = s_M;
-  __syncthreads();
-  const Ring mine = ring_regs(D, uni(W->ring));
-  unsigned head = 0;
-  unsigned count = W->wstate[0], tstep = W->wstate[1];
-  // Wave 1 takes the next batch while wave 0 publishes the present one, as in the cells: a batch is a chain of round
-  // trips (ring, slot, node, inputs), and with small batches -- an update every few gradients -- that chain is its time.
-  const int wave = threadIdx.x >> 6;
-  auto take_batch = [&](int room) {
-    const int n = poll_batch(D, mine, head, KB, room, s_codes, &s_n, [](unsigned) { return true; });
-    if (n > 0) {
-      const int k = threadIdx.x & 63;
-      if (k < n) {
-        const unsigned code = s_codes[k];
-        const int s = MSG_SLOT(code), nn = MSG_LOCAL(code);
-        const v4i sm = tree_slot(smeta, s);
-        const v4i tn = tree_node(tnode, sm.z, nn);
-        M.s[k] = s;
-        M.n[k] = nn;
-        M.seq[k] = (unsigned)sm.x;
-        M.a[k] = tn.w;
-        M.par[k] = tn.z;
-        M.L[k] = sm.y;
-        // 1 = a node of an evaluation instance: scored, then counted towards the instance's retirement; no gradient
-        M.aux[k] = (!wr.train || slot_inst[s] < 0) ? 1 : 0;
-        M.off0[k] = (int)(B.node(s, nn) * 2 * Hp);
-        M.dst0[k] = (int)(B.node(s, nn) * H);
-        // probe: this node's h (its cell's forward output) if the instance is sampled
-        int entry = -1;
-        if (probe_period && (unsigned)sm.x % probe_period == 0u) {
-          const unsigned e = __hip_atomic_fetch_add(probe_n, 1u, __ATOMIC_RELAXED, AGENT);
-          if (e < probe_cap) {
-            entry = (int)e;
-            GQ int* hdr = (GQ int*)(probe + (long long)e * probe_w);
-            hdr[0] = 0;
-            hdr[1] = sm.x;
-            hdr[2] = nn;
-            hdr[3] = 0;
-          }
-        }
-        M.b[k] = entry;
-      }
-      // the event record: a training node's message is a forward event followed by a backward event (the loss turns
-      // it round in place), an evaluation node's a forward event only
-      {
-        const bool in = k < n, tr = in && M.aux[k] == 0;
-        const unsigned long long mt = __ballot(tr);
-        if (k == 0) M.nB = __popcll(mt);   // gradients in this batch
-        if (wr.log_cap) {
-          const unsigned base = s_logn, at = base + (unsigned)k + (unsigned)__popcll(mt & ((1ull << k) - 1ull));
-          const unsigned total = (unsigned)n + (unsigned)__popcll(mt);
-          if (base + total > wr.log_cap) {
-            if (k == 0) raise_abort(D, ABORT_LOG_FULL, blockIdx.x);
-          } else {
-            if (in) {
-              const unsigned long long tail = ((unsigned long long)M.seq[k] << 32) | (3ull << 20) | ((unsigned)M.n[k] & 0xfffffu);
-              wr.log[at] = tail;
-              if (tr) wr.log[at + 1] = tail | (1ull << 28);
-            }
-            if (k == 0) s_logn = base + total;
-          }
-        }
-      }
-    }
-  };
-  if (wave == 1) take_batch(wr.train ? nd_muf - (int)count : KB_MAX);
-  lds_barrier();
-  for (;;) {
-    const int n = s_n;
-    if (n == 0) break;
-    head += n;
-    for (int idx = threadIdx.x; idx < n * (Hp >> 2); idx += AMP_THREADS) {
-      const int k = idx / (Hp >> 2), c = (idx - k * (Hp >> 2)) << 2;
-      const v4f hv = *(const GQ v4f*)(B.hc + M.off0[k] + c);
-      *(LDSQ v4f*)(hbuf + k * Hp + c) = hv;
-      if (probe_period && M.b[k] >= 0) *(GQ v4f*)(probe + (long long)M.b[k] * probe_w + 4 + c) = hv;
-    }
-    lds_barrier();
-    // logits z[k][r]
-    for (int idx = threadIdx.x; idx < n * R; idx += AMP_THREADS) {
-      const int k = idx / R, r = idx - k * R;
-      const LDSQ float* w = Wl + r * ldw;
-      const LDSQ float* h = hbuf + k * Hp;
-      float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
-      int c = 0;
-      // sixteen columns' operands are read together (rows start 16-byte aligned), then multiplied in column order
-      for (; c + 15 < C; c += 16) {
-        v4f wv[4], hv[4];
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          wv[g] = *(const LDSQ v4f*)(w + c + 4 * g);
-          hv[g] = *(const LDSQ v4f*)(h + c + 4 * g);
-        }
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          a0 = fmaf(wv[g].x, hv[g].x, a0);
-          a1 = fmaf(wv[g].y, hv[g].y, a1);
-          a2 = fmaf(wv[g].z, hv[g].z, a2);
-          a3 = fmaf(wv[g].w, hv[g].w, a3);
-        }
-      }
-      for (; c + 3 < C; c += 4) {
-        a0 = fmaf(w[c], h[c], a0);
-        a1 = fmaf(w[c + 1], h[c + 1], a1);
-        a2 = fmaf(w[c + 2], h[c + 2], a2);
-        a3 = fmaf(w[c + 3], h[c + 3], a3);
-      }
-      for (; c < C; ++c) a0 = fmaf(w[c], h[c], a0);
-      zbuf[k * 64 + r] = ((a0 + a1) + (a2 + a3)) + bl[r];
-    }
-    lds_barrier();
-    // softmax cross-entropy per message; z becomes dz = p - onehot(label)
-    if ((int)threadIdx.x < n) {
-      const int k = threadIdx.x, label = M.a[k];
-      LDSQ float* z = zbuf + k * 64;
-      float m = z[0];
-      int am = 0;
-      for (int r = 1; r < R; ++r)
-        if (z[r] > m) {
-          m = z[r];
-          am = r;
-        }
-      float se = 0.f;
-      for (int r = 0; r < R; ++r) se += expf(z[r] - m);
-      const float zl = z[label];
-      const float inv = 1.f / se;
-      // d logits; zero for an evaluation node, which then adds nothing to the gradient sums below
-      const float keep = M.aux[k] ? 0.f : 1.f;
-      for (int r = 0; r < R; ++r) z[r] = keep * (expf(z[r] - m) * inv - (r == label ? 1.f : 0.f));
-      const unsigned idx = M.seq[k] - s_first_seq;
-      __hip_atomic_fetch_add((GQ float*)&D->loss_out[idx], -(zl - m - logf(se)), __ATOMIC_RELAXED, AGENT);
-      if (am == label) __hip_atomic_fetch_add((GQ int*)&D->correct_out[idx], 1, __ATOMIC_RELAXED, AGENT);
-    }
-    if (wr.train) {
-      lds_barrier();
-      // dh[k][c] = sum_r W[r][c] dz[k][r]
-      for (int idx = threadIdx.x; idx < n * C; idx += AMP_THREADS) {
-        const int k = idx / C, c = idx - k * C;
-        const LDSQ float* z = zbuf + k * 64;
-        float a = 0.f;
-        for (int r = 0; r < R; ++r) a = fmaf(Wl[r * ldw + c], z[r], a);
-        B.gout[M.dst0[k] + c] = a;
-      }
-    }
-    // what lane k of wave 0 needs of message k for its joins, before the batch's record is given up
-    const int nB = uni(M.nB);
-    int js = 0, jn = 0, jaux = 0, jpar = 0, jL = 0;
-    if (threadIdx.x < 64 && (int)threadIdx.x < n) {
-      const int k = threadIdx.x;
-      js = M.s[k];
-      jn = M.n[k];
-      jaux = M.aux[k];
-      jpar = M.par[k];
-      jL = M.L[k];
-    }
-    // every wave's HBM stores have landed before wave 0 publishes the batch
-    publish_barrier();
-    if (threadIdx.x < 64) {
-      fence_release();
-      if ((int)threadIdx.x < n) {
-        if (jaux) {
-          if (atomicAdd((int*)&done_cnt[js], 1) + 1 == 2 * jL - 1) {
-            done_cnt[js] = 0;
-            ring_post(wr.ctl, MSG_MAKE(1, js, 0));
-          }
-        } else {
-          tree_grad_part_done(wr, B, js, jn, jpar < 0, jn < jL);
-        }
-      }
-    }
-    if (wr.train) {
-      // G[r][c] += sum_k dz[k][r] h[k][c], messages in ring order
-#pragma unroll
-      for (int j = 0; j < NE; ++j)
-        if (j < nj && er[j] >= 0) {
-          float a = gacc[j];
-          int k = 0;
-          for (; k + 7 < n; k += 8) {   // eight messages' operands are read together, then added in ring order
-            float zz[8], hh[8];
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-              zz[q] = zbuf[(k + q) * 64 + er[j]];
-              hh[q] = hbuf[(k + q) * Hp + ec[j]];
-            }
-#pragma unroll
-            for (int q = 0; q < 8; ++q) a = fmaf(zz[q], hh[q], a);
-          }
-          for (; k < n; ++k) a = fmaf(zbuf[k * 64 + er[j]], hbuf[k * Hp + ec[j]], a);
-          gacc[j] = a;
-        }
-      if ((int)threadIdx.x < R)
-        for (int k = 0; k < n; ++k) gb += zbuf[k * 64 + threadIdx.x];
-      count += nB;
-      if ((int)count >= nd_muf) {
-        // the node's own update (Section 3); every thread owns its elements, and the old weights have been read
-        tstep++;
-        if (bounded && threadIdx.x == 0) note_update(D);
-        const OptCoef o = opt_at(ob, tstep);
-        const float inv = mean ? 1.f / (float)count : 1.f;
-#pragma unroll
-        for (int j = 0; j < NE; ++j)
-          if (j < nj && er[j] >= 0) {
-            const int li = er[j] * ldw + ec[j];
-            Wl[li] = opt_step(o, Wl[li], gacc[j] * inv, sm[j], sv[j]);
-            gacc[j] = 0.f;
-          }
-        if ((int)threadIdx.x < R) {
-          bl[threadIdx.x] = opt_step(o, bl[threadIdx.x], gb * inv, bm, bv);
-          gb = 0.f;
-        }
-        count = 0;
-        // recorded by the wave that records the next batch's events, so that the update comes first
-        if (threadIdx.x == 64) log_event(D, W, &s_logn, 3, 2, 0, 0);
-      }
-    }
-    if (wave == 1) take_batch(wr.train ? nd_muf - (int)count : KB_MAX);
-    lds_barrier();
-  }
-  tile_store(nd, t, Wg, bg);
-#pragma unroll
-  for (int j = 0; j < NE; ++j)
-    if (er[j] >= 0) {
-      const int e = threadIdx.x + AMP_THREADS * j;
-      ndG[e] = gacc[j];
-      if (ob.kind != 0) ndM[e] = sm[j];
-      if (ob.kind == 2) ndV[e] = sv[j];
-    }
-  if ((int)threadIdx.x < R) {
-    ndG[R * C + threadIdx.x] = gb;
-    if (ob.kind != 0) ndM[R * C + threadIdx.x] = bm;
-    if (ob.kind == 2) ndV[R * C + threadIdx.x] = bv;
-  }
-  if (threadIdx.x == 0) {
-    W->wstate[0] = count;
-    W->wstate[1] = tstep;
-  }
-}
