@@ -589,6 +589,21 @@ def test_ggnn_tiled_nodes_replay_parity(dims, tiles, mak, muf, opt, n):
     compare(g, rt, len(data), opt=opt)
 
 
+@pytest.mark.parametrize("muf,n", [(1, 96), (2, 96), (7, 150), (40, 100)])
+def test_ggnn_messages_taken_out_of_turn(muf, n):
+    """24 graphs in flight, so that both directions wait in every ring, and nodes of two and three tiles: every tile must
+    apply each update between the same messages, whichever entries it saw ready (an update after every gradient, after a
+    few, and with gradients left over)."""
+    dims, tiles = dict(n_node_types=5, hidden=40, n_edge_types=2, n_steps=2), {1: 3, 2: 2, 3: 2, 4: 2, 5: 3}
+    data = synth.make_ggnn(n, 5, dims)[0]
+    fp = synth.init_params("ggnn", dims, 9)
+    opt = dict(kind="sgd", lr=0.005)
+    g = gpu_train("ggnn", dims, fp, data, 24, muf, opt, tiles=tiles)
+    check_controller_log(g["logs"], 24, len(data))
+    rt = oracle_replay("ggnn", dims, fp, data, g["logs"], muf, opt)
+    compare(g, rt, len(data), opt=opt)
+
+
 def test_ggnn_odd_sizes_and_tiny_graphs():
     """Hidden size not a multiple of anything, three edge types of which some
     graphs use only one, graphs of two nodes next to the largest ones."""
