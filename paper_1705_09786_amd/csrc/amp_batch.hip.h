@@ -139,6 +139,15 @@ __device__ __forceinline__ int wait_batch(const GQ AmpDev* D, const R& r, unsign
 // receives D[4*(l/16)+v][l%16], v = 0..3.  fp32 in, fp32 accumulate.
 #define MFMA(a, b, c) __builtin_amdgcn_mfma_f32_16x16x4f32((a), (b), (c), 0, 0, 0)
 
+// 16 bytes per active lane from `from` on to LDS from `to` on (lane l's at 16 l past either), without a register in between.  As an
+// instruction and not through the compiler's builtin, behind which every later LDS read waits for the transfer: the caller
+// waits for its vector memory (s_waitcnt vmcnt(0)) and then for the workgroup, before anyone reads the rows.
+__device__ __forceinline__ void global_to_lds(const GQ float* from, LDSQ float* to) {
+  const unsigned lane16 = (threadIdx.x & 63) * 16u;
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"((unsigned)(unsigned long long)to), "v"(lane16), "s"(from)
+               : "memory");
+}
+
 // Y[j][r] = b[r] + sum_c W[r][c] X[j][c]   (M = weight rows, N = messages, K = columns)
 // Generic shape: one (row block, message block) item per wave at a time.
 __device__ __noinline__ void mfma_rows_any(const LDSQ float* Wl, int ldw, int NRB, int NCG, const LDSQ float* bl,

@@ -695,19 +695,215 @@ __device__ __forceinline__ void g_pend_append(GQ float* pend, int Rp, int stride
   }
 }
 
+// The update of a tile of NRBT 16-row blocks and NCGT 16-column groups from its pending list (as tree_update_from_pend:
+// entry k = [delta | input], G = sum of delta (x) input in arrival order), the list brought through the LDS.  What
+// bounds tree_update_from_pend on such a list is its fetches, each input as often as there are row blocks: 40 us for the 380 pairs
+// of 20 graphs and a 34 x 200 tile with Adam, of which the products need 12.  Here, 28 us:
+//   * a 16 x 16 tile of the gradient belongs to one wave for the whole list, consecutive tiles to each, as many to every wave or one fewer;
+//   * CH entries at a time, CH / 8 a wave, go from memory to LDS rows without passing registers, twice CH ahead of the matrix cores
+//     (34 us with eight entries at a time, five times eight ahead: a barrier for every 640 cycles of products); rows are 16 modulo
+//     64 floats apart, so that the four entries a wave reads together lie in different banks.  The last rows repeat the last
+//     entry with a delta of zero;
+//   * the optimizer's slots of the first half of the tiles (of all, where a wave has five or fewer) arrive meanwhile.
+// buf: NBUF x CH rows of LD floats that nobody else uses -- the rows of X and Y, which are at least 32 of 328 floats or 96 of 232;
+// every wave's pending stores have landed.  Ends with a barrier behind the last use of buf, none behind the weights.
+template <int N>
+struct GInt {
+  static constexpr int v = N;
+};
+template <int N>
+struct GSlots {
+  int at[N][4];
+  float m[N][4], v[N][4];
+};
+template <int NRBT, int NCGT>
+struct GUpd {
+  static constexpr int STRIDE = 16 * (NRBT + NCGT), LD = (STRIDE + 47) / 64 * 64 + 16, NT = NRBT * NCGT, TPW = (NT + 7) / 8;
+  static constexpr int CH = NT > 60 ? 8 : 16, NBUF = 3;   // beside the weights of seven row blocks there is room for no more
+  static constexpr int RPW = CH / 8;                      // rows a wave brings
+};
+
+template <int NRBT, int NCGT>
+__device__ __noinline__ void g_update_lds(LDSQ float* Wl, LDSQ float* bl, const GQ NodeDev* ndp, Tile t, const GQ float* pend, unsigned rows,
+                                          unsigned n_grad, unsigned tstep, const LDSQ int* rowmap, const LDSQ int* colmap, float gb,
+                                          LDSQ float* buf) {
+  typedef GUpd<NRBT, NCGT> U;
+  constexpr int LD = U::LD, TPW = U::TPW, CH = U::CH, NBUF = U::NBUF, Rp = 16 * NRBT;
+  const int ldw = amp_ldrow(16 * NCGT);
+  constexpr int S1 = TPW > 5 ? (TPW + 1) / 2 : TPW, S2 = TPW - S1;   // tiles whose slots are fetched first / second
+  const GQ NodeDev& nd = *ndp;
+  const int wave = uni((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63, i = lane & 15, q = lane >> 4;
+  constexpr int base = U::NT / 8, rem = U::NT % 8;
+  const int first = wave * base + (wave < rem ? wave : rem), mine = base + (wave < rem ? 1 : 0);
+  const int n = uni((int)rows), cols = uni(t.C);
+  const GQ float* list = uni_gq<float>((const void*)pend);
+  buf = (LDSQ float*)(unsigned long long)uni((unsigned)(unsigned long long)buf);
+  const int kind = uni(s_opt.o.kind);
+  GQ float* Mq = uni_gq<float>(s_opt.M);
+  GQ float* Vq = uni_gq<float>(s_opt.V);
+  const v4f zero = {0.f, 0.f, 0.f, 0.f};
+  v4f g[TPW];
+  int ao[TPW], xo[TPW], rb16[TPW], cg16[TPW];
+#pragma unroll
+  for (int u = 0; u < TPW; ++u) {
+    const int id = first + (u < mine ? u : 0), cg = id / NRBT, rb = id - cg * NRBT;
+    rb16[u] = 16 * rb;
+    cg16[u] = 16 * cg;
+    ao[u] = q * LD + rb16[u] + i;
+    xo[u] = q * LD + Rp + cg16[u] + i;
+    g[u] = zero;
+  }
+  // this wave's rows of the CH entries from k0 on
+  auto bring = [&](int k0, int b) {
+#pragma unroll
+    for (int j = 0; j < U::RPW; ++j) {
+      const int r = 8 * j + wave;
+      const GQ float* from = uni_gq<float>((const void*)(list + (long long)(k0 + r < n ? k0 + r : n - 1) * U::STRIDE));
+      LDSQ float* to = buf + uni(b * CH + r) * LD;
+      if (lane < (U::STRIDE < 256 ? U::STRIDE : 256) / 4) global_to_lds(from, to);
+      if (U::STRIDE > 256 && lane < (U::STRIDE - 256) / 4) global_to_lds(from + 256, to + 256);
+    }
+  };
+  // the slots of tiles U0 .. U0 + N - 1: where they lie (-1: padding), then every fetch
+  auto slots = [&](auto U0, auto N, auto& sl) {
+#pragma unroll
+    for (int u = 0; u < N.v; ++u) {
+      const int nc = colmap[cg16[U0.v + u] + i];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int nr = rowmap[rb16[U0.v + u] + 4 * q + e];
+        sl.at[u][e] = nr >= 0 && nc >= 0 ? nr * cols + nc : -1;
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < N.v; ++u)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) sl.m[u][e] = Mq[sl.at[u][e] < 0 ? 0 : sl.at[u][e]];
+    if (kind == 2) {
+#pragma unroll
+      for (int u = 0; u < N.v; ++u)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sl.v[u][e] = Vq[sl.at[u][e] < 0 ? 0 : sl.at[u][e]];
+    }
+  };
+  GSlots<S1> s1;
+  GSlots<S2 ? S2 : 1> s2;
+  float bm = 0.f, bv = 0.f;
+  const bool bias = (int)threadIdx.x < t.R && nd.has_bias;
+  int bat = 0;
+  if (kind != 0) {
+    if (bias) {
+      bat = nd.rows * cols + rowmap[threadIdx.x];
+      bm = Mq[bat];
+      if (kind == 2) bv = Vq[bat];
+    }
+    slots(GInt<0>{}, GInt<S1>{}, s1);
+  }
+  asm volatile("" ::: "memory");   // the slots' fetches are issued first: what is waited for below is counted from the last one back
+  if (n > 0) {
+#pragma unroll
+    for (int b = 0; b < NBUF - 1; ++b) bring(b * CH, b);
+  }
+  for (int k0 = 0, b = 0; k0 < n; k0 += CH) {
+    if (U::STRIDE > 256)
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * U::RPW * (NBUF - 2)) : "memory");
+    else
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(U::RPW * (NBUF - 2)) : "memory");
+#pragma unroll
+    for (int j = 0; j < U::RPW; ++j)
+      if (k0 + 8 * j + wave >= n && lane < Rp / 4) *(LDSQ v4f*)(buf + (b * CH + 8 * j + wave) * LD + 4 * lane) = zero;
+    lds_barrier();
+    // the entries before these have been used by every wave; beyond the list the last entry is brought, and dropped
+    bring(k0 + (NBUF - 1) * CH, b == 0 ? NBUF - 1 : b - 1);
+    const LDSQ float* src = buf + b * CH * LD;
+    float a0[TPW], x0[TPW], a1[TPW], x1[TPW];
+    auto fetch = [&](int s, float (&a)[TPW], float (&x)[TPW]) {
+#pragma unroll
+      for (int u = 0; u < TPW; ++u) {
+        a[u] = src[4 * s * LD + ao[u]];
+        x[u] = src[4 * s * LD + xo[u]];
+      }
+    };
+    auto work = [&](float (&a)[TPW], float (&x)[TPW]) {
+#pragma unroll
+      for (int u = 0; u < TPW; ++u)
+        if (u < base || u < mine) g[u] = MFMA(a[u], x[u], g[u]);
+    };
+    fetch(0, a0, x0);
+    fetch(1, a1, x1);
+    asm volatile("" ::: "memory");
+    work(a0, x0);
+    if (CH == 16) {
+      fetch(2, a0, x0);
+      asm volatile("" ::: "memory");
+    }
+    work(a1, x1);
+    if (CH == 16) {
+      fetch(3, a1, x1);
+      asm volatile("" ::: "memory");
+      work(a0, x0);
+      work(a1, x1);
+    }
+    b = b + 1 == NBUF ? 0 : b + 1;
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  lds_barrier();
+  const OptCoef o = held_opt(tstep);
+  const float inv = uni(s_opt.mean) ? 1.f / (float)n_grad : 1.f;
+  // lane (i, q) holds rows 4 q .. 4 q + 3 of column i of its tiles
+  auto step = [&](auto U0, auto N, auto& sl) {
+#pragma unroll
+    for (int u = 0; u < N.v; ++u)
+      if (U0.v + u < mine) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int at = sl.at[u][e];
+          if (at >= 0) {
+            LDSQ float* w = Wl + (rb16[U0.v + u] + 4 * q + e) * ldw + cg16[U0.v + u] + i;
+            *w = opt_step(o, *w, g[U0.v + u][e] * inv, sl.m[u][e], sl.v[u][e]);
+            Mq[at] = sl.m[u][e];
+            if (kind == 2) Vq[at] = sl.v[u][e];
+          }
+        }
+      }
+  };
+  if (kind == 0) {
+    const float sc = o.lr * inv;   // padding rows and columns have a zero gradient
+#pragma unroll
+    for (int u = 0; u < TPW; ++u)
+      if (u < mine) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) Wl[(rb16[u] + 4 * q + e) * ldw + cg16[u] + i] -= sc * g[u][e];
+      }
+  } else {
+    if (S2) slots(GInt<S1>{}, GInt<S2>{}, s2);
+    asm volatile("" ::: "memory");   // every fetch is issued before the first store
+    step(GInt<0>{}, GInt<S1>{}, s1);
+    if (S2) step(GInt<S1>{}, GInt<S2>{}, s2);
+  }
+  if (bias) {
+    bl[threadIdx.x] = opt_step(o, bl[threadIdx.x], gb * inv, bm, bv);
+    if (kind != 0) Mq[bat] = bm;
+    if (kind == 2) Vq[bat] = bv;
+  }
+}
+
 // Counts nmsg gradients (grouped messages, K rows in all, already appended to the pending list) and updates when
-// min_update_frequency is reached.
+// min_update_frequency is reached.  buf = the rows of X and Y, free when an update is due.
 template <int NRBT, int NCGT>
 __device__ __forceinline__ void g_count_and_update(const GQ AmpDev* D, const GQ WorkerDev* W, const GQ NodeDev& nd, const Tile& t,
                                                    const GTile& g, const GQ float* pend, unsigned& count, unsigned& nrows,
-                                                   unsigned& tstep, int nmsg, int K, float& gb) {
+                                                   unsigned& tstep, int nmsg, int K, float& gb, LDSQ float* buf) {
   count += nmsg;
   nrows += K;
   if ((int)count >= uni(nd.muf)) {
     tstep++;
     if (threadIdx.x == 0) note_update(D);
     __syncthreads();   // the appended rows of every wave are in HBM
-    tree_update_from_pend<NRBT, NCGT>(g.Wl, g.bl, &nd, t, pend, nrows, count, tstep, g.rowmap, g.colmap, gb);
+    if constexpr (NRBT != 0)
+      g_update_lds<NRBT, NCGT>(g.Wl, g.bl, &nd, t, pend, nrows, count, tstep, g.rowmap, g.colmap, gb, buf);
+    else
+      tree_update_from_pend<NRBT, NCGT>(g.Wl, g.bl, &nd, t, pend, nrows, count, tstep, g.rowmap, g.colmap, gb);
     gb = 0.f;
     count = 0;
     nrows = 0;
@@ -991,8 +1187,9 @@ __device__ __noinline__ void role_g_edge(const GQ AmpDev* D, const GQ WorkerDev*
     }
     publish_barrier();
     const GPass pn = g_pass(pb ^ 1);
-    const bool have = pn.nm > 0;
-    if (have && threadIdx.x >= 64) stage(pn, threadIdx.x - 64, AMP_THREADS - 64);
+    // the rows of X and Y serve the update, if one is due
+    const bool have = pn.nm > 0, ahead = have && !(NRBT != 0 && p.bwd && (int)cnt_after >= uni(nd.muf));
+    if (ahead && threadIdx.x >= 64) stage(pn, threadIdx.x - 64, AMP_THREADS - 64);
     if (threadIdx.x < 64) {
       fence_release();
       const int m = threadIdx.x;
@@ -1015,11 +1212,11 @@ __device__ __noinline__ void role_g_edge(const GQ AmpDev* D, const GQ WorkerDev*
       }
     }
     PHASE(3);
-    if (p.bwd) g_count_and_update<NRBT, NCGT>(D, W, nd, t, g, pend, count, nrows, tstep, p.nm, p.Kt, gb);
+    if (p.bwd) g_count_and_update<NRBT, NCGT>(D, W, nd, t, g, pend, count, nrows, tstep, p.nm, p.Kt, gb, X);
     PHASE(7);
     if (!have && (threadIdx.x >> 6) == 1) g_form_pass(D, gd, B, mine, head, taken, CAP, maxm, room(count), ctype, true, true, pb ^ 1);
     lds_barrier();
-    staged = have;
+    staged = ahead;
     pb ^= 1;
   }
   tile_store(nd, t, g.Wg, g.bg);
@@ -1276,8 +1473,9 @@ __device__ __noinline__ void role_g_gate(const GQ AmpDev* D, const GQ WorkerDev*
     }
     publish_barrier();
     const GPass pn = g_pass(pb ^ 1);
-    const bool have = pn.nm > 0;
-    if (have && threadIdx.x >= 64) stage(pn, threadIdx.x - 64, AMP_THREADS - 64);
+    // the rows of X and Y serve the update, if one is due
+    const bool have = pn.nm > 0, ahead = have && !(NRBT != 0 && p.bwd && (int)cnt_after >= uni(nd.muf));
+    if (ahead && threadIdx.x >= 64) stage(pn, threadIdx.x - 64, AMP_THREADS - 64);
     if (threadIdx.x < 64) {
       fence_release();
       const int m = threadIdx.x;
@@ -1294,11 +1492,11 @@ __device__ __noinline__ void role_g_gate(const GQ AmpDev* D, const GQ WorkerDev*
       }
     }
     PHASE(3);
-    if (p.bwd) g_count_and_update<NRBT, NCGT>(D, W, nd, t, g, pend, count, nrows, tstep, p.nm, p.Kt, gb);
+    if (p.bwd) g_count_and_update<NRBT, NCGT>(D, W, nd, t, g, pend, count, nrows, tstep, p.nm, p.Kt, gb, X);
     PHASE(7);
     if (!have && (threadIdx.x >> 6) == 1) g_form_pass(D, gd, B, mine, head, taken, CAP, maxm, room(count), 0, false, true, pb ^ 1);
     lds_barrier();
-    staged = have;
+    staged = ahead;
     pb ^= 1;
   }
   tile_store(nd, t, g.Wg, g.bg);
@@ -1559,8 +1757,9 @@ __device__ __noinline__ void role_g_cand(const GQ AmpDev* D, const GQ WorkerDev*
     }
     publish_barrier();
     const GPass pn = g_pass(pb ^ 1);
-    const bool have = pn.nm > 0;
-    if (have && threadIdx.x >= 64) stage(pn, threadIdx.x - 64, AMP_THREADS - 64);
+    // the rows of X and Y serve the update, if one is due
+    const bool have = pn.nm > 0, ahead = have && !(NRBT != 0 && p.bwd && (int)cnt_after >= uni(nd.muf));
+    if (ahead && threadIdx.x >= 64) stage(pn, threadIdx.x - 64, AMP_THREADS - 64);
     if (threadIdx.x < 64) {
       fence_release();
       const int m = threadIdx.x;
@@ -1586,11 +1785,11 @@ __device__ __noinline__ void role_g_cand(const GQ AmpDev* D, const GQ WorkerDev*
       }
     }
     PHASE(3);
-    if (p.bwd) g_count_and_update<NRBT, NCGT>(D, W, nd, t, g, pend, count, nrows, tstep, p.nm, p.Kt, gb);
+    if (p.bwd) g_count_and_update<NRBT, NCGT>(D, W, nd, t, g, pend, count, nrows, tstep, p.nm, p.Kt, gb, X);
     PHASE(7);
     if (!have && (threadIdx.x >> 6) == 1) g_form_pass(D, gd, B, mine, head, taken, CAP, maxm, room(count), 0, false, true, pb ^ 1);
     lds_barrier();
-    staged = have;
+    staged = ahead;
     pb ^= 1;
   }
   tile_store(nd, t, g.Wg, g.bg);

@@ -29,15 +29,6 @@ struct SmallDiv {
   __device__ __forceinline__ int operator()(int x) const { return m ? (int)__umulhi((unsigned)x, m) : x; }
 };
 
-// 16 bytes per active lane from `from` on to LDS from `to` on (lane l's at 16 l past either), without a register in between.  As an
-// instruction and not through the compiler's builtin, behind which every later LDS read waits for the transfer: the caller
-// waits for its vector memory (s_waitcnt vmcnt(0)) and then for the workgroup, before anyone reads the rows.
-__device__ __forceinline__ void global_to_lds(const GQ float* from, LDSQ float* to) {
-  const unsigned lane16 = (threadIdx.x & 63) * 16u;
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"((unsigned)(unsigned long long)to), "v"(lane16), "s"(from)
-               : "memory");
-}
-
 // Four accumulators += W[r][c] x_j[c] over NCG 16-column groups, operands from LDS: the next four groups' operands are read while
 // the present four go through the matrix core.
 __device__ __forceinline__ void cell_rows(const LDSQ float* wp, const LDSQ float* xp, int NCG, v4f (&acc)[4]) {

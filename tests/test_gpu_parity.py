@@ -604,6 +604,23 @@ def test_ggnn_messages_taken_out_of_turn(muf, n):
     compare(g, rt, len(data), opt=opt)
 
 
+@pytest.mark.parametrize("hidden,tiles,muf,opt", [
+    (104, {}, 1, MOM),                             # seven row blocks: lists of 2 to 29 nodes' rows
+    (97, {}, 5, G_ADAM),                           # the same shape by single elements
+    (104, {1: 2, 2: 3, 3: 4, 4: 2, 5: 3}, 1, dict(kind="sgd", lr=0.005)),   # two, four and three row blocks
+    (100, {1: 4, 2: 2, 3: 2, 4: 3, 5: 4}, 6, MOM),
+    (112, {1: 2, 3: 2, 4: 3, 5: 2}, 3, MOM),       # the edge linears' only
+])
+def test_ggnn_update_of_fixed_shapes(hidden, tiles, muf, opt):
+    """The pending list brought through the LDS: every row-block count, lists shorter than one fetch and with remainders, each optimizer."""
+    dims = dict(n_node_types=5, hidden=hidden, n_edge_types=2, n_steps=2)
+    data = synth.make_ggnn(60, 5, dims, min_nodes=2, max_nodes=5)[0] + synth.make_ggnn(20, 6, dims, min_nodes=16, max_nodes=29)[0]
+    fp = synth.init_params("ggnn", dims, 9)
+    g = gpu_train("ggnn", dims, fp, data, 8, muf, opt, tiles=tiles)
+    rt = oracle_replay("ggnn", dims, fp, data, g["logs"], muf, opt)
+    compare(g, rt, len(data), opt=opt)
+
+
 def test_ggnn_odd_sizes_and_tiny_graphs():
     """Hidden size not a multiple of anything, three edge types of which some
     graphs use only one, graphs of two nodes next to the largest ones."""
