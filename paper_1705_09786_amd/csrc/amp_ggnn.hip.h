@@ -461,6 +461,47 @@ __device__ __forceinline__ void for_items2(int total, int tid, int nthr, Ld ld, 
   }
 }
 
+// Staging of a pass by `nw` waves, this one being wave w of them: row w + nw * j of the stack belongs to the wave, and lane j finds
+// out where it comes from, so that the indices in front of a row are fetched once for all rows together and the rows
+// themselves are all on their way at once.  (With every thread following the indices of its own 16 bytes, two at a time,
+// the pass of a quarter of the edge linear took 16 us with 2.9 graphs, of which 6 were staging; now 11.6 with 2.2.)
+__device__ __forceinline__ long long g_shfl64(long long v, int j) {
+  const unsigned lo = __shfl((unsigned)v, j), hi = __shfl((unsigned)((unsigned long long)v >> 32), j);
+  return (long long)(((unsigned long long)hi << 32) | lo);
+}
+// Row j = 0 .. n - 1 (4 * groups floats) from base + lane j's off to LDS, to + j * ld.  The caller waits (g_rows_landed) before
+// the barrier behind which they are read.
+__device__ __forceinline__ void g_rows_to_lds(const GQ float* base, long long off, int n, LDSQ float* to, int ld, int groups) {
+  const int lane = threadIdx.x & 63;
+  for (int j = 0; j < n; ++j) {
+    const unsigned lo = __builtin_amdgcn_readlane((unsigned)off, j), hi = __builtin_amdgcn_readlane((unsigned)((unsigned long long)off >> 32), j);
+    const GQ float* from = uni_gq<float>((const void*)(base + (long long)(((unsigned long long)hi << 32) | lo)));
+    LDSQ float* dst = (LDSQ float*)(unsigned long long)uni((unsigned)(unsigned long long)(to + j * ld));
+    for (int g = 0; g < groups; g += 64)
+      if (g + lane < groups) global_to_lds(from + 4 * g, dst + 4 * g);
+  }
+}
+__device__ __forceinline__ void g_rows_landed() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+// Items 0 .. total - 1 of a wave (total the same in every lane), U of a lane fetched (ld) before any is used (st); every lane of
+// the wave is in ld, so that it may read other lanes.
+template <int U, class It, class Ld, class St>
+__device__ __forceinline__ void g_wave_items(int total, Ld ld, St st) {
+  const int lane = threadIdx.x & 63;
+  for (int i0 = 0; i0 < total; i0 += 64 * U) {
+    It it[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = i0 + 64 * u + lane;
+      it[u] = ld(i < total ? i : total - 1);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = i0 + 64 * u + lane;
+      if (i < total) st(i, it[u]);
+    }
+  }
+}
+
 // Bit c set when the graph has edges of type c (at most 8 types).
 __device__ __forceinline__ unsigned g_present_types(const GView& v, int T) {
   unsigned m = 0;
@@ -572,6 +613,8 @@ __device__ __forceinline__ v4f g_state_gradient4(const GBufs& B, const GParts& e
 }
 
 // The same, with the instance's parts of dHe given packed (4 bits each, pn of them): the form a pass record holds.
+// MID: with up to eight parts of either kind, eight and eight fetches (compiled for split candidate tiles only).
+template <bool MID>
 __device__ __forceinline__ v4f g_state_gradient4p(const GBufs& B, unsigned plo, unsigned phi, int pn, int s, int i, int step) {
   const long long NH = (long long)B.N * B.H;
   const GQ float* he = B.dHe + (long long)s * B.PE * NH + i;
@@ -590,6 +633,20 @@ __device__ __forceinline__ v4f g_state_gradient4p(const GBufs& B, unsigned plo, 
       if (k < pn) a += e[k];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
+      if (k >= B.Th && k < B.PA) g += p[k];
+      if (k < B.Th) cnd += p[k];
+    }
+  } else if (MID && B.PE <= 8 && B.PA <= 8) {
+    v4f e[8], p[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) e[k] = *(const GQ v4f*)(he + (long long)((pk >> (4 * (k < pn ? k : 0))) & 15u) * NH);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) p[k] = *(const GQ v4f*)(hp + (k < B.PA ? k : 0) * NH);
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+      if (k < pn) a += e[k];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
       if (k >= B.Th && k < B.PA) g += p[k];
       if (k < B.Th) cnd += p[k];
     }
@@ -625,6 +682,15 @@ __device__ __forceinline__ v4f g_sum_dA4(const GBufs& B, const GQ float* dA, lon
     for (int k = 0; k < 4; ++k) p[k] = *(const GQ v4f*)(dA + (k < B.PA ? k : 0) * NH + o);
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
+      if (k >= B.Th && k < B.PA) g += p[k];
+      if (k < B.Th) cnd += p[k];
+    }
+  } else if (B.PA <= 8) {
+    v4f p[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) p[k] = *(const GQ v4f*)(dA + (k < B.PA ? k : 0) * NH + o);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
       if (k >= B.Th && k < B.PA) g += p[k];
       if (k < B.Th) cnd += p[k];
     }
@@ -1025,6 +1091,9 @@ __device__ __noinline__ void role_g_edge(const GQ AmpDev* D, const GQ WorkerDev*
   const int maxm = vec ? G_MB : 1;                    // the element-by-element paths take one message at a time
   const long long NH = (long long)B.N * H;
   const v4f zero4 = {0.f, 0.f, 0.f, 0.f};
+  // A split tile stages row by row; the whole node has as much delta as input, and stages both in one go (rows there: 24 replicas
+  // of the unsplit pipeline 8.51 instead of 8.40 ms).
+  constexpr bool ROWS = NRBT != NCGT;
   // What a pass needs in LDS before its product: row k of a message = its k-th edge of this type, ascending (Group
   // orders its rows by edge index).  Forward and backward: the source node's state.  Backward also delta_e = this
   // tile's units of dA[dst(e)] (Bcast backward on A: (update + reset) + candidate, each the sum of its tiles' parts).
@@ -1033,6 +1102,37 @@ __device__ __noinline__ void role_g_edge(const GQ AmpDev* D, const GQ WorkerDev*
       const int GY = Hs >> 2, GZ = GY - GU;
       for (int idx = tid; idx < p.Kt * (GY - G1); idx += nthr)   // padding columns of the used rows
         *(LDSQ v4f*)(X + (idx / (GY - G1)) * Hs + H + ((idx % (GY - G1)) << 2)) = zero4;
+      if constexpr (ROWS) {
+        const int lane = tid & 63, w = uni(tid >> 6), nw = nthr >> 6;
+        for (int b0 = w; b0 < p.Kt; b0 += 64 * nw) {
+          const int left = (p.Kt - b0 + nw - 1) / nw, n = left < 64 ? left : 64;
+          const int k = b0 + nw * (lane < n ? lane : n - 1);
+          const LDSQ unsigned* M = p.of_row(k);
+          const int s = M[2], it = M[3], q = (int)M[11] + (int)M[12] + k - (int)M[5];
+          const int sn = gd.tsrc[q], en = p.bwd ? gd.tdst[q] : gd.tedge[q];   // the target node / the edge
+          g_rows_to_lds(B.Hm, B.hm(s, it) + (long long)sn * H, n, X + b0 * Hs, nw * Hs, G1);
+          if (!p.bwd) {
+            erow[k] = en;
+          } else {
+            // the tile's units of the delta rows
+            const long long at = (long long)s * B.PA * NH + u0 + (long long)en * H;
+            g_wave_items<2, v4f>(n * GU,
+                                 [&](int idx) {
+                                   const int j = idx / GU;
+                                   return g_sum_dA4(B, B.dA, g_shfl64(at, j) + ((idx - j * GU) << 2));
+                                 },
+                                 [&](int idx, const v4f& d) {
+                                   const int j = idx / GU;
+                                   *(LDSQ v4f*)(Y + (b0 + nw * j) * Hs + ((idx - j * GU) << 2)) = d;
+                                 });
+          }
+        }
+        if (p.bwd)   // zeros fill the rest
+          for (int idx = tid; idx < p.Kt * GZ; idx += nthr)
+            *(LDSQ v4f*)(Y + (idx / GZ) * Hs + nu + ((idx % GZ) << 2)) = zero4;
+        g_rows_landed();
+        return;
+      }
       if (!p.bwd) {
         struct It {
           v4f x;
@@ -1588,7 +1688,7 @@ __device__ __noinline__ void role_g_cand(const GQ AmpDev* D, const GQ WorkerDev*
                    if (it + 1 == B.S)
                      r.gg = *(const GQ v4f*)(B.gH + B.sl(s) + o);
                    else
-                     r.gg = g_state_gradient4p(B, M[13], M[14], (int)M[15], s, o, it + 1);
+                     r.gg = g_state_gradient4p<NRBT != 0 && NRBT != 7>(B, M[13], M[14], (int)M[15], s, o, it + 1);
                    return r;
                  },
                  [&](int idx, const Ib& r) {
