@@ -250,6 +250,11 @@ __device__ __noinline__ void role_tree_cell_lds(const GQ AmpDev* D, const GQ Wor
     lds_barrier();
     PHASE(0);
     // ---------------- products
+    // One block of forward messages alone is as many items as the tile has row blocks -- three for four matrix pipes, and
+    // nothing else to do: its columns are then split over up to four items, whose sums meet in the rows of Y behind the batch's.
+    // (A validation pass of 1,101 trees of hidden size 150 was 0.8 % slower than with the weights' old worker, 12.26 against 12.16 ms,
+    // and is level with it so; an update every 3 gradients at hidden 37: 36.9 -> 35.9 ms.)
+    const int KS = nB == 0 && nF <= 16 && NRB <= 4 ? (KB < 4 * nF ? (KB < 2 * nF ? 1 : 2) : 4) : 1;
     {
       // gradient: G[r][c] += sum_k delta_k[r] x_k[c], k in ring order
       if (nB > 0 && unit_of(0) >= 0) {
@@ -283,7 +288,7 @@ __device__ __noinline__ void role_tree_cell_lds(const GQ AmpDev* D, const GQ Wor
           add(a1, x1);
         }
       }
-      const int NBF = (nF + 15) >> 4, nFI = NRB * NBF, items = nFI + NCG * ((nB + 31) >> 5);
+      const int NBF = (nF + 15) >> 4, nFI = NRB * NBF * KS, items = nFI + NCG * ((nB + 31) >> 5);
       auto next = [&]() {
         int it = 0;
         if (lane == 0) it = __hip_atomic_fetch_add((LDSQ int*)&s_item, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -298,12 +303,13 @@ __device__ __noinline__ void role_tree_cell_lds(const GQ AmpDev* D, const GQ Wor
         ahead = next();
         if (it < nFI) {
           // Y[j][r] = b[r] + sum_c W[r][c] x_j[c]
-          const int nb = by_nrb(it), rb = it - nb * NRB, j = nb * 16 + i;
-          const LDSQ float* wp = Wl + (rb * 16 + i) * ldw + 4 * q;
-          const LDSQ float* xp = X + (j < nF ? j : nF - 1) * ldw + 4 * q;
-          v4f acc[4] = {*(const LDSQ v4f*)(bl + rb * 16 + 4 * q), zero, zero, zero};
-          cell_rows(wp, xp, NCG, acc);
-          if (j < nF) *(LDSQ v4f*)(Y + j * ldy + rb * 16 + 4 * q) = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+          const int rest = by_nrb(it), rb = it - rest * NRB, nb = KS > 1 ? 0 : rest, ks = KS > 1 ? rest : 0, j = nb * 16 + i;
+          const int c0 = KS > 1 ? (NCG * ks) / KS : 0, c1 = KS > 1 ? (NCG * (ks + 1)) / KS : NCG;
+          const LDSQ float* wp = Wl + (rb * 16 + i) * ldw + 4 * q + 16 * c0;
+          const LDSQ float* xp = X + (j < nF ? j : nF - 1) * ldw + 4 * q + 16 * c0;
+          v4f acc[4] = {ks ? zero : *(const LDSQ v4f*)(bl + rb * 16 + 4 * q), zero, zero, zero};
+          cell_rows(wp, xp, c1 - c0, acc);
+          if (j < nF) *(LDSQ v4f*)(Y + (ks * nF + j) * ldy + rb * 16 + 4 * q) = (acc[0] + acc[1]) + (acc[2] + acc[3]);
         } else {
           // dx_j[c] = sum_r W[r][c] delta_j[r]: 16 columns for up to 32 messages, from the accumulators to HBM
           const int bi = it - nFI, pb = bi >= NCG ? 1 : 0, cb = bi - pb * NCG;
@@ -335,6 +341,16 @@ __device__ __noinline__ void role_tree_cell_lds(const GQ AmpDev* D, const GQ Wor
     // ---------------- outputs
     if (nF > 0) {
       lds_barrier();
+      if (KS > 1) {
+        for (int p = threadIdx.x; p < nF * 4 * NRB; p += AMP_THREADS) {
+          const int r = p / (4 * NRB);
+          LDSQ float* y = Y + r * ldy + 4 * (p - r * 4 * NRB);
+          v4f a = *(const LDSQ v4f*)y + *(const LDSQ v4f*)(y + nF * ldy);
+          if (KS == 4) a += *(const LDSQ v4f*)(y + 2 * nF * ldy) + *(const LDSQ v4f*)(y + 3 * nF * ldy);
+          *(LDSQ v4f*)y = a;
+        }
+        lds_barrier();
+      }
       for (int p = threadIdx.x; p < nF * nu; p += AMP_THREADS) {
         const int r = by_nu(p), j = p - r * nu, u = u0 + j;
         const bool first = p == (int)threadIdx.x;

@@ -669,6 +669,26 @@ def test_eval_matches_direct_forward(cfg, n, nv):
     a.train(1)
 
 
+@pytest.mark.parametrize("mak,tiles", [(1, {1: 2, 2: 3}), (3, {1: 2, 2: 3}), (12, {1: 1, 2: 2}), (64, {1: 3, 2: 5})])
+def test_tree_forward_only_batches(mak, tiles):
+    """Batches of forward messages alone, from one message to more than a block of sixteen: the cells split the
+    columns of few messages' products over four, two and one items."""
+    from paper_1705_09786_amd import runner
+    dims = TREE_ODD
+    valid = synth.make_tree(90, 31, dims, max_leaves=24)
+    fp = synth.init_params("tree", dims, 13)
+    ml, me = runner.max_len_of("tree", valid)
+    tr = runner.Trainer("tree", dims, fp, mak, ml, me, len(valid), tiles=tiles)
+    tr.amp.set_watchdog(5.0)
+    tr.submit_all(valid)
+    tr.submit_all(valid, which=1)
+    ev = tr.amp.eval()
+    ref_loss, ref_acc = direct.evaluate("tree", dims, direct.unpack("tree", dims, tr.params()), valid)
+    assert ev["n_instances"] == len(valid)
+    assert abs(ev["mean_loss"] - ref_loss) <= 1e-5 * max(1.0, abs(ref_loss))
+    assert abs(ev["accuracy"] - ref_acc) < 1e-9
+
+
 @pytest.mark.parametrize("cfg,n,nv,mak,muf", [(1, 300, 60, 4, 3), (2, 200, 50, 8, 5), (3, 60, 24, 16, 7), (4, 120, 30, 8, 6)])
 def test_train_and_eval_instances_in_one_launch(cfg, n, nv, mak, muf):
     """Section 1: training and inference at the same time.  One launch trains on the training set while the
