@@ -9,12 +9,13 @@
 // batch at once is the same as processing its messages one by one in ring
 // order.
 //
-// Gradients are not accumulated element by element per message.  Each
-// backward message appends its (delta, input) pair to a per-worker list in
-// HBM; when the node updates, the accumulated gradient
+// Gradients are not accumulated element by element per message.  Either the
+// sum over a batch's messages of delta (x) input is added to accumulators in registers
+// (role_tree_cell_lds), or each backward message appends its (delta, input) pair to a
+// per-worker list in HBM and the accumulated gradient
 //     G = sum_k delta_k (x) input_k      (k in arrival order)
-// is formed block by block in registers and goes straight into the optimizer
-// step on the weights (tree_update_from_pend, tree_update_stream).
+// is formed block by block in registers at the node's update, and goes straight into the optimizer
+// step on the weights (tree_update_from_pend, g_update_lds, tree_update_stream).
 #pragma once
 
 #define KB_MAX 64

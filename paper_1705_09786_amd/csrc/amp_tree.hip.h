@@ -8,13 +8,12 @@
 // units' h and c entirely, and contributes a partial W^T delta over all
 // input columns on the way back.
 //
-// A worker takes up to 64 waiting messages at once.  The inputs of the
-// forward product go from the slot storage in HBM straight into the matrix
-// cores' operand registers (rows there are padded to multiples of 4 floats so
-// that every 16-byte fetch is aligned); the input gradient goes from the
-// accumulators straight back to HBM.  Each backward message appends its (delta,
-// input) pair to the tile's pending list in HBM; the update forms the
-// accumulated gradient from that list on the matrix cores.
+// A worker takes up to 64 waiting messages at once.  Cells whose weights leave the LDS room for a batch's inputs are
+// role_tree_cell_lds (amp_tree_cell.hip.h), which keeps the node's gradient in registers.  In role_tree_cell the inputs of
+// the forward product go from the slot storage in HBM straight into the matrix cores' operand registers (rows there are
+// padded to multiples of 4 floats so that every 16-byte fetch is aligned); each backward message appends its (delta,
+// input) pair to the tile's pending list in HBM, and the update forms the accumulated gradient from that list on the
+// matrix cores.  In both the input gradient goes from the accumulators straight back to HBM.
 //
 // Slot storage (s = slot, n = tree node, l = leaf; Hp, Ep = H, E rounded up to 4;
 // padding entries stay zero):
