@@ -143,11 +143,17 @@ __device__ __forceinline__ int wait_batch(const GQ AmpDev* D, const R& r, unsign
 // 16 bytes per active lane from `from` on to LDS from `to` on (lane l's at 16 l past either), without a register in between.  As an
 // instruction and not through the compiler's builtin, behind which every later LDS read waits for the transfer: the caller
 // waits for its vector memory (s_waitcnt vmcnt(0)) and then for the workgroup, before anyone reads the rows.
+// m0 holds the LDS address and has to be named as clobbered: the compiler sets it once for several of its own transfers to one
+// address, and would leave out the second setting with this one in between.  (It warns that m0 is reserved; nothing here needs
+// it preserved.)
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ void global_to_lds(const GQ float* from, LDSQ float* to) {
   const unsigned lane16 = (threadIdx.x & 63) * 16u;
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"((unsigned)(unsigned long long)to), "v"(lane16), "s"(from)
-               : "memory");
+               : "memory", "m0");
 }
+#pragma clang diagnostic pop
 
 // Y[j][r] = b[r] + sum_c W[r][c] X[j][c]   (M = weight rows, N = messages, K = columns)
 // Generic shape: one (row block, message block) item per wave at a time.
