@@ -234,6 +234,8 @@ __device__ __forceinline__ GRings g_rings(const GQ AmpDev* D) {
 // handled, and none behind it, so that the tiles of a node, each of which sees other entries ready, apply the same
 // updates between the same messages.  The entries taken ahead of `head` are kept as bits.  The result is handed
 // to the workgroup through LDS, in one of two buffers: the next pass is formed while the present one is in use.
+// Whether a look ahead found one stands in a word of its own: if not, wave 1 waits for a message and then writes the same buffer,
+// when a wave behind the others may not yet have read that there was nothing.
 #define G_MB 4
 #define G_WIN 16  // ring entries looked at
 #define G_HW 8    // header words: 0 messages, 1 stop flag, 2 stacked rows, 3 stacked graph nodes, 4 direction bit,
@@ -243,6 +245,7 @@ __device__ __forceinline__ GRings g_rings(const GQ AmpDev* D) {
                   // 11 edge offset, 12 start of the worker's edge type in tedge / tsk, 13..14 the parts of dHe the
                   // instance's state gradient adds up (4 bits each, in order), 15 their number
 __shared__ unsigned s_gpass[2][G_HW + G_MB * G_RW];
+__shared__ int s_gahead;   // messages the last look ahead found
 
 // The parts of dHe a graph uses, packed 4 bits each (at most 12 parts): edge types present ascending, tiles ascending.
 __device__ __forceinline__ void g_pack_parts(const GBufs& B, unsigned present, unsigned& lo, unsigned& hi, unsigned& n) {
@@ -378,6 +381,7 @@ __device__ __forceinline__ void g_form_pass(const GQ AmpDev* D, const GData& d, 
     }
   }
   if (l == 0) {
+    if (!block) s_gahead = nm;
     P[0] = (unsigned)nm;
     P[1] = stop;
     P[2] = (unsigned)rows;
@@ -1286,10 +1290,9 @@ __device__ __noinline__ void role_g_edge(const GQ AmpDev* D, const GQ WorkerDev*
       }
     }
     publish_barrier();
-    const GPass pn = g_pass(pb ^ 1);
     // the rows of X and Y serve the update, if one is due
-    const bool have = pn.nm > 0, ahead = have && !(NRBT != 0 && p.bwd && (int)cnt_after >= uni(nd.muf));
-    if (ahead && threadIdx.x >= 64) stage(pn, threadIdx.x - 64, AMP_THREADS - 64);
+    const bool have = uni(s_gahead) > 0, ahead = have && !(NRBT != 0 && p.bwd && (int)cnt_after >= uni(nd.muf));
+    if (ahead && threadIdx.x >= 64) stage(g_pass(pb ^ 1), threadIdx.x - 64, AMP_THREADS - 64);
     if (threadIdx.x < 64) {
       fence_release();
       const int m = threadIdx.x;
@@ -1572,10 +1575,9 @@ __device__ __noinline__ void role_g_gate(const GQ AmpDev* D, const GQ WorkerDev*
       }
     }
     publish_barrier();
-    const GPass pn = g_pass(pb ^ 1);
     // the rows of X and Y serve the update, if one is due
-    const bool have = pn.nm > 0, ahead = have && !(NRBT != 0 && p.bwd && (int)cnt_after >= uni(nd.muf));
-    if (ahead && threadIdx.x >= 64) stage(pn, threadIdx.x - 64, AMP_THREADS - 64);
+    const bool have = uni(s_gahead) > 0, ahead = have && !(NRBT != 0 && p.bwd && (int)cnt_after >= uni(nd.muf));
+    if (ahead && threadIdx.x >= 64) stage(g_pass(pb ^ 1), threadIdx.x - 64, AMP_THREADS - 64);
     if (threadIdx.x < 64) {
       fence_release();
       const int m = threadIdx.x;
@@ -1856,10 +1858,9 @@ __device__ __noinline__ void role_g_cand(const GQ AmpDev* D, const GQ WorkerDev*
       }
     }
     publish_barrier();
-    const GPass pn = g_pass(pb ^ 1);
     // the rows of X and Y serve the update, if one is due
-    const bool have = pn.nm > 0, ahead = have && !(NRBT != 0 && p.bwd && (int)cnt_after >= uni(nd.muf));
-    if (ahead && threadIdx.x >= 64) stage(pn, threadIdx.x - 64, AMP_THREADS - 64);
+    const bool have = uni(s_gahead) > 0, ahead = have && !(NRBT != 0 && p.bwd && (int)cnt_after >= uni(nd.muf));
+    if (ahead && threadIdx.x >= 64) stage(g_pass(pb ^ 1), threadIdx.x - 64, AMP_THREADS - 64);
     if (threadIdx.x < 64) {
       fence_release();
       const int m = threadIdx.x;

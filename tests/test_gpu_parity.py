@@ -604,6 +604,21 @@ def test_ggnn_messages_taken_out_of_turn(muf, n):
     compare(g, rt, len(data), opt=opt)
 
 
+@pytest.mark.parametrize("hidden,tiles,mak", [(40, {1: 3, 2: 2, 3: 2, 4: 2, 5: 3}, 1), (40, {}, 2), (37, {1: 2, 3: 2, 5: 3}, 2),
+                                              (100, {1: 4, 3: 2, 4: 2, 5: 3}, 2), (100, {}, 1)])
+def test_ggnn_passes_waited_for(hidden, tiles, mak):
+    """One or two graphs in flight: the look for the next pass mostly finds nothing, and the pass waited for then is written while
+    waves may still be reading that."""
+    dims = dict(n_node_types=5, hidden=hidden, n_edge_types=2, n_steps=2)
+    data = synth.make_ggnn(60, 5, dims, min_nodes=2, max_nodes=9)[0]
+    fp = synth.init_params("ggnn", dims, 9)
+    opt = dict(kind="sgd", lr=0.005)
+    g = gpu_train("ggnn", dims, fp, data, mak, 3, opt, tiles=tiles)
+    check_controller_log(g["logs"], mak, len(data))
+    rt = oracle_replay("ggnn", dims, fp, data, g["logs"], 3, opt)
+    compare(g, rt, len(data), opt=opt)
+
+
 @pytest.mark.parametrize("hidden,tiles,muf,opt", [
     (104, {}, 1, MOM),                             # seven row blocks: lists of 2 to 29 nodes' rows
     (97, {}, 5, G_ADAM),                           # the same shape by single elements
