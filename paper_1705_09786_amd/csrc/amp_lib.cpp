@@ -322,6 +322,8 @@ size_t lds_floats(const amp_ctx* c, HostWorker& w) {
     case ROLE_TREE_OUT: {
       // the register-resident gradient accumulator holds 12 elements per thread
       if (R * C > 12 * AMP_THREADS) return 0;
+      // the sizes taken are those that leave room for sixteen messages' h and 64 logits each
+      if (wfl + 16 * r4(c->dims.hidden) + 16 * 64 + r4(c->max_mak) > avail) return 0;
       for (w.kb = 64; w.kb >= 4; w.kb -= 4) {
         f = wfl + (size_t)w.kb * amp_ldrow(amp_round4(c->dims.hidden)) + 2 * (size_t)w.kb * amp_ldrow((int)Rp) + r4(c->max_mak);
         if (f <= avail) break;

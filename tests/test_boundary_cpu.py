@@ -85,6 +85,20 @@ def test_tree_needs_tiles_that_fit_lds():
     expect(B.AMP_EUNSUPPORTED, a.finalize, 4, 60, 0, 100)
 
 
+@pytest.mark.parametrize("hidden,n_class,mak,fits", [(1192, 5, 4, True), (1196, 5, 4, False), (1228, 5, 4, False), (1536, 4, 4, False),
+                                                     (1128, 1, 2047, True), (1132, 1, 2047, False), (96, 64, 4, True)])
+def test_tree_output_layer_limit(hidden, n_class, mak, fits):
+    """The output layer keeps its weights and at least sixteen messages in LDS; larger ones are refused."""
+    a = new_ctx(1 << 40)
+    a.build("tree", dict(vocab=50, emb=64, hidden=hidden, n_class=n_class))
+    a.set_tiles(1, 32)
+    a.set_tiles(2, 60)
+    if fits:
+        a.finalize(mak, 8, 0, 10)
+    else:
+        expect(B.AMP_EUNSUPPORTED, a.finalize, mak, 8, 0, 10)
+
+
 def test_malformed_trees_and_graphs():
     a = new_ctx()
     a.build("tree", dict(vocab=10, emb=4, hidden=3, n_class=3))
