@@ -181,6 +181,24 @@ __device__ __forceinline__ GQ T* uni_gq(const void* p) {
   return (GQ T*)(unsigned long long)uni((long long)(unsigned long long)p);
 }
 
+// A value moved between lanes of a row of 16 without an LDS round trip.
+template <int CTRL>
+__device__ __forceinline__ int dpp(int v) {
+  return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, true);
+}
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v) {
+  return __int_as_float(dpp<CTRL>(__float_as_int(v)));
+}
+#define DPP_XOR1 0xB1          // quad_perm 1,0,3,2
+#define DPP_XOR2 0x4E          // quad_perm 2,3,0,1
+#define DPP_HALF_MIRROR 0x141  // lane i of 8 <-> 7 - i
+#define DPP_MIRROR 0x140       // lane i of 16 <-> 15 - i
+#define DPP_ROR8 0x128         // lane i of 16 <-> i ^ 8
+#define DPP_ROR4 0x124
+#define DPP_ROR2 0x122
+#define DPP_ROR1 0x121
+
 __device__ __forceinline__ Ring ring_regs(const GQ AmpDev* D, int idx) {
   Ring r;
   r.ent = uni_gq<unsigned long long>(D->ring[idx].ent);

@@ -104,18 +104,6 @@ __device__ __forceinline__ bool mlp_wait(const GQ AmpDev* D, MlpRings& q, unsign
 #define MLP_MAX 128   // rows and columns
 #define MLP_GS (MLP_MAX + 4)   // row stride of the 32 rows an optimizer with slots works on at a time
 
-template <int CTRL>
-__device__ __forceinline__ float dpp(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
-}
-#define DPP_XOR1 0xB1          // quad_perm 1,0,3,2
-#define DPP_XOR2 0x4E          // quad_perm 2,3,0,1
-#define DPP_HALF_MIRROR 0x141  // lane i of 8 <-> 7 - i
-#define DPP_ROR8 0x128         // lane i of 16 <-> i ^ 8
-#define DPP_ROR4 0x124
-#define DPP_ROR2 0x122
-#define DPP_ROR1 0x121
-
 // a of the lower and b of the upper half of the wave, each summed over the two halves.
 __device__ __forceinline__ float swap_add32(float a, float b) {
   auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);

@@ -103,8 +103,7 @@ __device__ __forceinline__ v4i tree_node(const GQ int* tnode, int noff, int n) {
 
 // One wave, all 64 lanes (k = lane), after lanes k < n have written M.aux[k]: positions
 // of the batch's forward and backward messages, and the event record (tile 0 only).
-__device__ __forceinline__ void batch_split_and_log(const GQ AmpDev* D, const WorkerRegs& W, BatchMsg& M, int n, int node,
-                                                    bool both_kinds) {
+__device__ __forceinline__ void batch_split_and_log(const GQ AmpDev* D, const WorkerRegs& W, BatchMsg& M, int n, int node) {
   const int k = threadIdx.x & 63;
   const bool in = k < n, isb = in && M.aux[k] != 0;
   const unsigned long long mb = __ballot(isb), mf = __ballot(in && !isb);
@@ -116,34 +115,16 @@ __device__ __forceinline__ void batch_split_and_log(const GQ AmpDev* D, const Wo
     M.nB = __popcll(mb);
   }
   if (W.log_cap && W.tile == 0) {
-    // both_kinds: every message is a forward event followed by a backward event (output layer in training)
-    const unsigned per = both_kinds ? 2u : 1u, base = s_logn;
-    if (base + per * (unsigned)n > W.log_cap) {
+    const unsigned base = s_logn;
+    if (base + (unsigned)n > W.log_cap) {
       if (k == 0) raise_abort(D, ABORT_LOG_FULL, blockIdx.x);
     } else {
       if (in) {
         const unsigned long long tail = ((unsigned long long)M.seq[k] << 32) | ((unsigned)node << 20) | ((unsigned)M.n[k] & 0xfffffu);
-        if (both_kinds) {
-          W.log[base + 2 * k] = tail;
-          W.log[base + 2 * k + 1] = tail | (1ull << 28);
-        } else {
-          W.log[base + k] = tail | ((unsigned long long)(isb ? 1 : 0) << 28);
-        }
+        W.log[base + k] = tail | ((unsigned long long)(isb ? 1 : 0) << 28);
       }
-      if (k == 0) s_logn = base + per * (unsigned)n;
+      if (k == 0) s_logn = base + (unsigned)n;
     }
-  }
-}
-
-// One gradient part for node n has been written by the output layer: Bcast's backward waits for its part and (unless n is
-// the root) every parent tile's.
-__device__ __forceinline__ void tree_grad_part_done(const WorkerRegs& W, const TreeBufs& B, int s, int n, bool is_root, bool is_leaf) {
-  const int expect = is_root ? 1 : 1 + B.TB;
-  if (join_arrive(B.cnt + B.node(s, n) * 4 + 2, expect)) {
-    if (is_leaf)
-      ring_post(W.leaf, MSG_MAKE(1, s, n));
-    else
-      ring_post(W.branch, MSG_MAKE(1, s, n));
   }
 }
 
@@ -268,7 +249,7 @@ __device__ __noinline__ void role_tree_lookup(const GQ AmpDev* D, const GQ Worke
         }
         M.par[k] = entry;
       }
-      batch_split_and_log(D, wr, M, n, 0, false);
+      batch_split_and_log(D, wr, M, n, 0);
       // backward message k is the b-th gradient of the batch: remember its token
       const bool isb = k < n && M.aux[k] != 0;
       const unsigned long long mb = __ballot(isb);

@@ -30,26 +30,13 @@ __device__ __forceinline__ void tree_out_publish(const WorkerRegs& W, const Tree
   if (fin) ring_put(W.ctl, tc + __popcll(mc & lt), MSG_MAKE(1, s, 0));
 }
 
-// Sums and maxima over groups of GS consecutive lanes (8 .. 64), left in every lane of the group; within 16 lanes by moves
-// between lanes of a row, which cost no LDS round trip.
-template <int CTRL>
-__device__ __forceinline__ float lane_move(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
-}
-template <int CTRL>
-__device__ __forceinline__ int lane_move(int v) {
-  return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, true);
-}
-#define LANE_XOR1 0xb1          // quad_perm 1 0 3 2
-#define LANE_XOR2 0x4e          // quad_perm 2 3 0 1
-#define LANE_HALF_MIRROR 0x141  // lane 7 - l of every 8
-#define LANE_MIRROR 0x140       // lane 15 - l of every 16
+// Sums and maxima over groups of GS consecutive lanes (8 .. 64), left in every lane of the group.
 template <int GS>
 __device__ __forceinline__ float group_sum(float v) {
-  v += lane_move<LANE_XOR1>(v);
-  v += lane_move<LANE_XOR2>(v);
-  v += lane_move<LANE_HALF_MIRROR>(v);
-  if (GS > 8) v += lane_move<LANE_MIRROR>(v);
+  v += dpp<DPP_XOR1>(v);
+  v += dpp<DPP_XOR2>(v);
+  v += dpp<DPP_HALF_MIRROR>(v);
+  if (GS > 8) v += dpp<DPP_MIRROR>(v);
   if (GS > 16) v += __shfl_xor(v, 16);
   if (GS > 32) v += __shfl_xor(v, 32);
   return v;
@@ -62,10 +49,10 @@ __device__ __forceinline__ void take_larger(float& m, int& am, float om, int oa)
 }
 template <int GS>
 __device__ __forceinline__ void group_argmax(float& m, int& am) {   // the first of equal ones
-  take_larger(m, am, lane_move<LANE_XOR1>(m), lane_move<LANE_XOR1>(am));
-  take_larger(m, am, lane_move<LANE_XOR2>(m), lane_move<LANE_XOR2>(am));
-  take_larger(m, am, lane_move<LANE_HALF_MIRROR>(m), lane_move<LANE_HALF_MIRROR>(am));
-  if (GS > 8) take_larger(m, am, lane_move<LANE_MIRROR>(m), lane_move<LANE_MIRROR>(am));
+  take_larger(m, am, dpp<DPP_XOR1>(m), dpp<DPP_XOR1>(am));
+  take_larger(m, am, dpp<DPP_XOR2>(m), dpp<DPP_XOR2>(am));
+  take_larger(m, am, dpp<DPP_HALF_MIRROR>(m), dpp<DPP_HALF_MIRROR>(am));
+  if (GS > 8) take_larger(m, am, dpp<DPP_MIRROR>(m), dpp<DPP_MIRROR>(am));
   if (GS > 16) take_larger(m, am, __shfl_xor(m, 16), __shfl_xor(am, 16));
   if (GS > 32) take_larger(m, am, __shfl_xor(m, 32), __shfl_xor(am, 32));
 }
