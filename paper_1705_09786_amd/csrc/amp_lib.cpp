@@ -292,9 +292,16 @@ size_t lds_floats(const amp_ctx* c, HostWorker& w) {
       // the update's register accumulator holds 8 waves x 4 (16-row, 64-column) units
       if ((Rp / 16) * ((amp_round16(n.cl()) + 63) / 64) > 32) return 0;
       if (w.role != ROLE_RNN_CELL) {
-        // a batch's inputs and deltas beside the weights, if there is room for 32 messages.  (96 x 304 weights leave 22
-        // rows: 16 replicas of the hidden-150 tree on 5 + 8 tiles then take 13.4 ms an epoch of 4,272 trees, and 11.4 ms
-        // with batches of up to 64 whose inputs come from HBM.)
+        // A batch's inputs and deltas beside the weights, if there is room for 32 messages; with less, batches of up to 64
+        // whose inputs come from HBM are faster.  An epoch of 2,136 trees (replicas: 4,272), 64 in flight, the older worker / this
+        // one, by the rows there is room for:
+        //   20 (128 x 244 weights, hidden 120)     83.4 / 97.0 ms
+        //   22 (96 x 308, hidden 150)              68.5 / 92.4 ms, 16 replicas 10.1 / 12.7
+        //   26 (128 x 228, hidden 112)             77.3 / 81.1 ms, 23 replicas 10.3 / 11.0
+        //   33 (128 x 212, hidden 100)             74.4 / 73.0 ms, 24 replicas 7.25 / 6.86
+        //   36 (80 x 308, hidden 150)              77.6 / 67.5 ms, 13 replicas 18.6 / 16.3
+        //   38 (112 x 228, hidden 108)             71.3 / 62.9 ms, 23 replicas 10.6 / 9.4
+        //   51 (64 x 308, hidden 150)              62.8 / 51.0 ms
         const size_t maps = 2 * r4(Rp) + (size_t)(amp_round16(n.cl()) + 63) / 64 * 64, row = ldw + ldy;
         const size_t rows = wfl + maps < avail ? std::min<size_t>(64, (avail - wfl - maps) / row) : 0;
         if (rows >= 32) {
