@@ -356,7 +356,7 @@ def test_tree_cell_sizes_replay_parity(hidden, emb, n_class, tl, tb, mak, muf, l
     check_controller_log(g["logs"], mak, len(data))
     rt = oracle_replay("tree", dims, fp, data, g["logs"], muf, opt, lookup_muf=lmuf)
     compare(g, rt, len(data), opt=opt)
-    # gradients, slots and update counts carried into a second call, and an evaluation in between
+    # an evaluation with gradients left over from the training call
     a, valid = g["trainer"].amp, synth.make_tree(12, 34, dims, max_leaves=12)
     for inst in valid:
         a.submit(inst, which=1)
@@ -365,19 +365,28 @@ def test_tree_cell_sizes_replay_parity(hidden, emb, n_class, tl, tb, mak, muf, l
     assert abs(ev["mean_loss"] - ref) <= 1e-5 * max(1.0, abs(ref)) and abs(ev["accuracy"] - acc) < 1e-9
 
 
-@pytest.mark.parametrize("opt", [SGD, TREE_MOM, dict(ADAM, lr=0.0002)])
-def test_tree_gradients_carried_between_calls(opt):
-    """Two calls of one epoch: what the cells and the output layer have accumulated since their last update, the optimizers'
-    slots and the numbers of updates rest in the arena between them.  The checker replays both as one run."""
-    dims = dict(vocab=97, emb=50, hidden=37, n_class=5)
+# cells with one to four gradient units a wave (slots in registers up to two, in memory beyond), output layers of one, two
+# and five column groups a thread
+@pytest.mark.parametrize("hidden,emb,n_class,tl,tb,opt", [
+    (37, 50, 5, 3, 5, SGD), (37, 50, 5, 3, 5, TREE_MOM), (37, 50, 5, 3, 5, dict(ADAM, lr=0.0002)),
+    (150, 300, 5, 10, 17, TREE_MOM), (150, 300, 12, 8, 16, dict(ADAM, lr=0.0002)), (150, 60, 40, 10, 10, TREE_MOM),
+    (150, 60, 40, 10, 10, SGD)])
+def test_tree_gradients_carried_between_calls(hidden, emb, n_class, tl, tb, opt):
+    """Two calls of one epoch with an evaluation in between: what the cells and the output layer have accumulated since their
+    last update, the optimizers' slots and the numbers of updates rest in the arena between them.  The checker replays both
+    as one run."""
+    dims = dict(vocab=97, emb=emb, hidden=hidden, n_class=n_class)
     data = synth.make_tree(24, 35, dims)
     fp = synth.init_params("tree", dims, 8)
     leaves = sum(i["n_leaves"] for i in data)
     muf = next(m for m in (7, 9, 11, 13) if leaves % m and (leaves - len(data)) % m and (2 * leaves - len(data)) % m)
-    g = gpu_train("tree", dims, fp, data, 8, muf, opt, tiles={1: 3, 2: 5}, lookup_muf=11)
+    g = gpu_train("tree", dims, fp, data, 8, muf, opt, tiles={1: tl, 2: tb}, lookup_muf=11)
     rt = oracle_replay("tree", dims, fp, data, g["logs"], muf, opt, lookup_muf=11)
     compare(g, rt, len(data), opt=opt)
     a = g["trainer"].amp
+    for inst in synth.make_tree(6, 36, dims, max_leaves=12):
+        a.submit(inst, which=1)
+    a.eval()
     a.train(1)
     rt.replay(data, named_logs("tree", dims, a.get_event_log()[1:]), first_seq=len(data))
     g2 = dict(g, params=g["trainer"].params(), losses=a.get_instance_losses().astype(np.float64))
