@@ -615,7 +615,8 @@ __device__ __forceinline__ void note_update(const GQ AmpDev* D) {
 // release fence precedes the post; the hand-overs inside one die get their agent-scope
 // fences back too (fence_release, ring_put_near).  The two builds must give the same
 // results; a parity test runs both.
-// In two halves, so that a lane with several arrivals has them on their way together.
+// In two halves, so that a lane with several arrivals has them on their way together (behind in_flight): the arrival, and what
+// the completing one does before it posts.
 __device__ __forceinline__ int join_add(GQ int* counter) {
 #ifdef AMP_STRICT_JOIN
   return __hip_atomic_fetch_add(counter, 1, __ATOMIC_ACQ_REL, AGENT);
@@ -623,13 +624,20 @@ __device__ __forceinline__ int join_add(GQ int* counter) {
   return __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, AGENT);
 #endif
 }
-__device__ __forceinline__ bool join_done(GQ int* counter, int old, int expect) {
-  if (old + 1 != expect) return false;
-  __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, AGENT);
+__device__ __forceinline__ void join_reset(GQ int* counter) { __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, AGENT); }
+__device__ __forceinline__ bool join_arrive(GQ int* counter, int expect) {
+  if (join_add(counter) + 1 != expect) return false;
+  join_reset(counter);
   strict_release();
   return true;
 }
-__device__ __forceinline__ bool join_arrive(GQ int* counter, int expect) { return join_done(counter, join_add(counter), expect); }
+
+// The results of two conditional fetches, used from here on: without this the compiler moves the first use of either into its
+// condition's branch, and waits there for the one before the other is issued.
+template <class A, class B>
+__device__ __forceinline__ void in_flight(A& a, B& b) {
+  asm volatile("" : "+v"(a), "+v"(b));
+}
 
 __device__ __forceinline__ bool join_arrive(int* counter, int expect) { return join_arrive((GQ int*)counter, expect); }
 

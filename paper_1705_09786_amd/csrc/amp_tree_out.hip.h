@@ -18,12 +18,15 @@ __device__ __forceinline__ void tree_out_publish(const WorkerRegs& W, const Tree
   GQ int* c = B.cnt + B.node(s, n) * 4 + 2;
   int old = 0;
   if (grad) old = join_add(c);
-  const bool done = grad && join_done(c, old, root ? 1 : 1 + B.TB), lf = done && is_leaf, br = done && !is_leaf;
+  const bool done = grad && old + 1 == (root ? 1 : 1 + B.TB), lf = done && is_leaf, br = done && !is_leaf;
   const unsigned long long ml = __ballot(lf), mb = __ballot(br), mc = __ballot(fin);
   const unsigned want = lane == 0 ? __popcll(ml) : lane == 1 ? __popcll(mb) : lane == 2 ? __popcll(mc) : 0u;
-  GQ unsigned* tail = lane == 0 ? W.leaf.tail : lane == 1 ? W.branch.tail : W.ctl.tail;
+  GQ unsigned *const tail_leaf = W.leaf.tail, *const tail_branch = W.branch.tail, *const tail_ctl = W.ctl.tail;
+  GQ unsigned* tail = lane == 0 ? tail_leaf : lane == 1 ? tail_branch : tail_ctl;
   unsigned t = 0;
   if (want) t = __hip_atomic_fetch_add(tail, want, __ATOMIC_RELAXED, AGENT);
+  if (done) join_reset(c);
+  strict_release();
   const unsigned tl = __shfl(t, 0), tb = __shfl(t, 1), tc = __shfl(t, 2);
   if (lf) ring_put(W.leaf, tl + __popcll(ml & lt), MSG_MAKE(1, s, n));
   if (br) ring_put(W.branch, tb + __popcll(mb & lt), MSG_MAKE(1, s, n));
