@@ -45,4 +45,4 @@ static __device__ __forceinline__ void ggnn_worker(const GQ AmpDev* D, const GQ 
   }
 }
 
-AMP_PERSISTENT_KERNEL(ggnn, ggnn_worker(D, W);)
+AMP_PERSISTENT_KERNEL(ggnn, false, ggnn_worker(D, W);)

@@ -4,5 +4,6 @@
 #include <hip/hip_runtime.h>
 #include "amp_worker.hip.h"
 #include "amp_mlp.hip.h"
+#include "amp_mlp_one.hip.h"
 
-AMP_PERSISTENT_KERNEL(mlp, role_mlp_lin(D, W);)
+AMP_PERSISTENT_KERNEL(mlp, mlp_one_fits(D), if (W->role == ROLE_CTRL) role_mlp_whole(D, W); else role_mlp_lin(D, W);)

@@ -1,5 +1,6 @@
 // Workers of the MLP: one per linear layer `aux` (0..2) with its ReLU fused; the last layer also hosts the softmax
-// loss, which turns the forward message round.
+// loss, which turns the forward message round.  For the models that one compute unit does not hold (amp_mlp_one.hip.h): inputs
+// wider than 128, optimizers with slots, gradients to keep for more than 64 x 64.
 //
 // Slot storage, rows of hidden rounded up to 4 floats: buf[0] = act1, buf[1] = act2 (post-ReLU outputs), buf[2] =
 // gradient w.r.t. act1, buf[3] = gradient w.r.t. act2.

@@ -29,4 +29,4 @@ static __device__ __forceinline__ void rnn_worker(const GQ AmpDev* D, const GQ W
   }
 }
 
-AMP_PERSISTENT_KERNEL(rnn, rnn_worker(D, W);)
+AMP_PERSISTENT_KERNEL(rnn, false, rnn_worker(D, W);)

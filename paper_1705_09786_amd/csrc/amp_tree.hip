@@ -49,4 +49,4 @@ static __device__ __forceinline__ void tree_worker(const GQ AmpDev* D, const GQ 
   }
 }
 
-AMP_PERSISTENT_KERNEL(tree, tree_worker(D, W);)
+AMP_PERSISTENT_KERNEL(tree, false, tree_worker(D, W);)

@@ -175,10 +175,11 @@ __device__ __forceinline__ void count_and_update(const GQ AmpDev* D, const GQ Wo
 }
 
 // ============================================================ the kernel's frame
-// `work(D, W)` runs the role of worker W until the launch is over.
-template <class Work>
+// `work(D, W)` runs the role of worker W until the launch is over.  `whole(D)`: worker 0's workgroup does the work of the whole
+// replica, by work(D, worker 0), and keeps the other workers' records; theirs leave at once.
+template <class Whole, class Work>
 __device__ __forceinline__ void persistent_worker(const AmpDev* Dp, int workers_per_replica, int n_replicas, int xcd_packed,
-                                                  const AmpLaunch& args, Work work) {
+                                                  const AmpLaunch& args, Whole whole, Work work) {
   // Every replica has its own descriptor.  Plain mapping: replica r = blocks [r * workers_per_replica, (r + 1) *
   // workers_per_replica).  Packed mapping: workgroups are dealt to the 8 XCDs round-robin by their index, so block
   // b lands on XCD b % 8; all workers of a replica take blocks of one residue, replicas x, x + 8, ... share XCD x,
@@ -224,7 +225,12 @@ __device__ __forceinline__ void persistent_worker(const AmpDev* Dp, int workers_
     }
     return;
   }
-  if (W->role == ROLE_CTRL)
+  const bool alone = whole(D);
+  if (alone && wi != 0) {
+    if (threadIdx.x == 0) W->stats[12] = (unsigned long long)(__builtin_amdgcn_s_getreg((3 << 11) | 20) & 0xf);
+    return;
+  }
+  if (W->role == ROLE_CTRL && !alone)
     role_ctrl(D, W);
   else
     work(D, W);
@@ -263,12 +269,12 @@ static inline hipError_t launch_persistent(const void* kernel, bool& attr_set, c
   return hipLaunchKernel(kernel, dim3(grid), dim3(AMP_THREADS), params, AMP_DYN_LDS_BYTES, stream);
 }
 
-// Defines model `name`'s kernel amp_persistent_<name> and its launcher amp_launch_<name>; the macro's last argument is
-// the statement that runs the role of worker (D, W).
-#define AMP_PERSISTENT_KERNEL(name, ...)                                                                                    \
+// Defines model `name`'s kernel amp_persistent_<name> and its launcher amp_launch_<name>; `whole` says whether worker 0 of a
+// replica (D) does all of its work, and the macro's last argument is the statement that runs the role of worker (D, W).
+#define AMP_PERSISTENT_KERNEL(name, whole, ...)                                                                                    \
   extern "C" __global__ void __launch_bounds__(AMP_THREADS) amp_persistent_##name(                                          \
       const AmpDev* Dp, int workers_per_replica, int n_replicas, int xcd_packed, AmpLaunch args) {                          \
-    persistent_worker(Dp, workers_per_replica, n_replicas, xcd_packed, args,                                                \
+    persistent_worker(Dp, workers_per_replica, n_replicas, xcd_packed, args, [](const GQ AmpDev* D) { return whole; },      \
                       [](const GQ AmpDev* D, const GQ WorkerDev* W) { __VA_ARGS__ });                                       \
   }                                                                                                                         \
   extern "C" hipError_t amp_launch_##name(const AmpDev* devs, int n_replicas, int workers_per_replica, const AmpLaunch* a,  \

@@ -9,7 +9,7 @@ from paper_1705_09786_amd import runner, synth
 
 from oracle import amp as oamp
 
-from util import (check_controller_log, compare, compare_up_to_relu_decisions, elem_tol, elementwise_err, gpu_train,
+from util import (RELU_TAU, check_controller_log, compare, compare_up_to_relu_decisions, elem_tol, elementwise_err, gpu_train,
                   named_logs, oracle_replay, oracle_runtime, rel_err)
 
 pytestmark = pytest.mark.gpu
@@ -84,6 +84,59 @@ def test_mlp_sizes_replay_parity(d_in, hidden, n_class, mak, muf, opt):
     for ev in evs:
         assert ev["n_instances"] == len(valid)
         assert abs(ev["mean_loss"] - ref) <= 1e-5 * max(1.0, abs(ref)) and abs(ev["accuracy"] - acc) < 1e-9
+
+
+@pytest.mark.parametrize("d_in,hidden,n_class,mak,mufs,n", [
+    (64, 128, 10, 4, (1, 1, 1), 30), (128, 128, 64, 3, (1, 1, 1), 29), (65, 65, 17, 4, (1, 1, 1), 27), (128, 64, 16, 8, (1, 1, 1), 30),
+    (16, 16, 1, 2, (1, 1, 1), 31), (64, 128, 10, 4, (7, 7, 7), 31), (33, 65, 33, 8, (5, 3, 2), 33), (128, 64, 64, 4, (1, 4, 6), 29),
+    (7, 3, 5, 5, (2, 1, 9), 30), (65, 65, 10, 4, (3, 3, 3), 31)])
+def test_mlp_on_one_workgroup_carries_gradients_and_thresholds(d_in, hidden, n_class, mak, mufs, n):
+    """The sizes at which the one-workgroup MLP changes its split (64 inputs, hidden units and classes, either side), groups of
+    four cut by thresholds that differ from layer to layer, and gradients that wait from one call for the next (the last
+    case, with gradients to keep at more than 64 x 64, is the layers' own workers').  Tolerance: that of every replay."""
+    dims = dict(d_in=d_in, hidden=hidden, n_class=n_class)
+    data = synth.make_mlp(n, 41, dims)
+    fp = synth.init_params("mlp", dims, 12)
+    tr = runner.Trainer("mlp", dims, fp, mak, 1, 0, n, arena_bytes=1 << 28)
+    a = tr.amp
+    a.set_optimizer(-1, 0, lr=0.02)
+    for node, muf in enumerate(mufs):
+        a.set_min_update_frequency(node, muf)
+    a.set_event_log(16 * n + 64)
+    tr.submit_all(data)
+    flips = []
+    for _ in range(8):   # a ReLU decision within rounding of zero may fall either way (compare_up_to_relu_decisions)
+        rt = oracle_runtime("mlp", dims, fp, 1, dict(kind="sgd", lr=0.02))
+        for node in rt.nodes:
+            if isinstance(node, oamp.NPT) and node.name.startswith("relu"):
+                node.kink_tau, node.flip = RELU_TAU, {(st, i) for (name, st, i) in flips if name == node.name}
+        for node, muf in zip(rt.ppt, mufs):
+            node.muf = muf
+        if not flips:
+            calls = []
+            for call in range(3):
+                a.train(1)
+                logs = a.get_event_log()
+                check = [(k, s - call * n) for (_, k, s, _) in logs[0] if k == "A"]
+                assert check == [("A", i) for i in range(n)]
+                calls.append((logs, a.get_instance_losses().astype(np.float64), tr.params()))
+        bad = None
+        for call, (logs, losses, params) in enumerate(calls):
+            rt.replay(data, named_logs("mlp", dims, logs[1:]), first_seq=call * n)
+            ref = np.array([rt.loss[call * n + s] for s in range(n)])
+            errs = [float(np.abs(losses - ref).max() / max(1.0, np.abs(ref).max()))]
+            errs += [rel_err(p, oamp.C.pack_node(node.P)) for p, node in zip(params, rt.ppt)]
+            if max(errs) > 1e-5:
+                bad = (call, errs)
+                break
+        if bad is None:
+            return
+        kinks = [(node.name, st, i) for node in rt.nodes if isinstance(node, oamp.NPT) for (st, i) in node.kinks]
+        kinks = [k for k in kinks if k not in flips]
+        if not kinks:
+            break
+        flips.append(kinks[0])
+    raise AssertionError((bad, flips))
 
 
 def test_mlp_logits_without_a_largest():
