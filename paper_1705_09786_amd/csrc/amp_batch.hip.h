@@ -23,7 +23,7 @@
 __device__ __forceinline__ int round8(int v) { return (v + 7) & ~7; }
 
 // Per-message scratch of the running batch, one per workgroup.
-struct BatchMsg {
+struct alignas(16) BatchMsg {
   int s[KB_MAX], n[KB_MAX], a[KB_MAX], b[KB_MAX], par[KB_MAX], L[KB_MAX], aux[KB_MAX];
   unsigned seq[KB_MAX];
   int fidx[KB_MAX], bidx[KB_MAX];

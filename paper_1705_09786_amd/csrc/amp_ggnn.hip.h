@@ -485,7 +485,7 @@ __device__ __forceinline__ void g_rows_to_lds(const GQ float* base, long long of
       if (g + lane < groups) global_to_lds(from + 4 * g, dst + 4 * g);
   }
 }
-__device__ __forceinline__ void g_rows_landed() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+__device__ __forceinline__ void g_rows_landed() { wait_vm(); }
 // Items 0 .. total - 1 of a wave (total the same in every lane), U of a lane fetched (ld) before any is used (st); every lane of
 // the wave is in ld, so that it may read other lanes.
 template <int U, class It, class Ld, class St>
@@ -572,7 +572,7 @@ __device__ __forceinline__ v4f g_sum_incoming4(const GQ float* msg, const GView&
 }
 
 __device__ __forceinline__ v4f sigmoid4(v4f y) { return (v4f){sigmoidf_(y.x), sigmoidf_(y.y), sigmoidf_(y.z), sigmoidf_(y.w)}; }
-__device__ __forceinline__ v4f tanh4(v4f y) { return (v4f){tanhf(y.x), tanhf(y.y), tanhf(y.z), tanhf(y.w)}; }
+__device__ __forceinline__ v4f tanh4(v4f y) { return (v4f){tanh_(y.x), tanh_(y.y), tanh_(y.z), tanh_(y.w)}; }
 
 // Four consecutive elements of the same sum.
 __device__ __forceinline__ v4f g_state_gradient4(const GBufs& B, const GParts& ep, int s, int i, int step) {
@@ -916,7 +916,7 @@ __device__ __noinline__ void g_update_lds(LDSQ float* Wl, LDSQ float* bl, const 
     }
     b = b + 1 == NBUF ? 0 : b + 1;
   }
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  wait_vm();
   lds_barrier();
   const OptCoef o = held_opt(tstep);
   const float inv = uni(s_opt.mean) ? 1.f / (float)n_grad : 1.f;
@@ -1792,7 +1792,7 @@ __device__ __noinline__ void role_g_cand(const GQ AmpDev* D, const GQ WorkerDev*
         GQ float* hn = B.Hm + B.hm(s, it + 1);
         for (int i = wtid; i < p.Kt * nu; i += wn) {
           const int k = i / nu, j = i - k * nu, o = k * H + u0 + j;
-          const float ht = tanhf(Y[k * Hs + j]), z = Z[o];
+          const float ht = tanh_(Y[k * Hs + j]), z = Z[o];
           Ht[o] = ht;
           hn[o] = (1.f - z) * h[o] + z * ht;
         }

@@ -223,7 +223,7 @@ __device__ __noinline__ void role_rnn_cell(const GQ AmpDev* D, const GQ WorkerDe
       PHASE(1);
       for (int i = threadIdx.x; i < nF * H; i += AMP_THREADS) {
         const int k = i / H, r = i - k * H, m = M.fidx[k];
-        B.hs[B.hrow(M.s[m], M.n[m] + 1) + r] = tanhf(Y[k * ldy + r]);
+        B.hs[B.hrow(M.s[m], M.n[m] + 1) + r] = tanh_(Y[k * ldy + r]);
       }
       lds_barrier();
       PHASE(2);

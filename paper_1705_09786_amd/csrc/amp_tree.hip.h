@@ -1231,7 +1231,7 @@ __device__ __forceinline__ void tree_activate(const TreeBufs& B, long long nn, c
   if (BR) {
     const float i_ = sigmoidf_(y[j]), fl = sigmoidf_(y[nu + j]), fr = sigmoidf_(y[2 * nu + j]);
     o_ = sigmoidf_(y[3 * nu + j]);
-    const float g_ = tanhf(y[4 * nu + j]);
+    const float g_ = tanh_(y[4 * nu + j]);
     c_ = i_ * g_ + fl * cl + fr * cr;
     gt[u] = i_;
     gt[H + u] = fl;
@@ -1241,13 +1241,13 @@ __device__ __forceinline__ void tree_activate(const TreeBufs& B, long long nn, c
   } else {
     const float i_ = sigmoidf_(y[j]);
     o_ = sigmoidf_(y[nu + j]);
-    const float g_ = tanhf(y[2 * nu + j]);
+    const float g_ = tanh_(y[2 * nu + j]);
     c_ = i_ * g_;
     gt[u] = i_;
     gt[3 * H + u] = o_;
     gt[4 * H + u] = g_;
   }
-  const float tc = tanhf(c_);
+  const float tc = tanh_(c_);
   gt[5 * H + u] = tc;
   hcn[u] = o_ * tc;
   hcn[Hp + u] = c_;

@@ -246,7 +246,7 @@ __device__ __noinline__ void role_tree_cell_lds(const GQ AmpDev* D, const GQ Wor
       const int k = p / (t.Rp - R);
       Y[(nF + k) * ldy + R + p - k * (t.Rp - R)] = 0.f;
     }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's rows are in LDS
+    wait_vm();   // this wave's rows are in LDS
     lds_barrier();
     PHASE(0);
     // ---------------- products

@@ -233,7 +233,7 @@ __device__ __noinline__ void role_tree_out(const GQ AmpDev* D, const GQ WorkerDe
         for (int k = 0; k < SG; k += 64)
           if (k + lane < SG) global_to_lds(from + 4 * k, hbuf + r * ldh + 4 * k);
       }
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      wait_vm();
     }
     lds_barrier();
     PHASE(0);

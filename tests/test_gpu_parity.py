@@ -180,6 +180,7 @@ def test_mlp_instances_beyond_a_message_s_index():
 RNN_ADAM = dict(ADAM)
 # an update every 3 gradients amplifies more: the same check asks for lr = 2e-4 there
 RNN_ADAM_MUF3 = dict(RNN_ADAM, lr=0.0002)
+RNN_MOM = dict(kind="momentum", lr=0.002, momentum=0.9)
 
 
 # With an update per gradient the cell's weights are rounded to fp32 after every one of about 18 updates per
@@ -296,7 +297,7 @@ def test_rnn_cell_at_the_edges_of_its_register_tiles(emb, hidden, mak, muf, opt)
 
 @pytest.mark.parametrize("emb,hidden,mak,muf,opt", [
     (32, 32, 40, 14, SGD), (32, 32, 39, 14, SGD), (32, 32, 40, 13, SGD), (64, 64, 64, 18, SGD), (64, 64, 55, 18, RNN_ADAM),
-    (70, 66, 60, 40, SGD)])
+    (70, 66, 60, 40, SGD), (32, 32, 45, 14, SGD), (32, 32, 44, 14, SGD), (56, 56, 62, 18, RNN_ADAM)])
 def test_rnn_cell_with_many_sequences_in_flight(emb, hidden, mak, muf, opt):
     """Either side of the lines between the two cell workers, and a model that crosses them: trained with `mak` in flight, then
     with 8, then with `mak` again, an evaluation with `mak` in front of each.  Pending pairs and sums are handed from worker
@@ -322,6 +323,25 @@ def test_rnn_cell_with_many_sequences_in_flight(emb, hidden, mak, muf, opt):
         rt.replay(data, named_logs("rnn", dims, a.get_event_log()[1:]), first_seq=first)
         g = dict(g, params=g["trainer"].params(), losses=a.get_instance_losses().astype(np.float64))
         compare(g, rt, len(data), opt=opt, ref_losses=[rt.loss[first + i] for i in range(len(data))])
+
+
+@pytest.mark.parametrize("emb,hidden,vocab,muf,opt", [
+    (50, 37, 13, 3, RNN_MOM), (64, 64, 20, 4, RNN_ADAM), (65, 64, 20, 4, RNN_MOM), (64, 65, 20, 4, RNN_MOM), (128, 64, 20, 5, RNN_ADAM),
+    (128, 128, 20, 5, RNN_MOM), (16, 16, 5, 1, RNN_ADAM_MUF3)])
+def test_rnn_cell_optimizer_slots_between_calls(emb, hidden, vocab, muf, opt):
+    """Slots in LDS for cells of two to four 64 x 64 pieces, in HBM beyond that: either way the second call goes on from what
+    the first one left, in more sequences in flight than the worker holds, with pairs carried over."""
+    dims = dict(vocab=vocab, emb=emb, hidden=hidden, n_class=7)
+    data = synth.make_rnn(62, 35, dims, min_len=1, max_len=11)
+    fp = synth.init_params("rnn", dims, 9)
+    g = gpu_train("rnn", dims, fp, data, 20, muf, opt)
+    rt = oracle_replay("rnn", dims, fp, data, g["logs"], muf, opt)
+    compare(g, rt, len(data), opt=opt)
+    a = g["trainer"].amp
+    a.train(1)
+    rt.replay(data, named_logs("rnn", dims, a.get_event_log()[1:]), first_seq=len(data))
+    g = dict(g, params=g["trainer"].params(), losses=a.get_instance_losses().astype(np.float64))
+    compare(g, rt, len(data), opt=opt, ref_losses=[rt.loss[len(data) + i] for i in range(len(data))])
 
 
 @pytest.mark.parametrize("mak,sync", [(80, 0), (80, 30), (78, 30)])
