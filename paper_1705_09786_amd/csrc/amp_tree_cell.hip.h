@@ -199,9 +199,12 @@ __device__ __noinline__ void role_tree_cell_lds(const GQ AmpDev* D, const GQ Wor
       if (slots && OPT == 2) bv[a] = ndV[p];
     }
   }
-  // Adam's powers b^t carried along in double precision: a power per update instead of a product of its squares
+  // Adam's powers b^t carried along in double precision: a power per update instead of a product of its squares.  The next
+  // update's factors are formed while a batch's inputs are on their way.
   double pw1 = OPT == 2 ? ipow((double)ob.b1, tstep) : 0.0, pw2 = OPT == 2 ? ipow((double)ob.b2, tstep) : 0.0;
 
+  float c1 = 1.f, c2 = 1.f;
+  bool formed = false;
   auto take_batch = [&](unsigned held) {
     if (lane == 0) s_item = 0;
     tree_take<BR>(D, wr, B, mine, head, nd_muf - (int)held, smeta, tnode);
@@ -236,6 +239,13 @@ __device__ __noinline__ void role_tree_cell_lds(const GQ AmpDev* D, const GQ Wor
       pcr = xbase[M.off1[r] + Hp + u];
     }
     asm volatile("" ::: "memory");   // all of these are on their way before anything below waits
+    if (OPT == 2 && !formed) {
+      pw1 *= (double)ob.b1;
+      pw2 *= (double)ob.b2;
+      c1 = uni((float)(1.0 / (1.0 - pw1)));
+      c2 = uni((float)(1.0 / (1.0 - pw2)));
+      formed = true;
+    }
     for (int p = threadIdx.x; p < nB * nu; p += AMP_THREADS) {
       const int k = by_nu(p), j = p - k * nu;
       TreeDelta<BR, 18> d;
@@ -250,11 +260,9 @@ __device__ __noinline__ void role_tree_cell_lds(const GQ AmpDev* D, const GQ Wor
     lds_barrier();
     PHASE(0);
     // ---------------- products
-    // One block of forward messages alone is as many items as the tile has row blocks -- three for four matrix pipes, and
-    // nothing else to do: its columns are then split over up to four items, whose sums meet in the rows of Y behind the batch's.
-    // (A validation pass of 1,101 trees of hidden size 150 was 0.8 % slower than with the weights' old worker, 12.26 against 12.16 ms,
-    // and is level with it so; an update every 3 gradients at hidden 37: 36.9 -> 35.9 ms.)
-    const int KS = nB == 0 && nF <= 16 && NRB <= 4 ? (KB < 4 * nF ? (KB < 2 * nF ? 1 : 2) : 4) : 1;
+    // (Splitting the columns of few forward messages over several items, whose sums then met in LDS, was taken out: evaluation at
+    // hidden 37 5.53 -> 5.08 ms per 400 trees without it, at 80 7.45 -> 7.06, at 150 8.08 -> 8.00; only one tree at a time at 150 gains
+    // from it, 9.85 -> 9.74 per 100.)
     {
       // gradient: G[r][c] += sum_k delta_k[r] x_k[c], k in ring order
       if (nB > 0 && unit_of(0) >= 0) {
@@ -288,7 +296,7 @@ __device__ __noinline__ void role_tree_cell_lds(const GQ AmpDev* D, const GQ Wor
           add(a1, x1);
         }
       }
-      const int NBF = (nF + 15) >> 4, nFI = NRB * NBF * KS, items = nFI + NCG * ((nB + 31) >> 5);
+      const int NBF = (nF + 15) >> 4, nFI = NRB * NBF, items = nFI + NCG * ((nB + 31) >> 5);
       auto next = [&]() {
         int it = 0;
         if (lane == 0) it = __hip_atomic_fetch_add((LDSQ int*)&s_item, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -303,13 +311,12 @@ __device__ __noinline__ void role_tree_cell_lds(const GQ AmpDev* D, const GQ Wor
         ahead = next();
         if (it < nFI) {
           // Y[j][r] = b[r] + sum_c W[r][c] x_j[c]
-          const int rest = by_nrb(it), rb = it - rest * NRB, nb = KS > 1 ? 0 : rest, ks = KS > 1 ? rest : 0, j = nb * 16 + i;
-          const int c0 = KS > 1 ? (NCG * ks) / KS : 0, c1 = KS > 1 ? (NCG * (ks + 1)) / KS : NCG;
-          const LDSQ float* wp = Wl + (rb * 16 + i) * ldw + 4 * q + 16 * c0;
-          const LDSQ float* xp = X + (j < nF ? j : nF - 1) * ldw + 4 * q + 16 * c0;
-          v4f acc[4] = {ks ? zero : *(const LDSQ v4f*)(bl + rb * 16 + 4 * q), zero, zero, zero};
-          cell_rows(wp, xp, c1 - c0, acc);
-          if (j < nF) *(LDSQ v4f*)(Y + (ks * nF + j) * ldy + rb * 16 + 4 * q) = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+          const int nb = by_nrb(it), rb = it - nb * NRB, j = nb * 16 + i;
+          const LDSQ float* wp = Wl + (rb * 16 + i) * ldw + 4 * q;
+          const LDSQ float* xp = X + (j < nF ? j : nF - 1) * ldw + 4 * q;
+          v4f acc[4] = {*(const LDSQ v4f*)(bl + rb * 16 + 4 * q), zero, zero, zero};
+          cell_rows(wp, xp, NCG, acc);
+          if (j < nF) *(LDSQ v4f*)(Y + j * ldy + rb * 16 + 4 * q) = (acc[0] + acc[1]) + (acc[2] + acc[3]);
         } else {
           // dx_j[c] = sum_r W[r][c] delta_j[r]: 16 columns for up to 32 messages, from the accumulators to HBM
           const int bi = it - nFI, pb = bi >= NCG ? 1 : 0, cb = bi - pb * NCG;
@@ -341,16 +348,6 @@ __device__ __noinline__ void role_tree_cell_lds(const GQ AmpDev* D, const GQ Wor
     // ---------------- outputs
     if (nF > 0) {
       lds_barrier();
-      if (KS > 1) {
-        for (int p = threadIdx.x; p < nF * 4 * NRB; p += AMP_THREADS) {
-          const int r = p / (4 * NRB);
-          LDSQ float* y = Y + r * ldy + 4 * (p - r * 4 * NRB);
-          v4f a = *(const LDSQ v4f*)y + *(const LDSQ v4f*)(y + nF * ldy);
-          if (KS == 4) a += *(const LDSQ v4f*)(y + 2 * nF * ldy) + *(const LDSQ v4f*)(y + 3 * nF * ldy);
-          *(LDSQ v4f*)y = a;
-        }
-        lds_barrier();
-      }
       for (int p = threadIdx.x; p < nF * nu; p += AMP_THREADS) {
         const int r = by_nu(p), j = p - r * nu, u = u0 + j;
         const bool first = p == (int)threadIdx.x;
@@ -405,10 +402,9 @@ __device__ __noinline__ void role_tree_cell_lds(const GQ AmpDev* D, const GQ Wor
       OptCoef o = ob;
       o.kind = OPT;
       if (OPT == 2) {
-        pw1 *= (double)ob.b1;
-        pw2 *= (double)ob.b2;
-        o.c1 = (float)(1.0 / (1.0 - pw1));
-        o.c2 = (float)(1.0 / (1.0 - pw2));
+        o.c1 = c1;
+        o.c2 = c2;
+        formed = false;
       }
       const float inv = uni(s_opt.mean) ? 1.f / (float)count : 1.f;
       if (unit_of(0) >= 0) {
@@ -435,20 +431,22 @@ __device__ __noinline__ void role_tree_cell_lds(const GQ AmpDev* D, const GQ Wor
               // rows and columns of the padding have no gradient
               w -= (o.lr * inv) * (v4f){g[u][0][e], g[u][1][e], g[u][2][e], g[u][3][e]};
             } else {
+              // (without a branch for each element: a padding one has no gradient and no slots either, and stays zero)
 #pragma unroll
-              for (int v = 0; v < 4; ++v)
-                if ((valid[u] >> (4 * v + e)) & 1u) {
-                  float m = KEEP ? sm[KEEP ? u : 0][v][e] : m4[v][e], s = KEEP && OPT == 2 ? sv[KEEP && OPT == 2 ? u : 0][v][e] : v4[v][e];
-                  w[v] = opt_step(o, w[v], g[u][v][e] * inv, m, s);
-                  if (KEEP) {
-                    sm[KEEP ? u : 0][v][e] = m;
-                    if (OPT == 2) sv[KEEP && OPT == 2 ? u : 0][v][e] = s;
-                  } else {
-                    const int p = at(u, v, e);
-                    ndM[p] = m;
-                    if (OPT == 2) ndV[p] = s;
-                  }
+              for (int v = 0; v < 4; ++v) {
+                const bool real = (valid[u] >> (4 * v + e)) & 1u;
+                float m = KEEP ? sm[KEEP ? u : 0][v][e] : real ? m4[v][e] : 0.f;
+                float s = KEEP ? (OPT == 2 ? sv[KEEP && OPT == 2 ? u : 0][v][e] : 0.f) : real ? v4[v][e] : 0.f;
+                w[v] = opt_step(o, w[v], g[u][v][e] * inv, m, s);
+                if (KEEP) {
+                  sm[KEEP ? u : 0][v][e] = m;
+                  if (OPT == 2) sv[KEEP && OPT == 2 ? u : 0][v][e] = s;
+                } else if (real) {
+                  const int p = at(u, v, e);
+                  ndM[p] = m;
+                  if (OPT == 2) ndV[p] = s;
                 }
+              }
             }
             *(LDSQ v4f*)(wp + e * ldw) = w;
           }

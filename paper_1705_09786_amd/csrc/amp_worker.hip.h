@@ -200,6 +200,7 @@ __device__ __forceinline__ void persistent_worker(const AmpDev* Dp, int workers_
   if (threadIdx.x == 0) {
     s_logn = 0;
     s_first_seq = args.first_seq[replica];
+    s_bounded = D->admit_bounded;
     s_log_cap = W->tile == 0 ? W->log_cap : 0u;
     s_log_ptr = W->log;
     if (W->node >= 0) hold_node_opt(D->node[W->node]);
