@@ -610,7 +610,7 @@ __device__ __forceinline__ void tree_slots_step(TreeSlots<US>& sl, int u0, int N
           const int at = sl.gi[u][v][e];
           if (at >= 0) {
             LDSQ float* w = Wl + (rb * 16 + 4 * q + e) * ldw + cm * 64 + 4 * i + v;
-            *w = opt_step(o, *w, g[(u0 + u) % GU][v][e] * inv, sl.m[u][v][e], sl.v[u][v][e]);
+            *w = opt_step<true>(o, *w, g[(u0 + u) % GU][v][e] * inv, sl.m[u][v][e], sl.v[u][v][e]);
             Mq[at] = sl.m[u][v][e];
             if (o.kind == 2) Vq[at] = sl.v[u][v][e];
           }
@@ -753,7 +753,7 @@ __device__ __forceinline__ void tree_update_units(LDSQ float* Wl, LDSQ float* bl
     }
   }
   if (bias) {
-    bl[threadIdx.x] = opt_step(o, bl[threadIdx.x], gb * inv, bm, bv);
+    bl[threadIdx.x] = opt_step<true>(o, bl[threadIdx.x], gb * inv, bm, bv);
     if (kind != 0) Mq[bat] = bm;
     if (kind == 2) Vq[bat] = bv;
   }
@@ -1078,7 +1078,7 @@ __device__ __noinline__ void tree_update_stream(GQ float* P, LDSQ float* bl, con
             GQ v4f* wp = (GQ v4f*)(P + gi);
             v4f wv = *wp;
 #pragma unroll
-            for (int v = 0; v < 4; ++v) wv[v] = opt_apply(o, wv[v], g[u][v][e] * inv, nd.M, nd.V, gi + v);
+            for (int v = 0; v < 4; ++v) wv[v] = opt_apply<true>(o, wv[v], g[u][v][e] * inv, (GQ float*)nd.M, (GQ float*)nd.V, gi + v);
             *wp = wv;
           }
         }
@@ -1087,7 +1087,7 @@ __device__ __noinline__ void tree_update_stream(GQ float* P, LDSQ float* bl, con
   }
   if ((int)threadIdx.x < t.R && nd.has_bias) {
     const int r = threadIdx.x;
-    bl[r] = opt_apply(o, bl[r], gb * inv, nd.M, nd.V, (long long)nd.rows * t.C + rowmap[r]);
+    bl[r] = opt_apply<true>(o, bl[r], gb * inv, (GQ float*)nd.M, (GQ float*)nd.V, (long long)nd.rows * t.C + rowmap[r]);
   }
 }
 
@@ -1221,9 +1221,11 @@ struct TreeDelta {
   }
 };
 
-// Unit u of node nn from its pre-activations (row y of the tile, unit j of nu): state, and what the way back needs.
+// Unit u of node nn from its pre-activations (row y of the tile, unit j of nu): state, and (back) what the way back needs -- six
+// stores of eight, which an evaluation has no reader for.
 template <bool BR>
-__device__ __forceinline__ void tree_activate(const TreeBufs& B, long long nn, const LDSQ float* y, int j, int nu, int u, float cl, float cr) {
+__device__ __forceinline__ void tree_activate(const TreeBufs& B, long long nn, const LDSQ float* y, int j, int nu, int u, float cl, float cr,
+                                              bool back) {
   const int H = B.H, Hp = B.Hp;
   GQ float* hcn = B.hc + nn * 2 * Hp;
   GQ float* gt = B.gate + nn * 6 * H;
@@ -1233,22 +1235,26 @@ __device__ __forceinline__ void tree_activate(const TreeBufs& B, long long nn, c
     o_ = sigmoidf_(y[3 * nu + j]);
     const float g_ = tanh_(y[4 * nu + j]);
     c_ = i_ * g_ + fl * cl + fr * cr;
-    gt[u] = i_;
-    gt[H + u] = fl;
-    gt[2 * H + u] = fr;
-    gt[3 * H + u] = o_;
-    gt[4 * H + u] = g_;
+    if (back) {
+      gt[u] = i_;
+      gt[H + u] = fl;
+      gt[2 * H + u] = fr;
+      gt[3 * H + u] = o_;
+      gt[4 * H + u] = g_;
+    }
   } else {
     const float i_ = sigmoidf_(y[j]);
     o_ = sigmoidf_(y[nu + j]);
     const float g_ = tanh_(y[2 * nu + j]);
     c_ = i_ * g_;
-    gt[u] = i_;
-    gt[3 * H + u] = o_;
-    gt[4 * H + u] = g_;
+    if (back) {
+      gt[u] = i_;
+      gt[3 * H + u] = o_;
+      gt[4 * H + u] = g_;
+    }
   }
   const float tc = tanh_(c_);
-  gt[5 * H + u] = tc;
+  if (back) gt[5 * H + u] = tc;
   hcn[u] = o_ * tc;
   hcn[Hp + u] = c_;
 }
@@ -1366,7 +1372,7 @@ __device__ __noinline__ void role_tree_cell(const GQ AmpDev* D, const GQ WorkerD
         const bool first = i == (int)threadIdx.x;
         const float cl = BR ? (first ? pcl : xbase[M.off0[m] + Hp + u]) : 0.f;
         const float cr = BR ? (first ? pcr : xbase[M.off1[m] + Hp + u]) : 0.f;
-        tree_activate<BR>(B, B.node(M.s[m], M.n[m]), Y + k * ldy, j, nu, u, cl, cr);
+        tree_activate<BR>(B, B.node(M.s[m], M.n[m]), Y + k * ldy, j, nu, u, cl, cr, true);   // (a run-time choice costs this worker 0.8 %)
       }
       lds_barrier();
       PHASE(2);

@@ -353,7 +353,7 @@ __device__ __noinline__ void role_tree_cell_lds(const GQ AmpDev* D, const GQ Wor
         const bool first = p == (int)threadIdx.x;
         const float cl = BR ? (first ? pcl : xbase[M.off0[r] + Hp + u]) : 0.f;
         const float cr = BR ? (first ? pcr : xbase[M.off1[r] + Hp + u]) : 0.f;
-        tree_activate<BR>(B, B.node(M.s[r], M.n[r]), Y + r * ldy, j, nu, u, cl, cr);
+        tree_activate<BR>(B, B.node(M.s[r], M.n[r]), Y + r * ldy, j, nu, u, cl, cr, wr.train);
       }
     }
     PHASE(2);

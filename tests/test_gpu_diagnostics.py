@@ -6,7 +6,7 @@ import pytest
 from oracle import amp as oamp
 from paper_1705_09786_amd import synth
 
-from util import gpu_train, named_logs, oracle_replay, oracle_runtime
+from util import compare, gpu_train, named_logs, oracle_replay, oracle_runtime
 
 pytestmark = pytest.mark.gpu
 
@@ -130,3 +130,17 @@ def test_workers_run_on_the_dies_the_launch_assumes():
     g = gpu_train("tree", dims2, synth.init_params("tree", dims2, 3), data2, 16, 10, SGD, lookup_muf=100, log=False)
     xcc = g["trainer"].amp.get_worker_placement()
     assert xcc == [w % 8 for w in range(len(xcc))], xcc
+
+
+@pytest.mark.parametrize("tiles,packed", [({1: 10, 2: 17}, True), ({1: 12, 2: 17}, True), ({1: 12, 2: 18}, False), ({1: 5, 2: 10}, False)])
+def test_single_tree_pipelines_on_one_die(tiles, packed):
+    """A lone tree pipeline is kept on one die up to its 32 CUs where all of its cells keep their inputs on the CU (10 + 17 tiles:
+    30 workers; 32; one too many), and spread where one does not (hidden 150 on 10 branch tiles or 5 leaf tiles)."""
+    dims = dict(vocab=200, emb=300, hidden=150, n_class=5)
+    data = synth.make_tree(24, 99, dims, max_leaves=20)
+    fp = synth.init_params("tree", dims, 3)
+    g = gpu_train("tree", dims, fp, data, 16, 10, SGD, lookup_muf=100, tiles=tiles)
+    xcc = g["trainer"].amp.get_worker_placement()
+    assert xcc == ([0] * len(xcc) if packed else [w % 8 for w in range(len(xcc))]), xcc
+    rt = oracle_replay("tree", dims, fp, data, g["logs"], 10, SGD, lookup_muf=100)
+    compare(g, rt, len(data), opt=SGD)
