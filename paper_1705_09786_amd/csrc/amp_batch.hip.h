@@ -308,79 +308,54 @@ __device__ __noinline__ void mfma_cols_any(const LDSQ float* Wl, int ldw, int NR
   }
 }
 
-// Fixed shape: a wave owns column group cb for all message blocks.
-template <int NRB, int NCG, int NB>
-__device__ __forceinline__ void mfma_cols_fixed(const LDSQ float* Wl, int ldw, const LDSQ float* Dl, int ldd, LDSQ float* DX,
-                                                int ldx) {
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, i = lane & 15, q = lane >> 4;
-  constexpr int NA = NB == 1 ? 4 : 2;
+// Fixed shape: (column group, message block) items dealt out to the waves; Rv rows hold anything.  Four of them in the last row
+// block are one product instead of four: a gate of hidden size 100 split in two has 52 rows.  (Thirteen column groups dealt to
+// eight waves for all message blocks left one SIMD with four and three with three; 39 items are ten and nine or ten: 24 replicas
+// of the graph model 8.38 -> 8.22 ms, the split pipeline 60.4 -> 60.0.  A shape known only at run time is faster in the loop above:
+// hidden 60 unsplit 51.5 ms, 51.9 by items of this kind.)
+template <int NRB, int NCG>
+__device__ __forceinline__ void mfma_cols_items(const LDSQ float* Wl, int ldw, const LDSQ float* Dl, int ldd, int NB, LDSQ float* DX,
+                                                int ldx, int Rv) {
+  const int wave = uni((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63, i = lane & 15, q = lane >> 4;
+  const bool one = uni(Rv) - 16 * (NRB - 1) <= 4;
+  const int full = one ? NRB - 1 : NRB;
   const v4f zero = {0.f, 0.f, 0.f, 0.f};
-  for (int cb = wave; cb < NCG; cb += AMP_THREADS / 64) {
-    const LDSQ float* wp = Wl + (4 * q) * ldw + cb * 16 + i;
-    const LDSQ float* dp = Dl + i * ldd + 4 * q;
-    v4f acc[NB][NA];
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-      for (int a = 0; a < NA; ++a) acc[nb][a] = zero;
+  for (int item = wave; item < NCG * NB; item += AMP_THREADS / 64) {
+    const int nb = item / NCG, cb = item - nb * NCG;
+    const LDSQ float* wp = Wl + 4 * q * ldw + cb * 16 + i;
+    const LDSQ float* dp = Dl + (nb * 16 + i) * ldd + 4 * q;
+    v4f acc[4] = {zero, zero, zero, zero};
     // operands of row block g + 1 are fetched from LDS before the products of block g are issued
-    v4f d[NB];
+    float w[4], wn[4];
+    v4f d = *(const LDSQ v4f*)dp, dn;
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) d[nb] = *(const LDSQ v4f*)(dp + nb * 16 * ldd);
-    float w0 = wp[0], w1 = wp[ldw], w2 = wp[2 * ldw], w3 = wp[3 * ldw];
+    for (int e = 0; e < 4; ++e) w[e] = wp[e * ldw];
+    const float wl = wp[(16 * (NRB - 1) - 3 * q) * ldw], dl = dp[16 * (NRB - 1) - 3 * q];   // row 16 (NRB - 1) + q
+    auto block = [&](int g) {
+      const int gn = g + 1 < full ? g + 1 : g;
+      dn = *(const LDSQ v4f*)(dp + 16 * gn);
 #pragma unroll
-    for (int g = 0; g < NRB; ++g) {
-      v4f dn[NB];
+      for (int e = 0; e < 4; ++e) wn[e] = wp[(16 * gn + e) * ldw];
+      asm volatile("" : "+v"(acc[0]) : : "memory");
 #pragma unroll
-      for (int nb = 0; nb < NB; ++nb) dn[nb] = d[nb];
-      float n0 = w0, n1 = w1, n2 = w2, n3 = w3;
-      if (g + 1 < NRB) {
+      for (int e = 0; e < 4; ++e) acc[e] = MFMA(w[e], d[e], acc[e]);
+      d = dn;
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb) dn[nb] = *(const LDSQ v4f*)(dp + nb * 16 * ldd + 16 * (g + 1));
-        const LDSQ float* w = wp + 16 * (g + 1) * ldw;
-        n0 = w[0];
-        n1 = w[ldw];
-        n2 = w[2 * ldw];
-        n3 = w[3 * ldw];
-        asm volatile("" : "+v"(acc[0][0]) : : "memory");
-      }
+      for (int e = 0; e < 4; ++e) w[e] = wn[e];
+    };
 #pragma unroll
-      for (int nb = 0; nb < NB; ++nb) {
-        acc[nb][0] = MFMA(w0, d[nb].x, acc[nb][0]);
-        acc[nb][1] = MFMA(w1, d[nb].y, acc[nb][1]);
-      }
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) {
-        acc[nb][NA == 4 ? 2 : 0] = MFMA(w2, d[nb].z, acc[nb][NA == 4 ? 2 : 0]);
-        acc[nb][NA == 4 ? 3 : 1] = MFMA(w3, d[nb].w, acc[nb][NA == 4 ? 3 : 1]);
-      }
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) d[nb] = dn[nb];
-      w0 = n0;
-      w1 = n1;
-      w2 = n2;
-      w3 = n3;
-    }
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-      v4f r = acc[nb][0] + acc[nb][1];
-      if (NA == 4) r += acc[nb][2] + acc[nb][3];
-      *(LDSQ v4f*)(DX + (nb * 16 + i) * ldx + cb * 16 + 4 * q) = r;
-    }
+    for (int g = 0; g < NRB; ++g)
+      if (g < full) block(g);
+    if (one) acc[0] = MFMA(wl, dl, acc[0]);
+    *(LDSQ v4f*)(DX + (nb * 16 + i) * ldx + cb * 16 + 4 * q) = (acc[0] + acc[1]) + (acc[2] + acc[3]);
   }
 }
 
 template <int NRBT, int NCGT>
 __device__ __forceinline__ void mfma_cols(const LDSQ float* Wl, int ldw, int NRB, int NCG, const LDSQ float* Dl, int ldd,
-                                          int NB, LDSQ float* DX, int ldx) {
-  if (NRBT && NB == 1)
-    mfma_cols_fixed<NRBT ? NRBT : 1, NCGT ? NCGT : 1, 1>(Wl, ldw, Dl, ldd, DX, ldx);
-  else if (NRBT && NB == 2)
-    mfma_cols_fixed<NRBT ? NRBT : 1, NCGT ? NCGT : 1, 2>(Wl, ldw, Dl, ldd, DX, ldx);
-  else if (NRBT && NB == 3)
-    mfma_cols_fixed<NRBT ? NRBT : 1, NCGT ? NCGT : 1, 3>(Wl, ldw, Dl, ldd, DX, ldx);
-  else if (NRBT && NB == 4)
-    mfma_cols_fixed<NRBT ? NRBT : 1, NCGT ? NCGT : 1, 4>(Wl, ldw, Dl, ldd, DX, ldx);
+                                          int NB, LDSQ float* DX, int ldx, int Rv) {
+  if constexpr (NRBT != 0)
+    mfma_cols_items<NRBT, NCGT>(Wl, ldw, Dl, ldd, NB, DX, ldx, Rv);
   else
     mfma_cols_any(Wl, ldw, NRB, NCG, Dl, ldd, NB, DX, ldx);
   lds_barrier();

@@ -1252,7 +1252,7 @@ __device__ __noinline__ void role_g_edge(const GQ AmpDev* D, const GQ WorkerDev*
       g_pend_append(pend, pd.Rp, pd.stride, nrows, Y, Hs, nu, X, Hs, H, p.Kt, gb);   // one gradient per group
       lds_barrier();
       PHASE(5);
-      mfma_cols<NRBT, NCGT>(g.Wl, t.ldw, NRB, NCG, Y, Hs, NB, X, Hs);
+      mfma_cols<NRBT, NCGT>(g.Wl, t.ldw, NRB, NCG, Y, Hs, NB, X, Hs, t.R);
       PHASE(6);
       // dh_src += W^T delta_e: per source node, its edges of this type in ascending order -> this tile's part
       if (scout) {
@@ -1547,7 +1547,7 @@ __device__ __noinline__ void role_g_gate(const GQ AmpDev* D, const GQ WorkerDev*
       g_pend_append(pend, pd.Rp, pd.stride, nrows, Y, Hs, nu, X, Cs, C, p.Kt, gb);
       lds_barrier();
       PHASE(5);
-      mfma_cols<NRBT, NCGT>(g.Wl, t.ldw, NRB, NCG, Y, Hs, NB, X, Cs);
+      mfma_cols<NRBT, NCGT>(g.Wl, t.ldw, NRB, NCG, Y, Hs, NB, X, Cs, t.R);
       PHASE(6);
       if (scout) {
         g_form_pass(D, gd, B, mine, head, taken, CAP, maxm, room(cnt_after), 0, false, false, pb ^ 1);
@@ -1805,7 +1805,7 @@ __device__ __noinline__ void role_g_cand(const GQ AmpDev* D, const GQ WorkerDev*
       g_pend_append(pend, pd.Rp, pd.stride, nrows, Y, Hs, nu, X, Cs, C, p.Kt, gb);
       lds_barrier();
       PHASE(5);
-      mfma_cols<NRBT, NCGT>(g.Wl, t.ldw, NRB, NCG, Y, Hs, NB, X, Cs);
+      mfma_cols<NRBT, NCGT>(g.Wl, t.ldw, NRB, NCG, Y, Hs, NB, X, Cs, t.R);
       PHASE(6);
       // This tile's parts, over all H columns: W^T delta w.r.t. A; the reset gate's pre-activation gradient, linear
       // in the tile's partial W^T delta w.r.t. r * h; the gradient w.r.t. h, to which the blend's direct term

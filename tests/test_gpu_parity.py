@@ -704,6 +704,8 @@ def test_ggnn_passes_waited_for(hidden, tiles, mak):
 @pytest.mark.parametrize("hidden,tiles,muf,opt", [
     (104, {}, 1, MOM),                             # seven row blocks: lists of 2 to 29 nodes' rows
     (97, {}, 5, G_ADAM),                           # the same shape by single elements
+    (99, {}, 4, dict(kind="sgd", lr=0.005)),       # three rows in the last block, and four:
+    (100, {1: 2, 3: 2, 4: 2, 5: 3}, 4, MOM),
     (104, {1: 2, 2: 3, 3: 4, 4: 2, 5: 3}, 1, dict(kind="sgd", lr=0.005)),   # two, four and three row blocks
     (100, {1: 4, 2: 2, 3: 2, 4: 3, 5: 4}, 6, MOM),
     (112, {1: 2, 3: 2, 4: 3, 5: 2}, 3, MOM),       # the edge linears' only
