@@ -34,8 +34,14 @@ __device__ __forceinline__ unsigned ld_u32(const unsigned* p) {
 // wherever strict_release / strict_acquire or ring_put_near stand.
 // Waits for the wave's own loads and stores.  By the builtin and not in inline asm, whose text the compiler does not read: it
 // would take every load in front of it for one that may still be on its way, and wait again -- for all that was issued since --
-// where such a load's register is next used.
+// where such a load's register is next used.  (AMP_WAIT_TEXT: in inline asm all the same.  The graph workers, whose passes differ
+// too much for a register to be taken up again that soon, gain nothing from the builtin, and their path for sizes that are
+// no multiples of 4 is 1 % slower with it, 1,000 graphs of hidden 37 forward 36.3 -> 36.8 ms.)
 __device__ __forceinline__ void wait_vm() {
+#ifdef AMP_WAIT_TEXT
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  return;
+#endif
   asm volatile("" ::: "memory");
   __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0), the other counters left alone
   asm volatile("" ::: "memory");

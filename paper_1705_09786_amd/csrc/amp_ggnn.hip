@@ -1,4 +1,5 @@
 // Persistent kernel of the gated graph network.
+#define AMP_WAIT_TEXT
 #include <hip/hip_runtime.h>
 #include "amp_worker.hip.h"
 #include "amp_batch.hip.h"
