@@ -37,14 +37,14 @@ DEFAULTS = {
     # cfg: mak, muf, lookup muf, optimizer
     1: dict(mak=4, muf=1, lmuf=None, opt=("sgd", dict(lr=0.05))),
     2: dict(mak=16, muf=16, lmuf=16, opt=("sgd", dict(lr=0.05))),
-    # 10 leaf + 17 branch tiles: the best rate for the CUs it takes (55.2k trees/s on 30 workgroups): 15 leaf and 9 or 8
+    # 10 leaf + 17 branch tiles: the best rate for the CUs it takes (56.2k trees/s on 30 workgroups): 15 leaf and 9 or 8
     # branch units per tile are 45 and 45 or 40 rows, three 16-row blocks almost full, where 8 + 16 tiles (57 and 50
     # rows, 44.5k trees/s) pad to four; the fewest tiles that fit LDS (5 + 8, 16 workgroups, 31.9k trees/s) use each CU
     # better and are what the replicated run packs two per XCD
     3: dict(mak=64, muf=50, lmuf=1000, opt=("sgd", dict(lr=0.05)), tiles={1: 10, 2: 17}, replica_tiles={1: 5, 2: 8},
             replica_workers=16),
     # the commonest edge type's linear split over four workgroups, the two GRU gates over two each, the candidate over
-    # three (17 workgroups): 24.4k graphs/s against 13.9k unsplit; that linear over two and more tiles of the GRU nodes were
+    # three (17 workgroups): 25.0k graphs/s against 13.9k unsplit; that linear over two and more tiles of the GRU nodes were
     # slower when this took 21.7k (18.7k; 20.8-21.4k on 18-22 workgroups)
     # the replicated run keeps the nodes whole: 24 replicas of 10 workgroups beat 16 of 15
     4: dict(mak=32, muf=20, lmuf=20, opt=("adam", dict(lr=0.001)), tiles={1: 4, 5: 2, 6: 2, 7: 3}, replica_tiles=None,
