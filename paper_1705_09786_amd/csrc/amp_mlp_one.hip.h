@@ -27,8 +27,11 @@
 #define MO_LT 132   // row stride of a layer's tile: rows 16-byte aligned and spread over the banks
 
 // Plain SGD at layers of up to 128 x 128, and every evaluation of such layers.  Gradients that wait for an update take as many
-// registers as the weights: with more than 64 inputs and more than 64 hidden units that is more than there are.  The same in
-// every workgroup of the replica.
+// registers as the weights: with more than 64 inputs and more than 64 hidden units that is more than there are, and with more
+// than 64 hidden units alone it pays from four gradients an update on (512 instances of 64-128-128-10, a workgroup per layer /
+// here: an update every 2 4.41 / 4.57 ms with one in flight, 2.77 / 2.96 with two, 2.22 / 2.95 with four; every 3 4.36 / 4.26,
+// 2.74 / 3.17, 2.20 / 2.13; every 4 4.36 / 4.08, 2.74 / 2.47, 2.19 / 1.68; up to 64 units 4.37 / 1.98, 2.73 / 1.24, 2.19 / 1.25 already
+// at every 2).  The same in every workgroup of the replica.
 __device__ __forceinline__ bool mlp_one_each(const GQ AmpDev* D) {   // no gradient ever waits
   bool each = true;
 #pragma unroll
@@ -39,7 +42,8 @@ __device__ __forceinline__ bool mlp_one_fits(const GQ AmpDev* D) {
   if (D->hidden > MLP_MAX || D->d_in > MLP_MAX || D->n_class > 64) return false;
   if (!D->train) return true;
   if (D->node[0].opt != 0 || D->node[1].opt != 0 || D->node[2].opt != 0) return false;
-  return D->hidden <= 64 || D->d_in <= 64 || mlp_one_each(D);
+  if (D->hidden <= 64 || mlp_one_each(D)) return true;
+  return D->d_in <= 64 && D->node[0].muf >= 4 && D->node[1].muf >= 4 && D->node[2].muf >= 4;
 }
 
 // A wave's share of a product: 64 outputs, one a lane, from out0 on, and NJ groups of 16 terms from k0 on.  The SPLITS waves that
