@@ -635,7 +635,12 @@ __device__ __forceinline__ void softmax_xent_wave0(const float* z, int n, int la
 // ONE thread, at every update a worker applies: the controller's staleness-bounded admission reads this count.
 __shared__ int s_bounded;   // whether it does: left here when the kernel starts, an update would wait for the descriptor's fetch
 __device__ __forceinline__ void note_update(const GQ AmpDev* D) {
-  if (s_bounded) __hip_atomic_fetch_add((GQ unsigned*)&D->ctl[3], 1u, __ATOMIC_RELAXED, AGENT);
+#ifdef AMP_BOUNDED_FETCHED   // the MLP keeps the descriptor's word in a register (946 instances of 84-79-79-15, an update every 6: 5.05 -> 4.80 ms)
+  if (D->admit_bounded)
+#else
+  if (s_bounded)
+#endif
+    __hip_atomic_fetch_add((GQ unsigned*)&D->ctl[3], 1u, __ATOMIC_RELAXED, AGENT);
 }
 
 // Arrival counter of a join: returns true for the arrival that completes
