@@ -124,7 +124,14 @@ typedef struct amp_eval_result {
 /* Creates a context that works inside [dev_arena, dev_arena + arena_bytes)
  * (DEVICE pointer, 256-byte aligned, caller keeps it alive until
  * amp_destroy) and launches on hip_stream (a hipStream_t passed as void*;
- * NULL = the default stream).  Model = IR graph + controller, Section 4. */
+ * NULL = the default stream).  Model = IR graph + controller, Section 4.
+ * Calls on several contexts may run at the same time, on streams or in
+ * processes of their own, where all their workers fit the GPU together: a
+ * worker occupies a compute unit of its own.  A pipeline of up to 12 workers
+ * has them on one of the eight dies, replicas x, x + 8, ... (amp_set_replicas,
+ * where they fit a die) on the x-th, and every other pipeline has them evenly
+ * on all dies; a die has 32.  Launches that do not fit beside each other may
+ * wait for each other until their watchdogs stop them (AMP_EDEVICE). */
 int amp_create(amp_ctx **out, void *dev_arena, size_t arena_bytes, void *hip_stream);
 /* amp_create for callers that cannot allocate device memory (tight serving
  * loops, harnesses that forbid hipMalloc, code that must not touch the

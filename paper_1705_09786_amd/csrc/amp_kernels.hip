@@ -20,19 +20,19 @@
 
 // One kernel per model, each in a source file of its own (amp_mlp.hip, amp_rnn.hip, amp_tree.hip, amp_ggnn.hip).
 #define AMP_LAUNCHER(name) \
-  extern "C" hipError_t amp_launch_##name(const AmpDev*, int, int, int, const AmpLaunch*, hipStream_t)
+  extern "C" hipError_t amp_launch_##name(const AmpDev*, int, int, const AmpLaunch*, hipStream_t)
 AMP_LAUNCHER(mlp);
 AMP_LAUNCHER(rnn);
 AMP_LAUNCHER(tree);
 AMP_LAUNCHER(ggnn);
 
-extern "C" hipError_t amp_launch(int model, const AmpDev* devs, int n_replicas, int workers_per_replica, int pack_alone,
-                                 const AmpLaunch* args, hipStream_t stream) {
+extern "C" hipError_t amp_launch(int model, const AmpDev* devs, int n_replicas, int workers_per_replica, const AmpLaunch* args,
+                                 hipStream_t stream) {
   switch (model) {
-    case 1: return amp_launch_mlp(devs, n_replicas, workers_per_replica, pack_alone, args, stream);
-    case 2: return amp_launch_rnn(devs, n_replicas, workers_per_replica, pack_alone, args, stream);
-    case 3: return amp_launch_tree(devs, n_replicas, workers_per_replica, pack_alone, args, stream);
-    case 4: return amp_launch_ggnn(devs, n_replicas, workers_per_replica, pack_alone, args, stream);
+    case 1: return amp_launch_mlp(devs, n_replicas, workers_per_replica, args, stream);
+    case 2: return amp_launch_rnn(devs, n_replicas, workers_per_replica, args, stream);
+    case 3: return amp_launch_tree(devs, n_replicas, workers_per_replica, args, stream);
+    case 4: return amp_launch_ggnn(devs, n_replicas, workers_per_replica, args, stream);
     default: return hipErrorInvalidValue;
   }
 }

@@ -18,8 +18,8 @@
 #include "amp_dev.h"
 #include "amp_graph.h"
 
-extern "C" hipError_t amp_launch(int model, const AmpDev* devs, int n_replicas, int workers_per_replica, int pack_alone,
-                                 const AmpLaunch* args, hipStream_t stream);
+extern "C" hipError_t amp_launch(int model, const AmpDev* devs, int n_replicas, int workers_per_replica, const AmpLaunch* args,
+                                 hipStream_t stream);
 extern "C" hipError_t amp_clear(void* a, size_t a_bytes, void* b, size_t b_bytes, size_t b_stride, int b_count, hipStream_t stream);
 extern "C" hipError_t amp_peak_lds_launch(int n_wg, int iters, float* sink, hipStream_t stream, double* seconds,
                                           double* bytes_per_wg);
@@ -253,17 +253,6 @@ size_t rows_per_message(const amp_ctx* c, const HostWorker& w) {
   if (w.role == ROLE_G_EDGE) return (size_t)c->max_edges;
   if (w.role == ROLE_G_GATE || w.role == ROLE_G_CAND) return (size_t)c->max_len;
   return 1;
-}
-
-// Most workers of a single pipeline that are kept on one die: all its 32 CUs for trees whose cells all keep their inputs and
-// gradients on the CU (amp_worker.hip.h says how packed launches exchange data) -- 2,136 trees on 30 workers 39.75 -> 39.55 ms, with
-// 16 in flight 65.2 -> 64.2, an update every 3 at hidden 80 on 15 workers 47.8 -> 45.7, evaluation of 1,101 trees 12.4 -> 11.7 -- and
-// twelve otherwise.
-int amp_pack_alone(const amp_ctx* c) {
-  if (c->model != AMP_MODEL_TREE) return 12;
-  for (const HostWorker& w : c->workers)
-    if ((w.role == ROLE_TREE_LEAF || w.role == ROLE_TREE_BRANCH) && w.aux != 2) return 12;
-  return 32;
 }
 
 // LDS floats a worker needs (mirrors the carving in the kernels); sets w.kb.
@@ -1603,7 +1592,7 @@ int launch_once(amp_ctx* c, const Resident& res, size_t out_begin, int epochs, b
   for (int r = 0; r < R; ++r) args.first_seq[r] = train ? c->rep_admitted[r] : 0;
   c->params_fresh = false;
   HIPCHK(c, hipEventRecord(c->ev_begin, c->stream));
-  HIPCHK(c, amp_launch(c->model, (const AmpDev*)(c->arena + c->off_devs[train ? 0 : 1]), R, (int)wpr, amp_pack_alone(c), &args, c->stream));
+  HIPCHK(c, amp_launch(c->model, (const AmpDev*)(c->arena + c->off_devs[train ? 0 : 1]), R, (int)wpr, &args, c->stream));
   HIPCHK(c, hipEventRecord(c->ev_end, c->stream));
   HIPCHK(c, hipMemcpyAsync(c->stage, c->arena + L.res_begin, res_bytes, hipMemcpyDeviceToHost, c->stream));
   if (params_too)

@@ -248,7 +248,7 @@ __device__ __forceinline__ void persistent_worker(const AmpDev* Dp, int workers_
 
 // Launches one model's persistent kernel.
 static inline hipError_t launch_persistent(const void* kernel, bool& attr_set, const AmpDev* devs, int n_replicas,
-                                           int workers_per_replica, int pack_alone, const AmpLaunch* args, hipStream_t stream) {
+                                           int workers_per_replica, const AmpLaunch* args, hipStream_t stream) {
   if (!attr_set) {
     hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, AMP_DYN_LDS_BYTES);
     if (e != hipSuccess) return e;
@@ -256,13 +256,15 @@ static inline hipError_t launch_persistent(const void* kernel, bool& attr_set, c
   }
   // One XCD has 32 CUs: the packed mapping needs the replicas that share an XCD to fit it.  Measured: replicas
   // gain from staying inside one L2 (15 Tree-LSTM replicas 184k -> 256k trees/s), and again from releases without
-  // an L2 write-back, which only a packed replica can do (16 replicas 316k -> 409k trees/s).  A single pipeline is packed up to
-  // pack_alone workers: with few workers that is faster (the 4-worker MLP 52k -> 55k instances/s; the RNN with eight copies of
-  // its cell, 10 workers, 105k -> 112k sequences/s; the unsplit 10-worker graph pipeline the same either way), with many
-  // whose exchange goes through HBM the eight L2s of a spread one are (17 graph workers 60.6 ms against 60.7 packed, 16
-  // workers of the older tree cell 69.2 against 70.2).  amp_pack_alone draws the line.
+  // an L2 write-back, which only a packed replica can do (16 replicas 316k -> 409k trees/s).  A single pipeline of up to 12
+  // workers is packed too (the RNN with eight copies of its cell, 10 workers, 105k -> 112k sequences/s; the unsplit 10-worker
+  // graph pipeline the same either way).  A longer one is spread: packed, it would leave another launch that runs at the same time
+  // -- a second context on a stream or in a process of its own -- too few CUs on that die, and two launches that hold a part of one die
+  // each would wait for the rest of it until their watchdogs end them.  (What packing gave trees whose cells all keep their
+  // inputs on the CU: 2,136 trees on 30 workers 39.75 -> 39.55 ms, evaluation of 1,101 12.4 -> 11.7; 17 graph workers 60.6 spread
+  // against 60.7, 16 workers of the older tree cell 69.2 against 70.2.)
   const int per_xcd = (n_replicas + 7) / 8;
-  const bool packed = per_xcd * workers_per_replica <= 32 && (n_replicas > 1 || workers_per_replica <= pack_alone);
+  const bool packed = per_xcd * workers_per_replica <= 32 && (n_replicas > 1 || workers_per_replica <= 12);
   const int grid = packed ? 8 * per_xcd * workers_per_replica : n_replicas * workers_per_replica;
   int packed_arg = packed ? 1 : 0;
   AmpLaunch by_value = *args;
@@ -278,9 +280,8 @@ static inline hipError_t launch_persistent(const void* kernel, bool& attr_set, c
     persistent_worker(Dp, workers_per_replica, n_replicas, xcd_packed, args, [](const GQ AmpDev* D) { return whole; },      \
                       [](const GQ AmpDev* D, const GQ WorkerDev* W) { __VA_ARGS__ });                                       \
   }                                                                                                                         \
-  extern "C" hipError_t amp_launch_##name(const AmpDev* devs, int n_replicas, int workers_per_replica, int pack_alone,      \
-                                          const AmpLaunch* a, hipStream_t stream) {                                         \
+  extern "C" hipError_t amp_launch_##name(const AmpDev* devs, int n_replicas, int workers_per_replica, const AmpLaunch* a,  \
+                                          hipStream_t stream) {                                                             \
     static bool attr_set = false;                                                                                           \
-    return launch_persistent((const void*)amp_persistent_##name, attr_set, devs, n_replicas, workers_per_replica, pack_alone, a, \
-                             stream);                                                                                       \
+    return launch_persistent((const void*)amp_persistent_##name, attr_set, devs, n_replicas, workers_per_replica, a, stream); \
   }

@@ -132,15 +132,29 @@ def test_workers_run_on_the_dies_the_launch_assumes():
     assert xcc == [w % 8 for w in range(len(xcc))], xcc
 
 
-@pytest.mark.parametrize("tiles,packed", [({1: 10, 2: 17}, True), ({1: 12, 2: 17}, True), ({1: 12, 2: 18}, False), ({1: 5, 2: 10}, False)])
-def test_single_tree_pipelines_on_one_die(tiles, packed):
-    """A lone tree pipeline is kept on one die up to its 32 CUs where all of its cells keep their inputs on the CU (10 + 17 tiles:
-    30 workers; 32; one too many), and spread where one does not (hidden 150 on 10 branch tiles or 5 leaf tiles)."""
+@pytest.mark.parametrize("tiles", [{1: 10, 2: 17}, {1: 12, 2: 17}, {1: 5, 2: 10}])
+def test_long_lone_pipelines_leave_room_on_every_die(tiles):
+    """Two tree pipelines of 18 .. 32 workers on streams of their own, at the same time: either has its workers dealt to all eight
+    dies in turn (from whichever die the stream's queue starts at), so that both together need at most eight of any die's 32
+    compute units and neither can keep the other from starting.  Each run replays as it does alone."""
+    import threading
+    import torch
     dims = dict(vocab=200, emb=300, hidden=150, n_class=5)
     data = synth.make_tree(24, 99, dims, max_leaves=20)
     fp = synth.init_params("tree", dims, 3)
-    g = gpu_train("tree", dims, fp, data, 16, 10, SGD, lookup_muf=100, tiles=tiles)
-    xcc = g["trainer"].amp.get_worker_placement()
-    assert xcc == ([0] * len(xcc) if packed else [w % 8 for w in range(len(xcc))]), xcc
-    rt = oracle_replay("tree", dims, fp, data, g["logs"], 10, SGD, lookup_muf=100)
-    compare(g, rt, len(data), opt=SGD)
+    out = [None, None]
+
+    def one(k, stream):
+        with torch.cuda.stream(stream):
+            out[k] = gpu_train("tree", dims, fp, data, 16, 10, SGD, lookup_muf=100, tiles=tiles)
+
+    threads = [threading.Thread(target=one, args=(k, torch.cuda.Stream())) for k in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for g in out:
+        xcc = g["trainer"].amp.get_worker_placement()
+        assert xcc == [(xcc[0] + w) % 8 for w in range(len(xcc))], xcc
+        rt = oracle_replay("tree", dims, fp, data, g["logs"], 10, SGD, lookup_muf=100)
+        compare(g, rt, len(data), opt=SGD)
