@@ -385,7 +385,7 @@ int amp_set_watchdog(amp_ctx *ctx, double seconds);
  * the gradients that reach it and applies its own update once
  * min_update_frequency of them have arrived, with no synchronisation between
  * nodes.  AMP_EDEVICE if the kernel stopped itself (watchdog, record full, or a
- * launch that packs whole replicas into single XCDs found a workgroup on another die than its index implies). */
+ * launch that packs whole replicas into single XCDs found one's workgroups on different dies). */
 int amp_train(amp_ctx *ctx, int epochs);
 /* Blocking: forward-only pass over the evaluation set with the present
  * parameters (Section 1: inference runs through the same graph; Table 2's

@@ -56,7 +56,7 @@ AMP_HD static inline int amp_stream_parts(int Rp, int ldy, int kb) { return amp_
 #define ABORT_WATCHDOG 1u
 #define ABORT_LOG_FULL 2u
 #define ABORT_BAD_STATE 3u
-#define ABORT_PLACEMENT 4u   // a packed launch found a workgroup on another die than its block index implies
+#define ABORT_PLACEMENT 4u   // a packed launch found a replica's workgroups on different dies
 
 enum AmpRole {
   ROLE_CTRL = 0,
@@ -166,7 +166,8 @@ struct AmpDev {
   int admit_bounded, n_updaters;  // staleness-bounded admission on / workers that apply updates
   float max_staleness;            // its bound: updates per worker during an instance's life
   unsigned* ctl;              // [0] abort code, [1] done, [2] abort detail, [3] updates applied by all workers,
-                              // [4] largest number of instances in flight, [5] admission limit at the end
+                              // [4] largest number of instances in flight, [5] admission limit at the end, [6] copies that
+                              // have published in a synchronisation round, [7] a packed replica's die + 1
   unsigned* slot_seq;         // [mak] admission number held by each slot
   int* slot_inst;             // [mak] the slot's instance: index into the launch's instance set; sign bit set = a
                               // forward-only (evaluation) instance, which the loss layer retires instead of turning round

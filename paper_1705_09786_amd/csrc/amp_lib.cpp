@@ -1615,7 +1615,7 @@ int launch_once(amp_ctx* c, const Resident& res, size_t out_begin, int epochs, b
     if (ctl[0]) {
       const char* why = ctl[0] == ABORT_WATCHDOG ? "a worker waited longer than the watchdog allows"
                         : ctl[0] == ABORT_LOG_FULL ? "event record full"
-                        : ctl[0] == ABORT_PLACEMENT ? "a workgroup of a packed launch ran on another die than its block index implies"
+                        : ctl[0] == ABORT_PLACEMENT ? "the workgroups of a packed replica ran on different dies"
                                                     : "inconsistent state";
       c->state_zeroed = false;   // device state is unreliable after an aborted run
       for (HostNode& n : c->nodes) n.dirty = true;
