@@ -195,6 +195,9 @@ __device__ __forceinline__ void mo_keep(v4f (&w)[N]) {
 }
 
 __shared__ unsigned s_mo_logn[3];
+// A record is full: set by the thread that writes them, read by all behind the barrier that follows a group's first events, so that
+// every wave leaves in front of the same group.
+__shared__ int s_mo_full;
 
 // An event of layer l, in its own worker's record.  ONE thread.
 __device__ __forceinline__ void mo_log(const GQ AmpDev* D, int l, int kind, unsigned seq) {
@@ -202,10 +205,16 @@ __device__ __forceinline__ void mo_log(const GQ AmpDev* D, int l, int kind, unsi
   const unsigned n = s_mo_logn[l];
   if (n >= w.log_cap) {
     raise_abort(D, ABORT_LOG_FULL, 1 + l);
+    s_mo_full = 1;
     return;
   }
   ((GQ unsigned long long*)w.log)[n] = ((unsigned long long)seq << 32) | ((unsigned)kind << 28) | ((unsigned)l << 20);
   s_mo_logn[l] = n + 1;
+}
+// The same of the controller.
+__device__ __forceinline__ void mo_log_ctrl(const GQ AmpDev* D, const GQ WorkerDev* W, int kind, unsigned seq, unsigned local) {
+  if (s_logn >= s_log_cap) s_mo_full = 1;
+  log_event(D, W, &s_logn, 0, kind, seq, local);
 }
 
 // EACH: an update per gradient at every layer (and every evaluation): no gradient is kept.  BIG: more than 64 hidden units, two
@@ -307,6 +316,7 @@ __device__ __forceinline__ void role_mlp_one(const GQ AmpDev* D, const GQ Worker
   int limit = bounded ? 1 : mak, max_active = 0;
   unsigned updates = 0, done = 0, groups = 0, trained_all = 0;
   if (threadIdx.x < 3) s_mo_logn[threadIdx.x] = 0;
+  if (threadIdx.x == 3) s_mo_full = 0;
   // the instance word of the launch's admission `at` (sign bit: forward only), the last one's beyond it
   auto word_of = [&](unsigned at) -> int {
     if (at >= n_total) at = n_total - 1u;
@@ -362,7 +372,7 @@ __device__ __forceinline__ void role_mlp_one(const GQ AmpDev* D, const GQ Worker
     groups++;
     trained_all += (unsigned)nt;
     if (logging && tid == 0) {
-      for (int m = 0; m < n; ++m) log_event(D, W, &s_logn, 0, 3, seq0 + done + m, word_of(done + m) < 0 ? 1u : 0u);
+      for (int m = 0; m < n; ++m) mo_log_ctrl(D, W, 3, seq0 + done + m, word_of(done + m) < 0 ? 1u : 0u);
       for (int l = 0; l < 3; ++l) {
         for (int m = 0; m < n; ++m) mo_log(D, l, 0, seq0 + done + m);
         for (int m = 0; m < n; ++m)
@@ -398,6 +408,7 @@ __device__ __forceinline__ void role_mlp_one(const GQ AmpDev* D, const GQ Worker
     }
     word = word_of(done + (unsigned)(n + m4));   // on its way
     lds_barrier();
+    if (logging && uni(s_mo_full)) break;
     PHASE(0);
     // ---------------- layer 2
     {
@@ -613,7 +624,7 @@ __device__ __forceinline__ void role_mlp_one(const GQ AmpDev* D, const GQ Worker
       }
     }
     if (logging && tid == 0)
-      for (int m = 0; m < n; ++m) log_event(D, W, &s_logn, 0, 4, seq0 + done + m, 0);
+      for (int m = 0; m < n; ++m) mo_log_ctrl(D, W, 4, seq0 + done + m, 0);
     if (bounded) {
       // a message retires behind the updates it has brought about; those of the group's messages up to it are what it has seen
       const float bound = uni(D->max_staleness);
@@ -627,7 +638,6 @@ __device__ __forceinline__ void role_mlp_one(const GQ AmpDev* D, const GQ Worker
     }
     updates += made;
     done += (unsigned)n;
-    if (logging && uni(ld_u32(&D->ctl[0]))) break;   // the record is full
     PHASE(7);
   }
   __syncthreads();

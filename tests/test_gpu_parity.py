@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 
 from oracle import direct
+from paper_1705_09786_amd import binding as B
 from paper_1705_09786_amd import runner, synth
 
 from oracle import amp as oamp
@@ -137,6 +138,31 @@ def test_mlp_on_one_workgroup_carries_gradients_and_thresholds(d_in, hidden, n_c
             break
         flips.append(kinks[0])
     raise AssertionError((bad, flips))
+
+
+@pytest.mark.parametrize("d_in,hidden,muf,cap,mixed", [
+    (64, 128, 1, 50, False), (64, 128, 1, 51, True), (64, 128, 5, 46, False), (16, 37, 3, 40, False), (16, 37, 1, 33, True)])
+def test_mlp_record_full_ends_the_call(d_in, hidden, muf, cap, mixed):
+    """A record too short for the call, filled by the layers' events or (mostly forward-only instances) by the controller's: all
+    waves leave in front of the same group, the call fails, and the next one, with room, starts from the same parameters."""
+    dims = dict(d_in=d_in, hidden=hidden, n_class=10)
+    data, valid = synth.make_mlp(40, 43, dims), synth.make_mlp(120, 44, dims)
+    fp = synth.init_params("mlp", dims, 13)
+    tr = runner.Trainer("mlp", dims, fp, 4, 1, 0, 160, arena_bytes=1 << 28)
+    a = tr.amp
+    a.set_optimizer(-1, 0, lr=0.002)
+    a.set_min_update_frequency(-1, muf)
+    tr.submit_all(data)
+    tr.submit_all(valid, which=1)
+    a.set_event_log(cap)
+    with pytest.raises(B.AmpError) as e:
+        a.train_eval(1) if mixed else a.train(1)
+    assert e.value.code == B.AMP_EDEVICE and "record full" in str(e.value)
+    a.set_event_log(16 * len(data) + 64)
+    a.train(1)
+    g = dict(params=tr.params(), losses=a.get_instance_losses().astype(np.float64), logs=a.get_event_log())
+    check_controller_log(g["logs"], 4, len(data))
+    compare_up_to_relu_decisions("mlp", dims, fp, data, g, muf, dict(kind="sgd", lr=0.002))
 
 
 def test_mlp_logits_without_a_largest():
