@@ -248,6 +248,9 @@ __device__ __forceinline__ void role_mlp_one(const GQ AmpDev* D, const GQ Worker
   LDSQ float* b1 = (LDSQ float*)L.take(MO_LD);
   LDSQ float* b2 = (LDSQ float*)L.take(MO_LD);
   LDSQ float* b3 = (LDSQ float*)L.take(MO_LD);
+  // [admission modulo max_active_keys + 4] updates applied before it; four more than can be in flight, so that a wave still at a
+  // group's end reads what another's next admissions do not write
+  LDSQ unsigned* upd_at = (LDSQ unsigned*)L.take(AMP_MAX_MAK + 4);
   const float lr1 = uni(D->node[0].lr), lr2 = uni(D->node[1].lr), lr3 = uni(D->node[2].lr);
   unsigned c1 = uni(D->worker[1].wstate[0]), c2 = uni(D->worker[2].wstate[0]), c3 = uni(D->worker[3].wstate[0]);
   unsigned t1 = uni(D->worker[1].wstate[1]), t2 = uni(D->worker[2].wstate[1]), t3 = uni(D->worker[3].wstate[1]);
@@ -314,7 +317,7 @@ __device__ __forceinline__ void role_mlp_one(const GQ AmpDev* D, const GQ Worker
   const int mak = uni(D->mak);
   const bool bounded = uni(D->admit_bounded) != 0, logging = uni(s_log_cap) != 0u;
   int limit = bounded ? 1 : mak, max_active = 0;
-  unsigned updates = 0, done = 0, groups = 0, trained_all = 0;
+  unsigned updates = 0, done = 0, admitted = 0, groups = 0, trained_all = 0;
   if (threadIdx.x < 3) s_mo_logn[threadIdx.x] = 0;
   if (threadIdx.x == 3) s_mo_full = 0;
   // the instance word of the launch's admission `at` (sign bit: forward only), the last one's beyond it
@@ -356,9 +359,19 @@ __device__ __forceinline__ void role_mlp_one(const GQ AmpDev* D, const GQ Worker
     asm volatile("" : "+v"(tid));
     const int lane = tid & 63, m4 = lane & 3, k4 = lane >> 2, o1 = p1.out0 + lane;
     const int mrow = m4 * MO_LD + k4;   // where an operand of this lane lies in a [message][unit] array, from its first term on
-    // ---------------- admission
-    int n = limit < 4 ? limit : 4;
-    if ((unsigned)n > n_total - done) n = (int)(n_total - done);
+    // ---------------- admission (role_ctrl has the policies): what is admitted and not in the group waits in front of the first layer
+    int flying = (int)(admitted - done);
+    if (flying < limit && admitted < n_total) {
+      const unsigned left = n_total - admitted, room = (unsigned)(limit - flying), more = room < left ? room : left;
+      if (logging && tid == 0)
+        for (unsigned a = admitted; a < admitted + more; ++a) mo_log_ctrl(D, W, 3, seq0 + a, word_of(a) < 0 ? 1u : 0u);
+      if (bounded)
+        for (unsigned a = (unsigned)tid; a < more; a += AMP_THREADS) upd_at[(admitted + a) % (unsigned)(mak + 4)] = updates;
+      admitted += more;
+      flying += (int)more;
+    }
+    if (flying > max_active) max_active = flying;
+    int n = flying < 4 ? flying : 4;
     if (!EACH) {
       const int r1 = uni(D->node[0].muf) - (int)c1, r2 = uni(D->node[1].muf) - (int)c2, r3 = uni(D->node[2].muf) - (int)c3;
       int room = r1 < r2 ? r1 : r2;
@@ -366,13 +379,11 @@ __device__ __forceinline__ void role_mlp_one(const GQ AmpDev* D, const GQ Worker
       if (room < 1) room = 1;   // a threshold lowered between two calls
       if (n > room) n = room;
     }
-    if (n > max_active) max_active = n;
     const unsigned tr = train ? ~(unsigned)__ballot(word < 0) & ((1u << n) - 1u) : 0u;   // those that train
     const int nt = __popc(tr), lab_now = label;
     groups++;
     trained_all += (unsigned)nt;
     if (logging && tid == 0) {
-      for (int m = 0; m < n; ++m) mo_log_ctrl(D, W, 3, seq0 + done + m, word_of(done + m) < 0 ? 1u : 0u);
       for (int l = 0; l < 3; ++l) {
         for (int m = 0; m < n; ++m) mo_log(D, l, 0, seq0 + done + m);
         for (int m = 0; m < n; ++m)
@@ -626,10 +637,11 @@ __device__ __forceinline__ void role_mlp_one(const GQ AmpDev* D, const GQ Worker
     if (logging && tid == 0)
       for (int m = 0; m < n; ++m) mo_log_ctrl(D, W, 4, seq0 + done + m, 0);
     if (bounded) {
-      // a message retires behind the updates it has brought about; those of the group's messages up to it are what it has seen
-      const float bound = uni(D->max_staleness);
+      // a message retires behind the updates it has brought about
+      const float bound = uni(D->max_staleness), per_worker = 1.f / (float)uni(D->n_updaters);
       for (int m = 0; m < n; ++m) {
-        const float seen = EACH ? (float)__popc(tr & ((2u << m) - 1u)) : m == n - 1 ? (float)made * (1.f / 3.f) : 0.f;
+        const unsigned now = updates + (EACH ? 3u * (unsigned)__popc(tr & ((2u << m) - 1u)) : m == n - 1 ? made : 0u);
+        const float seen = (float)(now - uni(upd_at[(done + (unsigned)m) % (unsigned)(mak + 4)])) * per_worker;
         if (seen > bound)
           limit = limit > 1 ? limit - 1 : 1;
         else

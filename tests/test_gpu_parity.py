@@ -280,6 +280,53 @@ def test_staleness_bounded_admission():
     compare(g, rt, len(tdata), opt=SGD)
 
 
+def seen_updates(logs, seq):
+    """Updates per layer that the MLP's record shows between each instance's admission and its retirement: the layers record an
+    update per gradient, so those of the instances that retire between the two, its own among them."""
+    order = [(k, s) for (_, k, s, _) in logs[0]]
+    at = {ev: i for i, ev in enumerate(order)}
+    return sum(1 for k, _ in order[at[("A", seq)]:at[("R", seq)] + 1] if k == "R")
+
+
+@pytest.mark.parametrize("d_in,hidden,mak,muf", [(64, 128, 8, 1), (16, 37, 11, 1), (128, 64, 3, 1), (16, 37, 9, 3), (64, 100, 6, 5)])
+def test_mlp_admission(d_in, hidden, mak, muf):
+    """The MLP on one workgroup admits as every model does.  Greedy: max_active_keys in flight as soon as there are as many, and again
+    after every retirement.  Bounded: bound 0 repeats the run with one in flight bit for bit, a bound nothing reaches ends at
+    max_active_keys, and one in between lets the limit follow what the record says each instance has seen."""
+    dims = dict(d_in=d_in, hidden=hidden, n_class=10)
+    data = synth.make_mlp(57, 45, dims)
+    fp = synth.init_params("mlp", dims, 14)
+    opt = dict(kind="sgd", lr=0.01)
+    one = gpu_train("mlp", dims, fp, data, 1, muf, opt)
+    for bound in (None, 0.0, 2.5, 1e9):
+        g = gpu_train("mlp", dims, fp, data, mak, muf, opt, max_staleness=bound)
+        check_controller_log(g["logs"], mak, len(data))
+        most = max_in_flight(g["logs"][0])
+        assert g["admission"]["max_in_flight"] == most
+        # at bound 0 the limit grows with every instance that retires without having seen an update, of which at most muf follow each other
+        lo, hi = {0.0: (1, 1 if muf == 1 else muf + 1), 2.5: (2, mak)}.get(bound, (mak, mak))
+        assert lo <= most <= hi, (bound, most)
+        compare_up_to_relu_decisions("mlp", dims, fp, data, g, muf, opt)
+        if bound is None:
+            continue
+        if bound == 0.0 and muf == 1:
+            assert all(np.array_equal(a, b) for a, b in zip(g["params"], one["params"]))
+            assert np.array_equal(g["losses"], one["losses"])
+        limit, active = 1, 0
+        for k, s in [(k, s) for (_, k, s, _) in g["logs"][0]]:
+            if k == "A":
+                active += 1
+                assert active <= limit, (bound, s, active, limit)
+            else:
+                active -= 1
+                if muf == 1:
+                    limit = max(1, limit - 1) if seen_updates(g["logs"], s) > bound else min(mak, limit + 1)
+                else:
+                    limit = mak
+        if muf == 1:
+            assert g["admission"]["final_limit"] == limit
+
+
 def test_rnn_edge_lengths():
     """Length-1 sequences, the maximum length, and a ragged mix."""
     dims = synth.DEFAULT_DIMS["rnn"]
