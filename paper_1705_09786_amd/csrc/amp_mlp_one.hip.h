@@ -195,14 +195,13 @@ __device__ __forceinline__ void mo_keep(v4f (&w)[N]) {
 }
 
 __shared__ unsigned s_mo_logn[3];
-// A record is full: set by the thread that writes them, read by all behind the barrier that follows a group's first events, so that
-// every wave leaves in front of the same group.
-__shared__ int s_mo_full;
+__shared__ int s_mo_full;   // a record is full: of the thread that writes them alone
 
 // An event of layer l, in its own worker's record.  ONE thread.
 __device__ __forceinline__ void mo_log(const GQ AmpDev* D, int l, int kind, unsigned seq) {
   const GQ WorkerDev& w = D->worker[1 + l];
   const unsigned n = s_mo_logn[l];
+  if (s_log_cap == 0u) return;
   if (n >= w.log_cap) {
     raise_abort(D, ABORT_LOG_FULL, 1 + l);
     s_mo_full = 1;
@@ -213,8 +212,41 @@ __device__ __forceinline__ void mo_log(const GQ AmpDev* D, int l, int kind, unsi
 }
 // The same of the controller.
 __device__ __forceinline__ void mo_log_ctrl(const GQ AmpDev* D, const GQ WorkerDev* W, int kind, unsigned seq, unsigned local) {
-  if (s_logn >= s_log_cap) s_mo_full = 1;
+  if (s_log_cap && s_logn >= s_log_cap) s_mo_full = 1;
   log_event(D, W, &s_logn, 0, kind, seq, local);
+}
+
+// The controller's books, kept by ONE thread and only where somebody asks: a bounded limit, or the record.  (As scalars of every
+// wave they cost the loop registers it does not have: 1,024 instances 1.21 -> 1.26 ms.)
+struct MoAdmission {
+  int limit, flying, most;   // in flight at most / now / at most so far
+  int full;                  // s_mo_full as the group begins: every wave leaves in front of the same one
+  unsigned admitted;
+};
+__shared__ MoAdmission s_mo_adm;
+
+// Admissions in front of a group, by the policies of role_ctrl: what is in flight and not in the group waits in front of the first
+// layer.  upd_at: [admission modulo max_active_keys] updates applied before it.
+__device__ __forceinline__ void mo_admit(const GQ AmpDev* D, const GQ WorkerDev* W, LDSQ unsigned* upd_at, unsigned done, unsigned updates) {
+  const unsigned n_total = D->n_total, n_inst = (unsigned)D->data.n_inst, mak = (unsigned)D->mak;
+  unsigned a = s_mo_adm.admitted;
+  for (; (int)(a - done) < s_mo_adm.limit && a < n_total; ++a) {
+    const int word = D->adm_inst ? D->adm_inst[a] : (int)(a % n_inst);
+    mo_log_ctrl(D, W, 3, s_first_seq + a, word < 0 ? 1u : 0u);
+    upd_at[a % mak] = updates;
+  }
+  s_mo_adm.full = s_mo_full;
+  s_mo_adm.admitted = a;
+  s_mo_adm.flying = (int)(a - done);
+  if ((int)(a - done) > s_mo_adm.most) s_mo_adm.most = (int)(a - done);
+}
+// An instance of admission `a` retires when `updates` have been applied.
+__device__ __forceinline__ void mo_retire(const GQ AmpDev* D, const LDSQ unsigned* upd_at, unsigned a, unsigned updates) {
+  const float seen = (float)(updates - upd_at[a % (unsigned)D->mak]) * (1.f / (float)D->n_updaters);
+  if (seen > D->max_staleness)
+    s_mo_adm.limit = s_mo_adm.limit > 1 ? s_mo_adm.limit - 1 : 1;
+  else
+    s_mo_adm.limit = s_mo_adm.limit < D->mak ? s_mo_adm.limit + 1 : D->mak;
 }
 
 // EACH: an update per gradient at every layer (and every evaluation): no gradient is kept.  BIG: more than 64 hidden units, two
@@ -248,12 +280,10 @@ __device__ __forceinline__ void role_mlp_one(const GQ AmpDev* D, const GQ Worker
   LDSQ float* b1 = (LDSQ float*)L.take(MO_LD);
   LDSQ float* b2 = (LDSQ float*)L.take(MO_LD);
   LDSQ float* b3 = (LDSQ float*)L.take(MO_LD);
-  // [admission modulo max_active_keys + 4] updates applied before it; four more than can be in flight, so that a wave still at a
-  // group's end reads what another's next admissions do not write
-  LDSQ unsigned* upd_at = (LDSQ unsigned*)L.take(AMP_MAX_MAK + 4);
+  LDSQ unsigned* upd_at = (LDSQ unsigned*)L.take(AMP_MAX_MAK);
   const float lr1 = uni(D->node[0].lr), lr2 = uni(D->node[1].lr), lr3 = uni(D->node[2].lr);
   unsigned c1 = uni(D->worker[1].wstate[0]), c2 = uni(D->worker[2].wstate[0]), c3 = uni(D->worker[3].wstate[0]);
-  unsigned t1 = uni(D->worker[1].wstate[1]), t2 = uni(D->worker[2].wstate[1]), t3 = uni(D->worker[3].wstate[1]);
+  unsigned u1 = 0, u2 = 0, u3 = 0;   // the layers' updates, where gradients wait; else one for every gradient
   const long long t_begin = wall_clock64();
   // ---- weights: rows of every layer (an output per lane), columns of the upper two
   v4f w1[4 * NJ1], w2[4 * NJ2], v2[4 * NJ2], w3[4 * NJ3], v3[4 * NJ3];
@@ -313,13 +343,16 @@ __device__ __forceinline__ void role_mlp_one(const GQ AmpDev* D, const GQ Worker
   const GQ int* adm = uni_gq<int>(D->adm_inst);
   GQ float* loss_out = uni_gq<float>(D->loss_out);
   GQ int* correct_out = uni_gq<int>(D->correct_out);
-  const unsigned n_total = uni(D->n_total), n_inst = (unsigned)uni(D->data.n_inst), seq0 = uni(s_first_seq);
-  const int mak = uni(D->mak);
-  const bool bounded = uni(D->admit_bounded) != 0, logging = uni(s_log_cap) != 0u;
-  int limit = bounded ? 1 : mak, max_active = 0;
-  unsigned updates = 0, done = 0, admitted = 0, groups = 0, trained_all = 0;
+  const unsigned n_total = uni(D->n_total), n_inst = (unsigned)uni(D->data.n_inst);
+  const int four_at_most = uni(D->mak) < 4 ? uni(D->mak) : 4;
+  const bool books = uni(D->admit_bounded) != 0 || uni(s_log_cap) != 0u;
+  unsigned done = 0, groups = 0, trained_all = 0;
+  auto updates = [&]() { return EACH ? 3u * trained_all : u1 + u2 + u3; };
   if (threadIdx.x < 3) s_mo_logn[threadIdx.x] = 0;
-  if (threadIdx.x == 3) s_mo_full = 0;
+  if (threadIdx.x == 0) {
+    s_mo_full = 0;
+    s_mo_adm = {D->admit_bounded ? 1 : D->mak, 0, 0, 0, 0u};
+  }
   // the instance word of the launch's admission `at` (sign bit: forward only), the last one's beyond it
   auto word_of = [&](unsigned at) -> int {
     if (at >= n_total) at = n_total - 1u;
@@ -359,19 +392,16 @@ __device__ __forceinline__ void role_mlp_one(const GQ AmpDev* D, const GQ Worker
     asm volatile("" : "+v"(tid));
     const int lane = tid & 63, m4 = lane & 3, k4 = lane >> 2, o1 = p1.out0 + lane;
     const int mrow = m4 * MO_LD + k4;   // where an operand of this lane lies in a [message][unit] array, from its first term on
-    // ---------------- admission (role_ctrl has the policies): what is admitted and not in the group waits in front of the first layer
-    int flying = (int)(admitted - done);
-    if (flying < limit && admitted < n_total) {
-      const unsigned left = n_total - admitted, room = (unsigned)(limit - flying), more = room < left ? room : left;
-      if (logging && tid == 0)
-        for (unsigned a = admitted; a < admitted + more; ++a) mo_log_ctrl(D, W, 3, seq0 + a, word_of(a) < 0 ? 1u : 0u);
-      if (bounded)
-        for (unsigned a = (unsigned)tid; a < more; a += AMP_THREADS) upd_at[(admitted + a) % (unsigned)(mak + 4)] = updates;
-      admitted += more;
-      flying += (int)more;
+    // ---------------- admission
+    int n = four_at_most;
+    if (books) {
+      if (tid == 0) mo_admit(D, W, upd_at, done, updates());
+      lds_barrier();
+      if (uni(s_mo_adm.full)) break;
+      const int flying = uni(s_mo_adm.flying);
+      n = flying < 4 ? flying : 4;
     }
-    if (flying > max_active) max_active = flying;
-    int n = flying < 4 ? flying : 4;
+    if ((unsigned)n > n_total - done) n = (int)(n_total - done);
     if (!EACH) {
       const int r1 = uni(D->node[0].muf) - (int)c1, r2 = uni(D->node[1].muf) - (int)c2, r3 = uni(D->node[2].muf) - (int)c3;
       int room = r1 < r2 ? r1 : r2;
@@ -383,12 +413,13 @@ __device__ __forceinline__ void role_mlp_one(const GQ AmpDev* D, const GQ Worker
     const int nt = __popc(tr), lab_now = label;
     groups++;
     trained_all += (unsigned)nt;
-    if (logging && tid == 0) {
+    if (books && tid == 0) {
+      const unsigned seq0 = s_first_seq + done;
       for (int l = 0; l < 3; ++l) {
-        for (int m = 0; m < n; ++m) mo_log(D, l, 0, seq0 + done + m);
+        for (int m = 0; m < n; ++m) mo_log(D, l, 0, seq0 + (unsigned)m);
         for (int m = 0; m < n; ++m)
           if ((tr >> m) & 1u) {
-            mo_log(D, l, 1, seq0 + done + m);
+            mo_log(D, l, 1, seq0 + (unsigned)m);
             if (EACH) mo_log(D, l, 2, 0);
           }
       }
@@ -419,7 +450,6 @@ __device__ __forceinline__ void role_mlp_one(const GQ AmpDev* D, const GQ Worker
     }
     word = word_of(done + (unsigned)(n + m4));   // on its way
     lds_barrier();
-    if (logging && uni(s_mo_full)) break;
     PHASE(0);
     // ---------------- layer 2
     {
@@ -576,13 +606,8 @@ __device__ __forceinline__ void role_mlp_one(const GQ AmpDev* D, const GQ Worker
     }
     PHASE(6);
     // ---------------- updates (Section 3), retirement
-    unsigned made = 0;
-    if constexpr (EACH) {
-      t1 += (unsigned)nt;
-      t2 += (unsigned)nt;
-      t3 += (unsigned)nt;
-      made = 3u * (unsigned)nt;
-    } else if (nt) {
+    const unsigned before = EACH ? updates() - 3u * (unsigned)nt : updates();
+    if constexpr (!EACH) if (nt) {
       c1 += (unsigned)nt;
       c2 += (unsigned)nt;
       c3 += (unsigned)nt;
@@ -601,13 +626,12 @@ __device__ __forceinline__ void role_mlp_one(const GQ AmpDev* D, const GQ Worker
         if (wave == 0) b3[lane] = fmaf(f, gb3, b3[lane]);
         gb3 = 0.f;
         c3 = 0;
-        t3++;
-        made++;
+        u3++;
         mo_rows_back(T, w3, p3);
         lds_barrier();
         mo_cols(T, v3, q3);
         lds_barrier();
-        if (logging && tid == 0) mo_log(D, 2, 2, 0);
+        if (books && tid == 0) mo_log(D, 2, 2, 0);
       }
       if ((int)c2 >= uni(D->node[1].muf)) {
         const float f = -lr2 * (uni(D->node[1].mean) ? 1.f / (float)c2 : 1.f);
@@ -615,13 +639,12 @@ __device__ __forceinline__ void role_mlp_one(const GQ AmpDev* D, const GQ Worker
         if (p1.part == 0) b2[o1] = fmaf(f, gb2, b2[o1]);
         gb2 = 0.f;
         c2 = 0;
-        t2++;
-        made++;
+        u2++;
         mo_rows_back(T, w2, p2);
         lds_barrier();
         mo_cols(T, v2, p2);
         lds_barrier();
-        if (logging && tid == 0) mo_log(D, 1, 2, 0);
+        if (books && tid == 0) mo_log(D, 1, 2, 0);
       }
       if ((int)c1 >= uni(D->node[0].muf)) {
         const float f = -lr1 * (uni(D->node[0].mean) ? 1.f / (float)c1 : 1.f);
@@ -629,26 +652,16 @@ __device__ __forceinline__ void role_mlp_one(const GQ AmpDev* D, const GQ Worker
         if (p1.part == 0) b1[o1] = fmaf(f, gb1, b1[o1]);
         gb1 = 0.f;
         c1 = 0;
-        t1++;
-        made++;
-        if (logging && tid == 0) mo_log(D, 0, 2, 0);
+        u1++;
+        if (books && tid == 0) mo_log(D, 0, 2, 0);
       }
     }
-    if (logging && tid == 0)
-      for (int m = 0; m < n; ++m) mo_log_ctrl(D, W, 4, seq0 + done + m, 0);
-    if (bounded) {
-      // a message retires behind the updates it has brought about
-      const float bound = uni(D->max_staleness), per_worker = 1.f / (float)uni(D->n_updaters);
+    if (books && tid == 0)   // a message retires behind the updates it has brought about
       for (int m = 0; m < n; ++m) {
-        const unsigned now = updates + (EACH ? 3u * (unsigned)__popc(tr & ((2u << m) - 1u)) : m == n - 1 ? made : 0u);
-        const float seen = (float)(now - uni(upd_at[(done + (unsigned)m) % (unsigned)(mak + 4)])) * per_worker;
-        if (seen > bound)
-          limit = limit > 1 ? limit - 1 : 1;
-        else
-          limit = limit < mak ? limit + 1 : mak;
+        mo_log_ctrl(D, W, 4, s_first_seq + done + (unsigned)m, 0);
+        const unsigned now = EACH ? before + 3u * (unsigned)__popc(tr & ((2u << m) - 1u)) : m == n - 1 ? updates() : before;
+        if (D->admit_bounded) mo_retire(D, upd_at, done + (unsigned)m, now);
       }
-    }
-    updates += made;
     done += (unsigned)n;
     PHASE(7);
   }
@@ -656,9 +669,10 @@ __device__ __forceinline__ void role_mlp_one(const GQ AmpDev* D, const GQ Worker
   const int tid = threadIdx.x, o1 = p1.out0 + (tid & 63);
   if (tid == 0) {
     D->clock[1] = wall_clock64();
-    D->ctl[3] = updates;
-    D->ctl[4] = (unsigned)max_active;
-    D->ctl[5] = (unsigned)limit;
+    const unsigned mak = (unsigned)D->mak;
+    D->ctl[3] = updates();
+    D->ctl[4] = D->admit_bounded ? (unsigned)s_mo_adm.most : mak < n_total ? mak : n_total;
+    D->ctl[5] = (unsigned)s_mo_adm.limit;
   }
   if (tid < 3) {   // the layers' records and counters
     const GQ WorkerDev& w = D->worker[1 + tid];
@@ -705,7 +719,7 @@ __device__ __forceinline__ void role_mlp_one(const GQ AmpDev* D, const GQ Worker
   if (tid < 3) {
     unsigned* ws = D->worker[1 + tid].wstate;
     ws[0] = tid == 0 ? c1 : tid == 1 ? c2 : c3;
-    ws[1] = tid == 0 ? t1 : tid == 1 ? t2 : t3;
+    ws[1] += EACH ? trained_all : tid == 0 ? u1 : tid == 1 ? u2 : u3;
   }
 }
 
