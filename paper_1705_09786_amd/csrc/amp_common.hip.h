@@ -497,22 +497,27 @@ __device__ __forceinline__ OptCoef opt_at(OptCoef o, unsigned tstep) {
 
 __device__ __forceinline__ OptCoef opt_coef(const GQ NodeDev& nd, unsigned tstep) { return opt_at(opt_base(nd), tstep); }
 
-// n / (sqrt(x) + eps), from the hardware's estimates with one correction each and none of the special cases that the compiler's
-// root and division spell out (30 instructions for this one's 13, in every element of every Adam update).  Against float64 over
-// x = 1e-30 .. 1e6 with eps = 1e-8: at most 1.2 .. 2.4 ulp and 0.35 .. 0.43 on average, range by range the figures of
-// n / (sqrtf(x) + eps).  A root below 3e-19 counts as that.
+// n / (sqrt(x) + eps), from the hardware's estimates with one correction each and without the steps in which the compiler's root
+// and division round correctly (30 instructions for this one's 20, in every element of every Adam update).  Against float64 with
+// eps = 1e-8 at most 1.2 .. 2.4 ulp and 0.35 .. 0.43 on average, range by range of x the figures of n / (sqrtf(x) + eps).  Small x
+// pass the root 2^64 times as large, where its correction is exact; zero, infinities and NaN come out as of that division, 0 / 0
+// among them: without eps an element that never had a gradient becomes a NaN.
 // DIV: root and division as the compiler has them, where the update's code shares its registers with more than Adam and
 // is faster so (tree_update_units, plain SGD: 16 replicas of the tree model 11.5 -> 11.2 ms).
 template <bool DIV>
 __device__ __forceinline__ float adam_quotient(float n, float x, float eps) {
   if (DIV) return n / (sqrtf(x) + eps);
-  const float c = x < 1e-37f ? 1e-37f : x;   // a NaN stays one
+  const bool small = x < 0x1p-96f;
+  const float c = small ? x * 0x1p64f : x;
   const float y = __builtin_amdgcn_rsqf(c), s0 = c * y;
-  const float d = fmaf(fmaf(-s0, s0, c), 0.5f * y, s0) + eps;
+  float s = fmaf(fmaf(-s0, s0, c), 0.5f * y, s0);
+  s = small ? s * 0x1p-32f : s;
+  s = __builtin_amdgcn_classf(x, 0x260) ? x : s;   // +-0 and +infinity are their own roots
+  const float d = s + eps;
   float r = __builtin_amdgcn_rcpf(d);
   r = fmaf(fmaf(-d, r, 1.f), r, r);
   const float q = n * r;
-  return x > 3.3e38f ? n * 0.f : fmaf(fmaf(-d, q, n), r, q);
+  return __builtin_amdgcn_div_fixupf(fmaf(fmaf(-d, q, n), r, q), d, n);
 }
 
 template <bool DIV = false>
@@ -712,7 +717,7 @@ __device__ __forceinline__ float tanh_(float x) {
 }
 
 // 1 / (1 + e^-x); the quotient from the hardware's estimate and one correction, exact to the same last bits as a division over
-// x = -80 .. 80 (at most 2.6 ulp either way, the exponential's).
+// x = -80 .. 80 (at most 2.6 ulp either way, the exponential's); a result below the smallest normal number may be zero.
 __device__ __forceinline__ float sigmoidf_(float x) {
   const float d = 1.f + expf(-x), r = __builtin_amdgcn_rcpf(d);
   return d > 8.5e37f ? r : fmaf(fmaf(-d, r, 1.f), r, r);

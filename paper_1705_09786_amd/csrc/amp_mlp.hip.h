@@ -602,7 +602,8 @@ __device__ __noinline__ void role_mlp_wide(const GQ AmpDev* D, const GQ WorkerDe
         }
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          wa[e] = opt_step(o, wa[e], ga[e] * inv, m[e], v[e]);
+          const float stepped = opt_step(o, wa[e], ga[e] * inv, m[e], v[e]);
+          if (4 * cq + e < C) wa[e] = stepped;   // the padding stays zero, whatever slots it was stepped with
           if (o.kind != 0 && 4 * cq + e < C) {
             ndM[at + e] = m[e];
             if (o.kind == 2) ndV[at + e] = v[e];

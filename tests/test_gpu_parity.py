@@ -417,6 +417,46 @@ def test_rnn_cell_optimizer_slots_between_calls(emb, hidden, vocab, muf, opt):
     compare(g, rt, len(data), opt=opt, ref_losses=[rt.loss[len(data) + i] for i in range(len(data))])
 
 
+def test_rnn_adam_with_gradients_whose_squares_vanish():
+    """Gradients around 1e-17 and eps far below: second moments of 1e-37 and less, whose roots the update must still take.  The output
+    layer stands still at weights that give such gradients.  A second moment is itself binary32, in steps of 1.4e-45 down there:
+    twelve updates of 4,000 elements on normally distributed gradients, with moments in binary32 and in float64, part by 4e-7 of
+    a weight at gradients of 1e-17 and by 3e-6 at 1e-18; the bound is 5e-5 of rms(W) = 0.1.  One in forty of the gradients is below
+    3e-19, the root of 1e-37."""
+    dims = dict(vocab=13, emb=50, hidden=37, n_class=7)
+    data = synth.make_rnn(60, 35, dims, min_len=2, max_len=9)
+    fp = synth.init_params("rnn", dims, 9)
+    fp[2] = (fp[2] * np.float32(1e-15)).astype(np.float32)
+    adam = dict(kind="adam", lr=0.0005, beta1=0.9, beta2=0.999, eps=1e-20)
+    ml, me = runner.max_len_of("rnn", data)
+    tr = runner.Trainer("rnn", dims, fp, 6, ml, me, len(data), arena_bytes=1 << 28)
+    a = tr.amp
+    a.set_min_update_frequency(-1, 24)
+    a.set_optimizer(-1, B.OPT_ADAM, **{k: v for k, v in adam.items() if k != "kind"})
+    a.set_optimizer(2, B.OPT_SGD, lr=0.0)
+    a.set_event_log(4096)
+    tr.submit_all(data)
+    a.train(1)
+    g = dict(params=tr.params(), losses=a.get_instance_losses().astype(np.float64), logs=a.get_event_log())
+    rt = oracle_runtime("rnn", dims, fp, 24, adam)
+    rt.set_optimizer("out", kind="sgd", lr=0.0)
+    rt.replay(data, named_logs("rnn", dims, g["logs"][1:]))
+    cell = rt.ppt[1]
+    assert np.abs(oamp.C.pack_node(cell.P) - fp[1]).max() > 3e-4   # whole steps were taken
+    compare(g, rt, len(data), opt=adam)
+
+
+def test_tree_adam_without_eps():
+    """Ragged tiles of 37 units: what pads them has neither gradient nor slots, and without eps its step would be 0 / 0."""
+    opt = dict(kind="adam", lr=1e-6, beta1=0.9, beta2=0.999, eps=0.0)
+    data = synth.make_tree(30, 5, TREE_ODD, min_leaves=2)
+    fp = synth.init_params("tree", TREE_ODD, 8)
+    for tiles in ({1: 3, 2: 5}, {1: 2, 2: 3}):
+        g = gpu_train("tree", TREE_ODD, fp, data, 8, 3, opt, tiles=tiles, lookup_muf=5)
+        rt = oracle_replay("tree", TREE_ODD, fp, data, g["logs"], 3, opt, lookup_muf=5)
+        compare(g, rt, len(data), opt=opt)
+
+
 @pytest.mark.parametrize("mak,sync", [(80, 0), (80, 30), (78, 30)])
 def test_rnn_cell_copies_with_many_sequences_in_flight(mak, sync):
     """Two copies of a small cell at and one below the number in flight that gives each the worker of the larger batches,
