@@ -10,7 +10,7 @@ from paper_1705_09786_amd import runner, synth
 
 from oracle import amp as oamp
 
-from util import (RELU_TAU, check_controller_log, compare, compare_up_to_relu_decisions, elem_tol, elementwise_err, gpu_train,
+from util import (OPT_KIND, RELU_TAU, check_controller_log, compare, compare_up_to_relu_decisions, elem_tol, elementwise_err, f32, gpu_train,
                   named_logs, oracle_replay, oracle_runtime, rel_err)
 
 pytestmark = pytest.mark.gpu
@@ -138,6 +138,56 @@ def test_mlp_on_one_workgroup_carries_gradients_and_thresholds(d_in, hidden, n_c
             break
         flips.append(kinks[0])
     raise AssertionError((bad, flips))
+
+
+SGD02 = dict(kind="sgd", lr=0.02)
+
+
+@pytest.mark.parametrize("n,calls", [
+    (33, [((4, 4, 4), SGD02), ((3, 3, 3), SGD02), ((4, 4, 4), SGD02)]),       # one workgroup -> a workgroup per layer -> one
+    (31, [((3, 3, 3), SGD02), ((4, 5, 6), SGD02), ((3, 3, 3), SGD02)]),       # the other way round
+    (33, [((4, 4, 4), SGD02), ((4, 4, 4), MLP_MOM), ((4, 4, 4), SGD02)])])
+def test_mlp_gradients_that_change_workers(n, calls):
+    """Gradients that wait between calls whose thresholds or optimizers put 64-128-128-10 on one workgroup, on a workgroup per layer
+    and back: either leaves them where the other takes them up.  Tolerance: that of every replay."""
+    dims = dict(d_in=64, hidden=128, n_class=10)
+    data = synth.make_mlp(n, 47, dims)   # n leaves gradients waiting behind every call
+    fp = synth.init_params("mlp", dims, 15)
+    tr = runner.Trainer("mlp", dims, fp, 4, 1, 0, n, arena_bytes=1 << 28)
+    a = tr.amp
+    a.set_event_log(16 * n + 64)
+    tr.submit_all(data)
+    taken = []
+    for mufs, opt in calls:
+        a.set_optimizer(-1, OPT_KIND[opt["kind"]], **{k: v for k, v in opt.items() if k != "kind"})
+        for node, muf in enumerate(mufs):
+            a.set_min_update_frequency(node, muf)
+        a.train(1)
+        taken.append((a.get_event_log(), a.get_instance_losses().astype(np.float64), tr.params()))
+    flips = []
+    for _ in range(8):   # a ReLU decision within rounding of zero may fall either way (compare_up_to_relu_decisions)
+        rt = oracle_runtime("mlp", dims, fp, 1, SGD02)
+        for node in rt.nodes:
+            if isinstance(node, oamp.NPT) and node.name.startswith("relu"):
+                node.kink_tau, node.flip = RELU_TAU, {(st, i) for (name, st, i) in flips if name == node.name}
+        bad = None
+        for call, ((mufs, opt), (logs, losses, params)) in enumerate(zip(calls, taken)):
+            if call == 0 or opt is not calls[call - 1][1]:
+                rt.set_optimizer(**{k: f32(v) if isinstance(v, float) else v for k, v in opt.items()})
+            for node, muf in zip(rt.ppt, mufs):
+                node.muf = muf
+            rt.replay(data, named_logs("mlp", dims, logs[1:]), first_seq=call * n)
+            ref = np.array([rt.loss[call * n + s] for s in range(n)])
+            errs = [float(np.abs(losses - ref).max() / max(1.0, np.abs(ref).max()))]
+            errs += [rel_err(p, oamp.C.pack_node(node.P)) for p, node in zip(params, rt.ppt)]
+            if max(errs) > 1e-5:
+                bad = (call, errs)
+                break
+        kinks = [k for k in [(node.name, st, i) for node in rt.nodes if isinstance(node, oamp.NPT) for (st, i) in node.kinks] if k not in flips]
+        if bad is None or not kinks:
+            break
+        flips.append(kinks[0])
+    assert bad is None, (bad, flips)
 
 
 @pytest.mark.parametrize("d_in,hidden,muf,cap,mixed", [
