@@ -26,12 +26,6 @@ extern __shared__ __attribute__((aligned(256))) float amp_lds[];
 __device__ __forceinline__ unsigned ld_u32(const unsigned* p) {
   return __hip_atomic_load((const GQ unsigned*)p, __ATOMIC_RELAXED, AGENT);
 }
-// s_nowb: every workgroup this one exchanges data with runs on the same XCD (a launch that packs a replica into
-// one die, checked against the hardware's die number when the kernel starts).  Stores that have been acknowledged
-// are then in the L2 all of them read through, so a release needs no L2 write-back, only the wait.  Measured with
-// two workgroups handing 4 KB back and forth on one die: 0.93 us per hand-over instead of 1.31 us, every word right.
-// The HIP memory model has no such rule: it is how gfx950's caches work.  -DAMP_STRICT_JOIN keeps to the model instead, here and
-// wherever strict_release / strict_acquire or ring_put_near stand.
 // Waits for the wave's own loads and stores.  By the builtin and not in inline asm, whose text the compiler does not read: it
 // would take every load in front of it for one that may still be on its way, and wait again -- for all that was issued since --
 // where such a load's register is next used.  (AMP_WAIT_TEXT: in inline asm all the same.  The graph workers, whose passes differ
@@ -46,6 +40,12 @@ __device__ __forceinline__ void wait_vm() {
   __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0), the other counters left alone
   asm volatile("" ::: "memory");
 }
+// s_nowb: every workgroup this one exchanges data with runs on the same XCD (a launch that packs a replica into
+// one die, checked against the hardware's die number when the kernel starts).  Stores that have been acknowledged
+// are then in the L2 all of them read through, so a release needs no L2 write-back, only the wait.  Measured with
+// two workgroups handing 4 KB back and forth on one die: 0.93 us per hand-over instead of 1.31 us, every word right.
+// The HIP memory model has no such rule: it is how gfx950's caches work.  -DAMP_STRICT_JOIN keeps to the model instead, here and
+// wherever strict_release / strict_acquire or ring_put_near stand.
 __shared__ int s_nowb;
 __shared__ unsigned s_first_seq;   // admission number of this replica's first admission of the launch
 __device__ __forceinline__ void fence_release() {

@@ -1,6 +1,7 @@
 // Workers of the MLP: one per linear layer `aux` (0..2) with its ReLU fused; the last layer also hosts the softmax
-// loss, which turns the forward message round.  For the models that one compute unit does not hold (amp_mlp_one.hip.h): inputs
-// wider than 128, optimizers with slots, gradients to keep for more than 64 x 64.
+// loss, which turns the forward message round.  For the models that are not the work of one workgroup (mlp_one_fits in
+// amp_mlp_one.hip.h has the rule and both sides' figures): inputs wider than 128, training with slots, and training with
+// gradients to keep at more than 64 hidden units where the inputs are wider than 64 too or an update comes every two or three.
 //
 // Slot storage, rows of hidden rounded up to 4 floats: buf[0] = act1, buf[1] = act2 (post-ReLU outputs), buf[2] =
 // gradient w.r.t. act1, buf[3] = gradient w.r.t. act2.

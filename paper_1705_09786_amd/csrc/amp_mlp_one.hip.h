@@ -5,8 +5,8 @@
 // workgroups (role_mlp_regs) nearly all of its time is hand-overs -- poll, fetch, product, drain, post.  Here a stage ends at a
 // workgroup barrier and its result is in LDS, and up to four instances at a time (the messages a 4x4x1 matrix instruction
 // takes) go through a stage together.  Measured, 64-128-128-10 with an update per gradient: 1,024 instances with four in
-// flight 3.54 -> 1.18 ms, 4.5 us a group, of which the 450 matrix instructions (8.4 cycles each) are 1.6; a call on eight
-// instances one at a time 124 -> 90 us.  Evaluation of a small model 2.07 -> 0.42 ms.
+// flight 3.54 -> 1.21 ms, 4.5 us a group, of which a wave's 454 matrix instructions (8 cycles each and 8.4 from one to the
+// next) are 1.6; a call on eight instances one at a time 124 -> 90 us.  Evaluation of a small model 2.07 -> 0.42 ms.
 //   * Weights stay in registers, once with an output per lane (forward) and, where a gradient goes on to the layer below, once
 //     with an input per lane (backward); one wave to a SIMD has 512 registers a lane.  Operands are the instances' values from
 //     LDS, broadcast to the sixteen blocks of the instruction; the four waves split outputs and contraction, their parts meet in
@@ -28,7 +28,8 @@
 
 // Plain SGD at layers of up to 128 x 128, and every evaluation of such layers.  Gradients that wait for an update take as many
 // registers as the weights: with more than 64 inputs and more than 64 hidden units that is more than there are, and with more
-// than 64 hidden units alone it pays from four gradients an update on (512 instances of 64-128-128-10, a workgroup per layer /
+// than 64 hidden units alone it pays from four gradients an update on -- at three, two in flight lose more than one or four
+// win -- (512 instances of 64-128-128-10, a workgroup per layer /
 // here: an update every 2 4.41 / 4.57 ms with one in flight, 2.77 / 2.96 with two, 2.22 / 2.95 with four; every 3 4.36 / 4.26,
 // 2.74 / 3.17, 2.20 / 2.13; every 4 4.36 / 4.08, 2.74 / 2.47, 2.19 / 1.68; up to 64 units 4.37 / 1.98, 2.73 / 1.24, 2.19 / 1.25 already
 // at every 2).  The same in every workgroup of the replica.

@@ -90,11 +90,11 @@ def test_mlp_sizes_replay_parity(d_in, hidden, n_class, mak, muf, opt):
 @pytest.mark.parametrize("d_in,hidden,n_class,mak,mufs,n", [
     (64, 128, 10, 4, (1, 1, 1), 30), (128, 128, 64, 3, (1, 1, 1), 29), (65, 65, 17, 4, (1, 1, 1), 27), (128, 64, 16, 8, (1, 1, 1), 30),
     (16, 16, 1, 2, (1, 1, 1), 31), (64, 128, 10, 4, (7, 7, 7), 31), (33, 65, 33, 8, (5, 3, 2), 33), (128, 64, 64, 4, (1, 4, 6), 29),
-    (7, 3, 5, 5, (2, 1, 9), 30), (65, 65, 10, 4, (3, 3, 3), 31)])
+    (7, 3, 5, 5, (2, 1, 9), 30), (65, 65, 10, 4, (3, 3, 3), 31), (33, 65, 33, 8, (5, 4, 7), 33)])
 def test_mlp_on_one_workgroup_carries_gradients_and_thresholds(d_in, hidden, n_class, mak, mufs, n):
     """The sizes at which the one-workgroup MLP changes its split (64 inputs, hidden units and classes, either side), groups of
-    four cut by thresholds that differ from layer to layer, and gradients that wait from one call for the next (the last
-    case, with gradients to keep at more than 64 x 64, is the layers' own workers').  Tolerance: that of every replay."""
+    four cut by thresholds that differ from layer to layer, and gradients that wait from one call for the next (at thresholds
+    of 5, 3, 2 and of 3 at more than 64 hidden units those of the layers' own workers).  Tolerance: that of every replay."""
     dims = dict(d_in=d_in, hidden=hidden, n_class=n_class)
     data = synth.make_mlp(n, 41, dims)
     fp = synth.init_params("mlp", dims, 12)
@@ -452,7 +452,7 @@ def test_rnn_cell_with_many_sequences_in_flight(emb, hidden, mak, muf, opt):
     (50, 37, 13, 3, RNN_MOM), (64, 64, 20, 4, RNN_ADAM), (65, 64, 20, 4, RNN_MOM), (64, 65, 20, 4, RNN_MOM), (128, 64, 20, 5, RNN_ADAM),
     (128, 128, 20, 5, RNN_MOM), (16, 16, 5, 1, RNN_ADAM_MUF3)])
 def test_rnn_cell_optimizer_slots_between_calls(emb, hidden, vocab, muf, opt):
-    """Slots in LDS for cells of two to four 64 x 64 pieces, in HBM beyond that: either way the second call goes on from what
+    """Slots in LDS for cells of two or three 64 x 64 pieces where they fit beside the table, in HBM otherwise: either way the second call goes on from what
     the first one left, in more sequences in flight than the worker holds, with pairs carried over."""
     dims = dict(vocab=vocab, emb=emb, hidden=hidden, n_class=7)
     data = synth.make_rnn(62, 35, dims, min_len=1, max_len=11)
