@@ -509,6 +509,9 @@ __device__ __noinline__ void role_rnn_cell_reg(const GQ AmpDev* D, const GQ Work
   if (tid0 < 64) lay_out(lane0, 0, (int)count, (int)lcount, false, 0ull);
   lds_barrier();
   bool landed = false;   // the stores of the batch before have been waited for already
+  // The loop begins at a set place: its matrix instructions, 8 bytes each, run slower where they straddle 8-byte boundaries (4,000
+  // sequences 68.5 -> 70.4 ms), and where they lie would otherwise follow from the size of other functions.
+  asm volatile(".p2align 5\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0");
   for (;;) {
     // thread indices and what follows from them are computed anew in every batch: cheaper than the spills they cost as
     // loop invariants
