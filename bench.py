@@ -37,7 +37,7 @@ DEFAULTS = {
     # cfg: mak, muf, lookup muf, optimizer
     1: dict(mak=4, muf=1, lmuf=None, opt=("sgd", dict(lr=0.05))),
     2: dict(mak=16, muf=16, lmuf=16, opt=("sgd", dict(lr=0.05))),
-    # 10 leaf + 17 branch tiles: the best rate for the CUs it takes (56.2k trees/s on 30 workgroups): 15 leaf and 9 or 8
+    # 10 leaf + 17 branch tiles: the best rate for the CUs it takes (56.0k trees/s on 30 workgroups): 15 leaf and 9 or 8
     # branch units per tile are 45 and 45 or 40 rows, three 16-row blocks almost full, where 8 + 16 tiles (57 and 50
     # rows, 44.5k trees/s) pad to four; the fewest tiles that fit LDS (5 + 8, 16 workgroups, 31.9k trees/s) use each CU
     # better and are what the replicated run packs two per XCD
