@@ -497,27 +497,24 @@ __device__ __forceinline__ OptCoef opt_at(OptCoef o, unsigned tstep) {
 
 __device__ __forceinline__ OptCoef opt_coef(const GQ NodeDev& nd, unsigned tstep) { return opt_at(opt_base(nd), tstep); }
 
-// n / (sqrt(x) + eps), from the hardware's estimates with one correction each and without the steps in which the compiler's root
-// and division round correctly (30 instructions for this one's 20, in every element of every Adam update).  Against float64 with
-// eps = 1e-8 at most 1.2 .. 2.4 ulp and 0.35 .. 0.43 on average, range by range of x the figures of n / (sqrtf(x) + eps).  Small x
-// pass the root 2^64 times as large, where its correction is exact; zero, infinities and NaN come out as of that division, 0 / 0
-// among them: without eps an element that never had a gradient becomes a NaN.
+// Adam's lr c1 m / (sqrt(c2 v) + eps), from the hardware's estimates with one correction each and without the steps in which the
+// compiler's root and division round correctly (33 instructions for this one's 20, in every element of every Adam update).  Against
+// float64 with eps = 1e-8 at most 1.2 .. 2.4 ulp and 0.35 .. 0.43 on average, range by range of c2 v the figures of the division.  Small
+// moments pass the root 2^64 times as large, where its correction is exact; zero, infinities and NaN come out as of that
+// division, 0 / 0 among them: without eps an element that never had a gradient becomes a NaN.
 // DIV: root and division as the compiler has them, where the update's code shares its registers with more than Adam and
 // is faster so (tree_update_units, plain SGD: 16 replicas of the tree model 11.5 -> 11.2 ms).
 template <bool DIV>
-__device__ __forceinline__ float adam_quotient(float n, float x, float eps) {
-  if (DIV) return n / (sqrtf(x) + eps);
-  const bool small = x < 0x1p-96f;
-  const float c = small ? x * 0x1p64f : x;
-  const float y = __builtin_amdgcn_rsqf(c), s0 = c * y;
-  float s = fmaf(fmaf(-s0, s0, c), 0.5f * y, s0);
-  s = small ? s * 0x1p-32f : s;
-  s = __builtin_amdgcn_classf(x, 0x260) ? x : s;   // +-0 and +infinity are their own roots
-  const float d = s + eps;
+__device__ __forceinline__ float adam_quotient(float m, float v, float lr, float c1, float c2, float eps) {
+  if (DIV) return lr * (m * c1) / (sqrtf(v * c2) + eps);
+  const bool small = v < 0x1p-96f;
+  const float c = v * (small ? c2 * 0x1p64f : c2), n = m * (lr * c1);
+  const float y = fminf(__builtin_amdgcn_rsqf(c), 3e38f), s0 = c * y;   // (finite: the root of zero is zero)
+  const float d = fmaf(fmaf(fmaf(-s0, s0, c), 0.5f * y, s0), small ? 0x1p-32f : 1.f, eps);
   float r = __builtin_amdgcn_rcpf(d);
   r = fmaf(fmaf(-d, r, 1.f), r, r);
   const float q = n * r;
-  return __builtin_amdgcn_div_fixupf(fmaf(fmaf(-d, q, n), r, q), d, n);
+  return __builtin_amdgcn_div_fixupf(fmaf(fmaf(-d, q, n), r, q), c + eps, n);   // c + eps is zero, infinite or no number where the denominator is
 }
 
 template <bool DIV = false>
@@ -532,7 +529,7 @@ __device__ __forceinline__ float opt_apply(const OptCoef& o, float w, float g, G
   const float v = fmaf(o.b2, V[gi], (1.f - o.b2) * g * g);
   M[gi] = m;
   V[gi] = v;
-  return w - adam_quotient<DIV>(o.lr * (m * o.c1), v * o.c2, o.eps);
+  return w - adam_quotient<DIV>(m, v, o.lr, o.c1, o.c2, o.eps);
 }
 
 // The optimizer of the node this workgroup serves, copied into LDS when the kernel starts: an update reads it there
@@ -577,7 +574,7 @@ __device__ __forceinline__ float opt_step(const OptCoef& o, float w, float g, fl
   }
   m = fmaf(o.b1, m, (1.f - o.b1) * g);
   v = fmaf(o.b2, v, (1.f - o.b2) * g * g);
-  return w - adam_quotient<DIV>(o.lr * (m * o.c1), v * o.c2, o.eps);
+  return w - adam_quotient<DIV>(m, v, o.lr, o.c1, o.c2, o.eps);
 }
 
 __device__ __forceinline__ float opt_apply(const OptCoef& o, float w, float g, float* Mp, float* Vp, long long gi) {

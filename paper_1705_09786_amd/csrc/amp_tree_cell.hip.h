@@ -431,14 +431,13 @@ __device__ __noinline__ void role_tree_cell_lds(const GQ AmpDev* D, const GQ Wor
               // rows and columns of the padding have no gradient
               w -= (o.lr * inv) * (v4f){g[u][0][e], g[u][1][e], g[u][2][e], g[u][3][e]};
             } else {
-              // (without a branch for each element: a padding one has no gradient and no slots either)
+              // (without a branch for each element: a padding one has no gradient and no slots either, and stays zero)
 #pragma unroll
               for (int v = 0; v < 4; ++v) {
                 const bool real = (valid[u] >> (4 * v + e)) & 1u;
                 float m = KEEP ? sm[KEEP ? u : 0][v][e] : real ? m4[v][e] : 0.f;
                 float s = KEEP ? (OPT == 2 ? sv[KEEP && OPT == 2 ? u : 0][v][e] : 0.f) : real ? v4[v][e] : 0.f;
-                const float stepped = opt_step(o, w[v], g[u][v][e] * inv, m, s);
-                w[v] = real ? stepped : 0.f;   // 0 / 0 without eps
+                w[v] = opt_step(o, w[v], g[u][v][e] * inv, m, s);
                 if (KEEP) {
                   sm[KEEP ? u : 0][v][e] = m;
                   if (OPT == 2) sv[KEEP && OPT == 2 ? u : 0][v][e] = s;
@@ -451,6 +450,9 @@ __device__ __noinline__ void role_tree_cell_lds(const GQ AmpDev* D, const GQ Wor
             }
             *(LDSQ v4f*)(wp + e * ldw) = w;
           }
+          if (OPT == 2 && ob.eps == 0.f)   // but for 0 / 0
+            for (int k = 0; k < 16; ++k)
+              if (!((valid[u] >> k) & 1u)) wp[(k & 3) * ldw + (k >> 2)] = 0.f;
 #pragma unroll
           for (int v = 0; v < 4; ++v) g[u][v] = zero;
         }

@@ -31,7 +31,6 @@ static float est(double v) {
 #define __builtin_amdgcn_rsqf(x) est(1.0 / std::sqrt((double)(x)))
 #define __builtin_amdgcn_rcpf(x) est(1.0 / (double)(x))
 #define __builtin_amdgcn_exp2f(x) est(std::exp2((double)(x)))
-#define __builtin_amdgcn_classf(x, mask) ((x) == 0.f || (std::isinf(x) && (x) > 0.f))
 static float __builtin_amdgcn_div_fixupf(float q, float d, float n) {
   if (std::isnan(d) || std::isnan(n) || (d == 0.f && n == 0.f) || (std::isinf(d) && std::isinf(n))) return NAN;
   const float sign = (std::signbit(d) != std::signbit(n)) ? -1.f : 1.f;
@@ -40,9 +39,9 @@ static float __builtin_amdgcn_div_fixupf(float q, float d, float n) {
   return std::copysign(std::fabs(q), sign);
 }
 %s
-extern "C" void run(int which, int off, const float* a, const float* b, float eps, float* o, int n) {
+extern "C" void run(int which, int off, const float* a, const float* b, float lr, float c2, float eps, float* o, int n) {
   g_off = off;
-  for (int i = 0; i < n; ++i) o[i] = which == 0 ? tanh_(a[i]) : which == 1 ? sigmoidf_(a[i]) : adam_quotient<false>(a[i], b[i], eps);
+  for (int i = 0; i < n; ++i) o[i] = which == 0 ? tanh_(a[i]) : which == 1 ? sigmoidf_(a[i]) : adam_quotient<false>(a[i], b[i], lr, 1.f, c2, eps);
 }
 """
 
@@ -62,12 +61,12 @@ def device_math(tmp_path_factory):
     assert p.returncode == 0, p.stdout
     lib = ct.CDLL(str(so))
 
-    def run(which, off, a, b=None, eps=0.0):
+    def run(which, off, a, b=None, eps=0.0, lr=1.0, c2=1.0):
         a = np.ascontiguousarray(a, np.float32)
         b = np.ascontiguousarray(a if b is None else b, np.float32)
         o = np.empty_like(a)
         p = lambda v: v.ctypes.data_as(ct.POINTER(ct.c_float))
-        lib.run(which, off, p(a), p(b), ct.c_float(eps), p(o), a.size)
+        lib.run(which, off, p(a), p(b), ct.c_float(lr), ct.c_float(c2), ct.c_float(eps), p(o), a.size)
         return o
     return run
 
@@ -118,6 +117,12 @@ def test_adam_quotient(device_math, lo, hi, eps, off):
     ref = n.astype(np.float64) / d
     assert ulps(device_math(2, off, n, x, eps), ref)[keep].max() <= 2.4
     assert np.allclose(device_math(2, off, n, x, eps), ref, rtol=1e-6, atol=1e-30)
+    # the bias correction of an early update on top of the moment
+    if hi < 1e30:
+        d = np.sqrt(x.astype(np.float64) * 1000.0) + float(eps)
+        got, ref = device_math(2, off, n, x, eps, lr=0.5, c2=1000.0), 0.5 * n.astype(np.float64) / d
+        normal = keep & (x > 1.2e-38)   # (the product is rounded to binary32's last denormal bit)
+        assert ulps(got, ref)[normal].max() <= 2.9
 
 
 def test_special_values(device_math):
