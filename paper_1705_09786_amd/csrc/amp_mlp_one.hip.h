@@ -27,12 +27,13 @@
 #define MO_LT 132   // row stride of a layer's tile: rows 16-byte aligned and spread over the banks
 
 // Plain SGD at layers of up to 128 x 128, and every evaluation of such layers.  Gradients that wait for an update take as many
-// registers as the weights: with more than 64 inputs and more than 64 hidden units that is more than there are, and with more
-// than 64 hidden units alone it pays from four gradients an update on -- at three, two in flight lose more than one or four
-// win -- (512 instances of 64-128-128-10, a workgroup per layer /
-// here: an update every 2 4.41 / 4.57 ms with one in flight, 2.77 / 2.96 with two, 2.22 / 2.95 with four; every 3 4.36 / 4.26,
-// 2.74 / 3.17, 2.20 / 2.13; every 4 4.36 / 4.08, 2.74 / 2.47, 2.19 / 1.68; up to 64 units 4.37 / 1.98, 2.73 / 1.24, 2.19 / 1.25 already
-// at every 2).  The same in every workgroup of the replica.
+// registers as the weights: with more than 64 inputs and more than 64 hidden units that is more than there are.  With more than 64
+// hidden units alone the line is at four gradients an update, where it was drawn when the loop with waiting gradients spilled
+// (an update every 3 then took as long on one workgroup as on three).  It no longer does, and equal thresholds of 2 and 3 would
+// gain as well; unequal ones as small cut the groups to one or two instances.  512 instances of 64-128-128-10, a workgroup per
+// layer / here, with one, two and four in flight: an update every 2 4.13 / 2.53 ms, 2.57 / 1.65, 2.09 / 1.64; every 3 4.12 / 2.33, 2.52 /
+// 1.74, 2.06 / 1.15; every 4 4.15 / 2.24, 2.55 / 1.34, 2.05 / 0.89; every 8 4.15 / 2.10, 2.53 / 1.19, 2.03 / 0.74; 64 hidden units
+// every 2 4.11 / 1.98, 2.54 / 1.25, 2.06 / 1.25.  The same in every workgroup of the replica.
 __device__ __forceinline__ bool mlp_one_each(const GQ AmpDev* D) {   // no gradient ever waits
   bool each = true;
 #pragma unroll
@@ -196,13 +197,12 @@ __device__ __forceinline__ void mo_keep(v4f (&w)[N]) {
 }
 
 __shared__ unsigned s_mo_logn[3];
-__shared__ int s_mo_full;   // a record is full: of the thread that writes them alone
+__shared__ int s_mo_full;   // a record is full: of the threads that write them alone
 
 // An event of layer l, in its own worker's record.  ONE thread.
 __device__ __forceinline__ void mo_log(const GQ AmpDev* D, int l, int kind, unsigned seq) {
   const GQ WorkerDev& w = D->worker[1 + l];
   const unsigned n = s_mo_logn[l];
-  if (s_log_cap == 0u) return;
   if (n >= w.log_cap) {
     raise_abort(D, ABORT_LOG_FULL, 1 + l);
     s_mo_full = 1;
@@ -213,41 +213,52 @@ __device__ __forceinline__ void mo_log(const GQ AmpDev* D, int l, int kind, unsi
 }
 // The same of the controller.
 __device__ __forceinline__ void mo_log_ctrl(const GQ AmpDev* D, const GQ WorkerDev* W, int kind, unsigned seq, unsigned local) {
-  if (s_log_cap && s_logn >= s_log_cap) s_mo_full = 1;
+  if (s_logn >= s_log_cap) s_mo_full = 1;
   log_event(D, W, &s_logn, 0, kind, seq, local);
 }
 
-// The controller's books, kept by ONE thread and only where somebody asks: a bounded limit, or the record.  (As scalars of every
-// wave they cost the loop registers it does not have: 1,024 instances 1.21 -> 1.26 ms.)
-struct MoAdmission {
+// The controller's books, kept by ONE wave and only where somebody asks: a bounded limit, or the record.  (As scalars of every
+// wave they cost the loop registers it does not have: 1,024 instances 1.21 -> 1.26 ms.)  What a group's events, its
+// retirements and the admissions behind them come to is known as it begins, so that wave settles it beside the loss layer.
+struct alignas(16) MoAdmission {
   int limit, flying, most;   // in flight at most / now / at most so far
   int full;                  // s_mo_full as the group begins: every wave leaves in front of the same one
+  int mak, in, out;          // places of the next admission and the next retirement in upd_at, which has max_active_keys of them
   unsigned admitted;
+  float bound, per_worker;   // (no bound: one that nothing reaches)
 };
 __shared__ MoAdmission s_mo_adm;
 
-// Admissions in front of a group, by the policies of role_ctrl: what is in flight and not in the group waits in front of the first
-// layer.  upd_at: [admission modulo max_active_keys] updates applied before it.
-__device__ __forceinline__ void mo_admit(const GQ AmpDev* D, const GQ WorkerDev* W, LDSQ unsigned* upd_at, unsigned done, unsigned updates) {
-  const unsigned n_total = D->n_total, n_inst = (unsigned)D->data.n_inst, mak = (unsigned)D->mak;
-  unsigned a = s_mo_adm.admitted;
-  for (; (int)(a - done) < s_mo_adm.limit && a < n_total; ++a) {
-    const int word = D->adm_inst ? D->adm_inst[a] : (int)(a % n_inst);
-    mo_log_ctrl(D, W, 3, s_first_seq + a, word < 0 ? 1u : 0u);
-    upd_at[a % mak] = updates;
-  }
-  s_mo_adm.full = s_mo_full;
-  s_mo_adm.admitted = a;
-  s_mo_adm.flying = (int)(a - done);
-  if ((int)(a - done) > s_mo_adm.most) s_mo_adm.most = (int)(a - done);
-}
-// An instance of admission `a` retires when `updates` have been applied.
-__device__ __forceinline__ void mo_retire(const GQ AmpDev* D, const LDSQ unsigned* upd_at, unsigned a, unsigned updates) {
-  const float seen = (float)(updates - upd_at[a % (unsigned)D->mak]) * (1.f / (float)D->n_updaters);
-  if (seen > D->max_staleness)
-    s_mo_adm.limit = s_mo_adm.limit > 1 ? s_mo_adm.limit - 1 : 1;
-  else
-    s_mo_adm.limit = s_mo_adm.limit < D->mak ? s_mo_adm.limit + 1 : D->mak;
+// A group's n <= 4 instances retire -- lane m's when `then` updates have been applied -- and others are admitted behind `after`, by the
+// policies of role_ctrl: what is in flight and not in a group waits in front of the first layer.  done: retired with this group;
+// upd_at: updates applied before each admission in flight.
+__device__ __forceinline__ void mo_settle(const GQ AmpDev* D, const GQ WorkerDev* W, int lane, LDSQ unsigned* upd_at, unsigned n_total,
+                                          unsigned done, int n, unsigned then, unsigned after) {
+  MoAdmission A = s_mo_adm;
+  const int full = s_mo_full, at = A.out + (lane < n ? lane : 0);
+  const float seen = (float)(then - upd_at[at < A.mak ? at : at - A.mak]) * A.per_worker;
+  const unsigned over = (unsigned)__ballot(seen > A.bound);
+#pragma unroll
+  for (int m = 0; m < 4; ++m)
+    if (m < n) {
+      A.limit += (over >> m) & 1u ? -1 : 1;
+      A.limit = A.limit < 1 ? 1 : A.limit > A.mak ? A.mak : A.limit;
+    }
+  A.out = A.out + n < A.mak ? A.out + n : A.out + n - A.mak;
+  const unsigned left = n_total - A.admitted;
+  A.flying = (int)(A.admitted - done);
+  int more = A.limit - A.flying;
+  more = more < 0 ? 0 : (unsigned)more < left ? more : (int)left;
+  for (int i = lane; i < more; i += 64) upd_at[A.in + i < A.mak ? A.in + i : A.in + i - A.mak] = after;
+  if (s_log_cap && lane == 0)
+    for (unsigned i = A.admitted; i < A.admitted + (unsigned)more; ++i)
+      mo_log_ctrl(D, W, 3, s_first_seq + i, D->adm_inst && D->adm_inst[i] < 0 ? 1u : 0u);
+  A.in = A.in + more < A.mak ? A.in + more : A.in + more - A.mak;
+  A.full = full;
+  A.admitted += (unsigned)more;
+  A.flying += more;
+  if (A.flying > A.most) A.most = A.flying;
+  if (lane == 0) s_mo_adm = A;
 }
 
 // EACH: an update per gradient at every layer (and every evaluation): no gradient is kept.  BIG: more than 64 hidden units, two
@@ -352,7 +363,7 @@ __device__ __forceinline__ void role_mlp_one(const GQ AmpDev* D, const GQ Worker
   if (threadIdx.x < 3) s_mo_logn[threadIdx.x] = 0;
   if (threadIdx.x == 0) {
     s_mo_full = 0;
-    s_mo_adm = {D->admit_bounded ? 1 : D->mak, 0, 0, 0, 0u};
+    s_mo_adm = {D->admit_bounded ? 1 : D->mak, 0, 0, 0, D->mak, 0, 0, 0u, D->admit_bounded ? D->max_staleness : 3e38f, 1.f / (float)D->n_updaters};
   }
   // the instance word of the launch's admission `at` (sign bit: forward only), the last one's beyond it
   auto word_of = [&](unsigned at) -> int {
@@ -374,6 +385,10 @@ __device__ __forceinline__ void role_mlp_one(const GQ AmpDev* D, const GQ Worker
     label = lab[inst];   // one label per instance
   };
   if (threadIdx.x == 0) D->clock[0] = wall_clock64();
+  if (books) {
+    __syncthreads();
+    if (wave == 3) mo_settle(D, W, threadIdx.x & 63, upd_at, n_total, 0u, 0, 0u, 0u);
+  }
   word = word_of(threadIdx.x & 3u);
   fetch(threadIdx.x & 63);
   __syncthreads();
@@ -396,8 +411,6 @@ __device__ __forceinline__ void role_mlp_one(const GQ AmpDev* D, const GQ Worker
     // ---------------- admission
     int n = four_at_most;
     if (books) {
-      if (tid == 0) mo_admit(D, W, upd_at, done, updates());
-      lds_barrier();
       if (uni(s_mo_adm.full)) break;
       const int flying = uni(s_mo_adm.flying);
       n = flying < 4 ? flying : 4;
@@ -413,18 +426,6 @@ __device__ __forceinline__ void role_mlp_one(const GQ AmpDev* D, const GQ Worker
     const unsigned tr = train ? ~(unsigned)__ballot(word < 0) & ((1u << n) - 1u) : 0u;   // those that train
     const int nt = __popc(tr), lab_now = label;
     groups++;
-    trained_all += (unsigned)nt;
-    if (books && tid == 0) {
-      const unsigned seq0 = s_first_seq + done;
-      for (int l = 0; l < 3; ++l) {
-        for (int m = 0; m < n; ++m) mo_log(D, l, 0, seq0 + (unsigned)m);
-        for (int m = 0; m < n; ++m)
-          if ((tr >> m) & 1u) {
-            mo_log(D, l, 1, seq0 + (unsigned)m);
-            if (EACH) mo_log(D, l, 2, 0);
-          }
-      }
-    }
     auto put = [&](LDSQ float* P, int part, int out0, v4f r) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) P[(part * 4 + e) * MO_LD + out0 + lane] = r[e];
@@ -494,6 +495,27 @@ __device__ __forceinline__ void role_mlp_one(const GQ AmpDev* D, const GQ Worker
           correct_out[done + (unsigned)wave] = best == lb;
         }
       }
+    }
+    if (books && wave == 3) {   // the group retires -- a message behind the updates it brings about -- and others are admitted
+      unsigned after = updates() + 3u * (unsigned)nt, mine = updates() + 3u * (unsigned)__popc(tr & ((2u << m4) - 1u));
+      if constexpr (!EACH) {
+        auto due = [&](int l, unsigned c) { return nt && (int)c + nt >= uni(D->node[l].muf) ? 1u : 0u; };
+        after = updates() + due(0, c1) + due(1, c2) + due(2, c3);
+        mine = m4 == n - 1 ? after : updates();
+      }
+      if (s_log_cap && lane == 0) {
+        const unsigned seq0 = s_first_seq + done;
+        for (int l = 0; l < 3; ++l) {
+          for (int m = 0; m < n; ++m) mo_log(D, l, 0, seq0 + (unsigned)m);
+          for (int m = 0; m < n; ++m)
+            if ((tr >> m) & 1u) {
+              mo_log(D, l, 1, seq0 + (unsigned)m);
+              if (EACH) mo_log(D, l, 2, 0);
+            }
+        }
+        for (int m = 0; m < n; ++m) mo_log_ctrl(D, W, 4, seq0 + (unsigned)m, 0);
+      }
+      mo_settle(D, W, lane, upd_at, n_total, done + (unsigned)n, n, mine, after);
     }
     lds_barrier();
     PHASE(3);
@@ -606,8 +628,8 @@ __device__ __forceinline__ void role_mlp_one(const GQ AmpDev* D, const GQ Worker
       }
     }
     PHASE(6);
-    // ---------------- updates (Section 3), retirement
-    const unsigned before = EACH ? updates() - 3u * (unsigned)nt : updates();
+    // ---------------- updates (Section 3)
+    trained_all += (unsigned)nt;
     if constexpr (!EACH) if (nt) {
       c1 += (unsigned)nt;
       c2 += (unsigned)nt;
@@ -632,7 +654,7 @@ __device__ __forceinline__ void role_mlp_one(const GQ AmpDev* D, const GQ Worker
         lds_barrier();
         mo_cols(T, v3, q3);
         lds_barrier();
-        if (books && tid == 0) mo_log(D, 2, 2, 0);
+        if (books && tid == 0 && s_log_cap) mo_log(D, 2, 2, 0);
       }
       if ((int)c2 >= uni(D->node[1].muf)) {
         const float f = -lr2 * (uni(D->node[1].mean) ? 1.f / (float)c2 : 1.f);
@@ -645,7 +667,7 @@ __device__ __forceinline__ void role_mlp_one(const GQ AmpDev* D, const GQ Worker
         lds_barrier();
         mo_cols(T, v2, p2);
         lds_barrier();
-        if (books && tid == 0) mo_log(D, 1, 2, 0);
+        if (books && tid == 0 && s_log_cap) mo_log(D, 1, 2, 0);
       }
       if ((int)c1 >= uni(D->node[0].muf)) {
         const float f = -lr1 * (uni(D->node[0].mean) ? 1.f / (float)c1 : 1.f);
@@ -654,15 +676,9 @@ __device__ __forceinline__ void role_mlp_one(const GQ AmpDev* D, const GQ Worker
         gb1 = 0.f;
         c1 = 0;
         u1++;
-        if (books && tid == 0) mo_log(D, 0, 2, 0);
+        if (books && tid == 0 && s_log_cap) mo_log(D, 0, 2, 0);
       }
     }
-    if (books && tid == 0)   // a message retires behind the updates it has brought about
-      for (int m = 0; m < n; ++m) {
-        mo_log_ctrl(D, W, 4, s_first_seq + done + (unsigned)m, 0);
-        const unsigned now = EACH ? before + 3u * (unsigned)__popc(tr & ((2u << m) - 1u)) : m == n - 1 ? updates() : before;
-        if (D->admit_bounded) mo_retire(D, upd_at, done + (unsigned)m, now);
-      }
     done += (unsigned)n;
     PHASE(7);
   }
