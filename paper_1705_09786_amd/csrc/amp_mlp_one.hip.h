@@ -5,7 +5,7 @@
 // workgroups (role_mlp_regs) nearly all of its time is hand-overs -- poll, fetch, product, drain, post.  Here a stage ends at a
 // workgroup barrier and its result is in LDS, and up to four instances at a time (the messages a 4x4x1 matrix instruction
 // takes) go through a stage together.  Measured, 64-128-128-10 with an update per gradient: 1,024 instances with four in
-// flight 3.54 -> 1.21 ms, 4.5 us a group, of which a wave's 454 matrix instructions (8 cycles each and 8.4 from one to the
+// flight 3.54 -> 1.18 ms, 4.4 us a group, of which a wave's 454 matrix instructions (8 cycles each and 8.4 from one to the
 // next) are 1.6; a call on eight instances one at a time 124 -> 90 us.  Evaluation of a small model 2.07 -> 0.42 ms.
 //   * Weights stay in registers, once with an output per lane (forward) and, where a gradient goes on to the layer below, once
 //     with an input per lane (backward); one wave to a SIMD has 512 registers a lane.  Operands are the instances' values from
