@@ -330,12 +330,22 @@ def test_staleness_bounded_admission():
     compare(g, rt, len(tdata), opt=SGD)
 
 
-def seen_updates(logs, seq):
-    """Updates per layer that the MLP's record shows between each instance's admission and its retirement: the layers record an
-    update per gradient, so those of the instances that retire between the two, its own among them."""
-    order = [(k, s) for (_, k, s, _) in logs[0]]
-    at = {ev: i for i, ev in enumerate(order)}
-    return sum(1 for k, _ in order[at[("A", seq)]:at[("R", seq)] + 1] if k == "R")
+def limits_follow_the_record(logs, mak, bound):
+    """The bounded limit as the controller's record has it, for the MLP at an update per gradient: an instance has seen, per layer, an
+    update of every one that trained and retired between its admission and its own retirement, itself among them.  No admission
+    stands above the limit of its moment; returns the last one."""
+    limit, active = 1, 0
+    trains, before, trained = {}, {}, 0
+    for (_, k, s, local) in logs[0]:
+        if k == "A":
+            active += 1
+            assert active <= limit, (bound, s, active, limit)
+            trains[s], before[s] = local == 0, trained
+        else:
+            active -= 1
+            trained += trains[s]
+            limit = max(1, limit - 1) if trained - before[s] > bound else min(mak, limit + 1)
+    return limit
 
 
 @pytest.mark.parametrize("d_in,hidden,mak,muf", [(64, 128, 8, 1), (16, 37, 11, 1), (128, 64, 3, 1), (16, 37, 9, 3), (64, 100, 6, 5)])
@@ -362,19 +372,23 @@ def test_mlp_admission(d_in, hidden, mak, muf):
         if bound == 0.0 and muf == 1:
             assert all(np.array_equal(a, b) for a, b in zip(g["params"], one["params"]))
             assert np.array_equal(g["losses"], one["losses"])
-        limit, active = 1, 0
-        for k, s in [(k, s) for (_, k, s, _) in g["logs"][0]]:
-            if k == "A":
-                active += 1
-                assert active <= limit, (bound, s, active, limit)
-            else:
-                active -= 1
-                if muf == 1:
-                    limit = max(1, limit - 1) if seen_updates(g["logs"], s) > bound else min(mak, limit + 1)
-                else:
-                    limit = mak
         if muf == 1:
-            assert g["admission"]["final_limit"] == limit
+            assert g["admission"]["final_limit"] == limits_follow_the_record(g["logs"], mak, bound)
+    # forward-only instances among them see updates and make none
+    valid = synth.make_mlp(23, 46, dims)
+    tr = runner.Trainer("mlp", dims, fp, mak, 1, 0, len(data), arena_bytes=1 << 28)
+    a = tr.amp
+    a.set_optimizer(-1, B.OPT_SGD, lr=0.01)
+    a.set_min_update_frequency(-1, muf)
+    a.set_admission(B.ADMIT_BOUNDED, 1.5)
+    a.set_event_log(2048)
+    tr.submit_all(data)
+    tr.submit_all(valid, which=1)
+    assert a.train_eval(1)["n_instances"] == len(valid)
+    logs = a.get_event_log()
+    check_controller_log(logs, mak, len(data) + len(valid))
+    if muf == 1:
+        assert a.get_admission()["final_limit"] == limits_follow_the_record(logs, mak, 1.5)
 
 
 def test_rnn_edge_lengths():
